@@ -316,6 +316,55 @@ int yoco_gret_decode(const void* q, const void* k, const void* v, const float* l
                      int B, int H, int dk, int dv, float scale, int group_norm, float eps, int dtype, void* stream);
 
 /*
+ * ---- One token through a whole bf16 stack (sections 2.1 - 2.3: Eq. 1, 2, 3, Fig. 3 "Generation") ----
+ * The attention calls above with everything between them (RMSNorm, projections, residual stream, SwiGLU,
+ * classifier) enqueued by one call, for a single sequence. All weights are bf16, row-major with a row per OUTPUT:
+ * [out][in]. Every intermediate (normalised input, projections, attention output, products, residual stream) is
+ * rounded to bf16 once where it is formed; sums are fp32.
+ */
+typedef struct yoco_stack_layer {
+  const void* ln1;  /* [d_model] gain of the norm before attention */
+  const void* w_in; /* self-decoder: rows of W_Q, W_K, W_V (gated retention: then W_gate, then W_gamma); cross-decoder: W_Q */
+  const void* w_o;  /* [d_model][Hq d] */
+  const void* ln2;  /* [d_model] gain of the norm before the SwiGLU */
+  const void* w_gu; /* [2 ffn][d_model]: rows of W_G, then of W_1 */
+  const void* w_2;  /* [d_model][ffn] */
+} yoco_stack_layer;
+
+typedef struct yoco_stack {
+  const yoco_stack_layer* self;  /* host: n_self layers */
+  const yoco_stack_layer* cross; /* host: n_cross layers */
+  const void* kv_ln;             /* Eq. 2: [d_model] gain */
+  const void* w_kv;              /* [2 Hkv d][d_model]: rows of W_K, then of W_V */
+  const void* final_ln;          /* [d_model] */
+  const void* w_out;             /* [vocab][d_model] */
+  int32_t n_self, n_cross, d_model, Hq, Hkv_self, Hkv, d, ffn, vocab;
+  int32_t gret;                  /* 0: sliding-window self-decoder; 1: gated retention */
+  float scale, eps, tau;
+} yoco_stack;
+
+/* Device scratch of yoco_stack_step (activations of one token). Host only. */
+int yoco_stack_step_scratch(const yoco_stack* st, size_t* bytes);
+
+/*
+ * x: [d_model], the token's embedding. rings: n_self rolling caches of one sequence (host array; NULL for gated
+ * retention), states: n_self fp32 states [1,Hq,d,d] (host array of device pointers; NULL for sliding windows).
+ * The token is at position pos: its rows are stored in the rings (or states) and in row pos of the cache before they
+ * are attended to (past the cache's capacity nothing is stored, as in yoco_kv_cache_append). With rings == states == NULL only the cross-decoder runs (the exit row of an early-exit prefill,
+ * Fig. 3: x is the self-decoder's last row, whose cache row has been written). logits: [vocab] or NULL; x_out:
+ * [d_model], the residual stream after the last layer, or NULL. workspace: yoco_cross_attn_decode_workspace of the
+ * larger of the ring and the cache. d must be 128, widths multiples of 8 and at most 16384.
+ */
+int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* rings, float* const* states, const yoco_kv_cache* cache,
+                    int64_t pos, void* x_out, void* logits, void* scratch, size_t scratch_bytes, void* workspace,
+                    size_t workspace_bytes, void* stream);
+
+/* Row-wise passes of the same stack for prompts, bf16: xn = RMSNorm(x + add) * gain with x + add stored in y (add ==
+ * NULL: no addition, y unused), and h = swish(gu[:, :ffn]) * gu[:, ffn:] for gu [rows][2 ffn]. */
+int yoco_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, void* stream);
+int yoco_glu_rows(const void* gu, void* h, int64_t rows, int ffn, void* stream);
+
+/*
  * ---- Measured ceilings (measurement aids for the benchmark, not part of the path) ----
  * yoco_ceiling_mfma: `workgroups` workgroups of 8 wavefronts each issue
  * 8 * iters back-to-back v_mfma_f32_32x32x16_bf16 (32768 flops each) on

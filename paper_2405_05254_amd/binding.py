@@ -13,6 +13,17 @@ class YocoError(RuntimeError):
     pass
 
 
+class _Layer(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("ln1", "w_in", "w_o", "ln2", "w_gu", "w_2")]
+
+
+class _Stack(C.Structure):
+    _fields_ = [("self", C.POINTER(_Layer)), ("cross", C.POINTER(_Layer))] + \
+               [(n, C.c_void_p) for n in ("kv_ln", "w_kv", "final_ln", "w_out")] + \
+               [(n, C.c_int32) for n in ("n_self", "n_cross", "d_model", "Hq", "Hkv_self", "Hkv", "d", "ffn", "vocab", "gret")] + \
+               [(n, C.c_float) for n in ("scale", "eps", "tau")]
+
+
 class _Cache(C.Structure):
     _fields_ = [("k", C.c_void_p), ("v", C.c_void_p), ("B", C.c_int32), ("Hkv", C.c_int32),
                 ("d", C.c_int32), ("dtype", C.c_int32), ("N_cap", C.c_int64)]
@@ -51,13 +62,18 @@ def lib():
     L.yoco_gret_prefill_workspace.argtypes = [i32, i64, i32, i32, i32, i32, i32, C.POINTER(sz)]
     L.yoco_gret_prefill.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, i32, i32, f32, i32, f32, i32, vp, sz, vp]
     L.yoco_gret_decode.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, f32, i32, f32, i32, vp]
+    L.yoco_stack_step_scratch.argtypes = [C.POINTER(_Stack), C.POINTER(sz)]
+    L.yoco_stack_step.argtypes = [C.POINTER(_Stack), vp, C.POINTER(_Cache), C.POINTER(vp), C.POINTER(_Cache), i64, vp, vp, vp, sz, vp, sz, vp]
+    L.yoco_norm_rows.argtypes = [vp, vp, vp, vp, vp, i64, i32, f32, vp]
+    L.yoco_glu_rows.argtypes = [vp, vp, i64, i32, vp]
     L.yoco_ceiling_mfma.argtypes = [vp, vp, i32, i32, vp]
     L.yoco_ceiling_attn_loop.argtypes = [vp, vp, i32, i32, i32, vp]
     L.yoco_ceiling_stream_read.argtypes = [vp, sz, vp, i32, vp]
     for name in ("yoco_ceiling_mfma", "yoco_ceiling_attn_loop", "yoco_ceiling_stream_read", "yoco_kv_cache_bytes", "yoco_kv_cache_init", "yoco_swa_prefill", "yoco_global_kv_write", "yoco_global_kv_write_scaled",
                  "yoco_cross_attn_prefill", "yoco_cross_attn_decode_workspace", "yoco_cross_attn_decode", "yoco_cross_attn_decode_noalloc",
                  "yoco_swa_cache_write", "yoco_kv_cache_append", "yoco_swa_decode",
-                 "yoco_gret_prefill_workspace", "yoco_gret_prefill", "yoco_gret_decode"):
+                 "yoco_gret_prefill_workspace", "yoco_gret_prefill", "yoco_gret_decode",
+                 "yoco_stack_step_scratch", "yoco_stack_step", "yoco_norm_rows", "yoco_glu_rows"):
         getattr(L, name).restype = i32
     _LIB = L
     return L
@@ -331,6 +347,36 @@ def gret_decode(q, k, v, log_gamma, state, scale, group_norm=True, eps=1e-6, out
                                   _state(state, "state", B, H, dk, dv), B, H, dk, dv, scale, int(bool(group_norm)), eps,
                                   _dtype(q), _stream()))
     return o
+
+
+def stack_step_scratch(stack):
+    n = C.c_size_t()
+    _check(lib().yoco_stack_step_scratch(C.byref(stack), C.byref(n)))
+    return n.value
+
+
+def stack_step(stack, x, rings, states, cache, pos, scratch, workspace, x_out=None, logits=None):
+    """One token through a bf16 stack (yoco_stack_step). rings: ctypes array of cache descriptors or None; states: ctypes
+    array of state pointers or None; both None: the cross-decoder alone."""
+    _check(lib().yoco_stack_step(C.byref(stack), _dev(x, "x"), rings, states, C.byref(cache.desc), pos,
+                                 None if x_out is None else _dev(x_out, "x_out"), None if logits is None else _dev(logits, "logits"),
+                                 *_ws(scratch), *_ws(workspace), _stream()))
+
+
+def norm_rows(x, gain, eps, add=None):
+    """RMSNorm(x) * gain over the rows of a bf16 [rows,dim] tensor; with `add`: (x + add, RMSNorm(x + add) * gain) (yoco_norm_rows)."""
+    xn = torch.empty_like(x)
+    y = None if add is None else torch.empty_like(x)
+    _check(lib().yoco_norm_rows(_dev(x, "x"), None if add is None else _dev(add, "add"), None if y is None else _dev(y, "y"),
+                                _dev(gain, "gain"), _dev(xn, "xn"), x.shape[0], x.shape[1], eps, _stream()))
+    return xn if add is None else (y, xn)
+
+
+def glu_rows(gu):
+    """bf16 [rows, 2 ffn] -> swish(first half) * second half (yoco_glu_rows)."""
+    h = torch.empty((gu.shape[0], gu.shape[1] // 2), dtype=gu.dtype, device=gu.device)
+    _check(lib().yoco_glu_rows(_dev(gu, "gu"), _dev(h, "h"), h.shape[0], h.shape[1], _stream()))
+    return h
 
 
 def ceiling_mfma(seed, sink, iters, workgroups):

@@ -124,6 +124,51 @@ int check_gret_shape(int B, int64_t T, int H, int dk, int dv, int dtype) {
   return YOCO_OK;
 }
 
+// ---- one token through a whole stack
+typedef unsigned short bf16_raw;
+
+int check_stack(const yoco_stack* st) {
+  if (st->n_self < 0 || st->n_cross <= 0 || (st->n_self && !st->self) || !st->cross || !st->final_ln || !st->w_out || (st->n_self && (!st->kv_ln || !st->w_kv)))
+    return fail(YOCO_ERR_INVALID_ARG, "stack: missing layers or weights");
+  if (st->d_model <= 0 || st->ffn <= 0 || st->vocab <= 0 || !(st->tau > 0.f)) return fail(YOCO_ERR_INVALID_ARG, "stack: non-positive size");
+  int rc = check_heads(st->Hq, st->Hkv);
+  if (rc) return rc;
+  if (st->n_self && !st->gret && (rc = check_heads(st->Hq, st->Hkv_self))) return rc;
+  if (st->n_self && st->gret && st->Hkv_self != st->Hq) return fail(YOCO_ERR_UNSUPPORTED, "stack: gated retention has no grouped heads");
+  if (st->d != 128) return fail(YOCO_ERR_UNSUPPORTED, "stack: head_dim %d, not 128", st->d);
+  if (st->d_model % 8 || st->ffn % 8) return fail(YOCO_ERR_ALIGNMENT, "stack: widths must be multiples of 8");
+  if (st->d_model > yoco::kGemvMaxK || st->ffn > yoco::kGemvMaxK || (int64_t)st->Hq * st->d > yoco::kGemvMaxK)
+    return fail(YOCO_ERR_UNSUPPORTED, "stack: a width exceeds %d", yoco::kGemvMaxK);
+  for (int i = 0; i < st->n_self + st->n_cross; ++i) {
+    const yoco_stack_layer& L = i < st->n_self ? st->self[i] : st->cross[i - st->n_self];
+    if (!L.ln1 || !L.w_in || !L.w_o || !L.ln2 || !L.w_gu || !L.w_2) return fail(YOCO_ERR_INVALID_ARG, "stack: layer %d has a null pointer", i);
+    if (!aligned16(L.ln1) || !aligned16(L.w_in) || !aligned16(L.w_o) || !aligned16(L.ln2) || !aligned16(L.w_gu) || !aligned16(L.w_2))
+      return fail(YOCO_ERR_ALIGNMENT, "stack: layer %d has a pointer that is not 16-byte aligned", i);
+  }
+  if (!aligned16(st->kv_ln) || !aligned16(st->w_kv) || !aligned16(st->final_ln) || !aligned16(st->w_out))
+    return fail(YOCO_ERR_ALIGNMENT, "stack: pointer not 16-byte aligned");
+  return YOCO_OK;
+}
+
+// The activations of one token, carved out of the caller's scratch.
+struct StackScratch {
+  bf16_raw *x, *y, *in, *o, *h;
+  float* log_gamma;
+  size_t bytes;
+  StackScratch(const yoco_stack& st, char* p) {
+    char* const p0 = p;
+    auto take = [&](size_t n) { char* r = p; p += (n + 255) & ~(size_t)255; return r; };
+    const size_t qd = (size_t)st.Hq * st.d, kd = (size_t)(st.Hkv_self > st.Hkv ? st.Hkv_self : st.Hkv) * st.d;
+    x = (bf16_raw*)take(2 * (size_t)st.d_model);
+    y = (bf16_raw*)take(2 * (size_t)st.d_model);
+    in = (bf16_raw*)take(2 * (2 * qd + 2 * kd));
+    o = (bf16_raw*)take(2 * qd);
+    h = (bf16_raw*)take(2 * (size_t)st.ffn);
+    log_gamma = (float*)take(4 * (size_t)st.Hq);
+    bytes = (size_t)(p - p0);
+  }
+};
+
 // ---- static scratch for callers that cannot allocate (yoco_cross_attn_decode_noalloc). Every GPU the library
 // runs on holds its own copy of the array, at its own address, until the process ends. In host code the array's name is
 // only a handle for hipGetSymbolAddress; kernels and copies get the per-device address looked up below.
@@ -468,6 +513,120 @@ int yoco_gret_decode(const void* q, const void* k, const void* v, const float* l
   if (!yoco::gret_recurrent_supported(a))
     return fail(YOCO_ERR_UNSUPPORTED, "gated retention: dk %d, dv %d have no kernel (at most 128)", dk, dv);
   return hip_result(yoco::launch_gret_recurrent(a, dtype, (hipStream_t)stream), "gret_decode");
+}
+
+int yoco_stack_step_scratch(const yoco_stack* st, size_t* bytes) {
+  if (!st || !bytes) return fail(YOCO_ERR_INVALID_ARG, "null argument");
+  int rc = check_stack(st);
+  if (rc) return rc;
+  *bytes = StackScratch(*st, nullptr).bytes;
+  return YOCO_OK;
+}
+
+int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* rings, float* const* states, const yoco_kv_cache* cache,
+                    int64_t pos, void* x_out, void* logits, void* scratch, size_t scratch_bytes, void* workspace,
+                    size_t workspace_bytes, void* stream) {
+  if (!st || !x || !cache || !scratch || !workspace) return fail(YOCO_ERR_INVALID_ARG, "null argument");
+  int rc = check_stack(st);
+  if (rc) return rc;
+  rc = check_cache(cache);
+  if (rc) return rc;
+  const bool self = rings || states;
+  if (self && (st->gret ? !states : !rings)) return fail(YOCO_ERR_INVALID_ARG, "the self-decoder's caches do not match its kind");
+  if (cache->B != 1 || cache->Hkv != st->Hkv || cache->d != st->d || io_dtype(*cache) != YOCO_BF16)
+    return fail(YOCO_ERR_INVALID_ARG, "the cache does not match the stack");
+  if (pos < 0) return fail(YOCO_ERR_INVALID_ARG, "negative position %lld", (long long)pos);
+  if (!aligned16(x) || !aligned16(x_out) || !aligned16(logits) || !aligned16(scratch) || !aligned16(workspace))
+    return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned");
+  const StackScratch t(*st, (char*)scratch);
+  if (scratch_bytes < t.bytes) return fail(YOCO_ERR_WORKSPACE, "scratch %zu < %zu bytes", scratch_bytes, t.bytes);
+  size_t need = 0;
+  int splits = 0, ring_splits = 0;
+  rc = yoco_cross_attn_decode_workspace(cache, st->Hq, &need, &splits);
+  if (rc) return rc;
+  if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
+  if (self && !st->gret) {
+    for (int i = 0; i < st->n_self; ++i) {
+      rc = check_cache(rings + i);
+      if (rc) return rc;
+      if (rings[i].B != 1 || rings[i].Hkv != st->Hkv_self || rings[i].d != st->d || rings[i].dtype != YOCO_BF16 ||
+          rings[i].N_cap != rings[0].N_cap)
+        return fail(YOCO_ERR_INVALID_ARG, "ring %d does not match the stack", i);
+    }
+    rc = yoco_cross_attn_decode_workspace(rings, st->Hq, &need, &ring_splits);
+    if (rc) return rc;
+    if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
+  }
+
+  hipStream_t s = (hipStream_t)stream;
+  const int dm = st->d_model, qd = st->Hq * st->d, kd = st->Hkv_self * st->d, ckd = st->Hkv * st->d;
+  hipError_t e = hipSuccess;
+  auto gemv = [&](const void* in, const void* gain, const void* W, int N, int K, const void* res, int glu, void* out, int n_plain) {
+    if (e != hipSuccess) return;
+    yoco::GemvArgs g;
+    g.x = in; g.gain = gain; g.W = W; g.res = res; g.out = out;
+    g.log_gamma = t.log_gamma;
+    g.N = N; g.K = K; g.n_plain = n_plain; g.glu = glu;
+    g.eps = st->eps; g.inv_tau = 1.f / st->tau;
+    e = yoco::launch_gemv(g, s);
+  };
+  const void* cur = x;
+  // W_O, the residual and the SwiGLU half of Eq. 1; `last`: where the residual stream goes
+  auto finish_layer = [&](const yoco_stack_layer& L, void* last) {
+    gemv(t.o, nullptr, L.w_o, dm, qd, cur, 0, t.y, dm);
+    gemv(t.y, L.ln2, L.w_gu, st->ffn, dm, nullptr, 1, t.h, st->ffn);
+    gemv(t.h, nullptr, L.w_2, dm, st->ffn, t.y, 0, last, dm);
+    cur = last;
+  };
+  if (self) {
+    for (int i = 0; i < st->n_self; ++i) {
+      const yoco_stack_layer& L = st->self[i];
+      const int plain = qd + 2 * kd + (st->gret ? qd : 0);
+      gemv(cur, L.ln1, L.w_in, plain + (st->gret ? st->Hq : 0), dm, nullptr, 0, t.in, plain);
+      if (e != hipSuccess) return hip_result(e, "stack_step");
+      bf16_raw *q = t.in, *k = q + qd, *v = k + kd, *gate = v + kd;
+      if (st->gret) {
+        rc = yoco_gret_decode(q, k, v, t.log_gamma, gate, t.o, states[i], 1, st->Hq, st->d, st->d, st->scale, 1, st->eps, YOCO_BF16, stream);
+      } else {
+        rc = run_decode(rings[i], q, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, ring_splits, s, "stack_step", k, v, 1);
+      }
+      if (rc) return rc;
+      finish_layer(L, t.x);
+    }
+    gemv(cur, st->kv_ln, st->w_kv, 2 * ckd, dm, nullptr, 0, t.in, 2 * ckd);
+    if (e != hipSuccess) return hip_result(e, "stack_step");
+    if (pos < cache->N_cap) {                 // past the capacity nothing is stored, as in yoco_kv_cache_append
+      rc = yoco_global_kv_write(cache, t.in, t.in + ckd, 0, pos, 1, YOCO_BF16, stream);
+      if (rc) return rc;
+    }
+  }
+  for (int i = 0; i < st->n_cross; ++i) {
+    const yoco_stack_layer& L = st->cross[i];
+    gemv(cur, L.ln1, L.w_in, qd, dm, nullptr, 0, t.in, qd);
+    if (e != hipSuccess) return hip_result(e, "stack_step");
+    rc = run_decode(*cache, t.in, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, splits, s, "stack_step");
+    if (rc) return rc;
+    finish_layer(L, i + 1 == st->n_cross && x_out ? x_out : t.x);
+  }
+  if (logits) gemv(cur, st->final_ln, st->w_out, st->vocab, dm, nullptr, 0, logits, st->vocab);
+  return hip_result(e, "stack_step");
+}
+
+int yoco_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, void* stream) {
+  if (!x || !gain || !xn || (add && !y)) return fail(YOCO_ERR_INVALID_ARG, "null pointer");
+  if (rows < 0 || rows > INT32_MAX || dim <= 0) return fail(YOCO_ERR_INVALID_ARG, "rows or dim out of range");
+  if (dim % 8 || !aligned16(x) || !aligned16(add) || !aligned16(y) || !aligned16(gain) || !aligned16(xn))
+    return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned or dim not a multiple of 8");
+  if (rows == 0) return YOCO_OK;
+  return hip_result(yoco::launch_norm_rows(x, add, y, gain, xn, rows, dim, eps, (hipStream_t)stream), "norm_rows");
+}
+
+int yoco_glu_rows(const void* gu, void* h, int64_t rows, int ffn, void* stream) {
+  if (!gu || !h) return fail(YOCO_ERR_INVALID_ARG, "null pointer");
+  if (rows < 0 || ffn <= 0) return fail(YOCO_ERR_INVALID_ARG, "rows or ffn out of range");
+  if (ffn % 8 || !aligned16(gu) || !aligned16(h)) return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned or ffn not a multiple of 8");
+  if (rows == 0) return YOCO_OK;
+  return hip_result(yoco::launch_glu_rows(gu, h, rows, ffn, (hipStream_t)stream), "glu_rows");
 }
 
 int yoco_ceiling_mfma(const void* seed, void* sink, int iters, int workgroups, void* stream) {

@@ -112,6 +112,25 @@ hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* 
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
                             float* ws, int splits, void* o_direct, hipStream_t s);   // q, o bf16
 
+// What stands between the attention calls of a whole bf16 stack (stack_glue.hip). One token: out = W x with W [N][K], the
+// input normalised first when gain != null; res: added behind the product; glu: W is [2 N][K] and output n is
+// swish(row n) * (row N + n); outputs from n_plain on are log-decays of gated retention, fp32 into log_gamma.
+struct GemvArgs {
+  const void* x;
+  const void* gain;
+  const void* W;
+  const void* res;
+  void* out;
+  float* log_gamma;
+  int N, K, n_plain, glu;
+  float eps, inv_tau;
+};
+constexpr int kGemvMaxK = 16384;      // the input row is held in LDS
+hipError_t launch_gemv(const GemvArgs& g, hipStream_t s);
+// xn = RMSNorm(x + add) * gain row by row (x + add is stored in y; add == null: no addition, y unused)
+hipError_t launch_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, hipStream_t s);
+hipError_t launch_glu_rows(const void* gu, void* h, int64_t rows, int ffn, hipStream_t s);
+
 // Measured-ceiling microbenchmarks (ceilings.hip).
 hipError_t launch_mfma_ceiling(const void* seed, void* sink, int iters, int workgroups, hipStream_t s);
 hipError_t launch_attn_loop_ceiling(const void* seed, void* sink, int iters, int workgroups, int mode, hipStream_t s);

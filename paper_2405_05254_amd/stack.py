@@ -1,13 +1,19 @@
 """YOCO decoder-decoder stack for the end-to-end early-exit and generation
 checks (section 2, Eq. 1-3, Fig. 2 and 3). Attention runs in libyoco; RMSNorm, the projections,
-SwiGLU and the classifier are plain torch ops on the GPU (the non-attention
-GEMMs are not part of the library).
+SwiGLU and the classifier are plain torch ops on the GPU for fp32 glue and for head dims other than 128.
+
+A bf16 stack (kernel dtype and glue bf16, head_dim 128) runs its token steps wholly in libyoco (yoco_stack_step: one
+call enqueues every launch of the token; as torch ops a step was bound by the host, 2.3 ms for 4 + 4 layers whose
+weights stream in 0.13 ms) and its prompts with torch GEMMs and libyoco's row-wise passes between them. Its weights
+are laid out once, a row per output, which is the order a matrix-vector product reads them in; the tensors in the
+layer dicts are views of that.
 
 Precision: the attention operands (Q, K, V, the global cache, O) have the
 kernel dtype; the residual stream and the glue GEMMs run in `glue_dtype`
 (fp32 by default, with the weights' stored values), so the only bf16 roundings
 on the path are the ones at the attention boundary.
 """
+import ctypes
 import math
 
 import torch
@@ -61,6 +67,65 @@ class YocoStack:
             self.kv["gW_V"] = (self.kv["ln"].float()[:, None] * self.kv["W_V"].float()).to(glue_dtype)
         self.cross_layers = [layer(L) for L in w["cross"]]
         self.final_ln, self.W_out = dev(w["final_ln"]), dev(w["W_out"])
+        self._native = self._lay_out() if dtype == glue_dtype == torch.bfloat16 and self.d == 128 else None
+
+    def _lay_out(self):
+        """The stack as libyoco sees it: every weight with a row per output, matrices that read the same input joined.
+        None when a width has no kernel (a torch step serves it)."""
+        layers = self.self_layers + self.cross_layers
+        if not self.cross_layers or self.embed.device.type != "cuda":
+            return None
+        dm, ffn, vocab = self.embed.shape[1], layers[0]["W_2"].shape[0], self.W_out.shape[1]
+        if dm % 8 or ffn % 8 or max(dm, ffn, self.Hq * self.d) > 16384 or any(L["W_2"].shape[0] != ffn for L in layers):
+            return None
+
+        def join(L, *names):
+            rows = torch.cat([L[n].t() for n in names])
+            at = 0
+            for n in names:
+                m = L[n].shape[1]
+                L[n] = rows[at:at + m].t()
+                at += m
+            return rows
+
+        gret = self.self_kind == "gret"
+        into = ("W_Q", "W_K", "W_V") + (("W_gate", "W_gamma") if gret else ())
+
+        def describe(layers, names):
+            out = (yb._Layer * len(layers))()
+            for s, L in zip(out, layers):
+                L["w_in"], L["w_o"], L["w_gu"], L["w_2"] = join(L, *names), join(L, "W_O"), join(L, "W_G", "W_1"), join(L, "W_2")
+                for n in ("ln1", "w_in", "w_o", "ln2", "w_gu", "w_2"):
+                    setattr(s, n, L[n].data_ptr())
+            return out
+
+        st = yb._Stack()
+        self._self_desc, self._cross_desc = describe(self.self_layers, into), describe(self.cross_layers, ("W_Q",))
+        st.self, st.cross = self._self_desc, self._cross_desc
+        self.kv["w_kv"] = join(self.kv, "W_K", "W_V")
+        out = {"W_out": self.W_out}
+        self.w_out = join(out, "W_out")
+        self.W_out = out["W_out"]
+        st.kv_ln, st.w_kv, st.final_ln, st.w_out = (t.data_ptr() for t in (self.kv["ln"], self.kv["w_kv"], self.final_ln, self.w_out))
+        st.n_self, st.n_cross, st.d_model, st.ffn, st.vocab = len(self.self_layers), len(self.cross_layers), dm, ffn, vocab
+        st.Hq, st.Hkv_self, st.Hkv, st.d, st.gret = self.Hq, self.Hkv_self, self.Hkv, self.d, int(gret)
+        st.scale, st.eps, st.tau = self.scale, self.eps, self.tau
+        self._scratch_bytes = yb.stack_step_scratch(st)
+        return st
+
+    def _scratch(self):
+        return torch.empty(self._scratch_bytes, dtype=torch.uint8, device=self.device)
+
+    def _norm(self, X, gain):
+        return _rmsnorm(X, gain, self.eps) if self._native is None else yb.norm_rows(X, gain, self.eps)
+
+    def _after_attention(self, a, X, L):
+        """W_O, the residual and the SwiGLU half of Eq. 1 for the rows of a prompt."""
+        if self._native is None:
+            Y = a @ L["W_O"] + X
+            return _rows(Y, lambda y: _swiglu(_rmsnorm(y, L["ln2"], self.eps), L) + y)
+        Y, xn = yb.norm_rows(a @ L["W_O"], L["ln2"], self.eps, add=X)
+        return Y.add_(_rows(xn, lambda x: yb.glu_rows(x @ L["w_gu"].t()) @ L["W_2"]))
 
     # -- self-decoder: Eq. 1 with sliding-window attention (Eq. 8)
     def _log_decay(self, xn, L):
@@ -73,7 +138,7 @@ class YocoStack:
         X = self.embed[tokens]
         T = X.shape[0]
         for n, L in enumerate(self.self_layers):
-            xn = _rmsnorm(X, L["ln1"], self.eps)
+            xn = self._norm(X, L["ln1"])
             q = (xn @ L["W_Q"]).to(self.dtype).view(1, T, self.Hq, self.d)
             k = (xn @ L["W_K"]).to(self.dtype).view(1, T, self.Hkv_self, self.d)
             v = (xn @ L["W_V"]).to(self.dtype).view(1, T, self.Hkv_self, self.d)
@@ -96,9 +161,9 @@ class YocoStack:
                 a = o.view(T, self.Hq * self.d).to(self.glue)
             if self.capture is not None and self.self_kind != "gret" and ("self%d" % n) in self.capture:
                 self.capture["self%d" % n] = (q[0], k[0], v[0], o[0])
-            Y = a @ L["W_O"] + X
-            del q, k, v, o, xn, a
-            X = _rows(Y, lambda y: _swiglu(_rmsnorm(y, L["ln2"], self.eps), L) + y)
+            del q, k, v, o, xn
+            X = self._after_attention(a, X, L)
+            del a
         return X
 
     # -- Eq. 2: the global cache, written once
@@ -113,7 +178,7 @@ class YocoStack:
             v = (X @ self.kv["gW_V"]).view(T, self.Hkv, self.d)
             yb.global_kv_write_scaled(cache, k, v, rs, 0, pos0)
             return cache
-        xn = _rmsnorm(X, self.kv["ln"], self.eps)
+        xn = self._norm(X, self.kv["ln"])
         k = (xn @ self.kv["W_K"]).to(self.dtype).view(T, self.Hkv, self.d)
         v = (xn @ self.kv["W_V"]).to(self.dtype).view(T, self.Hkv, self.d)
         yb.global_kv_write(cache, k, v, 0, pos0)
@@ -122,11 +187,10 @@ class YocoStack:
     # -- cross-decoder: Eq. 3
     def _cross_layer(self, X, L, attn):
         Tq = X.shape[0]
-        q = (_rmsnorm(X, L["ln1"], self.eps) @ L["W_Q"]).to(self.dtype).view(Tq, self.Hq, self.d)
+        q = (self._norm(X, L["ln1"]) @ L["W_Q"]).to(self.dtype).view(Tq, self.Hq, self.d)
         a = attn(q).view(Tq, self.Hq * self.d).to(self.glue)
-        Y = a @ L["W_O"] + X
-        del q, a
-        return _rows(Y, lambda y: _swiglu(_rmsnorm(y, L["ln2"], self.eps), L) + y)
+        del q
+        return self._after_attention(a, X, L)
 
     def cross_decoder_rows(self, X, cache, q_pos0):
         ws = None
@@ -146,6 +210,10 @@ class YocoStack:
         """One token through the cross-decoder with the split-KV decode kernel."""
         nbytes, _ = yb.cross_attn_decode_workspace(cache, self.Hq)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        if self._native is not None:
+            X = torch.empty_like(x_last)
+            yb.stack_step(self._native, x_last, None, None, cache, length - 1, self._scratch(), ws, x_out=X)
+            return X
         lens = torch.tensor([length], dtype=torch.int64, device=self.device)
         X = x_last
         for L in self.cross_layers:
@@ -188,7 +256,21 @@ class YocoStack:
         for c in ((cache, cache) if self.self_kind == "gret" else (rings[0], cache)):
             nbytes, _ = yb.cross_attn_decode_workspace(c, self.Hq)
             ws.append(torch.empty(nbytes, dtype=torch.uint8, device=self.device))
-        return dict(rings=rings, cache=cache, ws_ring=ws[0], ws_cache=ws[1], length=0)
+        state = dict(rings=rings, cache=cache, ws_ring=ws[0], ws_cache=ws[1], length=0)
+        if self._native is not None:
+            state["scratch"], state["ws"] = self._scratch(), max(ws, key=torch.numel)
+            if self.self_kind == "gret":
+                state["ring_descs"], state["state_ptrs"] = None, (ctypes.c_void_p * len(rings))(*(r.data_ptr() for r in rings))
+            else:
+                state["ring_descs"], state["state_ptrs"] = (yb._Cache * len(rings))(*(r.desc for r in rings)), None
+        return state
+
+    def _native_logits(self, x, state, pos, whole):
+        """Logits [1,vocab] of one token at position pos; whole: through both decoders, else through the cross-decoder alone."""
+        logits = torch.empty((1, self._native.vocab), dtype=self.glue, device=self.device)
+        yb.stack_step(self._native, x, state["ring_descs"] if whole else None, state["state_ptrs"] if whole else None, state["cache"], pos,
+                      state["scratch"], state["ws"], logits=logits)
+        return logits
 
     def prefill(self, tokens, state):
         """Early-exit prefill of a prompt (state must be fresh); returns the logits of its last position."""
@@ -197,6 +279,8 @@ class YocoStack:
         T = X.shape[0]
         self.write_cache(X, state["cache"], 0)
         state["length"] = T
+        if self._native is not None:
+            return self._native_logits(X[T - 1:T], state, T - 1, False)
         lens = torch.tensor([T], dtype=torch.int64, device=self.device)
         x = X[T - 1:T].contiguous()
         for L in self.cross_layers:
@@ -206,6 +290,10 @@ class YocoStack:
     def decode_step(self, token, state):
         """One new token through both decoders; returns its logits [1,vocab]."""
         p = state["length"]
+        if self._native is not None:
+            logits = self._native_logits(self.embed[torch.as_tensor(token, device=self.device).view(1)], state, p, True)
+            state["length"] = p + 1
+            return logits
         pos = torch.tensor([p], dtype=torch.int64, device=self.device)
         lens = pos + 1
         x = self.embed[torch.as_tensor(token, device=self.device).view(1)]

@@ -1,0 +1,72 @@
+"""One token through a bf16 stack in one call (yoco_stack_step) and the row-wise passes of its prompts, against the same
+stack as torch ops: the same roundings in the same places, so the two differ by the order of fp32 sums alone."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2405_05254_amd as yoco  # noqa: E402
+import yoco_synth as ys  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def stack_config(Hq, Hkv_self, Hkv, dm, ffn, vocab, kind):
+    return dict(d_model=dm, Hq=Hq, Hkv_self=Hkv_self, Hkv=Hkv, d=128, n_self=2, n_cross=2, window=64, ffn=ffn, vocab=vocab, eps=1e-6, self_kind=kind)
+
+
+@pytest.mark.parametrize("Hq,Hkv_self,Hkv,dm,ffn,vocab,kind,cache", [
+    (2, 2, 1, 256, 704, 1001, "swa", "bf16"),        # odd vocabulary: surplus rows of the last workgroup
+    (4, 2, 4, 520, 1032, 300, "swa", "int8"),        # widths that are no multiple of a wavefront's 512 elements
+    (17, 17, 17, 2184, 4104, 16390, "swa", "bf16"),  # more than one trip over K (2048), the wide classifier's variant
+    (3, 3, 3, 384, 1056, 97, "gret", "bf16"),        # gated retention: log-decay rows behind the projections, odd head count
+])
+def test_bf16_stack_matches_the_torch_ops(Hq, Hkv_self, Hkv, dm, ffn, vocab, kind, cache):
+    from paper_2405_05254_amd.stack import YocoStack
+    w = ys.stack_weights(3, stack_config(Hq, Hkv_self, Hkv, dm, ffn, vocab, kind), "bf16")
+    if kind == "gret":
+        for L in w["self"]:
+            L["W_gamma"] = (L["W_gamma"] * 0.05).astype(np.float32)
+    for L in w["self"] + w["cross"] + [w["kv"]]:                     # gains that matter
+        for n in ("ln1", "ln2", "ln"):
+            if n in L:
+                L[n] = (1.0 + 0.2 * np.random.default_rng(7).standard_normal(L[n].shape)).astype(np.float32)
+    cdt = torch.int8 if cache == "int8" else torch.bfloat16
+    new, old = (YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16, cache_dtype=cdt) for _ in range(2))
+    assert new._native is not None
+    old._native = None
+    toks = torch.from_numpy(ys.tokens(1, 75, vocab)).cuda()
+    got, ref = [], []
+    for st, out in ((new, got), (old, ref)):
+        state = st.new_generation_state(75)
+        out.append(st.prefill(toks[:70], state))
+        for t in toks[70:]:
+            out.append(st.decode_step(t, state))
+        assert state["length"] == 75
+        out.append(st.forward_early_exit(toks)[0])
+    got, ref = torch.cat(got).double(), torch.cat(ref).double()
+    assert got.shape == ref.shape == (7, vocab)
+    assert ((got - ref).norm() / ref.norm()).item() < 1.5e-2         # bf16 roundings that fall the other way, over eight layer halves
+    assert (got[5] - got[6]).norm() < 3e-2 * got[6].norm()           # token by token against the early-exit prefill
+
+
+@pytest.mark.parametrize("rows,dim", [(1, 8), (3, 2048), (5, 4104), (2, 16384)])
+def test_row_passes(rows, dim):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dim)
+    x, add = (torch.randn(rows, dim, device="cuda", generator=g).bfloat16() for _ in range(2))
+    gain = (1 + 0.1 * torch.randn(dim, device="cuda", generator=g)).bfloat16()
+    from paper_2405_05254_amd import binding as yb
+
+    def norm(t):
+        f = t.float()
+        return (f * torch.rsqrt(f.pow(2).mean(-1, keepdim=True) + 1e-6) * gain.float()).bfloat16().float()
+    y, xn = yb.norm_rows(x, gain, 1e-6, add=add)
+    assert torch.equal(y, x + add)
+    for got, ref in ((xn, norm(x + add)), (yb.norm_rows(x, gain, 1e-6), norm(x))):
+        assert ((got.float() - ref).abs() <= 2 ** -7 * ref.abs()).all()       # one bf16 step at most
+    gu = torch.randn(rows, 2 * dim, device="cuda", generator=g).bfloat16()
+    ref = (torch.nn.functional.silu(gu[:, :dim]) * gu[:, dim:]).float()
+    assert ((yb.glu_rows(gu).float() - ref).abs() <= 2 ** -6 * ref.abs() + 1e-30).all()
+    with pytest.raises(yoco.YocoError):
+        yb.norm_rows(x[:, ::2], gain, 1e-6)
