@@ -18,6 +18,7 @@
 // Coding rule (float32 throughout, because a rounding decides the integer):
 // a = max|x| over the row, scale = a / 127, code = rint(x * (127 / a)) clamped
 // to +-127; a zero row has scale 0 and codes 0.
+#include "decode_tail.h"
 #include "yoco_common.h"
 
 namespace yoco {
@@ -26,7 +27,6 @@ namespace {
 
 constexpr int kD = 128;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kNegBig = -1.0e30f;
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -258,29 +258,25 @@ __device__ __forceinline__ void step(State& st, const i32x4 (&qhi)[2], const i32
   }
 }
 
-// Workgroup = 4 wavefronts on one (sequence, KV head, split); each wavefront walks a contiguous run of blocks,
+// Workgroup = 4 wavefronts on one (sequence, KV head, split); the wavefronts take turns at its blocks,
 // the next block's loads in flight while the current one is reduced. q, o are bf16.
 // GMAX sizes the merge buffers (4 or 16 heads per KV head); G = Hq / Hkv <= GMAX is the real group size.
 template <int GMAX>
 __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                         const int64_t* __restrict__ lens, int64_t fixed_len, int Hq, float scale_log2,
-                                                        float* __restrict__ ws, int splits, bf16_t* __restrict__ o_direct) {
+                                                        SplitOut out) {
   __shared__ float red_o[4][GMAX][kD];
   __shared__ float red_ml[4][GMAX][2];
   const int G = Hq / c.Hkv;
   __shared__ __attribute__((aligned(16))) float scales[4][2][64];
-  const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, qg = lane >> 4;
 
-  const int64_t len_raw = lens ? lens[b] : fixed_len;
-  const int64_t len = len_raw < 0 ? 0 : (len_raw > c.N_cap ? c.N_cap : len_raw);
-  const int64_t chunk = (((len + splits - 1) / splits) + 255) & ~(int64_t)255;   // rows per split, 256 | chunk
-  const int64_t j_lo = sp * chunk;
-  const int64_t j_hi = (j_lo + chunk < len) ? j_lo + chunk : len;
-  const int64_t sub = chunk >> 2;                                                // rows per wave, 64 | sub
-  const int64_t w_lo = j_lo + wave * sub;
-  const int64_t w_hi = (w_lo + sub < j_hi) ? w_lo + sub : j_hi;
+  const SplitRows part = split_rows<256>(out, c, lens, fixed_len, b, sp);
+  if (sp > 0 && sp >= part.splits) return;
+  const int64_t j_lo = part.lo, j_hi = part.hi;
+  const int64_t w_lo = j_lo + wave * 64;                  // the wavefronts take turns at the split's blocks
 
   // The query of head n as two int8 operands: dims 64 half + 16 qg + j in byte j of half `half`.
   i32x4 qhi[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, qlo[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
@@ -340,7 +336,7 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
   const u32x4* kp = (const u32x4*)c.k + plane;
   const u32x4* vp = (const u32x4*)c.v + plane;
 
-  if (w_lo < w_hi) {
+  if (w_lo < j_hi) {
     Block nx;
     auto load = [&](int64_t row0) {                       // row0 is a multiple of 64
       const int64_t base = (row0 >> 6) * (kI8BlockBytes / 16);
@@ -354,12 +350,12 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
     };
     load(w_lo);
     int64_t row0 = w_lo;
-    for (; row0 + 64 < w_hi; row0 += 64) {
+    for (; row0 + 256 < j_hi; row0 += 256) {
       const Block cur = nx;
-      load(row0 + 64);
+      load(row0 + 256);
       step<false>(st, qhi, qlo, qs, cur, qg, 64, scales[wave]);
     }
-    step<true>(st, qhi, qlo, qs, nx, qg, (int)(w_hi - row0), scales[wave]);   // last block of the run, 1..64 rows
+    step<true>(st, qhi, qlo, qs, nx, qg, (int)(j_hi - row0), scales[wave]);   // last block, 1 row or more
   }
 
   // One state per head and wavefront: gather the partial sums of the four row groups, rebase the output on 2^m.
@@ -375,27 +371,7 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
     if (qg == 0) { red_ml[wave][n][0] = st.m; red_ml[wave][n][1] = l; }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < G * kD; t += 256) {
-    const int h = t / kD, e = t % kD;
-    const float M = fmaxf(fmaxf(red_ml[0][h][0], red_ml[1][h][0]), fmaxf(red_ml[2][h][0], red_ml[3][h][0]));
-    float ls = 0.f, o = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float fw = __builtin_amdgcn_exp2f(red_ml[w][h][0] - M);
-      ls = fmaf(fw, red_ml[w][h][1], ls);
-      o = fmaf(fw, red_o[w][h][e], o);
-    }
-    if (o_direct) {
-      o_direct[((size_t)b * Hq + g * G + h) * kD + e] = f32_to_bf16(ls > 0.f ? o / ls : 0.f);
-      continue;
-    }
-    float* out = ws + (((size_t)b * Hq + g * G + h) * splits + sp) * partial_stride(kD);
-    out[e] = o;
-    if (e == 0) {
-      out[kD] = (ls > 0.f) ? M * kLn2 : -INFINITY;
-      out[kD + 1] = ls;
-    }
-  }
+  finish_split<GMAX>(out, red_o, red_ml, G, (size_t)b * Hq + g * G, sp, part.splits);
 }
 
 }  // namespace
@@ -448,17 +424,17 @@ hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* 
 }
 
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, void* o_direct, hipStream_t s) {
-  bf16_t* od = splits == 1 ? (bf16_t*)o_direct : nullptr;
-  dim3 grid(splits, c.Hkv, c.B), block(256);
+                            float* ws, int splits, float inv_workgroups, unsigned long long tag, void* o, hipStream_t s) {
+  const SplitOut out = {ws, (bf16_t*)o, splits, inv_workgroups, tag};
+  dim3 grid(c.Hkv, c.B, splits), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;
   const int G = Hq / c.Hkv;
-  if (G < 1 || G > 16) return hipErrorInvalidValue;
+  if (G < 1 || G > 16 || splits > kMaxFusedSplits) return hipErrorInvalidValue;
   if (G <= 4)
-    hipLaunchKernelGGL(decode_i8_kernel<4>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od);
+    hipLaunchKernelGGL(decode_i8_kernel<4>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out);
   else
-    hipLaunchKernelGGL(decode_i8_kernel<16>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od);
+    hipLaunchKernelGGL(decode_i8_kernel<16>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out);
   return hipGetLastError();
 }
 

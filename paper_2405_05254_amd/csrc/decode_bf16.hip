@@ -4,10 +4,9 @@
 // are served from that one read.
 //
 // Workgroup = 4 wavefronts on one (sequence, KV head, split). Each wavefront
-// streams a contiguous quarter of the split, 32 rows (16 KiB of K and V) per step,
+// takes every fourth 32-row step (16 KiB of K and V) of the split,
 // with the next step's loads in flight while the current one is reduced. States are
-// merged once at the end (lanes by shuffles, wavefronts through LDS) and written as
-// one partial (m, l, o[128]) per (sequence, query head, split).
+// merged once at the end (lanes by shuffles, wavefronts through LDS, splits as decode_tail.h says).
 //
 // Two kernels share that frame. decode_bf16_mfma_kernel (further down) puts both
 // products on the matrix cores and serves 1..16 heads per KV head at the rate of a
@@ -15,6 +14,9 @@
 // that cover whole 256-byte rows (16 lanes per row), each group of 16 lanes keeping
 // its own online-softmax state (m, l, o[8 dims]) per query head; it serves the
 // one-token sliding-window step, which also stores the new row.
+#include <type_traits>
+
+#include "decode_tail.h"
 #include "yoco_common.h"
 
 namespace yoco {
@@ -23,7 +25,6 @@ namespace {
 
 constexpr int kD = 128;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kNegBig = -1.0e30f;   // "no row seen yet": finite, so m - m never makes NaN
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -108,24 +109,20 @@ __device__ __forceinline__ void step(State<G>& st, const u32x4 (&kq)[G], const u
 template <int G, int R>
 __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                           const int64_t* __restrict__ lens, int64_t fixed_len, int Hq, float scale_log2,
-                                                          float* __restrict__ ws, int splits, bf16_t* __restrict__ o_direct,
-                                                          const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
+                                                          SplitOut out, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
                                                           int ring) {
   constexpr int kRowsPerStep = 4 * R;
   __shared__ float red_o[4][G][kD];
   __shared__ float red_ml[4][G][2];
-  const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = lane >> 4, seg = lane & 15;
 
-  const int64_t len_raw = lens ? lens[b] : fixed_len;   // a host-known length serves the few-row prefill case
-  const int64_t len = len_raw < 0 ? 0 : (len_raw > c.N_cap ? c.N_cap : len_raw);
-  const int64_t chunk = (((len + splits - 1) / splits) + 127) & ~(int64_t)127;  // rows per split, 128 | chunk
-  const int64_t j_lo = sp * chunk;
-  const int64_t j_hi = (j_lo + chunk < len) ? j_lo + chunk : len;
-  const int64_t sub = chunk >> 2;                                               // rows per wave, 32 | sub
-  const int64_t w_lo = j_lo + wave * sub;
-  const int64_t w_hi = (w_lo + sub < j_hi) ? w_lo + sub : j_hi;
+  const SplitRows part = split_rows<128>(out, c, lens, fixed_len, b, sp);
+  if (sp > 0 && sp >= part.splits) return;
+  const int64_t j_lo = part.lo, j_hi = part.hi;
+  const int64_t w_lo = j_lo + wave * kRowsPerStep;        // the wavefronts take turns at the split's steps
+  constexpr int kTurn = 4 * kRowsPerStep;
 
   u32x4 kq[G];
 #pragma unroll
@@ -148,7 +145,7 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
   int64_t slot = -1;                                   // where the new row goes, -1 = nowhere
   u32x4 knew = {0, 0, 0, 0}, vnew = knew;
   {
-    const int64_t pos = len_raw - 1;
+    const int64_t pos = (lens ? lens[b] : fixed_len) - 1;
     if (pos >= 0 && (ring || pos < c.N_cap)) slot = pos >= c.N_cap ? pos % c.N_cap : pos;
     knew = *(const u32x4*)(k_new + ((int64_t)b * c.Hkv + g) * kD + seg * 8);
     vnew = *(const u32x4*)(v_new + ((int64_t)b * c.Hkv + g) * kD + seg * 8);
@@ -158,8 +155,8 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
     }
   }
 
-  if (w_lo < w_hi) {
-    const int64_t last = w_hi - 1;
+  if (w_lo < j_hi) {
+    const int64_t last = j_hi - 1;
     u32x4 kn[R], vn[R];
     auto load = [&](int64_t row0) {
 #pragma unroll
@@ -176,14 +173,14 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
     };
     load(w_lo);
     int64_t row0 = w_lo;
-    for (; row0 + kRowsPerStep < w_hi; row0 += kRowsPerStep) {   // steps followed by another step
+    for (; row0 + kTurn < j_hi; row0 += kTurn) {               // steps followed by another step
       u32x4 kc[R], vc[R];
 #pragma unroll
       for (int u = 0; u < R; ++u) { kc[u] = kn[u]; vc[u] = vn[u]; }
-      load(row0 + kRowsPerStep);
+      load(row0 + kTurn);
       step<G, R, false>(st, kq, kc, vc, scale_log2, r, kRowsPerStep);
     }
-    step<G, R, true>(st, kq, kn, vn, scale_log2, r, (int)(w_hi - row0));   // last step, 1..4R rows
+    step<G, R, true>(st, kq, kn, vn, scale_log2, r, (int)(j_hi - row0));   // last step, 1 row or more
   }
 
   // merge the 4 lane groups of the wave
@@ -210,30 +207,8 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
     }
   }
   __syncthreads();
-  // merge the 4 waves; thread t owns (head t / 128, dimension t % 128)
-  for (int t = threadIdx.x; t < G * kD; t += 256) {
-    const int h = t / kD, e = t % kD;
-    const float M = fmaxf(fmaxf(red_ml[0][h][0], red_ml[1][h][0]), fmaxf(red_ml[2][h][0], red_ml[3][h][0]));
-    float l = 0.f, o = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float f = __builtin_amdgcn_exp2f(red_ml[w][h][0] - M);
-      l = fmaf(f, red_ml[w][h][1], l);
-      o = fmaf(f, red_o[w][h][e], o);
-    }
-    if (o_direct) {          // a single split is the whole answer: normalise and store, no merge pass
-      o_direct[((size_t)b * Hq + g * G + h) * kD + e] = f32_to_bf16(l > 0.f ? o / l : 0.f);
-      continue;
-    }
-    float* out = ws + (((size_t)b * Hq + g * G + h) * splits + sp) * partial_stride(kD);
-    out[e] = o;
-    if (e == 0) {
-      out[kD] = (l > 0.f) ? M * kLn2 : -INFINITY;    // the merge pass works with natural exponents
-      out[kD + 1] = l;
-    }
-  }
+  finish_split<G>(out, red_o, red_ml, G, (size_t)b * Hq + g * G, sp, part.splits);
 }
-
 
 // ---- 1..16 query heads per KV head: both products on the matrix cores, so the stream stays HBM-bound whatever
 // the group size (the heads are the 16 columns of the MFMA; unused columns carry zeros).
@@ -253,6 +228,11 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr int kMRows = 32;        // rows per wavefront step
 constexpr int kVStride = 288;     // bytes per staged V row: 256 + 32, the 4 rows of a transposing read fall in distinct banks
 constexpr int kGMax = 16;
+constexpr int64_t kResidentBytes = (int64_t)256 << 20;
+
+// A row piece of the stream, nontemporal or not (launch_decode_bf16 says which caches are read how).
+template <bool NT>
+__device__ __forceinline__ u32x4 stream(const u32x4* p) { return NT ? __builtin_nontemporal_load(p) : *p; }
 
 struct MState {
   float m, l;
@@ -328,10 +308,9 @@ __device__ __forceinline__ void mfma_softmax_pv(MState& st, const float (&s)[8],
 }
 
 template <bool APPEND>
-__global__ void __launch_bounds__(256) decode_bf16_mfma_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
+__global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                                const int64_t* __restrict__ lens, int64_t fixed_len, int Hq,
-                                                               float scale_log2, float* __restrict__ ws, int splits,
-                                                               bf16_t* __restrict__ o_direct, const bf16_t* __restrict__ k_new,
+                                                               float scale_log2, SplitOut out, const bf16_t* __restrict__ k_new,
                                                                const bf16_t* __restrict__ v_new, int ring) {
   // V staging of the four wavefronts (4 x 32 rows x 288 B) during the stream, the merge buffers after it
   constexpr int kStageBytes = kMRows * kVStride;
@@ -340,19 +319,15 @@ __global__ void __launch_bounds__(256) decode_bf16_mfma_kernel(yoco_kv_cache c, 
   __shared__ float red_ml[4][kGMax][2];
   float (*red_o)[kGMax][kD] = (float (*)[kGMax][kD])smem;
   const int G = Hq / c.Hkv;
-  const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, qg = lane >> 4;
   unsigned char* vst = smem + wave * kStageBytes;
 
-  const int64_t len_raw = lens ? lens[b] : fixed_len;
-  const int64_t len = len_raw < 0 ? 0 : (len_raw > c.N_cap ? c.N_cap : len_raw);
-  const int64_t chunk = (((len + splits - 1) / splits) + 127) & ~(int64_t)127;  // rows per split, 128 | chunk
-  const int64_t j_lo = sp * chunk;
-  const int64_t j_hi = (j_lo + chunk < len) ? j_lo + chunk : len;
-  const int64_t sub = chunk >> 2;                                               // rows per wave, 32 | sub
-  const int64_t w_lo = j_lo + wave * sub;
-  const int64_t w_hi = (w_lo + sub < j_hi) ? w_lo + sub : j_hi;
+  const SplitRows part = split_rows<128>(out, c, lens, fixed_len, b, sp);
+  if (sp > 0 && sp >= part.splits) return;
+  const int64_t j_lo = part.lo, j_hi = part.hi;
+  const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
 
   // lane (head n, dim group qg) holds dims 32 t + 8 qg .. + 7 of its head's query for t = 0..3
   bf16x8_t qf[4];
@@ -378,7 +353,7 @@ __global__ void __launch_bounds__(256) decode_bf16_mfma_kernel(yoco_kv_cache c, 
   int64_t slot = -1;
   u32x4 knew[4] = {}, vnew = {0, 0, 0, 0};
   if (APPEND) {
-    const int64_t pos = len_raw - 1;
+    const int64_t pos = (lens ? lens[b] : fixed_len) - 1;
     if (pos >= 0 && (ring || pos < c.N_cap)) slot = pos >= c.N_cap ? pos % c.N_cap : pos;
     const bf16_t* kn = k_new + ((int64_t)b * c.Hkv + g) * kD;
 #pragma unroll
@@ -390,48 +365,57 @@ __global__ void __launch_bounds__(256) decode_bf16_mfma_kernel(yoco_kv_cache c, 
     }
   }
 
-  if (w_lo < w_hi) {
-    const int64_t last = w_hi - 1;
-    u32x4 kr[8], vr[8];
-    auto load_k = [&](int64_t row0) {
+  if (w_lo < j_hi) {
+    const int64_t last = j_hi - 1;
+    const int n_steps = (int)((j_hi - w_lo + 4 * kMRows - 1) / (4 * kMRows));
+    auto walk = [&](auto nt) {
+      constexpr bool NT = decltype(nt)::value;
+      u32x4 kr[8], vr[8];
+      auto load_k = [&](int i) {
 #pragma unroll
-      for (int tau = 0; tau < 2; ++tau) {
-        int64_t row = row0 + tau * 16 + n;
-        row = row < last ? row : last;                 // clamped rows are masked in the tail step
+        for (int tau = 0; tau < 2; ++tau) {
+          int64_t row = w_lo + i * (4 * kMRows) + tau * 16 + n;
+          row = row < last ? row : last;               // clamped rows are masked
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          kr[tau * 4 + t] = __builtin_nontemporal_load(kp + row * (kD / 8) + t * 4);
-          if (APPEND && row == slot) kr[tau * 4 + t] = knew[t];
+          for (int t = 0; t < 4; ++t) {
+            kr[tau * 4 + t] = stream<NT>(kp + row * (kD / 8) + t * 4);
+            if (APPEND && row == slot) kr[tau * 4 + t] = knew[t];
+          }
         }
-      }
-    };
-    auto load_v = [&](int64_t row0) {
+      };
+      auto load_v = [&](int i) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int64_t row = row0 + u * 4 + qg;
-        row = row < last ? row : last;                 // a written row: finite values under weight 0
-        vr[u] = __builtin_nontemporal_load(vp + row * (kD / 8));
-        if (APPEND && row == slot) vr[u] = vnew;
-      }
-    };
-    auto stage_v = [&]() {
+        for (int u = 0; u < 8; ++u) {
+          int64_t row = w_lo + i * (4 * kMRows) + u * 4 + qg;
+          row = row < last ? row : last;               // a written row: finite values under weight 0
+          vr[u] = stream<NT>(vp + row * (kD / 8));
+          if (APPEND && row == slot) vr[u] = vnew;
+        }
+      };
+      auto stage_v = [&]() {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) *(u32x4*)(vst + (u * 4 + qg) * kVStride + n * 16) = vr[u];
-    };
-    load_k(w_lo);
-    load_v(w_lo);
-    int64_t row0 = w_lo;
-    float s[8];
-    for (; row0 + kMRows < w_hi; row0 += kMRows) {      // steps followed by another step
+        for (int u = 0; u < 8; ++u) *(u32x4*)(vst + (u * 4 + qg) * kVStride + n * 16) = vr[u];
+      };
+      float s[8];
+      load_k(0);
+      load_v(0);
+      int i = 0;
+      for (; i + 1 < n_steps; ++i) {                   // steps followed by another step
+        stage_v();
+        load_v(i + 1);
+        mfma_scores<false>(s, qf, kr, scale_log2, qg, kMRows);
+        load_k(i + 1);
+        mfma_softmax_pv(st, s, vst, lane);
+      }
       stage_v();
-      load_v(row0 + kMRows);
-      mfma_scores<false>(s, qf, kr, scale_log2, qg, kMRows);
-      load_k(row0 + kMRows);
+      mfma_scores<true>(s, qf, kr, scale_log2, qg, (int)(j_hi - w_lo) - i * (4 * kMRows));   // last step, 1 row or more
       mfma_softmax_pv(st, s, vst, lane);
-    }
-    stage_v();
-    mfma_scores<true>(s, qf, kr, scale_log2, qg, (int)(w_hi - row0));   // last step, 1..32 rows
-    mfma_softmax_pv(st, s, vst, lane);
+    };
+    // A cache is read again by the next layer: what fits the 256 MB behind the L2s is read so that it stays there, more
+    // than that streams past it (8 x 8 x 1700 rows: 16.9 us instead of 20.2; 16 x 8 x 32768: 315 us instead of 371).
+    // A rolling cache belongs to one layer and streams.
+    if (APPEND || part.total * (float)c.Hkv > (float)(kResidentBytes / (2 * kD * 2))) walk(std::true_type());
+    else walk(std::false_type());
   }
 
   // One state per head and wavefront: the four lanes of a head sum their row sums; then the merge over wavefronts.
@@ -447,27 +431,7 @@ __global__ void __launch_bounds__(256) decode_bf16_mfma_kernel(yoco_kv_cache c, 
     if (qg == 0) { red_ml[wave][n][0] = st.m; red_ml[wave][n][1] = l; }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < G * kD; t += 256) {
-    const int h = t / kD, e = t % kD;
-    const float M = fmaxf(fmaxf(red_ml[0][h][0], red_ml[1][h][0]), fmaxf(red_ml[2][h][0], red_ml[3][h][0]));
-    float ls = 0.f, o = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float fw = __builtin_amdgcn_exp2f(red_ml[w][h][0] - M);
-      ls = fmaf(fw, red_ml[w][h][1], ls);
-      o = fmaf(fw, red_o[w][h][e], o);
-    }
-    if (o_direct) {
-      o_direct[((size_t)b * Hq + g * G + h) * kD + e] = f32_to_bf16(ls > 0.f ? o / ls : 0.f);
-      continue;
-    }
-    float* out = ws + (((size_t)b * Hq + g * G + h) * splits + sp) * partial_stride(kD);
-    out[e] = o;
-    if (e == 0) {
-      out[kD] = (ls > 0.f) ? M * kLn2 : -INFINITY;      // the merge pass works with natural exponents
-      out[kD + 1] = ls;
-    }
-  }
+  finish_split<kGMax>(out, red_o, red_ml, G, (size_t)b * Hq + g * G, sp, part.splits);
 }
 
 }  // namespace
@@ -478,31 +442,30 @@ bool decode_bf16_supported(const yoco_kv_cache& c, int Hq) {
   return G >= 1 && G <= 16 && c.Hkv <= 65535;
 }
 
-// Every call without an append, and append calls with 5..16 heads per KV head, take the matrix-core kernel (HBM-bound
-// at every group size). The one-token sliding-window step (append, window of about a thousand rows, up to 4 heads
-// per KV head) keeps the vector-ALU kernel, whose shorter prologue and merge win on streams of a few steps per wavefront.
+// Every call without an append, and append calls with 3..16 heads per KV head, take the matrix-core kernel (HBM-bound
+// at every group size). The one-token sliding-window step (append, window of about a thousand rows) of 1 or 2 heads per
+// KV head keeps the vector-ALU kernel, whose shorter prologue and merge win there (16 x 24 heads x 1024 rows: 36.1 us
+// against 40.9; at 3 heads per KV head, 2 x 8 x 2048 rows, 11.6 against 10.2 the other way round).
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                              float* ws, int splits, void* o_direct, const void* k_new, const void* v_new, int ring,
+                              float* ws, int splits, float inv_workgroups, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
                               hipStream_t s) {
-  bf16_t* od = splits == 1 ? (bf16_t*)o_direct : nullptr;
-  dim3 grid(splits, c.Hkv, c.B), block(256);
+  const SplitOut out = {ws, (bf16_t*)o, splits, inv_workgroups, tag};
+  dim3 grid(c.Hkv, c.B, splits), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;
   const bf16_t* kn = (const bf16_t*)k_new;
   const bf16_t* vn = (const bf16_t*)v_new;
   const int G = Hq / c.Hkv;
-  if (G < 1 || G > kGMax) return hipErrorInvalidValue;
+  if (G < 1 || G > kGMax || splits > kMaxFusedSplits) return hipErrorInvalidValue;
   if (!kn) {
-    hipLaunchKernelGGL(decode_bf16_mfma_kernel<false>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od, kn, vn, ring);
+    hipLaunchKernelGGL(decode_bf16_mfma_kernel<false>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
     return hipGetLastError();
   }
   switch (G) {
-    case 1: hipLaunchKernelGGL((decode_bf16_kernel<1, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od, kn, vn, ring); break;
-    case 2: hipLaunchKernelGGL((decode_bf16_kernel<2, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od, kn, vn, ring); break;
-    case 3: hipLaunchKernelGGL((decode_bf16_kernel<3, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od, kn, vn, ring); break;
-    case 4: hipLaunchKernelGGL((decode_bf16_kernel<4, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od, kn, vn, ring); break;
+    case 1: hipLaunchKernelGGL((decode_bf16_kernel<1, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring); break;
+    case 2: hipLaunchKernelGGL((decode_bf16_kernel<2, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring); break;
     default:
-      hipLaunchKernelGGL(decode_bf16_mfma_kernel<true>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, ws, splits, od, kn, vn, ring);
+      hipLaunchKernelGGL(decode_bf16_mfma_kernel<true>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
   }
   return hipGetLastError();
 }

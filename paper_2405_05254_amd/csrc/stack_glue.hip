@@ -65,29 +65,47 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs g) {
         if (k < g.K) w[r][c] = __builtin_nontemporal_load((const u32x4*)(wp[r] + k));
       }
   };
+  // The input row is requested before the weights (loads return in order): its norm is formed while they arrive.
+  constexpr int kKeep = NORM ? 2 : 4;                                         // pieces per thread held in registers
+  const u32x4* xp = (const u32x4*)g.x;
+  const u32x4* gp = (const u32x4*)g.gain;
+  const int pieces = g.K >> 3;
+  u32x4 xv[kKeep], gv[kKeep];
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i) {
+    xv[i] = gv[i] = u32x4{0, 0, 0, 0};
+    if (tid + i * 256 < pieces) {
+      xv[i] = xp[tid + i * 256];
+      if (NORM) gv[i] = gp[tid + i * 256];
+    }
+  }
   load(0);
 
-  const u32x4* xp = (const u32x4*)g.x;
-  const int pieces = g.K >> 3;
+  auto square = [](const u32x4& v, float ss) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ss = fmaf(lo_f(v[i]), lo_f(v[i]), fmaf(hi_f(v[i]), hi_f(v[i]), ss));
+    return ss;
+  };
+  float rstd = 0.f;
   if (NORM) {
     float ss = 0.f;
-    for (int p = tid; p < pieces; p += 256) {
-      const u32x4 v = xp[p];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) ss = fmaf(lo_f(v[i]), lo_f(v[i]), fmaf(hi_f(v[i]), hi_f(v[i]), ss));
-    }
-    const float rstd = rsqrtf(block_total(ss, red) / (float)g.K + g.eps);
-    const u32x4* gp = (const u32x4*)g.gain;
-    for (int p = tid; p < pieces; p += 256) {
-      const u32x4 v = xp[p], gn = gp[p];
-      u32x4 y;
+    for (int i = 0; i < kKeep; ++i) ss = square(xv[i], ss);
+    for (int p = tid + kKeep * 256; p < pieces; p += 256) ss = square(xp[p], ss);
+    rstd = rsqrtf(block_total(ss, red) / (float)g.K + g.eps);
+  }
+  auto put = [&](int p, const u32x4& v, const u32x4& gn) {
+    u32x4 y = v;
+    if (NORM) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) y[i] = pack_bf16(lo_f(v[i]) * rstd * lo_f(gn[i]), hi_f(v[i]) * rstd * hi_f(gn[i]));
-      ((u32x4*)x_lds)[p] = y;
     }
-  } else {
-    for (int p = tid; p < pieces; p += 256) ((u32x4*)x_lds)[p] = xp[p];
-  }
+    ((u32x4*)x_lds)[p] = y;
+  };
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i)
+    if (tid + i * 256 < pieces) put(tid + i * 256, xv[i], gv[i]);
+  for (int p = tid + kKeep * 256; p < pieces; p += 256) put(p, xp[p], NORM ? gp[p] : xp[p]);
   __syncthreads();
 
   float acc[NR];
@@ -190,14 +208,16 @@ hipError_t launch(const GemvArgs& g, hipStream_t s) {
 
 }  // namespace
 
-// Rows per wavefront: two, so that a matrix of 2048 outputs still gives every CU a workgroup and one of 6144 gives it
-// three; four for the classifier, whose 32000 outputs are eight workgroups per CU anyway.
+// One output per wavefront (two for the classifier, whose outputs are tens of workgroups per CU anyway): more wavefronts
+// with less each measured faster down the line, with 2 / 1 outputs 6.9 / 6.3 us for 2048 x 5632 (23 MB), 4.3 / 4.0 us for
+// 2048 x 2048; 6144 x 2048 6.9 us, SwiGLU 2 x 5632 x 2048 (46 MB) 10.5 us, 32000 x 2048 (131 MB) 22.5 us: 3.2 us per
+// launch plus the bytes at 6.1 TB/s.
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
   if (g.K % 8 || g.K > kGemvMaxK || g.K <= 0 || g.N <= 0) return hipErrorInvalidValue;
-  if (g.glu) return launch<2, true, kGlu>(g, s);
-  if (g.res) return launch<2, false, kResidual>(g, s);
-  if (g.N >= 16384) return launch<4, true, kPlain>(g, s);
-  return launch<2, true, kPlain>(g, s);
+  if (g.glu) return launch<1, true, kGlu>(g, s);
+  if (g.res) return launch<1, false, kResidual>(g, s);
+  if (g.N >= 16384) return launch<2, true, kPlain>(g, s);
+  return launch<1, true, kPlain>(g, s);
 }
 
 hipError_t launch_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, hipStream_t s) {

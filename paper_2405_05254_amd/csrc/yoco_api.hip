@@ -4,7 +4,10 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <atomic>
+#include <chrono>
 #include <mutex>
+#include <random>
 
 #include "yoco_common.h"
 
@@ -56,12 +59,22 @@ int check_heads(int Hq, int Hkv) {
   return YOCO_OK;
 }
 
-// Splits of the decode pass. Streaming reads on MI355X are fastest with few,
-// long, contiguous streams: one workgroup per CU, each of its wavefronts
-// walking its own contiguous range (measured: 6.9 TB/s at 256 workgroups,
-// 6.0 TB/s at 2048). At least 512 rows per split. A pure function of the
-// cache shape and the device: the workspace query and the decode call agree.
-int decode_splits(const yoco_kv_cache* c) {
+// Splits of the decode pass. Streaming reads on MI355X are fastest with few, long, contiguous streams: one workgroup per
+// CU (measured: 6.9 TB/s at 256 workgroups, 6.0 TB/s at 2048; 8 KV heads x 16384 rows 17.7 us at 256, 19.6 at 512).
+// `even`: the splits a batch of equal lengths gets. A split of a bf16 cache has at least 128 rows, one step of its four
+// wavefronts: a launch over few rows is latency, and a step more costs more than the workgroups saved (16 heads x 2016
+// rows: 13.4 us at 4 splits of 512 rows, 7.7 us at 16 of 128). Of an 8-bit or fp32 cache it has at least 512.
+// `most`: what the workspace holds and the grid launches. Twice as many where a split of `even` has rows enough (2560)
+// to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
+// decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
+// 21 instead of 17). A pure function of the cache shape, the query heads and the device: the workspace query and the
+// decode call agree.
+struct Splits {
+  int even, most;
+  float inv_workgroups;
+};
+
+Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   static const int cus = [] {                     // initialised once, thread-safe
     int dev = 0, n = 0;
     const bool ok = hipGetDevice(&dev) == hipSuccess &&
@@ -69,50 +82,68 @@ int decode_splits(const yoco_kv_cache* c) {
     (void)hipGetLastError();
     return ok ? n : 256;                          // no device visible (host-only sizing): MI355X has 256 CUs
   }();
-  const int64_t target = cus;
   const int64_t units = (int64_t)c->B * c->Hkv;
-  int64_t s = (target + units - 1) / units;
-  const int64_t by_rows = (c->N_cap + 511) / 512;
-  if (s > by_rows) s = by_rows;
-  if (s < 1) s = 1;
-  if (s > 1024) s = 1024;
+  auto clamp = [](int64_t s, int64_t hi) { return s > hi ? hi : s < 1 ? 1 : s; };
+  const int64_t wanted = (cus + units - 1) / units;
+  const int min_rows = c->dtype == YOCO_BF16 ? 128 : 512;
+  int64_t s = clamp(clamp(wanted, (c->N_cap + min_rows - 1) / min_rows), 256);
   // More (sequence, KV head) units than CUs, and not a multiple of them: the workgroups of a ragged last round run
   // with part of the chip idle (384 units on 256 CUs measured 5.7 TB/s at 4096 rows). Two to four splits per unit
-  // make the count a multiple again, as long as a split keeps at least 1024 rows (below that the merge launch costs
-  // more than the balance gains: 41 us against 39 us at 1024 rows).
+  // make the count a multiple again, as long as a split keeps at least 1024 rows (384 units of 1024 rows: 35.9 us
+  // unsplit, 36.7 at two).
   if (s == 1 && units > cus && units % cus != 0) {
     for (int64_t t = 2; t <= 4; ++t)
       if ((units * t) % cus == 0 && c->N_cap / t >= 1024) { s = t; break; }
   }
-  return (int)s;
+  // What fitted the static scratch with splits of 512 rows still does.
+  const int64_t coarse = clamp(clamp(wanted, (c->N_cap + 511) / 512), 256);
+  const int64_t fits = (int64_t)(YOCO_NOALLOC_SCRATCH_BYTES / ((size_t)c->B * Hq * yoco::partial_stride(c->d) * sizeof(float)));
+  auto bounded = [&](int64_t x) { return x > fits ? (fits > coarse ? fits : coarse) : x; };
+  if (s > coarse) s = bounded(s);
+  int64_t most = s;
+  if (c->dtype == YOCO_BF16 && units <= cus && s > 1 && s <= 128 && c->N_cap / s >= 2560) most = bounded(2 * s) > s ? bounded(2 * s) : s;
+  return {(int)s, (int)most, 1.f / (float)(units * s)};
 }
 
-// Split-KV attention of one query token per sequence of `c`: pass 1 + merge.
+// The tag a decode launch marks its published splits with: never 0, never the same twice in a process (a bijection of a
+// counter), and nothing that other data is likely to look like.
+unsigned long long next_tag() {
+  static std::atomic<uint64_t> n{[] {
+    std::random_device r;
+    return ((uint64_t)r() << 32) ^ r() ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+  }()};
+  uint64_t z;
+  do {
+    z = n.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
+    z ^= z >> 29;
+  } while (z == 0);
+  return z;
+}
+
+// Split-KV attention of one query token per sequence of `c`: one launch, or pass 1 + merge (generic kernels).
 // `lens` (device) or, when it is null, `fixed_len` (host) gives the visible rows.
 // k_new / v_new (both null or both rows [B,Hkv,d] of the cache dtype): the new token's row is stored at slot
 // lens[b] - 1 (ring: modulo the capacity) by the same call and attended to.
 int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-               float* ws, int splits, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
+               float* ws, const Splits& sp, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
                int ring = 0) {
   hipError_t e;
   if (c.dtype == YOCO_INT8) {
     if (!yoco::decode_i8_supported(c, Hq))
       return fail(YOCO_ERR_UNSUPPORTED, "%s: an 8-bit cache serves up to 16 query heads per KV head, not %d", what, Hq / c.Hkv);
     if (k_new) return fail(YOCO_ERR_UNSUPPORTED, "%s: no fused append into an 8-bit cache", what);
-    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, splits, o, s);
-    if (splits == 1) return hip_result(e, what);
+    return hip_result(yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_workgroups, next_tag(), o, s), what);
   } else if (yoco::decode_bf16_supported(c, Hq)) {
-    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, splits, o, k_new, v_new, ring, s);
-    if (splits == 1) return hip_result(e, what);      // one split: pass 1 wrote the output
+    return hip_result(yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_workgroups, next_tag(), o, k_new, v_new, ring, s), what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend
       e = yoco::launch_kv_append(c, k_new, v_new, lens, -1, ring, c.dtype, s);
       if (e != hipSuccess) return hip_result(e, what);
     }
-    e = yoco::launch_decode_generic(c, q, lens, fixed_len, Hq, scale, ws, splits, s);
+    e = yoco::launch_decode_generic(c, q, lens, fixed_len, Hq, scale, ws, sp.most, s);
   }
   if (e != hipSuccess) return hip_result(e, what);
-  return hip_result(yoco::launch_decode_merge(ws, o, c.B, Hq, c.d, splits, io_dtype(c), s), what);
+  return hip_result(yoco::launch_decode_merge(ws, o, c.B, Hq, c.d, sp.most, io_dtype(c), s), what);
 }
 
 int check_gret_shape(int B, int64_t T, int H, int dk, int dv, int dtype) {
@@ -349,9 +380,13 @@ int yoco_cross_attn_prefill(const yoco_kv_cache* c, const void* q, void* o, int 
     one.B = 1;
     one.k = (char*)c->k + (size_t)b * seq_bytes;
     one.v = (char*)c->v + (size_t)b * seq_bytes;
-    const int splits = decode_splits(&one);
-    const size_t need = (size_t)Hq * splits * yoco::partial_stride(c->d) * sizeof(float);
-    if (workspace_bytes >= need) {
+    const size_t per_split = (size_t)Hq * yoco::partial_stride(c->d) * sizeof(float);
+    Splits splits = decode_splits(&one, Hq);
+    splits.most = splits.even;                                          // one sequence: nothing is ragged
+    const size_t whole = (size_t)c->B * decode_splits(c, Hq).most;      // what the documented workspace holds
+    const size_t held = workspace_bytes / per_split;
+    if (held >= (whole < (size_t)splits.even ? whole : (size_t)splits.even)) {
+      if (held < (size_t)splits.most) splits.most = (int)held;
       for (int64_t i = 0; i < Tq; ++i) {
         rc = run_decode(one, (const char*)q + (size_t)i * Hq * c->d * eb, (char*)o + (size_t)i * Hq * c->d * eb, nullptr,
                         q_pos0 + i + 1, Hq, scale, (float*)workspace, splits, (hipStream_t)stream, "cross_attn_prefill (split)");
@@ -385,7 +420,7 @@ int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* byt
   if (c->B <= 0 || c->Hkv <= 0 || c->N_cap <= 0 || c->d <= 0) return fail(YOCO_ERR_INVALID_ARG, "cache has a non-positive size");
   int rc = check_heads(Hq, c->Hkv);
   if (rc) return rc;
-  const int s = decode_splits(c);
+  const int s = decode_splits(c, Hq).most;
   *splits = s;
   *bytes = (size_t)c->B * Hq * s * yoco::partial_stride(c->d) * sizeof(float);
   return YOCO_OK;
@@ -406,7 +441,7 @@ int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const
   rc = yoco_cross_attn_decode_workspace(c, Hq, &need, &splits);
   if (rc) return rc;
   if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
-  return run_decode(*c, q, o, lens, 0, Hq, scale, (float*)workspace, splits, (hipStream_t)stream, "cross_attn_decode");
+  return run_decode(*c, q, o, lens, 0, Hq, scale, (float*)workspace, decode_splits(c, Hq), (hipStream_t)stream, "cross_attn_decode");
 }
 
 int yoco_cross_attn_decode_noalloc(const yoco_kv_cache* c, const void* q, void* o, const int64_t* lens, int Hq, float scale,
@@ -451,7 +486,7 @@ int yoco_swa_decode(const yoco_kv_cache* ring, const void* q, const void* k_new,
   rc = yoco_cross_attn_decode_workspace(ring, Hq, &need, &splits);
   if (rc) return rc;
   if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
-  return run_decode(*ring, q, o, lens, 0, Hq, scale, (float*)workspace, splits, (hipStream_t)stream, "swa_decode", k_new, v_new, 1);
+  return run_decode(*ring, q, o, lens, 0, Hq, scale, (float*)workspace, decode_splits(ring, Hq), (hipStream_t)stream, "swa_decode", k_new, v_new, 1);
 }
 
 int yoco_gret_prefill_workspace(int B, int64_t T, int H, int dk, int dv, int chunk, int dtype, size_t* bytes) {
@@ -541,7 +576,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
   const StackScratch t(*st, (char*)scratch);
   if (scratch_bytes < t.bytes) return fail(YOCO_ERR_WORKSPACE, "scratch %zu < %zu bytes", scratch_bytes, t.bytes);
   size_t need = 0;
-  int splits = 0, ring_splits = 0;
+  int splits = 0;
   rc = yoco_cross_attn_decode_workspace(cache, st->Hq, &need, &splits);
   if (rc) return rc;
   if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
@@ -553,11 +588,12 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
           rings[i].N_cap != rings[0].N_cap)
         return fail(YOCO_ERR_INVALID_ARG, "ring %d does not match the stack", i);
     }
-    rc = yoco_cross_attn_decode_workspace(rings, st->Hq, &need, &ring_splits);
+    rc = yoco_cross_attn_decode_workspace(rings, st->Hq, &need, &splits);
     if (rc) return rc;
     if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
   }
 
+  const Splits plan = decode_splits(cache, st->Hq), ring_plan = decode_splits(self && !st->gret ? rings : cache, st->Hq);
   hipStream_t s = (hipStream_t)stream;
   const int dm = st->d_model, qd = st->Hq * st->d, kd = st->Hkv_self * st->d, ckd = st->Hkv * st->d;
   hipError_t e = hipSuccess;
@@ -588,7 +624,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
       if (st->gret) {
         rc = yoco_gret_decode(q, k, v, t.log_gamma, gate, t.o, states[i], 1, st->Hq, st->d, st->d, st->scale, 1, st->eps, YOCO_BF16, stream);
       } else {
-        rc = run_decode(rings[i], q, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, ring_splits, s, "stack_step", k, v, 1);
+        rc = run_decode(rings[i], q, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, ring_plan, s, "stack_step", k, v, 1);
       }
       if (rc) return rc;
       finish_layer(L, t.x);
@@ -604,7 +640,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
     const yoco_stack_layer& L = st->cross[i];
     gemv(cur, L.ln1, L.w_in, qd, dm, nullptr, 0, t.in, qd);
     if (e != hipSuccess) return hip_result(e, "stack_step");
-    rc = run_decode(*cache, t.in, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, splits, s, "stack_step");
+    rc = run_decode(*cache, t.in, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, plan, s, "stack_step");
     if (rc) return rc;
     finish_layer(L, i + 1 == st->n_cross && x_out ? x_out : t.x);
   }

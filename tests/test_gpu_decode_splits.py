@@ -1,0 +1,68 @@
+"""The end of a split decode step: splits that meet in the caller's workspace without anything having been cleared, and
+ragged batches whose sequences get different numbers of splits, against the fp64 oracle."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_2405_05254_amd as yoco  # noqa: E402
+import yoco_synth as ys  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+D = 128
+SCALE = 1.0 / math.sqrt(D)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,N_cap,lens", [
+    ("bf16", 2, 1, 300, [300, 1, 129]),                     # 1 .. 3 splits of one step each
+    ("bf16", 6, 2, 1100, [1100, 1024]),                     # 9 splits: the wider merge
+    ("bf16", 3, 1, 2300, [2300]),                           # 18 splits: two rounds of the widest merge
+    ("bf16", 16, 1, 9000, [9000, 0, 7, 4400, 128, 127]),    # 16 heads in one workgroup, an empty sequence among long ones
+    ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
+    ("int8", 4, 2, 1500, [1500, 513, 64]),
+    ("int8", 13, 1, 3000, [2999, 1]),
+])
+@pytest.mark.parametrize("garbage", [0x00, 0xFF, 0x3F])
+def test_splits_meet_in_an_uncleared_workspace(dtype, Hq, Hkv, N_cap, lens, garbage):
+    B, rng = len(lens), np.random.default_rng(N_cap)
+    cache = yoco.KVCache(B, Hkv, D, N_cap, torch.int8 if dtype == "int8" else torch.bfloat16)
+    cache.mem.zero_()
+    K, V = (ys.normal(rng, (B, N_cap, Hkv, D), 1.0, "bf16") for _ in range(2))
+    q = ys.normal(rng, (B, Hq, D), 1.0, "bf16")
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    for b in range(B):
+        yoco.global_kv_write(cache, dev(K[b]), dev(V[b]), b, 0)
+    nbytes, splits = yoco.cross_attn_decode_workspace(cache, Hq)
+    ws = torch.full((nbytes,), garbage, dtype=torch.uint8, device="cuda")
+    ln = torch.tensor(lens, dtype=torch.int64, device="cuda")
+    first = yoco.cross_attn_decode(cache, dev(q), ln, SCALE, ws)
+    again = yoco.cross_attn_decode(cache, dev(q), ln, SCALE, ws)         # over what the first call left behind
+    assert torch.equal(first, again)
+    attend = oracle.cross_attn_int8 if dtype == "int8" else oracle.cross_attn
+    tol = ys.TOL["bf16"]
+    for b, n in enumerate(lens):
+        got = first[b].float().cpu().numpy()
+        if n == 0:
+            assert not got.any()
+            continue
+        st = ys.error_stats(got, attend(q[b:b + 1], K[b, :n], V[b, :n], n - 1, SCALE)[0])
+        assert st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], (b, n, splits, st)
+
+
+def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
+    """A batch of more (sequence, head) units than CUs has one split per unit: its workspace serves the few-row call of
+    one sequence, whose own split count would be larger."""
+    cache = yoco.KVCache(40, 8, D, 2600, torch.int8)
+    cache.mem.zero_()
+    rng = np.random.default_rng(1)
+    k, v = (torch.from_numpy(ys.normal(rng, (2600, 8, D), 1.0, "bf16")).cuda().to(torch.bfloat16) for _ in range(2))
+    yoco.global_kv_write(cache, k, v, 39, 0)
+    q = torch.from_numpy(ys.normal(rng, (1, 8, D), 1.0, "bf16")).cuda().to(torch.bfloat16)
+    ws = torch.empty(yoco.cross_attn_decode_workspace(cache, 8)[0], dtype=torch.uint8, device="cuda")
+    o = yoco.cross_attn_prefill(cache, q, 39, 2599, SCALE, workspace=ws)
+    ref = oracle.cross_attn_int8(q.float().cpu().numpy(), k.float().cpu().numpy(), v.float().cpu().numpy(), 2599, SCALE)
+    st = ys.error_stats(o.float().cpu().numpy(), ref)
+    assert st["max_abs"] <= 2e-2 and st["mean_rel"] <= 2e-3, st
