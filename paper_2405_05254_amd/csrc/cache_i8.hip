@@ -278,26 +278,48 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * 64;                  // the wavefronts take turns at the split's blocks
 
+  // The query of head n, as stored: dims 64 half + 16 qg ..
+  u32x4 qraw[2][2] = {};
+  if (n < G) {
+    const bf16_t* qp = q + ((int64_t)b * Hq + g * G + n) * kD + qg * 16;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      qraw[half][0] = *(const u32x4*)(qp + half * 64);
+      qraw[half][1] = *(const u32x4*)(qp + half * 64 + 8);
+    }
+  }
+  const int64_t plane = ((int64_t)b * c.Hkv + g) * (i8_plane_bytes(c.N_cap) / 16);   // in 16-byte units
+  const u32x4* kp = (const u32x4*)c.k + plane;
+  const u32x4* vp = (const u32x4*)c.v + plane;
+
+  Block nx;
+      auto load = [&](int64_t row0) {                       // row0 is a multiple of 64
+        const int64_t base = (row0 >> 6) * (kI8BlockBytes / 16);
+  #pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          nx.k[u] = __builtin_nontemporal_load(kp + base + u * 64 + lane);
+          nx.v[u] = __builtin_nontemporal_load(vp + base + u * 64 + lane);
+        }
+        nx.ks = __builtin_nontemporal_load((const float*)(kp + base + kI8ScaleOffset / 16) + lane);
+        nx.vs = __builtin_nontemporal_load((const float*)(vp + base + kI8ScaleOffset / 16) + lane);
+      };
+  load(w_lo < j_hi ? w_lo : 0);                           // in flight while the query is coded; a wavefront without rows loads block 0
+  // (unconditional: behind a branch the compiler waits for all of it before the first use of the query. 8 heads x 32768
+  // rows 18.7 -> 17.6 us a layer, 8 ragged sequences of up to 3000 rows 13.2 -> 11.9 us)
+
   // The query of head n as two int8 operands: dims 64 half + 16 qg + j in byte j of half `half`.
   i32x4 qhi[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, qlo[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   float qs = 0.f;
   {
     float x[32];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) x[i] = 0.f;
-    if (n < G) {
-      const bf16_t* qp = q + ((int64_t)b * Hq + g * G + n) * kD + qg * 16;
+    for (int half = 0; half < 2; ++half)
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const u32x4 a = *(const u32x4*)(qp + half * 64), bq = *(const u32x4*)(qp + half * 64 + 8);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const unsigned w = i < 4 ? a[i] : bq[i - 4];
-          x[half * 16 + 2 * i] = __uint_as_float(w << 16);
-          x[half * 16 + 2 * i + 1] = __uint_as_float(w & 0xffff0000u);
-        }
+      for (int i = 0; i < 8; ++i) {
+        const unsigned w = qraw[half][i >> 2][i & 3];
+        x[half * 16 + 2 * i] = __uint_as_float(w << 16);
+        x[half * 16 + 2 * i + 1] = __uint_as_float(w & 0xffff0000u);
       }
-    }
     float amax = 0.f;
 #pragma unroll
     for (int i = 0; i < 32; ++i) amax = fmaxf(amax, fabsf(x[i]));
@@ -332,23 +354,7 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
 #pragma unroll
   for (int tt = 0; tt < 8; ++tt) st.o[tt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-  const int64_t plane = ((int64_t)b * c.Hkv + g) * (i8_plane_bytes(c.N_cap) / 16);   // in 16-byte units
-  const u32x4* kp = (const u32x4*)c.k + plane;
-  const u32x4* vp = (const u32x4*)c.v + plane;
-
   if (w_lo < j_hi) {
-    Block nx;
-    auto load = [&](int64_t row0) {                       // row0 is a multiple of 64
-      const int64_t base = (row0 >> 6) * (kI8BlockBytes / 16);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        nx.k[u] = __builtin_nontemporal_load(kp + base + u * 64 + lane);
-        nx.v[u] = __builtin_nontemporal_load(vp + base + u * 64 + lane);
-      }
-      nx.ks = __builtin_nontemporal_load((const float*)(kp + base + kI8ScaleOffset / 16) + lane);
-      nx.vs = __builtin_nontemporal_load((const float*)(vp + base + kI8ScaleOffset / 16) + lane);
-    };
-    load(w_lo);
     int64_t row0 = w_lo;
     for (; row0 + 256 < j_hi; row0 += 256) {
       const Block cur = nx;

@@ -154,7 +154,8 @@ __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)
 
   if (S <= 4) merge_splits<4>(out, G, head0, S);
   else if (S <= 8) merge_splits<8>(out, G, head0, S);
-  else merge_splits<16>(out, G, head0, S);
+  else if (S <= 16) merge_splits<16>(out, G, head0, S);
+  else merge_splits<32>(out, G, head0, S);
   for (int s = threadIdx.x; s < S; s += 256) put_u64(tags + s * stride, 0ull);
 }
 
