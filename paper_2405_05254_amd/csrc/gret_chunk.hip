@@ -2,31 +2,27 @@
 // equivalence with Eq. 4 and Eq. 5 is appendix B). bf16, dk = dv = 128.
 //
 // With G_j the sum of log2(gamma) from the first row of j's chunk up to and
-// including j, chunk [i] of one head computes
-//   U_i      = K^T (V * 2^(G_last - G_j))                local state of the chunk
-//   R_i      = U_i + 2^G_last R_{i-1}                    state after the chunk
-//   O_[i]    = scale * ((Q K^T * D) V + (Q R_{i-1}) * 2^(G_j)),  D(j,k) = 2^(G_j - G_k), k <= j
-// in four launches:
-//   0  cumulative decays G (one wavefront per chunk)
-//   1  the states, scanned inside a segment: a workgroup walks a run of consecutive chunks of one head with the
-//      running state L in its accumulators (L <- 2^G_last L + U_i after each chunk; fp16 MFMA, V scaled while
-//      staged) and leaves, for every chunk but the first of the run, the state before the chunk *within the
-//      segment* in fp32. U_i itself never reaches memory. The run's total goes out in fp32 as well.
-//   2  the scan across segments (a few states per head, element-wise), leaving the state before each segment
-//   3  outputs, one workgroup per 128 query rows: R_{i-1} = (state before the chunk within its segment) +
-//      2^(decay since the segment's start) * (state before the segment), formed in fp32 while it is staged and
-//      split into two bf16 planes hi + lo (16 significant bits, fp32's exponent range: no scaling to track, and
-//      both feed the bf16 MFMA against the bf16 Q as it stands); the cross-chunk product R_{i-1}^T Q^T (bf16 MFMA on both planes) scaled per
-//      row, then the key tiles of the chunk up to the diagonal as in the sliding-window kernel, with the decay
-//      2^(G_j - G_k) in place of the softmax; optional GroupNorm and swish gate (Eq. 7) before the store.
-// States are stored transposed ([dv][dk]); this is also the layout of
-// the caller's state_in / state_out.
+// including j, a chunk of rows that finds the state S before it computes
+//   O = scale * ((Q K^T * D) V + (Q S) * 2^(G_j)),   D(j,k) = 2^(G_j - G_k), k <= j
+//   S <- 2^(G_last) S + K^T (V * 2^(G_last - G_j))
+// The sequence is cut into segments, about two workgroups' worth per CU over all heads, and a segment into chunks of 64
+// rows (the caller's chunk size plays no part: the result does not depend on it). Launches:
+//   1  what a segment adds to the state, for all segments but the last (reads K and V)
+//   2  the scan across segments, element-wise and in place: the state before each segment. Up to three earlier segments
+//      are folded by launch 3 itself.
+//   3  outputs: a workgroup walks its segment with the state in its MFMA accumulators, and hands over the final state.
+// Nothing but one state per segment touches memory in between: Q, gate and O move once, K and V twice (1.41 GB at
+// T = 32768 x 24 heads with the gate, against 2.1 GB of a form that wrote and read one state per 256-row chunk). Bound by
+// HBM: 1.01 GB algorithmic.
 //
-// Orientation, tiling, LDS swizzles, the fp16 second product (P rounded to fp16,
-// V converted while staged) are those of swa_mfma.hip, for the same reasons.
-// Launch 1 converts K as well (both operands of its product are fp16), and the
-// weights scale * s * decay are not bounded by 1 as softmax weights are: |k|,
-// |v| and |scale * q.k| of 65520 or more are outside these kernels' domain.
+// Partition: wavefront w owns dims 32 w .. 32 w + 31 of V, of the outputs and of the state, S[128 ek][32 ev] with ev
+// along the lanes. A state accumulator is then, rounded to bf16, the A operand of O^T = S^T Q^T as it stands (the rows of
+// S are assigned to dims ek so that a lane's eight registers are eight consecutive ones), and the V^T operand of
+// O^T += V^T P^T is the B operand of S += K^T V: no operand of either product of the state passes through LDS.
+// The scores of a chunk are formed once, a 32 x 32 block per wavefront, and shared through LDS in operand order.
+//
+// Precision: every operand that is not bf16 by nature (scores times decay, V times decay, the state) is split into a
+// bf16 high and low part, 16 significant bits, two products each; accumulation is fp32.
 #include "mfma_util.h"
 #include "yoco_common.h"
 
@@ -35,461 +31,531 @@ namespace yoco {
 namespace {
 
 constexpr int kD = 128;
-constexpr int kBN = 64;                       // keys per tile
-constexpr int kBM = 128;                      // query rows per workgroup of launch 3
-constexpr int kTileBytes = kBN * kD * 2;      // 16 KiB
+constexpr int kC = 64;                        // rows per chunk
+constexpr int kTileBytes = kC * kD * 2;       // 16 KiB
 constexpr int kState = kD * kD;               // elements of one state
-constexpr int kMaxChunk = 1024;
+constexpr int kMaxChunk = 1024;               // of the caller's chunk size
+constexpr int kFold = 3;                      // earlier segments an output workgroup adds up itself
 constexpr float kLog2e = 1.4426950408889634f;
 
-struct ChunkArgs {
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+struct SegArgs {
   GretView a;
-  int chunk, nc;       // rows per chunk, chunks per sequence
-  int seg, nseg;       // chunks per segment, segments per sequence
-  float* gc;           // [B][H][nc * chunk]   cumulative log2 decay within the chunk, inclusive
-  float* rw;           // [B][H][nc][dv][dk]   state before the chunk within its segment
-  float* seg_total;    // [B][H][nseg][dv][dk] state a segment adds, started from zero
-  float* seg_init;     // [B][H][nseg][dv][dk] state before the segment
-  float* gpre;         // [B][H][nc]           log2 decay from the start of the chunk's segment to the start of the chunk
-  float* gseg;         // [B][H][nseg]         log2 decay over the whole segment
+  int n_chunks, per_seg, nseg;   // chunks per sequence and per segment, segments per sequence
+  float* state;                  // [B][H][nseg - 1][dv][dk]: what segment s adds; after the scan, the state before segment s + 1
+  float* decay;                  // [B][H][nseg - 1]: log2 decay over segment s
+  float* init;                   // [B][H][dv][dk]: launch 1's copy of state_in, which launch 3 may overwrite (state_out); null without one
 };
 
-__device__ __forceinline__ int64_t last_row_of_chunk(const ChunkArgs& g, int c) {
-  const int64_t e = (int64_t)(c + 1) * g.chunk;
-  return (e < g.a.T ? e : g.a.T) - 1;
+__device__ __forceinline__ float lo_f(unsigned x) { return __uint_as_float(x << 16); }
+__device__ __forceinline__ float hi_f(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
+// (x0, x1) = hi + lo in packed bf16; the remainders as dot products of hi with (-1, 0) and (0, -1), one instruction each.
+// (The constants pass through registers: as a literal, the compiler hands (-1, 0) to the instruction as (0, -1).)
+__device__ __forceinline__ void split_bf16(float x0, float x1, unsigned& hi, unsigned& lo) {
+  unsigned first = 0x0000bf80u, second = 0xbf800000u;
+  asm("" : "+s"(first), "+s"(second));
+  hi = pack_bf16(x0, x1);
+  const bf16x2 h = __builtin_bit_cast(bf16x2, hi);
+  lo = pack_bf16(__builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, first), x0, false),
+                 __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, second), x1, false));
+}
+__device__ __forceinline__ f32x16 mfma(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// ---- launch 0: G. One wavefront per (chunk, head, sequence); lane l owns chunk / 64 consecutive rows.
-__global__ void __launch_bounds__(64) gret_cumdecay_kernel(ChunkArgs g) {
-  const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x, rpl = g.chunk / 64;
-  const int64_t row0 = (int64_t)c * g.chunk + lane * rpl;
-  float x[kMaxChunk / 64];
-  float acc = 0.f;
+// Byte offsets of 16-byte piece c16 of row `row` in a [64][128] bf16 tile: for row-wise operand reads (pieces XOR
+// row & 15), and for transposing reads (32-byte pieces XOR row & 7).
+__device__ __forceinline__ int row_off(int row, int c16) { return row * 256 + ((c16 ^ (row & 15)) << 4); }
+__device__ __forceinline__ int tr_off(int row, int c16) { return row * 256 + (((((c16 >> 1) ^ (row & 7)) << 1) | (c16 & 1)) << 4); }
+
+// Operand of 32 dims x 16 rows from a tile: lane l gets one dim of block blk and, with hf = l / 32, the rows
+// 16 t + 4 hf + 0..3, then 16 t + 8 + 4 hf + 0..3. `base` says which dim: in order, or with bits 2 and 3 of the dim exchanged.
+__device__ __forceinline__ int tr_base(int lane, bool exchanged) {
+  const int s16 = lane & 15, db = (lane >> 4) & 1, z = (lane >> 5) * 4 + (s16 >> 2), p = s16 & 3;
+  return z * 256 + ((db ^ z) << 5) + ((exchanged ? ((p & 1) << 1) | (p >> 1) : p) << 3);
+}
+__device__ __forceinline__ u32x4 tr_frag(const char* tile, int base, int blk, int t) {
+  lds_char* p = (lds_char*)tile + (base ^ (blk << 6)) + t * 16 * 256;
+  const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
+  const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 8 * 256)));
+  return {a[0], a[1], b[0], b[1]};
+}
+
+// The V operand of 16 rows (step t) times their weights in LDS, as high and low part.
+__device__ __forceinline__ void weigh(const u32x4& vf, const float* w, int t, int hf, u32x4& vh, u32x4& vl) {
+  const f32x4 w0 = *(const f32x4*)(w + t * 16 + hf * 4), w1 = *(const f32x4*)(w + t * 16 + 8 + hf * 4);
 #pragma unroll
-  for (int i = 0; i < kMaxChunk / 64; ++i) {
-    if (i < rpl) {
-      const int64_t row = row0 + i;
-      acc += row < g.a.T ? g.a.log_gamma[((int64_t)b * g.a.T + row) * g.a.H + h] * kLog2e : 0.f;
-      x[i] = acc;
-    }
+  for (int i = 0; i < 4; ++i) {
+    const f32x4& ww = i < 2 ? w0 : w1;
+    unsigned h, l;
+    split_bf16(lo_f(vf[i]) * ww[(i & 1) * 2], hi_f(vf[i]) * ww[(i & 1) * 2 + 1], h, l);
+    vh[i] = h;
+    vl[i] = l;
   }
-  float incl = acc;
-  for (int o = 1; o < 64; o <<= 1) {
-    const float t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  const float before = incl - acc;
-  float* out = g.gc + (((int64_t)b * g.a.H + h) * g.nc + c) * g.chunk + lane * rpl;
+}
+// S += K^T (V * w) for the 16 rows of step t.
+__device__ __forceinline__ void add_rows(f32x16 (&S)[4], const char* k_t, int kbase, const u32x4& vh, const u32x4& vl, int t) {
+  u32x4 kf[4];
 #pragma unroll
-  for (int i = 0; i < kMaxChunk / 64; ++i)
-    if (i < rpl) out[i] = x[i] + before;
+  for (int eb = 0; eb < 4; ++eb) kf[eb] = tr_frag(k_t, kbase, eb, t);
+#pragma unroll
+  for (int eb = 0; eb < 4; ++eb) S[eb] = mfma(kf[eb], vh, S[eb]);
+#pragma unroll
+  for (int eb = 0; eb < 4; ++eb) S[eb] = mfma(kf[eb], vl, S[eb]);
 }
 
-// Byte offset of 16-byte chunk c16 of row `row` in a 64-row tile, "transposing read" layout
-// (32-byte chunk XOR row & 7), and the per-lane base of the transposing fragment reads.
-__device__ __forceinline__ int tr_store_off(int row, int c16) {
-  return row * 256 + (((((c16 >> 1) ^ (row & 7)) << 1) | (c16 & 1)) << 4);
+// Workgroup -> (head, segment, sequence). Heads vary fastest, so that workgroups that run together read neighbouring
+// 256-byte pieces of the same rows; and the workgroups, dealt to the 8 XCDs round robin, are renumbered so that each XCD
+// has a run of them, all heads among it: with one head in eight per XCD, its rows (24 heads apart) fall into 2 of the 16
+// channels of its L2, and both passes stop at 4.2 TB/s.
+struct Unit {
+  int h, sg, b;
+};
+__device__ __forceinline__ Unit unit_of(int H, int segs) {
+  const int total = gridDim.x, bid = blockIdx.x, per = total >> 3, rem = total & 7, xcd = bid & 7;
+  const int n = xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
+  return {n % H, n / H % segs, n / (H * segs)};
 }
 
-// A (or B) operand fragment of 32 dims x 16 keys from a [64 keys][128 dims] fp16 tile: lane l gets dim
-// blk * 32 + l % 32 and, with hf = l / 32, the keys t*16 + hf*4 + 0..3 then t*16 + 8 + hf*4 + 0..3.
-__device__ __forceinline__ f16x8 tr_frag(lds_char* tile, int base, int blk, int t) {
-  const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(tile + (base ^ (blk << 6)) + (t * 16) * 256));
-  const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(tile + (base ^ (blk << 6)) + (t * 16 + 8) * 256));
-  const u32x2 a0 = __builtin_bit_cast(u32x2, v0), a1 = __builtin_bit_cast(u32x2, v1);
-  const u32x4 vu = {a0[0], a0[1], a1[0], a1[1]};
-  return __builtin_bit_cast(f16x8, vu);
+// Inclusive sum of one value per lane over the wavefront: within rows of 16 lanes, then a row's total into the next one,
+// then the lower half's total into the upper half.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_scan(float x) {
+  x = dpp_add<0x111, 0xf>(x);    // row_shr:1
+  x = dpp_add<0x112, 0xf>(x);    // row_shr:2
+  x = dpp_add<0x114, 0xf>(x);    // row_shr:4
+  x = dpp_add<0x118, 0xf>(x);    // row_shr:8
+  x = dpp_add<0x142, 0xa>(x);    // row_bcast:15 into rows 1 and 3
+  x = dpp_add<0x143, 0xc>(x);    // row_bcast:31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ float lane63(float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63)); }
+
+// A state in memory ([ev][ek], fp32) against a wavefront's accumulators: lane (hf, lq) holds ev = 32 wave + lq and, in
+// registers 8 u .. 8 u + 7 of block eb, ek = 32 eb + 16 u + 8 hf + 0..7.
+template <typename F>
+__device__ __forceinline__ void each_piece(int wave, int lane, F f) {
+  const int off = (wave * 32 + (lane & 31)) * kD + (lane >> 5) * 8;
+#pragma unroll
+  for (int eb = 0; eb < 4; ++eb)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) f(eb, u * 8 + p * 4, off + eb * 32 + u * 16 + p * 4);
+}
+__device__ __forceinline__ void store_state(float* dst, const f32x16 (&S)[4], int wave, int lane) {
+  each_piece(wave, lane, [&](int eb, int r, int off) {
+    *(f32x4*)(dst + off) = f32x4{S[eb][r], S[eb][r + 1], S[eb][r + 2], S[eb][r + 3]};
+  });
 }
 
-// ---- launch 1: the states of a segment. Workgroup = 4 wavefronts, each a 64 x 64 block of L^T = sum (V * w)^T K;
-// at every chunk boundary inside the segment the block is stored and decayed by the next chunk's 2^G_last.
-__global__ void __launch_bounds__(256, 3) gret_chunk_state_kernel(ChunkArgs g) {
-  __shared__ __attribute__((aligned(1024))) char k_t[kTileBytes], v_t[kTileBytes];
+// ---- launch 1. The segment's chunks are walked from the last to the first, every row weighted by its decay to the end of
+// the segment, so the accumulators need no rescaling, and the rows read last are the ones launch 3 starts with.
+__global__ void __launch_bounds__(256, 2) gret_segment_kernel(SegArgs g) {
+  __shared__ __attribute__((aligned(1024))) char k_t[2][kTileBytes], v_t[2][kTileBytes];
+  __shared__ __attribute__((aligned(16))) float w_t[2][kC];
   const GretView& a = g.a;
-  // heads vary fastest over the grid: workgroups that run together read neighbouring 256-byte segments of the same rows
-  const int h = blockIdx.x, sg = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const Unit un = unit_of(a.H, g.nseg - 1);
+  const int h = un.h, sg = un.sg, b = un.b;
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int hf = lane >> 5, lq = lane & 31;
-  const int64_t bh = (int64_t)b * a.H + h;
-  const int first = sg * g.seg;                                       // first chunk of the segment
-  const int c_end = first + g.seg < g.nc ? first + g.seg : g.nc;
-  const int64_t r0 = (int64_t)first * g.chunk;
-  const int64_t last = last_row_of_chunk(g, c_end - 1);               // last row of the segment
-  const float* gc = g.gc + bh * g.nc * g.chunk;                       // indexed by the row within the sequence
-  const bf16_t* kg = (const bf16_t*)a.k + ((int64_t)b * a.T * a.H + h) * kD;
-  const bf16_t* vg = (const bf16_t*)a.v + ((int64_t)b * a.T * a.H + h) * kD;
-  const int64_t row_stride = (int64_t)a.H * kD;
-
+  const int c_lo = sg * g.per_seg, c_hi = c_lo + g.per_seg;           // never the last segment: all its rows exist
+  const int64_t row_bytes = (int64_t)a.H * kD * 2, head0 = ((int64_t)b * a.T * a.H + h) * kD * 2;
   const int c16 = tid & 15, srow = tid >> 4;
-  const int s16 = lane & 15, db = (lane >> 4) & 1, z = hf * 4 + (s16 >> 2);
-  const int fbase = z * 256 + ((db ^ z) << 5) + ((s16 & 3) << 3);
-  const int mb0 = (wave >> 1) * 2, nb0 = (wave & 1) * 2;
+  const char* kg = (const char*)a.k + head0;
+  const char* vg = (const char*)a.v + head0;
+  const float* lg = a.log_gamma + (int64_t)b * a.T * a.H + h;
+  const int kbase = tr_base(lane, true), vbase = tr_base(lane, false);
+  const int st_off = tr_off(srow, c16);                               // row srow + 16 i is 4096 i further
+  uint32_t off[4];                                                    // a thread's pieces from the start of a chunk
+#pragma unroll
+  for (int i = 0; i < 4; ++i) off[i] = (uint32_t)(srow + 16 * i) * (uint32_t)row_bytes + (uint32_t)(c16 * 16);
 
-  f32x16 acc[2][2];
+  f32x16 S[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int eb = 0; eb < 4; ++eb)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int tiles_per_chunk = g.chunk / kBN;
-  const int n_tiles = (int)((last - r0) / kBN) + 1;
-  u32x4 kr[4], vr[4];
-  float w[4];
-  auto load_tile = [&](int t0) {
-    const float g_last = gc[last_row_of_chunk(g, first + t0 / tiles_per_chunk)];
+    for (int r = 0; r < 16; ++r) S[eb][r] = 0.f;
+  struct Rows { u32x4 k[4], v[4]; float lg; } even, odd;               // two chunks in flight
+  float after = 0.f;                                                   // log2 decay of the later chunks (wavefront 0 keeps it)
+  auto load = [&](Rows& x, int c) {
+    const int64_t r0 = (int64_t)c * kC;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int64_t row = r0 + (int64_t)t0 * kBN + srow + 16 * i;
-      const int64_t grow = row <= last ? row : last;                // rows past the end weigh nothing
-      w[i] = row <= last ? __builtin_amdgcn_exp2f(g_last - gc[grow]) : 0.f;
-      kr[i] = *(const u32x4*)(kg + grow * row_stride + c16 * 8);
-      vr[i] = *(const u32x4*)(vg + grow * row_stride + c16 * 8);
+      x.k[i] = __builtin_nontemporal_load((const u32x4*)(kg + r0 * row_bytes + off[i]));
+      x.v[i] = __builtin_nontemporal_load((const u32x4*)(vg + r0 * row_bytes + off[i]));
     }
+    x.lg = wave == 0 ? lg[(r0 + lane) * a.H] : 0.f;
   };
-  load_tile(0);
-  float gsum = 0.f;                                                  // log2 decay from the segment's start (thread 0 keeps it)
-  if (tid == 0) g.gpre[bh * g.nc + first] = 0.f;
-  for (int t0 = 0; t0 < n_tiles; ++t0) {
-    if (t0 > 0 && t0 % tiles_per_chunk == 0) {                       // a chunk of the segment ends here
-      const int c = first + t0 / tiles_per_chunk;                    // the chunk that starts
-      const float decay = __builtin_amdgcn_exp2f(gc[last_row_of_chunk(g, c)]);
-      int lane_off = (mb0 * 32 + hf * 4) * kD + nb0 * 32 + lq;       // kept local: 64 hoisted store addresses cost an occupancy step
-      asm volatile("" : "+v"(lane_off));
-      float* rw = g.rw + (bh * g.nc + c) * kState + lane_off;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            rw[(i * 32 + (r >> 2) * 8 + (r & 3)) * kD + j * 32] = acc[i][j][r];
-            acc[i][j][r] *= decay;
-          }
-      if (tid == 0) g.gpre[bh * g.nc + c] = (gsum += gc[last_row_of_chunk(g, c - 1)]);
+  auto chunk = [&](Rows& x, int c, char* k_d, char* v_d, float* w_d) {
+    if (wave == 0) {
+      const float G = wave_scan(x.lg * kLog2e), last = lane63(G);
+      w_d[lane] = __builtin_amdgcn_exp2f(last - G + after);
+      after += last;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int lrow = srow + 16 * i;
-      u32x4 kh, vh;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        kh[e] = bf16x2_to_f16x2(kr[i][e]);
-        vh[e] = pack_f16(__uint_as_float(vr[i][e] << 16) * w[i], __uint_as_float(vr[i][e] & 0xffff0000u) * w[i]);
-      }
-      *(u32x4*)(k_t + tr_store_off(lrow, c16)) = kh;
-      *(u32x4*)(v_t + tr_store_off(lrow, c16)) = vh;
+      *(u32x4*)(k_d + st_off + i * 4096) = x.k[i];
+      *(u32x4*)(v_d + st_off + i * 4096) = x.v[i];
     }
-    if (t0 + 1 < n_tiles) load_tile(t0 + 1);                        // in flight during the products
+    load(x, c - 2 > c_lo ? c - 2 : c_lo);                              // in flight during the products of two chunks
     __syncthreads();
+    u32x4 vh[4], vl[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const f16x8 a0 = tr_frag((lds_char*)v_t, fbase, mb0, t), a1 = tr_frag((lds_char*)v_t, fbase, mb0 + 1, t);
-      const f16x8 b0 = tr_frag((lds_char*)k_t, fbase, nb0, t), b1 = tr_frag((lds_char*)k_t, fbase, nb0 + 1, t);
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    __syncthreads();
+    for (int t = 0; t < 4; ++t) weigh(tr_frag(v_d, vbase, wave, t), w_d, t, hf, vh[t], vl[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) add_rows(S, k_d, kbase, vh[t], vl[t], t);
+  };
+  load(even, c_hi - 1);
+  load(odd, c_hi - 2 > c_lo ? c_hi - 2 : c_lo);
+  for (int c = c_hi - 1; c >= c_lo; c -= 2) {
+    chunk(even, c, k_t[0], v_t[0], w_t[0]);
+    if (c - 1 < c_lo) break;
+    chunk(odd, c - 1, k_t[1], v_t[1], w_t[1]);
   }
-  if (tid == 0) g.gseg[bh * g.nseg + sg] = gsum + gc[last];
-  float* u = g.seg_total + (bh * g.nseg + sg) * kState;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = (mb0 + i) * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
-        u[row * kD + (nb0 + j) * 32 + lq] = acc[i][j][r];
-      }
+  const int64_t slot = ((int64_t)b * a.H + h) * (g.nseg - 1) + sg;
+  store_state(g.state + slot * kState, S, wave, lane);
+  if (tid == 0) g.decay[slot] = after;
+  if (g.init && sg == 0) {
+    const int64_t at = ((int64_t)b * a.H + h) * kState;
+    for (int e = tid * 4; e < kState; e += 1024) *(f32x4*)(g.init + at + e) = *(const f32x4*)(a.state_in + at + e);
+  }
 }
 
-// ---- launch 2: scan over the segments; thread owns 4 consecutive elements of the state. The totals of a group of
-// segments are loaded together (independent addresses) before the dependent updates run.
-__global__ void __launch_bounds__(256) gret_state_scan_kernel(ChunkArgs g) {
+// ---- launch 2: scan over the segments, in place; thread owns 4 consecutive elements of the state. A group of segments is
+// loaded together (independent addresses) before the dependent updates run.
+__global__ void __launch_bounds__(256) gret_state_scan_kernel(SegArgs g) {
   constexpr int kAhead = 8;
-  const GretView& a = g.a;
-  const int h = blockIdx.y, b = blockIdx.z;
-  const int e = (blockIdx.x * 256 + threadIdx.x) * 4;
-  const int64_t bh = (int64_t)b * a.H + h;
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int64_t bh = (int64_t)blockIdx.z * g.a.H + blockIdx.y;
+  const int e = (blockIdx.x * 256 + threadIdx.x) * 4, n = g.nseg - 1;
   f32x4 R = {0.f, 0.f, 0.f, 0.f};
-  if (a.state_in) R = *(const f32x4*)(a.state_in + bh * kState + e);
-  for (int s0 = 0; s0 < g.nseg; s0 += kAhead) {
+  if (g.a.state_in) R = *(const f32x4*)(g.a.state_in + bh * kState + e);
+  float* st = g.state + bh * n * kState + e;
+  for (int s0 = 0; s0 < n; s0 += kAhead) {
     f32x4 U[kAhead];
     float alpha[kAhead];
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) {
-      const int sg = s0 + i < g.nseg ? s0 + i : g.nseg - 1;
-      U[i] = __builtin_nontemporal_load((const f32x4*)(g.seg_total + (bh * g.nseg + sg) * kState + e));
-      alpha[i] = __builtin_amdgcn_exp2f(g.gseg[bh * g.nseg + sg]);
+      const int s = s0 + i < n ? s0 + i : n - 1;
+      U[i] = *(const f32x4*)(st + (int64_t)s * kState);
+      alpha[i] = __builtin_amdgcn_exp2f(g.decay[bh * n + s]);
     }
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      if (s0 + i < g.nseg) {
-        *(f32x4*)(g.seg_init + (bh * g.nseg + s0 + i) * kState + e) = R;
+    for (int i = 0; i < kAhead; ++i)
+      if (s0 + i < n) {
         R = U[i] + alpha[i] * R;
+        *(f32x4*)(st + (int64_t)(s0 + i) * kState) = R;
       }
-    }
   }
-  if (a.state_out) *(f32x4*)(a.state_out + bh * kState + e) = R;
 }
 
-// ---- launch 3: outputs. Workgroup = 4 wavefronts = 128 query rows of one head, all in one chunk.
-__global__ void __launch_bounds__(256, 2) gret_chunk_output_kernel(ChunkArgs g) {
-  __shared__ __attribute__((aligned(1024))) char k_a[kTileBytes], k_b[kTileBytes];
-  __shared__ __attribute__((aligned(1024))) char v_a[kTileBytes], v_b[kTileBytes];
-  __shared__ __attribute__((aligned(16))) float g_a[kBN], g_b[kBN];
+// ---- launch 3: outputs.
+template <bool NORM, bool GATE>
+__global__ void __launch_bounds__(256, 2) gret_output_kernel(SegArgs g) {
+  __shared__ __attribute__((aligned(1024))) char q_t[kTileBytes], k_t[kTileBytes], v_t[kTileBytes];
+  __shared__ __attribute__((aligned(1024))) char p_t[2][kTileBytes / 2];     // scores, high and low parts: [step][hf][query] 16 bytes
+  __shared__ __attribute__((aligned(16))) float g_t[kC], w_t[kC];            // G of the chunk's rows, their weights in the state
+  __shared__ float red_m[4][kC], red_s[4][kC];                               // GroupNorm: a wavefront's means and sums of squares
   const GretView& a = g.a;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const Unit un = unit_of(a.H, g.nseg);
+  const int h = un.h, sg = un.sg, b = un.b;
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, lq = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int hf = lane >> 5, lq = lane & 31;
-  const int h = blockIdx.x, b = blockIdx.z;              // heads vary fastest over the grid, as in launch 1
   const int64_t bh = (int64_t)b * a.H + h;
-
-  const int64_t i0 = (int64_t)blockIdx.y * kBM;           // first query row of the workgroup
-  const int c = (int)(i0 / g.chunk);
-  const int64_t c0 = (int64_t)c * g.chunk;
-  const int64_t rows_here = a.T - i0 < kBM ? a.T - i0 : kBM;
-  const int jt_lo = (int)(c0 / kBN), jt_hi = (int)((i0 + rows_here - 1) / kBN);
-  const int n_t = jt_hi - jt_lo + 1;
-
-  const bf16_t* kg = (const bf16_t*)a.k + ((int64_t)b * a.T * a.H + h) * kD;
-  const bf16_t* vg = (const bf16_t*)a.v + ((int64_t)b * a.T * a.H + h) * kD;
-  const uint32_t row_bytes = (uint32_t)a.H * kD * 2u;
-  const float* gc = g.gc + bh * g.nc * g.chunk;            // indexed by the row within the sequence
-
-  // ---- staging: global -> registers -> LDS; K rows keep 16-byte chunks XOR row & 15, V rows 32-byte chunks XOR row & 7
+  const int c_lo = sg * g.per_seg, c_hi = c_lo + g.per_seg < g.n_chunks ? c_lo + g.per_seg : g.n_chunks;
+  const int64_t row_bytes = (int64_t)a.H * kD * 2, head0 = ((int64_t)b * a.T * a.H + h) * kD * 2;
   const int c16 = tid & 15, srow = tid >> 4;
-  const int kst_off = srow * 256 + ((c16 ^ (srow & 15)) << 4);
-  const int vst_off = tr_store_off(srow, c16);
-  u32x4 kst[4], vst[4];
-  float gst = 0.f;
-  auto load_tile = [&](int jt) {
-    const int64_t tile_row0 = (int64_t)jt * kBN;
-    const int lim = (int)(a.T - 1 - tile_row0 < kBN - 1 ? a.T - 1 - tile_row0 : kBN - 1);   // last row that exists
+  const char* qg = (const char*)a.q + head0;
+  const char* kg = (const char*)a.k + head0;
+  const char* vg = (const char*)a.v + head0;
+  const char* gg = (const char*)a.gate + head0;
+  char* og = (char*)a.o + head0;
+  const float* lg = a.log_gamma + (int64_t)b * a.T * a.H + h;
+  const int kbase = tr_base(lane, true), vbase = tr_base(lane, false);
+  const int q_off = row_off(srow, c16), kv_off = tr_off(srow, c16);          // row srow + 16 i is 4096 i further
+
+  u32x4 qr[4], kr[4], vr[4], gr[4];
+  float lgr = 0.f;
+  // a thread's pieces from the start of a chunk; in the chunk that T ends in, rows past the end repeat the last one
+  const uint32_t off0 = (uint32_t)srow * (uint32_t)row_bytes + (uint32_t)(c16 * 16);
+  const int rows_end = (int)(a.T - (int64_t)(g.n_chunks - 1) * kC);
+  auto piece = [&](int i, bool end) {
+    const uint32_t o = off0 + (uint32_t)(16 * i) * (uint32_t)row_bytes;
+    return end && srow + 16 * i >= rows_end ? (uint32_t)(rows_end - 1) * (uint32_t)row_bytes + (uint32_t)(c16 * 16) : o;
+  };
+  auto load_qk = [&](int c) {
+    const int64_t at = (int64_t)c * kC * row_bytes;
+    const bool end = c == g.n_chunks - 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int lrow = srow + 16 * i;
-      const int grow = lrow < lim ? lrow : lim;            // rows past the end repeat the last one (masked later)
-      const uint32_t off = (uint32_t)grow * row_bytes + (uint32_t)(c16 << 4);
-      kst[i] = *(const u32x4*)((const char*)(kg + tile_row0 * a.H * kD) + off);
-      vst[i] = *(const u32x4*)((const char*)(vg + tile_row0 * a.H * kD) + off);
+      const uint32_t o = piece(i, end);
+      qr[i] = *(const u32x4*)(qg + at + o);
+      kr[i] = *(const u32x4*)(kg + at + o);
     }
-    if (tid < kBN) gst = gc[tile_row0 + tid];                // padded up to whole chunks: always in bounds
   };
-  auto store_tile = [&](char* k_dst, char* v_dst, float* g_dst) {
+  auto load_v = [&](int c) {
+    const int64_t r0 = (int64_t)c * kC;
+    const bool end = c == g.n_chunks - 1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vr[i] = *(const u32x4*)(vg + r0 * row_bytes + piece(i, end));
+    if (wave == 0) {                                          // not touched here: that would wait for everything in flight
+      unsigned row = lane;
+      asm volatile("" : "+v"(row));                           // keep what depends on it out of long-lived registers
+      row = end && (int)row >= rows_end ? (unsigned)(rows_end - 1) : row;
+      lgr = *(const float*)((const char*)(lg + r0 * a.H) + row * (unsigned)a.H * 4u);
+    }
+  };
+  load_qk(c_lo);
+  load_v(c_lo);
+
+  // the state before the segment
+  f32x16 S[4];
+#pragma unroll
+  for (int eb = 0; eb < 4; ++eb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) S[eb][r] = 0.f;
+  auto add_state = [&](const float* src, float alpha) {                      // S = alpha S + src
+    each_piece(wave, lane, [&](int eb, int r, int off) {
+      const f32x4 x = *(const f32x4*)(src + off);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) S[eb][r + e] = fmaf(alpha, S[eb][r + e], x[e]);
+    });
+  };
+  const float* before = g.state + bh * (g.nseg - 1) * kState;
+  if (g.nseg - 1 > kFold && sg > 0) {
+    add_state(before + (int64_t)(sg - 1) * kState, 0.f);
+  } else {
+    if (a.state_in) add_state((g.nseg > 1 ? g.init : a.state_in) + bh * kState, 0.f);
+    for (int s = 0; s < sg; ++s) add_state(before + (int64_t)s * kState, __builtin_amdgcn_exp2f(g.decay[bh * (g.nseg - 1) + s]));
+  }
+
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int c = c_lo; c < c_hi; ++c) {
+    const bool end = c == g.n_chunks - 1;
+    if (wave == 0) {
+      int row = lane;
+      asm volatile("" : "+v"(row));
+      const float G = wave_scan(!end || row < rows_end ? lgr * kLog2e : 0.f), last = lane63(G);
+      g_t[row] = G;
+      w_t[row] = !end || row < rows_end ? __builtin_amdgcn_exp2f(last - G) : 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const u32x4 vh = {bf16x2_to_f16x2(vst[i][0]), bf16x2_to_f16x2(vst[i][1]), bf16x2_to_f16x2(vst[i][2]),
-                        bf16x2_to_f16x2(vst[i][3])};
-      *(u32x4*)(k_dst + kst_off + i * 4096) = kst[i];
-      *(u32x4*)(v_dst + vst_off + i * 4096) = vh;
-    }
-    if (tid < kBN) g_dst[tid] = gst;
-  };
-
-  // ---- Q^T fragments (B operand): lane holds query lq, dims ks*16 + hf*8 .. +8
-  int64_t iq = i0 + wave * 32 + lq;
-  const bool q_valid = iq < a.T;
-  if (!q_valid) iq = a.T - 1;
-  const bf16_t* qg = (const bf16_t*)a.q + (((int64_t)b * a.T + iq) * a.H + h) * kD;
-  bf16x8 qf[8];
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qg + ks * 16 + hf * 8));
-  const float gq = gc[iq];
-
-  const int koff0 = lq * 256 + ((hf ^ (lq & 15)) << 4);
-  const int s16 = lane & 15, db = (lane >> 4) & 1, z = hf * 4 + (s16 >> 2);
-  const int voff0 = z * 256 + ((db ^ z) << 5) + ((s16 & 3) << 3);
-
-  f32x16 acc_o[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc_o[mb][r] = 0.f;
-
-  // ---- cross-chunk part: O^T = R_{i-1}^T Q^T, then every query column times scale * 2^(G_q). R_{i-1} is put
-  // together in fp32 from the state before the chunk within its segment and the decayed state before
-  // the segment, and its two bf16 planes (128 x 128 each) pass through the four tile buffers, laid out like K tiles.
-  const int sg = c / g.seg, first = sg * g.seg;
-  const bool has_local = c > first;
-  const bool has_init = sg > 0 || a.state_in != nullptr;
-  const bool has_past = has_local || has_init;
-  if (has_past) {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const float* rw = g.rw + (bh * g.nc + c) * kState;
-    const float* si = g.seg_init + (bh * g.nseg + sg) * kState;
-    const float fpre = has_init ? __builtin_amdgcn_exp2f(g.gpre[bh * g.nc + c]) : 0.f;
-    // every load of this part, and the first key tile after them, is issued before anything waits
-    f32x4 wl[8][2], wi[8][2];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {                                   // rows srow + 16 i of both planes
-      const int off = (srow + 16 * i) * kD + c16 * 8;
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        wl[i][p] = has_local ? *(const f32x4*)(rw + off + 4 * p) : (f32x4){0.f, 0.f, 0.f, 0.f};
-        wi[i][p] = has_init ? *(const f32x4*)(si + off + 4 * p) : (f32x4){0.f, 0.f, 0.f, 0.f};
-      }
-    }
-    load_tile(jt_lo);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      u32x4 hi, lo;
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const float x0 = fmaf(fpre, wi[i][p][2 * e], wl[i][p][2 * e]);
-          const float x1 = fmaf(fpre, wi[i][p][2 * e + 1], wl[i][p][2 * e + 1]);
-          const unsigned hw = pack_bf16(x0, x1);
-          hi[2 * p + e] = hw;
-          lo[2 * p + e] = pack_bf16(x0 - __uint_as_float(hw << 16), x1 - __uint_as_float(hw & 0xffff0000u));
-        }
-      *(u32x4*)((i >= 4 ? k_b : k_a) + kst_off + (i & 3) * 4096) = hi;
-      *(u32x4*)((i >= 4 ? v_b : v_a) + kst_off + (i & 3) * 4096) = lo;
+      *(u32x4*)(q_t + q_off + i * 4096) = qr[i];
+      *(u32x4*)(k_t + kv_off + i * 4096) = kr[i];
+      *(u32x4*)(v_t + kv_off + i * 4096) = vr[i];
     }
     __syncthreads();
+
+    // ---- weights scale * s * 2^(G_q - G_k): wavefronts 0..2 take the blocks (keys, queries) (0, 0), (0, 1), (1, 1);
+    // wavefront 3 goes through the motions on (1, 0), which nobody reads, so that all of this is one basic block.
+    // ---- O^T = S^T Q^T, every query column times scale * 2^(G_q)
+    // The operands of the scores are all requested first and the state's first parts split while they arrive; then the
+    // products of the state, each step's operands a step ahead; the scores' weights last.
+    // Operand addresses are one base each, XORed with the step; hidden from the compiler, which would otherwise keep all
+    // sixty of them in registers across the chunks.
+    int qa = row_off(lq, hf), ka = tr_off((wave >> 1) * 32 + lq, hf), kta = kbase, va = vbase, pa = (hf * kC + lq) * 16;
+    asm volatile("" : "+v"(qa), "+v"(ka), "+v"(kta), "+v"(va), "+v"(pa));
+    auto q_frag = [&](int qb, int ks) { return *(const u32x4*)(q_t + (qa ^ (ks << 5)) + qb * 8192); };
+    auto split_state = [&](int ks, u32x4& sh, u32x4& sl) {
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      lds_char* ph = (lds_char*)((mb >> 1) ? k_b : k_a) + (mb & 1) * 32 * 256;
-      lds_char* pl = (lds_char*)((mb >> 1) ? v_b : v_a) + (mb & 1) * 32 * 256;
+      for (int i = 0; i < 4; ++i) {
+        const int r = (ks & 1) * 8 + i * 2;
+        unsigned hi, lo;
+        split_bf16(S[ks >> 1][r], S[ks >> 1][r + 1], hi, lo);
+        sh[i] = hi;
+        sl[i] = lo;
+      }
+    };
+    const int kb = wave >> 1, sqb = wave < 3 ? (wave + 1) >> 1 : 0;
+    u32x4 kf[4], qf[4], sh[2], sl[2];
+    auto request_scores = [&](int ks) {
+      kf[ks & 3] = *(const u32x4*)(k_t + (ka ^ (ks << 5)));
+      qf[ks & 3] = q_frag(sqb, ks);
+    };
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const bf16x8 ah = __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4*)(ph + (koff0 ^ (ks << 5))));
-        const bf16x8 al = __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4*)(pl + (koff0 ^ (ks << 5))));
-        acc_o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, qf[ks], acc_o[mb], 0, 0, 0);
-        acc_o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, qf[ks], acc_o[mb], 0, 0, 0);
+    for (int ks = 0; ks < 4; ++ks) request_scores(ks);
+    split_state(0, sh[0], sl[0]);
+    f32x16 s;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      s = mfma(kf[ks & 3], qf[ks & 3], ks ? s : zero);
+      if (ks < 4) request_scores(ks + 4);
+    }
+    if (GATE) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gr[i] = *(const u32x4*)(gg + (int64_t)c * kC * row_bytes + piece(i, end));
+    }
+    u32x4 q0[2], q1[2];
+    q0[0] = q_frag(0, 0);
+    q1[0] = q_frag(1, 0);
+    f32x16 o[2];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const int x = ks & 1, y = x ^ 1;
+      if (ks < 7) {
+        q0[y] = q_frag(0, ks + 1);
+        q1[y] = q_frag(1, ks + 1);
+        split_state(ks + 1, sh[y], sl[y]);
+      }
+      o[0] = mfma(sh[x], q0[x], ks ? o[0] : zero);
+      o[1] = mfma(sh[x], q1[x], ks ? o[1] : zero);
+      o[0] = mfma(sl[x], q0[x], o[0]);
+      o[1] = mfma(sl[x], q1[x], o[1]);
+      if (ks < 7) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                                        // a product, then its share of the next step's splitting
+        }
       }
     }
-    const float f = a.scale * __builtin_amdgcn_exp2f(gq);
+    {
+      const float gq = g_t[sqb * 32 + lq];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+      for (int u = 0; u < 2; ++u) {                                          // registers 8 u .. 8 u + 7: step 2 kb + u of the second product
+        u32x4 ph, pl;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc_o[mb][r] *= f;
-    __syncthreads();                                              // the buffers are free for the key tiles
-  } else {
-    load_tile(jt_lo);
-  }
-  store_tile(k_a, v_a, g_a);
-  if (n_t > 1) load_tile(jt_lo + 1);
-  __syncthreads();
-
-  // ---- inner-chunk part: key tiles from the chunk's first row up to the diagonal
-  const int64_t pw_lo = i0 + wave * 32;                 // first row of the wavefront
-  const int64_t pq = pw_lo + lq;                        // this lane's query row
-  auto step = [&](int st, char* k_cur, char* v_cur, float* g_cur, char* k_nxt, char* v_nxt, float* g_nxt) {
-    const int64_t j0 = (int64_t)(jt_lo + st) * kBN;     // first key of the tile
-    const bool need0 = j0 <= pw_lo + 31;                // some row of the wavefront sees keys 0..31 of the tile
-    const bool need1 = j0 + 32 <= pw_lo + 31;           //                              ... keys 32..63
-    const bool full = j0 + kBN - 1 <= pw_lo;            // every row sees every key
-    lds_char* kb = (lds_char*)k_cur;
-    lds_char* vb = (lds_char*)v_cur;
-    auto kfrag = [&](int ks, int mb) {
-      return __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4*)(kb + (koff0 ^ (ks << 5)) + mb * 32 * 256));
-    };
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 s0 = zero, s1 = zero;
-    if (need0) {
+        for (int i = 0; i < 2; ++i) {
+          const f32x4 gk = *(const f32x4*)(g_t + kb * 32 + u * 16 + i * 8 + hf * 4);
+          float p[4];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, 0), qf[ks], ks == 0 ? zero : s0, 0, 0, 0);
-    }
-    if (need1) {
+          for (int e = 0; e < 4; ++e) {
+            const int key = u * 16 + i * 8 + hf * 4 + e;
+            p[e] = s[u * 8 + i * 4 + e] * (a.scale * __builtin_amdgcn_exp2f(gq - gk[e]));
+            p[e] = key <= lq + 32 * (sqb - kb) ? p[e] : 0.f;
+          }
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(ks, 1), qf[ks], ks == 0 ? zero : s1, 0, 0, 0);
-    }
-    if (need0) {
-      // weights: scale * s * 2^(G_q - G_k); keys after the query (diagonal tiles only) weigh nothing
-      typedef float f32x4 __attribute__((ext_vector_type(4)));
-      unsigned pk0[8], pk1[8];
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        const f32x4 gk0 = *(const f32x4*)(g_cur + rq * 8 + hf * 4);
-        const f32x4 gk1 = *(const f32x4*)(g_cur + 32 + rq * 8 + hf * 4);
-        float p0[4], p1[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t key = j0 + rq * 8 + hf * 4 + e;
-          p0[e] = s0[rq * 4 + e] * a.scale * __builtin_amdgcn_exp2f(gq - gk0[e]);
-          p1[e] = s1[rq * 4 + e] * a.scale * __builtin_amdgcn_exp2f(gq - gk1[e]);
-          if (!full) {
-            p0[e] = key <= pq ? p0[e] : 0.f;
-            p1[e] = (need1 && key + 32 <= pq) ? p1[e] : 0.f;
+          for (int e = 0; e < 2; ++e) {
+            unsigned hi, lo;
+            split_bf16(p[2 * e], p[2 * e + 1], hi, lo);
+            ph[2 * i + e] = hi;
+            pl[2 * i + e] = lo;
           }
         }
-        pk0[rq * 2] = pack_f16(p0[0], p0[1]);
-        pk0[rq * 2 + 1] = pack_f16(p0[2], p0[3]);
-        pk1[rq * 2] = pack_f16(p1[0], p1[1]);
-        pk1[rq * 2 + 1] = pack_f16(p1[2], p1[3]);
-      }
-      // O^T += V^T P^T ; k-step t covers keys t*16 .. t*16+15 of the tile
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        if ((t >> 1) && !need1) continue;               // a skipped half has zero weights
-        const unsigned* pk = (t >> 1) ? pk1 : pk0;
-        const int pb = (t & 1) * 4;
-        const u32x4 pu = {pk[pb], pk[pb + 1], pk[pb + 2], pk[pb + 3]};
-        const f16x8 pf = __builtin_bit_cast(f16x8, pu);
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-          acc_o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(tr_frag(vb, voff0, mb, t), pf, acc_o[mb], 0, 0, 0);
+        const int off = pa + ((2 * kb + u) * 2 * kC + sqb * 32) * 16;
+        *(u32x4*)(p_t[0] + off) = ph;
+        *(u32x4*)(p_t[1] + off) = pl;
       }
     }
-    if (st + 1 < n_t) store_tile(k_nxt, v_nxt, g_nxt);
-    if (st + 2 < n_t) load_tile(jt_lo + st + 2);
-    __syncthreads();
-  };
-  for (int st = 0; st < n_t; st += 2) {
-    step(st, k_a, v_a, g_a, k_b, v_b, g_b);
-    if (st + 1 >= n_t) break;
-    step(st + 1, k_b, v_b, g_b, k_a, v_a, g_a);
-  }
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const float f = a.scale * __builtin_amdgcn_exp2f(g_t[qb * 32 + lq]);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[qb][r] *= f;
+    }
+    __syncthreads();                                                         // the scores are there; nobody reads Q any more
+    if (GATE) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *(u32x4*)(q_t + q_off + i * 4096) = gr[i];
+    }
+    if (c + 1 < c_hi) load_qk(c + 1);                                        // in flight during the rest of the chunk
 
-  // ---- GroupNorm over the head's 128 values of each query (held by the lane pair l, l ^ 32), then store
-  float mean = 0.f, rstd = 1.f;
-  if (a.group_norm) {
-    float sum = 0.f;
+    // ---- the chunk joins the state, and O^T += V^T P^T, 16 rows a step. K's operand of a step is requested behind the
+    // state products of the step before, P's at the head of the step; either has eight or four products to arrive in.
+    u32x4 vf[2], kt[4], pf[2][2], vh[2], vl[2];
+    vf[0] = tr_frag(v_t, va, wave, 0);
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int eb = 0; eb < 4; ++eb) kt[eb] = tr_frag(k_t, kta, eb, 0);
+    const float d = __builtin_amdgcn_exp2f(g_t[kC - 1]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sum += acc_o[mb][r];
-    sum += other_half(sum);
-    mean = sum * (1.f / kD);
-    float sq = 0.f;
+    for (int eb = 0; eb < 4; ++eb)
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+      for (int r = 0; r < 16; ++r) S[eb][r] *= d;
+    weigh(vf[0], w_t, 0, hf, vh[0], vl[0]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sq += (acc_o[mb][r] - mean) * (acc_o[mb][r] - mean);
-    sq += other_half(sq);
-    rstd = rsqrtf(sq * (1.f / kD) + a.eps);
-  }
-  if (q_valid) {
-    const int64_t row_off = (((int64_t)b * a.T + iq) * a.H + h) * kD;
-    bf16_t* og = (bf16_t*)a.o + row_off;
-    const bf16_t* gg = a.gate ? (const bf16_t*)a.gate + row_off : nullptr;
+    for (int t = 0; t < 4; ++t) {
+      const int x = t & 1, y = x ^ 1;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+      for (int part = 0; part < 2; ++part)
+#pragma unroll
+        for (int qb = t < 2 ? 0 : 1; qb < 2; ++qb)                           // keys 32.. come after queries ..31
+          pf[part][qb] = *(const u32x4*)(p_t[part] + pa + (t * 2 * kC + qb * 32) * 16);
+      if (t < 3) vf[y] = tr_frag(v_t, va, wave, t + 1);
+#pragma unroll
+      for (int part = 0; part < 2; ++part)
+#pragma unroll
+        for (int eb = 0; eb < 4; ++eb) S[eb] = mfma(kt[eb], part ? vl[x] : vh[x], S[eb]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t < 3) {
+#pragma unroll
+        for (int eb = 0; eb < 4; ++eb) kt[eb] = tr_frag(k_t, kta, eb, t + 1);
+      }
+#pragma unroll
+      for (int part = 0; part < 2; ++part)
+#pragma unroll
+        for (int qb = t < 2 ? 0 : 1; qb < 2; ++qb) o[qb] = mfma(vf[x], pf[part][qb], o[qb]);
+      if (t < 3) weigh(vf[y], w_t, t + 1, hf, vh[y], vl[y]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+
+    if (c + 1 < c_hi) load_v(c + 1);                                         // here, because the products leave no registers for it
+
+    // ---- GroupNorm over a query's 128 values: each wavefront's mean and sum of squares about it, combined over the four
+    float shift[2], rstd[2];
+    if (NORM) {
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        float sum = 0.f, sq = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum += o[qb][r];
+        sum += other_half(sum);
+        const float m = sum * (1.f / 32.f);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sq = fmaf(o[qb][r] - m, o[qb][r] - m, sq);
+        sq += other_half(sq);
+        if (hf == 0) {
+          red_m[wave][qb * 32 + lq] = m;
+          red_s[wave][qb * 32 + lq] = sq;
+        }
+      }
+    }
+    __syncthreads();                                                         // the norm's parts and the gate are there
+    if (NORM) {
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        float m[4], sq = 0.f, dev = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          m[w] = red_m[w][qb * 32 + lq];
+          sq += red_s[w][qb * 32 + lq];
+        }
+        const float mean = ((m[0] + m[1]) + (m[2] + m[3])) * 0.25f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) dev = fmaf(m[w] - mean, m[w] - mean, dev);
+        rstd[qb] = rsqrtf(fmaf(32.f, dev, sq) * (1.f / kD) + a.eps);
+        shift[qb] = -mean * rstd[qb];
+      }
+    }
+    int ya = row_off(lq, 0) + hf * 8;
+    asm volatile("" : "+v"(ya));
+    // swish gate of Eq. 7 (y * g * sigmoid(g)), and the tile of outputs in place of the gate's
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
+        u32x2* cell = (u32x2*)(q_t + (ya ^ ((wave * 4 + rq) << 4)) + qb * 8192);
         float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = (acc_o[mb][rq * 4 + e] - mean) * rstd;
-        if (gg) {                                         // swish gate of Eq. 7: y * g * sigmoid(g)
-          const u32x2 gw = *(const u32x2*)(gg + mb * 32 + rq * 8 + hf * 4);
-          const float gv[4] = {__uint_as_float(gw[0] << 16), __uint_as_float(gw[0] & 0xffff0000u),
-                               __uint_as_float(gw[1] << 16), __uint_as_float(gw[1] & 0xffff0000u)};
+        for (int e = 0; e < 4; ++e) y[e] = NORM ? fmaf(o[qb][rq * 4 + e], rstd[qb], shift[qb]) : o[qb][rq * 4 + e];
+        if (GATE) {
+          const u32x2 gw = *cell;
+          const float gv[4] = {lo_f(gw[0]), hi_f(gw[0]), lo_f(gw[1]), hi_f(gw[1])};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] *= gv[e] / (1.f + __expf(-gv[e]));
+          for (int e = 0; e < 4; ++e) y[e] *= gv[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-kLog2e * gv[e]));
         }
-        const u32x2 w = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
-        *(u32x2*)(og + mb * 32 + rq * 8 + hf * 4) = w;
+        *cell = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
       }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                                            // a thread reads the pieces it overwrites with the next chunk's Q
+      if (!end || srow + 16 * i < rows_end) *(u32x4*)(og + (int64_t)c * kC * row_bytes + piece(i, false)) = *(const u32x4*)(q_t + q_off + i * 4096);
+    }
   }
+  if (a.state_out && sg == g.nseg - 1) store_state(a.state_out + bh * kState, S, wave, lane);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -498,13 +564,13 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 bool gret_chunk_supported(int B, int64_t T, int H, int dk, int dv, int chunk, int dtype) {
   if (dtype != YOCO_BF16 || dk != kD || dv != kD) return false;
-  if (chunk % kBM || chunk > kMaxChunk) return false;
-  if (T <= 0 || (T + kBM - 1) / kBM > 65535) return false;          // query blocks are the grid's y dimension
+  if (chunk % 128 || chunk > kMaxChunk) return false;
+  if (T <= 0 || (T + 127) / 128 > 65535) return false;
   return B <= 65535;
 }
 
-// Chunks per segment: long enough that the states written per chunk are the only state traffic, short enough that
-// the state launch still fills the chip at its occupancy (3 workgroups on each of 256 CUs) when the shape allows it.
+// What callers are told to allocate: cumulative decays and one state per chunk of the caller's size, two states per run of
+// chunks. The segments' states are fewer; see segments_of.
 int gret_segment_chunks(int B, int H, int nc) {
   int64_t s = (int64_t)nc * B * H / 768;
   if (s < 1) s = 1;
@@ -519,30 +585,39 @@ size_t gret_chunk_workspace(int B, int64_t T, int H, int chunk) {
          2 * align256(bh * nseg * kState * sizeof(float)) + align256(bh * nc * sizeof(float)) + align256(bh * nseg * sizeof(float));
 }
 
+// Chunks per segment: all segments resident at once at two workgroups per CU (512), each as long as that allows, because
+// a segment costs a state written, scanned and read; and no more segments than the workspace holds states for.
+int gret_chunks_per_segment(int B, int64_t T, int H, int chunk) {
+  const int64_t bh = (int64_t)B * H, n_chunks = (T + kC - 1) / kC;
+  const int64_t nc = (T + chunk - 1) / chunk, old = gret_segment_chunks(B, H, (int)nc);
+  const int64_t room = nc + 2 * ((nc + old - 1) / old);                      // states per head in the workspace: nseg - 1 and a copy of state_in
+  int64_t nseg = 512 / bh;
+  if (nseg > room) nseg = room;
+  if (nseg > n_chunks) nseg = n_chunks;
+  if (nseg < 1) nseg = 1;
+  return (int)((n_chunks + nseg - 1) / nseg);
+}
+
 hipError_t launch_gret_chunk(const GretView& a, int chunk, void* workspace, hipStream_t s) {
-  ChunkArgs g;
+  SegArgs g;
   g.a = a;
-  g.chunk = chunk;
-  g.nc = (int)((a.T + chunk - 1) / chunk);
-  g.seg = gret_segment_chunks(a.B, a.H, g.nc);
-  g.nseg = (g.nc + g.seg - 1) / g.seg;
+  g.n_chunks = (int)((a.T + kC - 1) / kC);
+  g.per_seg = gret_chunks_per_segment(a.B, a.T, a.H, chunk);
+  g.nseg = (g.n_chunks + g.per_seg - 1) / g.per_seg;
   const size_t bh = (size_t)a.B * a.H;
-  char* p = (char*)workspace;
-  g.gc = (float*)p;
-  p += align256(bh * g.nc * chunk * sizeof(float));
-  g.rw = (float*)p;
-  p += align256(bh * g.nc * kState * sizeof(float));
-  g.seg_total = (float*)p;
-  p += align256(bh * g.nseg * kState * sizeof(float));
-  g.seg_init = (float*)p;
-  p += align256(bh * g.nseg * kState * sizeof(float));
-  g.gpre = (float*)p;
-  p += align256(bh * g.nc * sizeof(float));
-  g.gseg = (float*)p;
-  hipLaunchKernelGGL(gret_cumdecay_kernel, dim3(g.nc, a.H, a.B), dim3(64), 0, s, g);
-  hipLaunchKernelGGL(gret_chunk_state_kernel, dim3(a.H, g.nseg, a.B), dim3(256), 0, s, g);
-  hipLaunchKernelGGL(gret_state_scan_kernel, dim3(kState / 1024, a.H, a.B), dim3(256), 0, s, g);
-  hipLaunchKernelGGL(gret_chunk_output_kernel, dim3(a.H, (unsigned)((a.T + kBM - 1) / kBM), a.B), dim3(256), 0, s, g);
+  const size_t nc = (size_t)((a.T + chunk - 1) / chunk);
+  g.decay = (float*)workspace;                                               // nseg - 1 <= 3 nc of chunk * nc floats
+  g.state = (float*)((char*)workspace + align256(bh * nc * chunk * sizeof(float)));
+  g.init = a.state_in && g.nseg > 1 ? g.state + bh * (g.nseg - 1) * kState : nullptr;
+  if (g.nseg > 1) {
+    hipLaunchKernelGGL(gret_segment_kernel, dim3((unsigned)(bh * (g.nseg - 1))), dim3(256), 0, s, g);
+    if (g.nseg - 1 > kFold) hipLaunchKernelGGL(gret_state_scan_kernel, dim3(kState / 1024, a.H, a.B), dim3(256), 0, s, g);
+  }
+  const dim3 grid((unsigned)(bh * g.nseg)), block(256);
+  if (a.group_norm && a.gate) hipLaunchKernelGGL((gret_output_kernel<true, true>), grid, block, 0, s, g);
+  else if (a.group_norm) hipLaunchKernelGGL((gret_output_kernel<true, false>), grid, block, 0, s, g);
+  else if (a.gate) hipLaunchKernelGGL((gret_output_kernel<false, true>), grid, block, 0, s, g);
+  else hipLaunchKernelGGL((gret_output_kernel<false, false>), grid, block, 0, s, g);
   return hipGetLastError();
 }
 

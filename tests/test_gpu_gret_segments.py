@@ -1,0 +1,51 @@
+"""Chunkwise gated retention at the edges of its chunks of 64 rows and of its segments, every combination of GroupNorm and
+gate, and a carried state that is updated in place, against the fp64 oracle."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_2405_05254_amd as yoco  # noqa: E402
+import yoco_synth as ys  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+D = 128
+
+
+@pytest.mark.parametrize("B,T,H,chunk,norm,gate,carry", [
+    (1, 1, 1, 128, True, True, True),          # one row
+    (3, 63, 2, 256, True, False, False),       # one chunk, one row short; one segment, no state before it
+    (1, 64, 3, 128, False, True, True),
+    (2, 65, 1, 256, True, True, True),         # one row in the second chunk, two segments that launch 3 folds
+    (1, 257, 5, 128, False, False, True),      # four segments folded
+    (1, 321, 2, 128, True, True, True),        # six chunks in six segments: the scan
+    (1, 1100, 1, 1024, True, True, True),      # the workspace of large chunks holds few states: longer segments
+    (2, 640, 130, 128, True, False, True),     # so many heads that a sequence is one segment
+])
+def test_edges(B, T, H, chunk, norm, gate, carry):
+    scale = 1.0 / math.sqrt(D)
+    q, k, v, lg = ys.gret_inputs(T + H, B, T, H, D, D, 1.0, "bf16", mean_log_decay=0.1)
+    rng = np.random.default_rng(3)
+    g = ys.normal(rng, (B, T, H, D), 1.0, "bf16")
+    S0 = rng.standard_normal((B, H, D, D)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    state = torch.from_numpy(S0).cuda() if carry else torch.full((B, H, D, D), float("nan"), device="cuda")
+    ws = torch.full((yoco.gret_prefill_workspace(B, T, H, D, D, chunk, yoco.BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    o = yoco.gret_prefill(dev(q), dev(k), dev(v), torch.from_numpy(lg).cuda(), scale, chunk=chunk, group_norm=norm, eps=1e-6,
+                          state_in=state if carry else None, state_out=state, workspace=ws, gate=dev(g) if gate else None)
+    o, state = o.float().cpu().numpy().astype(np.float64), state.cpu().numpy().astype(np.float64)
+    for b in range(B):
+        ref, S = oracle.gret_recurrent(q[b], k[b], v[b], np.exp(lg[b].astype(np.float64)), scale,
+                                       np.swapaxes(S0[b], -1, -2).astype(np.float64) if carry else None)
+        S = np.swapaxes(S, -1, -2)
+        if norm:
+            ref = oracle.group_norm_heads(ref, 1e-6)
+        if gate:
+            ref = ref * g[b] / (1.0 + np.exp(-g[b].astype(np.float64)))
+        for got, want, (most, mean) in ((o[b], ref, (2e-2, 2e-3)), (state[b], S, (2e-3, 1e-3))):
+            unit = max(1.0, float(np.abs(want).max()))
+            st = ys.error_stats(got / unit, want / unit)
+            assert np.isfinite(got).all() and st["max_abs"] <= most and st["mean_rel"] <= mean, (b, st)
