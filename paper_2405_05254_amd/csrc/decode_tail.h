@@ -30,7 +30,7 @@ struct SplitOut {
 struct SplitRows {
   int64_t lo, hi;            // rows of this split, lo >= hi: nothing to do
   int splits;                // of this sequence; 0: the sequence is empty, split 0 stores zeros
-  float total;               // rows of the whole batch
+  float total;               // rows of the whole batch (of its capacity where nothing is split)
 };
 
 template <int GRAIN>
@@ -39,14 +39,15 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
   auto clamp_len = [&](int64_t n) { return (unsigned)(n < 0 ? 0 : n > c.N_cap ? c.N_cap : n); };
   const unsigned len = clamp_len(lens ? lens[b] : fixed_len);
   unsigned n = 1;
-  float total = (float)len;
-  if (lens && c.B > 1) {                             // the same float arithmetic in every workgroup: all agree on every sequence's splits
-    total = 0.f;
-    for (int i = threadIdx.x & 63; i < c.B; i += 64) total += (float)clamp_len(lens[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
-  }
+  float total = (float)c.B * (float)c.N_cap;         // unsplit: nothing depends on the other lengths
   if (out.splits > 1) {
+    total = (float)len;
+    if (lens && c.B > 1) {                           // the same float arithmetic in every workgroup: all agree on every sequence's splits
+      total = 0.f;
+      for (int i = threadIdx.x & 63; i < c.B; i += 64) total += (float)clamp_len(lens[i]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+    }
     const float share = fmaxf(total * (float)c.Hkv * out.inv_workgroups, (float)GRAIN);
     n = (unsigned)__builtin_amdgcn_readfirstlane((int)ceilf((float)len / share - 0.1f));
     n = n < 1 ? 1 : n > (unsigned)out.splits ? (unsigned)out.splits : n;

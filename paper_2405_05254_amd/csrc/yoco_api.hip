@@ -87,6 +87,9 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   const int64_t wanted = (cus + units - 1) / units;
   const int min_rows = c->dtype == YOCO_BF16 ? 128 : 512;
   int64_t s = clamp(clamp(wanted, (c->N_cap + min_rows - 1) / min_rows), 256);
+  // Splits of a bf16 cache have to save three steps of 128 rows to be worth the meeting at the end (240 units of 355 rows:
+  // 10.1 us unsplit, 12.0 in two; 16 units of 400: 9.2 unsplit, 7.6 in four).
+  if (c->dtype == YOCO_BF16 && (c->N_cap + 127) / 128 - (c->N_cap + 128 * s - 1) / (128 * s) < 3) s = 1;
   // More (sequence, KV head) units than CUs, and not a multiple of them: the workgroups of a ragged last round run
   // with part of the chip idle (384 units on 256 CUs measured 5.7 TB/s at 4096 rows). Two to four splits per unit
   // make the count a multiple again, as long as a split keeps at least 1024 rows (384 units of 1024 rows: 35.9 us
