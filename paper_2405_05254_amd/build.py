@@ -9,7 +9,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libyoco.so")
 CALLS = os.path.join(PKG, "_calls.so")          # the binding's calls in native code (csrc/py_calls.cpp, host only)
 STAMP = os.path.join(PKG, "libyoco.stamp")      # hash of the sources the library was built from
-SOURCES = ["yoco_api.hip", "attn_generic.hip", "swa_mfma.hip", "decode_bf16.hip", "gret_generic.hip", "gret_chunk.hip", "cache_i8.hip", "stack_glue.hip", "ceilings.hip"]
+SOURCES = ["yoco_api.hip", "attn_generic.hip", "attn_f32.hip", "swa_mfma.hip", "decode_bf16.hip", "gret_generic.hip", "gret_chunk.hip", "cache_i8.hip", "stack_glue.hip", "ceilings.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 code generation
          "-fno-honor-nans",        # fmax without NaN canonicalisation; -inf (the mask value) is still honoured

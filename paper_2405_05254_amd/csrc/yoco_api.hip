@@ -298,6 +298,7 @@ int yoco_swa_prefill(const void* q, const void* k, const void* v, void* o, int B
   a.window = window > T ? T : window;
   a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.B = B; a.scale = scale;
   if (yoco::swa_mfma_supported(a, dtype)) return hip_result(yoco::launch_swa_mfma(a, (hipStream_t)stream), "swa_prefill");
+  if (yoco::attn_f32_supported(a)) return hip_result(yoco::launch_attn_f32(a, dtype, (hipStream_t)stream), "swa_prefill");
   return hip_result(yoco::launch_attn_generic(a, dtype, (hipStream_t)stream), "swa_prefill");
 }
 
@@ -415,6 +416,7 @@ int yoco_cross_attn_prefill(const yoco_kv_cache* c, const void* q, void* o, int 
   a.Hq = Hq; a.Hkv = c->Hkv; a.d = c->d; a.B = 1; a.scale = scale;
   if (yoco::swa_mfma_supported(a, c->dtype))
     return hip_result(yoco::launch_swa_mfma(a, (hipStream_t)stream), "cross_attn_prefill");
+  if (yoco::attn_f32_supported(a)) return hip_result(yoco::launch_attn_f32(a, c->dtype, (hipStream_t)stream), "cross_attn_prefill");
   return hip_result(yoco::launch_attn_generic(a, c->dtype, (hipStream_t)stream), "cross_attn_prefill");
 }
 

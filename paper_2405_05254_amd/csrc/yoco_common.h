@@ -64,6 +64,9 @@ struct GretView {
 
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_attn_generic(const AttnView& a, int dtype, hipStream_t s);
+// fp32 arithmetic on the matrix cores, head_dim 64 or 128 (attn_f32.hip).
+bool attn_f32_supported(const AttnView& a);
+hipError_t launch_attn_f32(const AttnView& a, int dtype, hipStream_t s);
 hipError_t launch_decode_generic(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq,
                                  float scale, float* ws, int splits, hipStream_t s);
 hipError_t launch_decode_merge(const float* ws, void* o, int B, int Hq, int d, int splits, int dtype,

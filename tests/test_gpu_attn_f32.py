@@ -1,0 +1,43 @@
+"""The fp32 matrix-core prefill kernel at the edges of its tiles of 16 keys and 16 or 32 query rows, both storage types,
+against the fp64 oracle."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_2405_05254_amd as yoco  # noqa: E402
+import yoco_synth as ys  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,B,T,Hq,Hkv,d,window,scale", [
+    ("f32", 1, 1, 1, 1, 64, 1, None),
+    ("f32", 2, 15, 4, 2, 128, 3, None),            # windows shorter than a tile: wavefronts without a visible key
+    ("f32", 1, 17, 2, 1, 64, 17, None),
+    ("f32", 1, 129, 3, 3, 128, 64, -0.7),          # a negative scale: the smallest products weigh most
+    ("f32", 3, 337, 24, 8, 64, 100, None),         # 32-row workgroups, a ragged last one
+    ("f32", 1, 2065, 8, 8, 128, 500, None),
+    ("bf16", 1, 333, 6, 2, 64, 128, None),
+    ("bf16", 2, 70, 2, 2, 128, 70, 0.0),           # no scale: plain means, bf16 storage
+])
+def test_edges(dtype, B, T, Hq, Hkv, d, window, scale):
+    scale = 1.0 / math.sqrt(d) if scale is None else scale
+    rng = np.random.default_rng(T + Hq)
+    q, k, v = (ys.normal(rng, (B, T, h, d), 1.0, dtype) for h in (Hq, Hkv, Hkv))
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)  # noqa: E731
+    o = yoco.swa_prefill(dev(q), dev(k), dev(v), window, scale).float().cpu().numpy()
+    pos0 = T - T // 3                              # the last third again, as rows that follow a cache
+    cache = yoco.KVCache(1, Hkv, d, T, torch.float32 if dtype == "f32" else torch.bfloat16)
+    yoco.global_kv_write(cache, dev(k[B - 1]), dev(v[B - 1]), 0, 0)
+    rows = [None] if pos0 == T else [yoco.cross_attn_prefill(cache, dev(q[B - 1, pos0:]), 0, pos0, scale).float().cpu().numpy()]
+    tol = ys.TOL[dtype]
+    pairs = [(o[b], oracle.swa(q[b], k[b], v[b], window, scale)) for b in range(B)]
+    if rows[0] is not None:
+        pairs.append((rows[0], oracle.cross_attn(q[B - 1, pos0:], k[B - 1], v[B - 1], pos0, scale)))
+    for got, ref in pairs:
+        st = ys.error_stats(got, ref)
+        assert np.isfinite(got).all() and st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], st
