@@ -8,8 +8,9 @@
 // with the dims of a product dealt to the lanes so that a lane's operands are what 128-bit loads of the rows deliver, and
 // the scores' accumulator registers are the second product's operand as they stand. K of the next tile is requested
 // behind the first product, V behind the second. Measured against one wavefront per query row on the vector ALU, which it
-// replaces at these head dims: 512 rows x 4 heads of 64, window 128: 14.8 -> 5.8 us (launch and latency); 2 x 1455 rows x
+// replaces at these head dims: 512 rows x 4 heads of 64, window 128: 14.1 -> 6.0 us (launch and latency); 2 x 1455 rows x
 // 4 heads of 128, window 1024: 650 -> 83 us; 2 x 2048 x 8 heads of 128: 1854 -> 186 us (69 TFLOP/s).
+#include "attend_range.h"
 #include "yoco_common.h"
 
 namespace yoco {
@@ -31,6 +32,11 @@ __device__ __forceinline__ f32x4 load4(const bf16_t* p) {
 __device__ __forceinline__ void store4(float* p, const f32x4& x) { *(f32x4*)p = x; }
 __device__ __forceinline__ void store4(bf16_t* p, const f32x4& x) {
   *(u32x2*)p = {(unsigned)f32_to_bf16(x[0]) | ((unsigned)f32_to_bf16(x[1]) << 16), (unsigned)f32_to_bf16(x[2]) | ((unsigned)f32_to_bf16(x[3]) << 16)};
+}
+__device__ __forceinline__ bool not_finite(float x) {
+  unsigned u = __float_as_uint(x);
+  asm("" : "+v"(u));                                  // the compiler is told to expect no NaN from arithmetic
+  return (u & 0x7f800000u) == 0x7f800000u;
 }
 __device__ __forceinline__ float finite_or_zero(float m) { return m == -INFINITY ? 0.f : m; }     // the base of an empty row's exponents
 
@@ -161,6 +167,7 @@ __global__ void __launch_bounds__(64 * kWaves, QB == 1 ? 3 : 2) attn_f32_kernel(
   }
   __syncthreads();
   T* ob = (T*)a.o + b * a.q_stride_b + (int64_t)h * D;
+  bool bad = false;
   for (int t = threadIdx.x; t < kRows * (D / 4); t += 64 * kWaves) {
     const int row = t / (D / 4), e = (t % (D / 4)) * 4;
     if (i0 + row >= a.Tq) continue;
@@ -173,7 +180,25 @@ __global__ void __launch_bounds__(64 * kWaves, QB == 1 ? 3 : 2) attn_f32_kernel(
       L = fmaf(f, red_l[w][row], L);
       x += f * *(const f32x4*)&red_o[w][row][e];
     }
-    store4(ob + (i0 + row) * a.q_stride_t + e, x * (1.f / L));
+    x *= 1.f / L;
+    bad |= not_finite(x[0]) | not_finite(x[1]) | not_finite(x[2]) | not_finite(x[3]);
+    store4(ob + (i0 + row) * a.q_stride_t + e, x);
+  }
+
+  // Keys that a query of these rows does not see were weighed with 0, and 0 * inf is NaN: where anything came out infinite
+  // or NaN, the rows are done again over the keys that each of them sees.
+  if (!__syncthreads_or(bad)) return;
+  float* const q_s = &red_o[wave][0][0];
+  float* const p_s = q_s + D;
+  for (int row = wave; row < kRows && i0 + row < a.Tq; row += kWaves) {
+    const T* q = qb0 + (i0 + row) * a.q_stride_t;
+    for (int e = lane; e < D; e += 64) q_s[e] = Elem<T>::load(q + e);
+    lds_wave_sync();
+    const int64_t pos = a.q_pos0 + i0 + row, j_lo = pos - a.window + 1 > 0 ? pos - a.window + 1 : 0;
+    float m1 = -INFINITY, l1 = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
+    attend_range<T>(kb, vb, a.kv_stride_n, j_lo, pos, D, a.scale, q_s, p_s, m1, l1, acc);
+#pragma unroll
+    for (int t = 0; t < D / 64; ++t) Elem<T>::store(ob + (i0 + row) * a.q_stride_t + lane + 64 * t, acc[t] * (1.f / l1));
   }
 }
 

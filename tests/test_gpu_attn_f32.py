@@ -41,3 +41,19 @@ def test_edges(dtype, B, T, Hq, Hkv, d, window, scale):
     for got, ref in pairs:
         st = ys.error_stats(got, ref)
         assert np.isfinite(got).all() and st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], st
+
+
+@pytest.mark.parametrize("d,T,H", [(64, 70, 2), (128, 70, 2), (64, 2065, 8)])     # 16- and 32-row workgroups
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_values_that_a_query_does_not_see_do_not_reach_it(d, T, H, value):
+    window, at = 24, 37
+    rng = np.random.default_rng(d + T)
+    q, k, v = (ys.normal(rng, (1, T, H, d), 1.0, "f32") for _ in range(3))
+    ref = oracle.swa(q[0], k[0], v[0], window, 1.0 / math.sqrt(d))
+    v[0, at, :, 3] = value
+    o = yoco.swa_prefill(*(torch.from_numpy(a).cuda() for a in (q, k, v)), window, 1.0 / math.sqrt(d))[0].cpu().numpy()
+    sees = np.zeros((T, H, d), bool)
+    sees[at:at + window, :, 3] = True
+    assert not np.isfinite(o[sees]).any()
+    st = ys.error_stats(o[~sees], ref[~sees])
+    assert np.isfinite(o[~sees]).all() and st["max_abs"] <= ys.TOL["f32"]["max_abs"] and st["mean_rel"] <= ys.TOL["f32"]["mean_rel"], st
