@@ -248,6 +248,12 @@ def gret_decode(q, k, v, log_gamma, state, scale, group_norm=True, eps=1e-6, out
     return (_CALLS or _calls()).gret_decode(q, k, v, log_gamma, state, scale, group_norm, eps, out, gate)
 
 
+def _state(t, name, B, H, dk, dv):
+    if t.dtype != torch.float32 or t.shape != (B, H, dv, dk):
+        raise YocoError("%s must be float32 [B,H,dv,dk]" % name)
+    return _dev(t, name)
+
+
 def stack_step_scratch(stack):
     n = C.c_size_t()
     _check(lib().yoco_stack_step_scratch(C.byref(stack), C.byref(n)))
@@ -266,6 +272,8 @@ def norm_rows(x, gain, eps, add=None):
     """RMSNorm(x) * gain over the rows of a bf16 [rows,dim] tensor; with `add`: (x + add, RMSNorm(x + add) * gain) (yoco_norm_rows)."""
     xn = torch.empty_like(x)
     y = None if add is None else torch.empty_like(x)
+    if not x.shape[0]:
+        return xn if add is None else (y, xn)
     _check(lib().yoco_norm_rows(_dev(x, "x"), None if add is None else _dev(add, "add"), None if y is None else _dev(y, "y"),
                                 _dev(gain, "gain"), _dev(xn, "xn"), x.shape[0], x.shape[1], eps, _stream()))
     return xn if add is None else (y, xn)
@@ -274,6 +282,8 @@ def norm_rows(x, gain, eps, add=None):
 def glu_rows(gu):
     """bf16 [rows, 2 ffn] -> swish(first half) * second half (yoco_glu_rows)."""
     h = torch.empty((gu.shape[0], gu.shape[1] // 2), dtype=gu.dtype, device=gu.device)
+    if not h.shape[0]:
+        return h
     _check(lib().yoco_glu_rows(_dev(gu, "gu"), _dev(h, "h"), h.shape[0], h.shape[1], _stream()))
     return h
 

@@ -38,6 +38,12 @@ def _swiglu(x, L):
     return (torch.nn.functional.silu(x @ L["W_G"]) * (x @ L["W_1"])) @ L["W_2"]
 
 
+def _plain(X):
+    """Rows as the row-wise kernels read them: contiguous and 16-byte aligned (a copy where they are not)."""
+    X = X.contiguous()
+    return X if X.data_ptr() % 16 == 0 else X.clone()
+
+
 class YocoStack:
     """weights: the dict produced by the synthetic generator (numpy arrays);
     dtype: torch.float32 or torch.bfloat16."""
@@ -117,14 +123,14 @@ class YocoStack:
         return torch.empty(self._scratch_bytes, dtype=torch.uint8, device=self.device)
 
     def _norm(self, X, gain):
-        return _rmsnorm(X, gain, self.eps) if self._native is None else yb.norm_rows(X, gain, self.eps)
+        return _rmsnorm(X, gain, self.eps) if self._native is None else yb.norm_rows(_plain(X), gain, self.eps)
 
     def _after_attention(self, a, X, L):
         """W_O, the residual and the SwiGLU half of Eq. 1 for the rows of a prompt."""
         if self._native is None:
             Y = a @ L["W_O"] + X
             return _rows(Y, lambda y: _swiglu(_rmsnorm(y, L["ln2"], self.eps), L) + y)
-        Y, xn = yb.norm_rows(a @ L["W_O"], L["ln2"], self.eps, add=X)
+        Y, xn = yb.norm_rows(a @ L["W_O"], L["ln2"], self.eps, add=_plain(X))
         return Y.add_(_rows(xn, lambda x: yb.glu_rows(x @ L["w_gu"].t()) @ L["W_2"]))
 
     # -- self-decoder: Eq. 1 with sliding-window attention (Eq. 8)
@@ -211,8 +217,8 @@ class YocoStack:
         nbytes, _ = yb.cross_attn_decode_workspace(cache, self.Hq)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         if self._native is not None:
-            X = torch.empty_like(x_last)
-            yb.stack_step(self._native, x_last, None, None, cache, length - 1, self._scratch(), ws, x_out=X)
+            X = torch.empty_like(x_last, memory_format=torch.contiguous_format)
+            yb.stack_step(self._native, _plain(x_last), None, None, cache, length - 1, self._scratch(), ws, x_out=X)
             return X
         lens = torch.tensor([length], dtype=torch.int64, device=self.device)
         X = x_last
@@ -259,17 +265,17 @@ class YocoStack:
         state = dict(rings=rings, cache=cache, ws_ring=ws[0], ws_cache=ws[1], length=0)
         if self._native is not None:
             state["scratch"], state["ws"] = self._scratch(), max(ws, key=torch.numel)
-            if self.self_kind == "gret":
-                state["ring_descs"], state["state_ptrs"] = None, (ctypes.c_void_p * len(rings))(*(r.data_ptr() for r in rings))
-            else:
-                state["ring_descs"], state["state_ptrs"] = (yb._Cache * len(rings))(*(r.desc for r in rings)), None
         return state
 
     def _native_logits(self, x, state, pos, whole):
         """Logits [1,vocab] of one token at position pos; whole: through both decoders, else through the cross-decoder alone."""
         logits = torch.empty((1, self._native.vocab), dtype=self.glue, device=self.device)
-        yb.stack_step(self._native, x, state["ring_descs"] if whole else None, state["state_ptrs"] if whole else None, state["cache"], pos,
-                      state["scratch"], state["ws"], logits=logits)
+        rings, descs, states = state["rings"], None, None       # described anew: a caller may have put copies in their place
+        if whole and self.self_kind == "gret":
+            states = (ctypes.c_void_p * len(rings))(*(yb._state(r, "state", 1, self.Hq, self.d, self.d) for r in rings))
+        elif whole:
+            descs = (yb._Cache * len(rings))(*(r.desc for r in rings))
+        yb.stack_step(self._native, _plain(x), descs, states, state["cache"], pos, state["scratch"], state["ws"], logits=logits)
         return logits
 
     def prefill(self, tokens, state):
