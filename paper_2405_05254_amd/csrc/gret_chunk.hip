@@ -406,11 +406,6 @@ __global__ void __launch_bounds__(256, 2) gret_output_kernel(SegArgs g) {
       o[1] = mfma(sh[x], q1[x], ks ? o[1] : zero);
       o[0] = mfma(sl[x], q0[x], o[0]);
       o[1] = mfma(sl[x], q1[x], o[1]);
-      if (ks < 7) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {                                        // a product, then its share of the next step's splitting
-        }
-      }
     }
     {
       const float gq = g_t[sqb * 32 + lq];
