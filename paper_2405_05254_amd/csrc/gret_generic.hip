@@ -125,53 +125,51 @@ __global__ void __launch_bounds__(256) gret_recurrent_kernel(GretView a) {
 
 }
 
-// ---- the decode step (T = 1) at dk = dv = 128, state updated in place: same thread -> state mapping as above, but
-// written for the memory system. The small operands are requested before the state, so that the first rows can be
-// worked on as soon as they land (loads come back in issue order); the state moves in four quarters of four rows per
-// thread with two quarters in flight, and a quarter is stored as soon as it is updated, so the launch reads and writes
-// at the same time instead of in two phases; the 16 row sums of a thread are reduced together (at every exchange a
-// lane keeps half of its rows: 16 exchanges instead of 80), after which lane pair kk / 2 of a half wavefront holds
-// row rr + 8 (kk / 2).
-template <typename T>
-__global__ void __launch_bounds__(256) gret_decode_kernel(GretView a) {
-  constexpr int kDim = 128;
-  __shared__ float red[4];
+// ---- the decode step (T = 1) at dk = dv = 128, state updated in place. Bound by HBM (a state read and written once) and,
+// below some hundred units, by latency; so a (sequence, head) gets 16 wavefronts, a thread only four rows
+// ev = rr + 32 r of four elements, and the whole state is requested behind the small operands before anything is
+// computed. A row is stored as soon as it is updated. The four row sums of a thread are reduced together (at the first two
+// exchanges a lane keeps half of its rows), after which the eight lanes kk / 8 of a half wavefront hold row
+// rr + 32 (kk / 8). Measured against 4 wavefronts of 16 rows a thread, 13 layers: 1 x 24 heads 94 -> 59 us, 8 x 24
+// 113 -> 90, 16 x 24 174 -> 158 (4.1 TB/s of 50 MB a layer), 32 x 24 272 -> 256; 8 wavefronts of 8 rows 67, 95, 168, 260.
+// NT: nontemporal accesses, see launch_gret_recurrent.
+constexpr int kStepRows = 4, kStepGroups = 128 / kStepRows;
+
+template <typename T, bool NT>
+__global__ void __launch_bounds__(32 * kStepGroups) gret_decode_kernel(GretView a) {
+  constexpr int kDim = 128, kR = kStepRows, kSame = 32 / kR;
+  __shared__ float red[2][kStepGroups / 2];
   const int h = blockIdx.x, b = blockIdx.y;
   const int kk = threadIdx.x & 31, rr = threadIdx.x >> 5;
   const int ek = kk * 4;
   const size_t bh = (size_t)b * a.H + h;
-  const T* q = (const T*)a.q + bh * kDim;
-  const T* k = (const T*)a.k + bh * kDim;
   const T* v = (const T*)a.v + bh * kDim;
-  float* st = a.state_out + bh * kDim * kDim + (size_t)rr * kDim + ek;    // row rr + 8 r is 8 r rows further
+  f32x4* st = (f32x4*)(a.state_out + bh * kDim * kDim + (size_t)rr * kDim + ek);
+  constexpr int kStride = kStepGroups * kDim / 4;             // from a thread's row to its next one
 
   const float gamma = __expf(a.log_gamma[bh]);
-  const f32x4 kf = load4<T>(k + ek), qf = load4<T>(q + ek);
-  float vv[16];
+  const f32x4 kf = load4<T>((const T*)a.k + bh * kDim + ek), qf = load4<T>((const T*)a.q + bh * kDim + ek);
+  float vv[kR];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) vv[r] = Elem<T>::load(v + rr + 8 * r);
+  for (int r = 0; r < kR; ++r) vv[r] = Elem<T>::load(v + rr + kStepGroups * r);
+  const int ev = rr + kStepGroups * (kk / kSame);             // the row whose output this lane ends up with
+  const bool first = kk % kSame == 0;                         // of the lanes that hold the same row
+  const float gate = a.gate && first ? Elem<T>::load((const T*)a.gate + bh * kDim + ev) : 0.f;
+  f32x4 S[kR];
+#pragma unroll
+  for (int r = 0; r < kR; ++r) S[r] = NT ? __builtin_nontemporal_load(st + r * kStride) : st[r * kStride];
 
-  f32x4 S[16];
-  auto load_quarter = [&](int qt) {
+  float part[kR];
 #pragma unroll
-    for (int r = 4 * qt; r < 4 * qt + 4; ++r) S[r] = __builtin_nontemporal_load((const f32x4*)(st + (size_t)r * 8 * kDim));
-  };
-  float part[16];
-  load_quarter(0);
-  load_quarter(1);
-#pragma unroll
-  for (int qt = 0; qt < 4; ++qt) {
-    if (qt + 2 < 4) load_quarter(qt + 2);
-#pragma unroll
-    for (int r = 4 * qt; r < 4 * qt + 4; ++r) {
-      S[r] = gamma * S[r] + kf * vv[r];
-      __builtin_nontemporal_store(S[r], (f32x4*)(st + (size_t)r * 8 * kDim));
-      part[r] = qf[0] * S[r][0] + qf[1] * S[r][1] + qf[2] * S[r][2] + qf[3] * S[r][3];
-    }
+  for (int r = 0; r < kR; ++r) {
+    S[r] = gamma * S[r] + kf * vv[r];
+    if (NT) __builtin_nontemporal_store(S[r], st + r * kStride);
+    else st[r * kStride] = S[r];
+    part[r] = qf[0] * S[r][0] + qf[1] * S[r][1] + qf[2] * S[r][2] + qf[3] * S[r][3];
   }
-  // reduce-scatter over the 32 lanes of the half wavefront
+  // reduce-scatter over the 32 lanes of the half wavefront: bit o of kk chooses the half of the rows at exchange o
 #pragma unroll
-  for (int w = 8, o = 16; w >= 1; w >>= 1, o >>= 1) {       // w rows stay per lane after the exchange with lane ^ o
+  for (int w = kR / 2, o = 16; w >= 1; w >>= 1, o >>= 1) {  // w rows stay per lane after the exchange with lane ^ o
     const bool upper = (kk & o) != 0;
 #pragma unroll
     for (int i = 0; i < w; ++i) {
@@ -180,22 +178,40 @@ __global__ void __launch_bounds__(256) gret_decode_kernel(GretView a) {
       part[i] = keep + __shfl_xor(send, o);
     }
   }
-  float out = a.scale * (part[0] + __shfl_xor(part[0], 1));
-  const int ev = rr + 8 * (kk >> 1);                         // the row this lane pair holds: bit o of kk chose its half at exchange o
+#pragma unroll
+  for (int o = kSame / 2; o >= 1; o >>= 1) part[0] += __shfl_xor(part[0], o);
+  float out = a.scale * part[0];
+  auto total = [&](float x, float* sums) {                    // over the workgroup
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = x;
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kStepGroups / 2; ++w) s += sums[w];
+    return s;
+  };
   if (a.group_norm) {
     const float inv_dv = 1.f / (float)kDim;
-    const float mean = block_sum((kk & 1) ? 0.f : out, red) * inv_dv;
+    const float mean = total(first ? out : 0.f, red[0]) * inv_dv;
     const float dlt = out - mean;
-    const float var = block_sum((kk & 1) ? 0.f : dlt * dlt, red) * inv_dv;
+    const float var = total(first ? dlt * dlt : 0.f, red[1]) * inv_dv;
     out = dlt * rsqrtf(var + a.eps);
   }
-  if (!(kk & 1)) {
-    if (a.gate) {                                            // swish gate of Eq. 7: y * g * sigmoid(g)
-      const float gv = Elem<T>::load((const T*)a.gate + bh * kDim + ev);
-      out *= gv / (1.f + __expf(-gv));
-    }
+  if (first) {
+    if (a.gate) out *= gate / (1.f + __expf(-gate));         // swish gate of Eq. 7: y * g * sigmoid(g)
     Elem<T>::store((T*)a.o + bh * kDim + ev, out);
   }
+}
+
+template <typename T>
+void launch_step(const GretView& a, hipStream_t s) {
+  // A layer's states are met again at the next token. Up to 16 MB of them, those of 16 layers fit the 256 MB behind the
+  // L2s and are left there; more than that is kept from displacing itself (13 layers: 8 x 24 heads 90 us against 102
+  // nontemporal, 12 x 24, just past the line, 136 against 145; 21 x 16 163 against 149, 16 x 24 182 against 156).
+  if ((size_t)a.B * a.H * 128 * 128 * sizeof(float) <= ((size_t)16 << 20))
+    hipLaunchKernelGGL((gret_decode_kernel<T, false>), dim3(a.H, a.B), dim3(32 * kStepGroups), 0, s, a);
+  else
+    hipLaunchKernelGGL((gret_decode_kernel<T, true>), dim3(a.H, a.B), dim3(32 * kStepGroups), 0, s, a);
 }
 
 __global__ void __launch_bounds__(256) fill_zero_kernel(float* p, size_t n) {
@@ -220,10 +236,8 @@ bool gret_recurrent_supported(const GretView& a) {
 hipError_t launch_gret_recurrent(const GretView& a, int dtype, hipStream_t s) {
   dim3 grid(a.H, a.B), block(256);
   if (a.T == 1 && a.dk == 128 && a.dv == 128 && a.state_in && a.state_in == a.state_out) {   // the decode step
-    if (dtype == YOCO_F32)
-      hipLaunchKernelGGL(gret_decode_kernel<float>, grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL(gret_decode_kernel<bf16_t>, grid, block, 0, s, a);
+    if (dtype == YOCO_F32) launch_step<float>(a, s);
+    else launch_step<bf16_t>(a, s);
     return hipGetLastError();
   }
   if (dtype == YOCO_F32)

@@ -345,3 +345,22 @@ def test_bf16_gret_stack_early_exit_and_generation(yoco):
     err = np.abs(np.stack(logits) - full).max()
     print("bf16 gret stack prompt + 8 decode steps vs full forward: %.3e" % err, flush=True)
     assert err <= 0.05 * np.abs(full).max()
+
+
+@pytest.mark.parametrize("dtype,B,H,gn,gated", [("f32", 1, 1, False, False), ("bf16", 2, 3, False, True), ("f32", 16, 16, True, True),
+                                                ("bf16", 1, 257, True, True), ("f32", 19, 24, True, False)])   # on both sides of 16 MB of states
+def test_gret_decode_step_of_many_units(yoco, dtype, B, H, gn, gated):
+    d, scale = 128, 128 ** -0.5
+    rng = np.random.default_rng(B * H)
+    q, k, v, gate = (ys.normal(rng, (B, H, d), 1.0, dtype) for _ in range(4))
+    lg = -rng.exponential(0.1, (B, H)).astype(np.float32)
+    S = rng.standard_normal((B, H, d, d)).astype(np.float32)
+    state = torch.from_numpy(S).cuda()
+    o = yoco.gret_decode(dev(q, dtype), dev(k, dtype), dev(v, dtype), torch.from_numpy(lg).cuda(), state, scale, group_norm=gn, eps=1e-6,
+                         gate=dev(gate, dtype) if gated else None)
+    one = lambda x: x[:, None]
+    ref, ref_s = oracle_gret(one(q), one(k), one(v), one(lg), scale, gn, 1e-6, S)
+    if gated:
+        ref = ref * oracle.swish(one(gate))
+    check(host(o), ref[:, 0], dtype, "gret decode step", relative=True)
+    check(host(state), ref_s, "f32", "gret decode step, state", relative=True)
