@@ -127,12 +127,12 @@ __global__ void __launch_bounds__(256) gret_recurrent_kernel(GretView a) {
 
 // ---- the decode step (T = 1) at dk = dv = 128, state updated in place. Bound by HBM (a state read and written once) and,
 // below some hundred units, by latency; so a (sequence, head) gets 16 wavefronts, a thread only four rows
-// ev = rr + 32 r of four elements, and the whole state is requested behind the small operands, the gate behind it (ahead of
-// it: 158 us at 16 x 24), before anything is computed. A row is stored as soon as it is updated. The four row sums of a thread are reduced together (at the first two
-// exchanges a lane keeps half of its rows), after which the eight lanes kk / 8 of a half wavefront hold row
-// rr + 32 (kk / 8). Measured against 4 wavefronts of 16 rows a thread, 13 layers: 1 x 24 heads 94 -> 59 us, 8 x 24
-// 113 -> 86, 16 x 24 174 -> 155 (4.2 TB/s of 50 MB a layer), 32 x 24 272 -> 248; 8 wavefronts of 8 rows 67, 95, 168, 260.
-// NT: nontemporal accesses, see launch_gret_recurrent.
+// ev = rr + 32 r of four elements, and the whole state is requested behind the small operands, the gate behind it (ahead
+// of it: 158 us at 16 x 24), before anything is computed. A row is stored as soon as it is updated. The four row sums of
+// a thread are reduced together (at the first two exchanges a lane keeps half of its rows), after which the eight lanes
+// kk / 8 of a half wavefront hold row rr + 32 (kk / 8). Measured against 4 wavefronts of 16 rows a thread, 13 layers:
+// 1 x 24 heads 94 -> 59 us, 8 x 24 113 -> 86, 16 x 24 174 -> 155 (4.2 TB/s of 50 MB a layer), 32 x 24 272 -> 248;
+// 8 wavefronts of 8 rows 67, 95, 168, 260. NT: nontemporal accesses, see launch_step.
 constexpr int kStepRows = 4, kStepGroups = 128 / kStepRows;
 
 template <typename T, bool NT>
