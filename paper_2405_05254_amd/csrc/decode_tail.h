@@ -19,7 +19,8 @@ struct SplitOut {
   float* ws;                 // [B][Hq][splits][128 + 4]: vector, max (log2 units), sum, tag
   bf16_t* o;                 // [B,Hq,128]
   int splits;                // the most a sequence can be split into
-  float inv_workgroups;      // 1 / how many workgroups the whole batch should make
+  float inv_ragged;          // 1 / how many workgroups the whole batch should make, when its lengths differ
+  float inv_even;            // ... and when they do not
   unsigned long long tag;
 };
 
@@ -42,13 +43,29 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
   float total = (float)c.B * (float)c.N_cap;         // unsplit: nothing depends on the other lengths
   if (out.splits > 1) {
     total = (float)len;
+    float inv = out.inv_even;
     if (lens && c.B > 1) {                           // the same float arithmetic in every workgroup: all agree on every sequence's splits
       total = 0.f;
-      for (int i = threadIdx.x & 63; i < c.B; i += 64) total += (float)clamp_len(lens[i]);
+      if (out.inv_ragged == out.inv_even) {
+        for (int i = threadIdx.x & 63; i < c.B; i += 64) total += (float)clamp_len(lens[i]);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
+      } else {
+        float longest = 0.f;
+        for (int i = threadIdx.x & 63; i < c.B; i += 64) {
+          const float n_i = (float)clamp_len(lens[i]);
+          total += n_i;
+          longest = fmaxf(longest, n_i);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          total += __shfl_xor(total, o);
+          longest = fmaxf(longest, __shfl_xor(longest, o));
+        }
+        if (longest * (float)c.B * 16.f > total * 17.f) inv = out.inv_ragged;   // equal: the longest is within a sixteenth of the mean
+      }
     }
-    const float share = fmaxf(total * (float)c.Hkv * out.inv_workgroups, (float)GRAIN);
+    const float share = fmaxf(total * (float)c.Hkv * inv, (float)GRAIN);
     n = (unsigned)__builtin_amdgcn_readfirstlane((int)ceilf((float)len / share - 0.1f));
     n = n < 1 ? 1 : n > (unsigned)out.splits ? (unsigned)out.splits : n;
   }

@@ -61,7 +61,7 @@ int check_heads(int Hq, int Hkv) {
 
 // Splits of the decode pass. Streaming reads on MI355X are fastest with few, long, contiguous streams: one workgroup per
 // CU (measured: 6.9 TB/s at 256 workgroups, 6.0 TB/s at 2048; 8 KV heads x 16384 rows 17.7 us at 256, 19.6 at 512).
-// `even`: the splits a batch of equal lengths gets. A split of a bf16 cache has at least 128 rows, one step of its four
+// `even`: the splits a sequence gets on average (a batch of equal lengths possibly fewer: inv_even). A split of a bf16 cache has at least 128 rows, one step of its four
 // wavefronts: a launch over few rows is latency, and a step more costs more than the workgroups saved (16 heads x 2016
 // rows: 13.4 us at 4 splits of 512 rows, 7.7 us at 16 of 128). Of an 8-bit or fp32 cache it has at least 512.
 // `most`: what the workspace holds and the grid launches. Twice as many where a split of `even` has rows enough (2560)
@@ -71,7 +71,7 @@ int check_heads(int Hq, int Hkv) {
 // decode call agree.
 struct Splits {
   int even, most;
-  float inv_workgroups;
+  float inv_ragged, inv_even;   // 1 / how many workgroups a batch of ragged, of equal lengths should make
 };
 
 Splits decode_splits(const yoco_kv_cache* c, int Hq) {
@@ -105,7 +105,20 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   if (s > coarse) s = bounded(s);
   int64_t most = s;
   if (c->dtype == YOCO_BF16 && units <= cus && s > 1 && s <= 128 && c->N_cap / s >= 2560) most = bounded(2 * s) > s ? bounded(2 * s) : s;
-  return {(int)s, (int)most, 1.f / (float)(units * s)};
+  // Equal lengths: no more workgroups than CUs where the count is no multiple, because a workgroup or two too many share
+  // a CU and the launch waits for them (24 units x 32768 rows: 264 workgroups 47.6 us in 8 bits and 87.4 in bf16, 240 36.2
+  // and 64.1; 200 units x 8192: 400 workgroups 74.7 and 144, 200 63.6 and 136; rolling caches, 160 units x 2048: 36.9
+  // -> 31.1). Where that leaves a quarter of the CUs without one, two rounds' worth is better for a bf16 cache (160 units x
+  // 16384: 160 workgroups 258 us, 320 268, 480 203; in 8 bits 107, 130, 108), if it makes at least one and a half (200 x 2
+  // does not) of splits of 1024 rows or more. Ragged lengths keep the larger count, of which short sequences take less
+  // (200 units of 1000 to 8192 rows: 88 us, at 200 workgroups 137).
+  int64_t n = s;
+  if (units < cus && units * s > cus) {
+    n = cus / units;
+    const int64_t twice = 2 * cus / units;
+    if (c->dtype == YOCO_BF16 && 4 * units * n < 3 * cus && 2 * units * twice >= 3 * cus && twice <= most && c->N_cap / twice >= 1024) n = twice;
+  }
+  return {(int)s, (int)most, 1.f / (float)(units * s), 1.f / (float)(units * n)};
 }
 
 // The tag a decode launch marks its published splits with: never 0, never the same twice in a process (a bijection of a
@@ -135,9 +148,9 @@ int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* le
     if (!yoco::decode_i8_supported(c, Hq))
       return fail(YOCO_ERR_UNSUPPORTED, "%s: an 8-bit cache serves up to 16 query heads per KV head, not %d", what, Hq / c.Hkv);
     if (k_new) return fail(YOCO_ERR_UNSUPPORTED, "%s: no fused append into an 8-bit cache", what);
-    return hip_result(yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_workgroups, next_tag(), o, s), what);
+    return hip_result(yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, next_tag(), o, s), what);
   } else if (yoco::decode_bf16_supported(c, Hq)) {
-    return hip_result(yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_workgroups, next_tag(), o, k_new, v_new, ring, s), what);
+    return hip_result(yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, next_tag(), o, k_new, v_new, ring, s), what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend
       e = yoco::launch_kv_append(c, k_new, v_new, lens, -1, ring, c.dtype, s);

@@ -22,6 +22,11 @@ SCALE = 1.0 / math.sqrt(D)
     ("bf16", 3, 1, 2300, [2300]),                           # 18 splits: two rounds of the widest merge
     ("bf16", 16, 1, 9000, [9000, 0, 7, 4400, 128, 127]),    # 16 heads in one workgroup, an empty sequence among long ones
     ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
+    ("bf16", 12, 12, 1100, [1100, 1100, 1090, 1100, 1100, 1100, 1100]),   # 84 units of equal lengths: 3 splits, not 4
+    ("bf16", 12, 12, 1100, [1100, 1100, 900, 1100, 1100, 1100, 1100]),    # ... just past what counts as equal
+    ("bf16", 34, 17, 4200, [4200] * 8),                     # 136 units: three splits, on half as many CUs as two rounds have
+    ("bf16", 17, 17, 1000, [1000] * 9),                     # 153 units: unsplit, in a workspace for two
+    ("int8", 3, 3, 5700, [5700] * 8),                       # 24 units: 10 splits, not 11
     ("int8", 4, 2, 1500, [1500, 513, 64]),
     ("int8", 13, 1, 3000, [2999, 1]),
 ])
