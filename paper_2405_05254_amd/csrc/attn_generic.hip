@@ -237,8 +237,8 @@ __global__ void __launch_bounds__(256) kv_write_kernel(yoco_kv_cache c, const S*
 }
 
 // One row per sequence at a device-side position: k, v [B,Hkv,d]; sequence b's
-// row goes to slot pos[b] + bias (ring: modulo N_cap). Out-of-range positions write
-// nothing.
+// row goes to slot pos[b] + bias (ring: modulo N_cap), to slot bias where the host
+// knows it (pos null). Out-of-range positions write nothing.
 template <typename S, typename D>
 __global__ void __launch_bounds__(256) kv_append_kernel(yoco_kv_cache c, const S* __restrict__ k,
                                                         const S* __restrict__ v, const int64_t* __restrict__ pos,
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(256) kv_append_kernel(yoco_kv_cache c, const S
     const int e8 = (int)(idx % d8);
     const int g = (int)((idx / d8) % c.Hkv);
     const int b = (int)(idx / ((int64_t)d8 * c.Hkv));
-    int64_t slot = pos[b] + bias;
+    int64_t slot = (pos ? pos[b] : 0) + bias;
     if (slot < 0) continue;
     if (slot >= c.N_cap) {
       if (!ring) continue;

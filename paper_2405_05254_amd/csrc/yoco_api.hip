@@ -153,7 +153,7 @@ int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* le
     return hip_result(yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, next_tag(), o, k_new, v_new, ring, s), what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend
-      e = yoco::launch_kv_append(c, k_new, v_new, lens, -1, ring, c.dtype, s);
+      e = yoco::launch_kv_append(c, k_new, v_new, lens, lens ? -1 : fixed_len - 1, ring, c.dtype, s);
       if (e != hipSuccess) return hip_result(e, what);
     }
     e = yoco::launch_decode_generic(c, q, lens, fixed_len, Hq, scale, ws, sp.most, s);

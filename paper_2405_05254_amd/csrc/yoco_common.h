@@ -74,7 +74,7 @@ hipError_t launch_decode_merge(const float* ws, void* o, int B, int Hq, int d, i
 hipError_t launch_kv_write(const yoco_kv_cache& c, const void* k, const void* v, const float* row_scale, int b, int64_t pos0, int64_t r0,
                            int64_t n, int src_dtype, hipStream_t s);
 hipError_t launch_kv_append(const yoco_kv_cache& c, const void* k, const void* v, const int64_t* pos, int64_t bias, int ring,
-                            int src_dtype, hipStream_t s);   // slot = pos[b] + bias
+                            int src_dtype, hipStream_t s);   // slot = pos[b] + bias; pos null: bias, of every sequence
 
 bool gret_recurrent_supported(const GretView& a);
 hipError_t launch_gret_recurrent(const GretView& a, int dtype, hipStream_t s);

@@ -19,6 +19,8 @@ def stack_config(Hq, Hkv_self, Hkv, dm, ffn, vocab, kind):
     (2, 2, 1, 256, 704, 1001, "swa", "bf16"),        # odd vocabulary: surplus rows of the last workgroup
     (4, 2, 4, 520, 1032, 300, "swa", "int8"),        # widths that are no multiple of a wavefront's 512 elements
     (17, 17, 17, 2184, 4104, 16390, "swa", "bf16"),  # more than one trip over K (2048), the wide classifier's variant
+    (17, 1, 1, 128, 256, 99, "swa", "bf16"),         # more heads per KV head than the fused decode serves: the row is appended by itself
+    (34, 2, 17, 256, 256, 50, "swa", "bf16"),
     (3, 3, 3, 384, 1056, 97, "gret", "bf16"),        # gated retention: log-decay rows behind the projections, odd head count
 ])
 def test_bf16_stack_matches_the_torch_ops(Hq, Hkv_self, Hkv, dm, ffn, vocab, kind, cache):
