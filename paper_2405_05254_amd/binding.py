@@ -254,6 +254,11 @@ def _state(t, name, B, H, dk, dv):
     return _dev(t, name)
 
 
+def _bf16(t, name, shape):
+    if t.dtype != torch.bfloat16 or t.shape != shape:
+        raise YocoError("%s must be bfloat16 %s, not %s %s" % (name, list(shape), t.dtype, list(t.shape)))
+
+
 def stack_step_scratch(stack):
     n = C.c_size_t()
     _check(lib().yoco_stack_step_scratch(C.byref(stack), C.byref(n)))
@@ -261,8 +266,14 @@ def stack_step_scratch(stack):
 
 
 def stack_step(stack, x, rings, states, cache, pos, scratch, workspace, x_out=None, logits=None):
-    """One token through a bf16 stack (yoco_stack_step). rings: ctypes array of cache descriptors or None; states: ctypes
-    array of state pointers or None; both None: the cross-decoder alone."""
+    """One token through a bf16 stack (yoco_stack_step). x, x_out [1,d_model], logits [1,vocab]; rings: ctypes array of
+    cache descriptors or None; states: ctypes array of state pointers or None; both None: the cross-decoder alone."""
+    for t, name, width in ((x, "x", stack.d_model), (x_out, "x_out", stack.d_model), (logits, "logits", stack.vocab)):
+        if t is not None:
+            _bf16(t, name, (1, width))
+    for per_layer, name in ((rings, "rings"), (states, "states")):
+        if per_layer is not None and len(per_layer) != stack.n_self:
+            raise YocoError("%s must hold one entry per self-decoder layer" % name)
     _check(lib().yoco_stack_step(C.byref(stack), _dev(x, "x"), rings, states, C.byref(cache.desc), pos,
                                  None if x_out is None else _dev(x_out, "x_out"), None if logits is None else _dev(logits, "logits"),
                                  *_ws(scratch), *_ws(workspace), _stream()))
@@ -270,6 +281,12 @@ def stack_step(stack, x, rings, states, cache, pos, scratch, workspace, x_out=No
 
 def norm_rows(x, gain, eps, add=None):
     """RMSNorm(x) * gain over the rows of a bf16 [rows,dim] tensor; with `add`: (x + add, RMSNorm(x + add) * gain) (yoco_norm_rows)."""
+    if x.dim() != 2:
+        raise YocoError("x must be [rows,dim]")
+    _bf16(x, "x", x.shape)
+    _bf16(gain, "gain", x.shape[1:])
+    if add is not None:
+        _bf16(add, "add", x.shape)
     xn = torch.empty_like(x)
     y = None if add is None else torch.empty_like(x)
     if not x.shape[0]:
@@ -281,6 +298,9 @@ def norm_rows(x, gain, eps, add=None):
 
 def glu_rows(gu):
     """bf16 [rows, 2 ffn] -> swish(first half) * second half (yoco_glu_rows)."""
+    if gu.dim() != 2 or gu.shape[1] % 2:
+        raise YocoError("gu must be [rows, 2 ffn]")
+    _bf16(gu, "gu", gu.shape)
     h = torch.empty((gu.shape[0], gu.shape[1] // 2), dtype=gu.dtype, device=gu.device)
     if not h.shape[0]:
         return h

@@ -123,7 +123,9 @@ class YocoStack:
         return torch.empty(self._scratch_bytes, dtype=torch.uint8, device=self.device)
 
     def _norm(self, X, gain):
-        return _rmsnorm(X, gain, self.eps) if self._native is None else yb.norm_rows(_plain(X), gain, self.eps)
+        if self._native is None or X.dtype != torch.bfloat16 or X.dim() != 2 or X.shape[1] != gain.shape[0]:
+            return _rmsnorm(X, gain, self.eps)
+        return yb.norm_rows(_plain(X), gain, self.eps)
 
     def _after_attention(self, a, X, L):
         """W_O, the residual and the SwiGLU half of Eq. 1 for the rows of a prompt."""

@@ -236,3 +236,31 @@ def test_eight_bit_cache_sizes_and_validation():
     assert L.yoco_cross_attn_decode_workspace(C.byref(d), 34, C.byref(ws), C.byref(s)) == 0
     assert L.yoco_cross_attn_decode(C.byref(d), p, p, p, 34, 1.0, p, ws.value, None) == -2
     assert L.yoco_cross_attn_decode(C.byref(d), p, p, p, 4, 1.0, p, 16, None) == -4
+
+
+def test_stack_calls_refuse_tensors_of_another_shape_or_type():
+    """The wrappers of a stack's step and row passes look at shapes and types before the device (CPU tensors here)."""
+    import torch
+    st = yb._Stack(d_model=16, vocab=24, n_self=2)
+    bf = lambda *shape, dtype=torch.bfloat16: torch.zeros(shape, dtype=dtype)  # noqa: E731
+
+    def step(x=bf(1, 16), rings=None, states=None, **out):
+        yb.stack_step(st, x, rings, states, None, 0, None, None, **out)
+    two = (yb._Cache * 2)(), (C.c_void_p * 2)()
+    for bad in (dict(x=bf(2, 16)), dict(x=bf(1, 8)), dict(x=bf(16)), dict(x=bf(1, 16, dtype=torch.float32)), dict(x_out=bf(1, 8)),
+                dict(x_out=bf(1, 16, dtype=torch.float16)), dict(logits=bf(1, 23)), dict(logits=bf(1, 24, dtype=torch.float32))):
+        with pytest.raises(yoco.YocoError, match="must be bfloat16"):
+            step(**bad)
+    for bad in (dict(rings=(yb._Cache * 1)()), dict(states=(C.c_void_p * 1)())):
+        with pytest.raises(yoco.YocoError, match="one entry per"):
+            step(**bad)
+    for ok in (dict(), dict(rings=two[0], logits=bf(1, 24)), dict(states=two[1], x_out=bf(1, 16))):
+        with pytest.raises(yoco.YocoError, match="device tensor"):           # shapes pass, the CPU tensor does not
+            step(**ok)
+    for x, gain, add in ((bf(3, 16, dtype=torch.float32), bf(16), None), (bf(3, 16), bf(8), None), (bf(3, 16), bf(16, dtype=torch.float32), None),
+                         (bf(3, 16), bf(16), bf(2, 16)), (bf(3, 16), bf(16), bf(3, 16, dtype=torch.float32)), (bf(16), bf(16), None)):
+        with pytest.raises(yoco.YocoError, match="must be"):
+            yb.norm_rows(x, gain, 1e-6, add=add)
+    for gu in (bf(3, 15), bf(30), bf(3, 16, dtype=torch.float32)):
+        with pytest.raises(yoco.YocoError, match="must be"):
+            yb.glu_rows(gu)

@@ -112,3 +112,19 @@ def test_a_state_whose_caches_were_replaced_by_copies(kind):
     for t in toks[30:34]:
         a, b = st.decode_step(t, state), st.decode_step(t, held)
         assert torch.equal(a, b)
+
+
+def test_rows_that_do_not_fit_the_stack_are_refused():
+    st = small_stack("swa")
+    X = st.self_decoder(torch.from_numpy(ys.tokens(1, 40, 200)).cuda())
+    cache = st.write_cache(X)
+    for bad in (X[38:], X[39:].float(), X[39:, :128]):
+        with pytest.raises(RuntimeError):
+            st.cross_decoder_decode(bad, cache, 40)
+    for bad in (X.float(), X[:, :128].contiguous()):
+        with pytest.raises(RuntimeError):
+            st.cross_decoder_rows(bad, cache, 0)
+        with pytest.raises(RuntimeError):
+            st.write_cache(bad)
+    again = st.write_cache(X[:, None])                               # rows with a dim of 1 between: as torch ops take them
+    assert torch.allclose(again.planes()[0].float(), cache.planes()[0].float(), rtol=2 ** -6, atol=1e-3)
