@@ -106,12 +106,19 @@ const yoco_kv_cache& cache(PyObject* o) {
   return *(const yoco_kv_cache*)p;
 }
 
+// The interpreter lock is given up for the lifetime; taken back also where an exception passes (a device that is not there).
+struct Unlocked {
+  PyThreadState* s = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(s); }
+};
 // Runs the call without the interpreter lock (a full launch queue blocks) and raises what it reports.
 template <typename F>
 void call(F f) {
-  PyThreadState* s = PyEval_SaveThread();
-  const int rc = f();
-  PyEval_RestoreThread(s);
+  int rc;
+  {
+    Unlocked u;
+    rc = f();
+  }
   if (rc) fail("libyoco error %d: %s", rc, p_yoco_last_error_string());
 }
 

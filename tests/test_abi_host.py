@@ -264,3 +264,33 @@ def test_stack_calls_refuse_tensors_of_another_shape_or_type():
     for gu in (bf(3, 15), bf(30), bf(3, 16, dtype=torch.float32)):
         with pytest.raises(yoco.YocoError, match="must be"):
             yb.glu_rows(gu)
+
+
+def test_a_call_without_a_device_raises():
+    """Where there is no GPU, torch's stream query throws while the interpreter lock is given up; the caller gets its
+    error. In a process of its own: the lock must be held again when the error is raised."""
+    import subprocess
+    import sys
+    text = """
+import ctypes as C, threading, types, torch
+import paper_2405_05254_amd as yoco
+from paper_2405_05254_amd import binding as yb
+d = yb._Cache()
+p = 0x7f0000000000
+assert yoco.lib().yoco_kv_cache_init(p, yoco.kv_cache_bytes(1, 2, 64, 8, yoco.BF16), 1, 2, 64, 8, yoco.BF16, C.byref(d)) == 0
+none = torch.zeros((0, 2, 64), dtype=torch.bfloat16)
+busy = threading.Thread(target=lambda: [sum(range(100)) for _ in range(20000)])
+busy.start()
+for _ in range(50):
+    try:
+        yoco.global_kv_write(types.SimpleNamespace(address=C.addressof(d), desc=d), none, none, 0, 0)
+    except RuntimeError as e:
+        pass
+    else:
+        raise SystemExit("no error")
+busy.join()
+print("raised")
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="", ROCR_VISIBLE_DEVICES="")
+    r = subprocess.run([sys.executable, "-c", text], cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("raised"), (r.returncode, r.stdout, r.stderr[-2000:])
