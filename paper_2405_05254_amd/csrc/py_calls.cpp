@@ -11,6 +11,7 @@
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
 #include <stdarg.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "yoco.h"
@@ -127,14 +128,13 @@ struct Entry {
   template <int N>
   static PyObject* run(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != N) return PyErr_Format(PyExc_TypeError, "expected %d arguments, got %zd", N, n);
+    HANDLE_TH_ERRORS                     // torch's exceptions arrive as the types that torch raises (OutOfMemoryError)
     try {
       return F(a);
     } catch (const Failed&) {
       return nullptr;
-    } catch (const std::exception& e) {
-      PyErr_SetString(PyExc_RuntimeError, e.what());
-      return nullptr;
     }
+    END_HANDLE_TH_ERRORS
   }
 };
 PyObject* wrap(const at::Tensor& t, PyObject* given) {

@@ -519,3 +519,10 @@ def test_e2e_early_exit_128k(yoco):
         ref.append(oracle.cross_attn_row(host(qc[i:i + 1, h:h + 1]), Kh, Vh, 0, 0, i, scale))
         got.append(host(oc[i, h]))
     check(np.array(got), np.array(ref), "bf16", "e2e %s sampled rows" % last_cross)
+
+
+def test_an_output_that_does_not_fit_raises_torchs_out_of_memory_error(yoco):
+    one = torch.zeros((1, 1, 1, 128), dtype=torch.bfloat16, device="cuda")
+    huge = one.expand(1, 1 << 36, 1, 128)                   # 16 TiB once it is contiguous, 256 bytes as it stands
+    with pytest.raises(torch.OutOfMemoryError):
+        yoco.swa_prefill(huge, huge, huge, 128, 1.0)
