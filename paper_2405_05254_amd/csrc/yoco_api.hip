@@ -3,11 +3,11 @@
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>
+#include <sys/random.h>
 
 #include <atomic>
 #include <chrono>
 #include <mutex>
-#include <random>
 
 #include "yoco_common.h"
 
@@ -124,9 +124,10 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
 // The tag a decode launch marks its published splits with: never 0, never the same twice in a process (a bijection of a
 // counter), and nothing that other data is likely to look like.
 unsigned long long next_tag() {
-  static std::atomic<uint64_t> n{[] {
-    std::random_device r;
-    return ((uint64_t)r() << 32) ^ r() ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+  static std::atomic<uint64_t> n{[] {                // nothing here throws: callers are C
+    uint64_t start = 0;
+    if (getrandom(&start, sizeof(start), GRND_NONBLOCK) != (ssize_t)sizeof(start)) start = (uint64_t)(uintptr_t)&start;
+    return start ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
   }()};
   uint64_t z;
   do {

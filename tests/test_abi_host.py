@@ -294,3 +294,10 @@ print("raised")
     env = dict(os.environ, HIP_VISIBLE_DEVICES="", ROCR_VISIBLE_DEVICES="")
     r = subprocess.run([sys.executable, "-c", text], cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("raised"), (r.returncode, r.stdout, r.stderr[-2000:])
+
+
+def test_no_c_entry_draws_from_a_source_that_throws():
+    """std::random_device throws where the system has no randomness to give; a C caller has nothing to catch it with."""
+    import subprocess
+    imported = subprocess.run(["nm", "-D", "--undefined-only", yb.lib_path()], capture_output=True, text=True, check=True).stdout
+    assert "random_device" not in imported
