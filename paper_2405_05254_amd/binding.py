@@ -145,9 +145,13 @@ class KVCache:
         self.mem = torch.empty(self.bytes, dtype=torch.uint8, device=device)
         self.desc = _Cache()
         _check(lib().yoco_kv_cache_init(self.mem.data_ptr(), self.bytes, B, Hkv, d, N_cap, code, C.byref(self.desc)))
-        self.address = C.addressof(self.desc)                # what the native calls take
         self.B, self.Hkv, self.d, self.N_cap, self.dtype = B, Hkv, d, N_cap, dtype
         self.io_dtype = torch.bfloat16 if dtype == torch.int8 else dtype     # of the queries and outputs on this cache
+
+    @property
+    def address(self):
+        """Where the descriptor is, for the native calls (asked each time: a program may put another in its place)."""
+        return C.addressof(self.desc)
 
     def planes(self):
         """Views [B,Hkv,N_cap,d] of the K and V planes (for tests and for filling synthetic caches)."""

@@ -98,7 +98,7 @@ bool truth(PyObject* o) {
   if (x < 0) throw Failed();
   return x != 0;
 }
-const yoco_kv_cache& cache(PyObject* o) {
+yoco_kv_cache cache(PyObject* o) {        // a copy: the call runs without the interpreter lock
   void* p = PyLong_AsVoidPtr(o);
   if (!p) {
     if (!PyErr_Occurred()) PyErr_SetString(g_error, "null cache");
@@ -171,7 +171,7 @@ PyObject* swa_prefill(PyObject* const* a) {
 
 // cache, k, v, row_scale or None, b, pos0
 PyObject* global_kv_write(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &k = tensor(a[1], "k"), &v = tensor(a[2], "v");
   const int64_t n = k.dim() ? k.size(0) : 0;
   if (n && (!same_rows(k, n, c) || v.sizes() != k.sizes() || v.scalar_type() != k.scalar_type())) fail("k/v rows do not match the cache");
@@ -190,7 +190,7 @@ PyObject* global_kv_write(PyObject* const* a) {
 
 // ring, k, v, b, pos0
 PyObject* swa_cache_write(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &k = tensor(a[1], "k"), &v = tensor(a[2], "v");
   const int64_t n = k.dim() ? k.size(0) : 0;
   if (n && (!same_rows(k, n, c) || v.sizes() != k.sizes() || v.scalar_type() != k.scalar_type())) fail("k/v rows do not match the cache");
@@ -203,7 +203,7 @@ PyObject* swa_cache_write(PyObject* const* a) {
 
 // cache, k, v, pos, ring
 PyObject* kv_cache_append(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &k = tensor(a[1], "k"), &v = tensor(a[2], "v"), &pos = tensor(a[3], "pos");
   if (!same_rows(k, c.B, c) || v.sizes() != k.sizes() || v.scalar_type() != k.scalar_type()) fail("k/v rows do not match the cache");
   check_lens(c, pos, "pos");
@@ -216,7 +216,7 @@ PyObject* kv_cache_append(PyObject* const* a) {
 
 // cache, q, b, q_pos0, scale, out, workspace
 PyObject* cross_attn_prefill(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor& q = tensor(a[1], "q");
   if (q.dim() != 3 || q.size(2) != c.d || q.scalar_type() != io_dtype(c)) fail("q does not match the cache");
   const int64_t b = integer(a[2]), q_pos0 = integer(a[3]);
@@ -230,7 +230,7 @@ PyObject* cross_attn_prefill(PyObject* const* a) {
 
 // cache, q, lens, scale, workspace, out
 PyObject* cross_attn_decode(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &q = tensor(a[1], "q"), &lens = tensor(a[2], "lens");
   check_query(c, q);
   check_lens(c, lens, "lens");
@@ -244,7 +244,7 @@ PyObject* cross_attn_decode(PyObject* const* a) {
 
 // cache, q, lens, scale, out
 PyObject* cross_attn_decode_noalloc(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &q = tensor(a[1], "q"), &lens = tensor(a[2], "lens");
   check_query(c, q);
   check_lens(c, lens, "lens");
@@ -258,7 +258,7 @@ PyObject* cross_attn_decode_noalloc(PyObject* const* a) {
 
 // ring, q, lens, scale, workspace, out, k_new, v_new
 PyObject* swa_decode(PyObject* const* a) {
-  const yoco_kv_cache& c = cache(a[0]);
+  const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &q = tensor(a[1], "q"), &lens = tensor(a[2], "lens");
   check_query(c, q);
   if (c.dtype == YOCO_INT8) fail("q does not match the cache");

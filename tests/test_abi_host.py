@@ -301,3 +301,22 @@ def test_no_c_entry_draws_from_a_source_that_throws():
     import subprocess
     imported = subprocess.run(["nm", "-D", "--undefined-only", yb.lib_path()], capture_output=True, text=True, check=True).stdout
     assert "random_device" not in imported
+
+
+def bare_cache():
+    """A KVCache whose planes are addresses that nothing reads."""
+    cache = yb.KVCache.__new__(yb.KVCache)
+    cache.desc = yb._Cache()
+    assert yoco.lib().yoco_kv_cache_init(0x7f0000000000, yoco.kv_cache_bytes(1, 2, 64, 8, yoco.BF16), 1, 2, 64, 8, yoco.BF16, C.byref(cache.desc)) == 0
+    return cache
+
+
+def test_calls_see_the_descriptor_that_a_cache_has_now():
+    import torch
+    cache = bare_cache()
+    cache.desc = yb._Cache(cache.desc.k, cache.desc.v, 1, 3, 64, yoco.BF16, 8)     # another one in its place: 3 KV heads
+    rows = lambda heads: torch.zeros((1, heads, 64), dtype=torch.bfloat16)  # noqa: E731
+    with pytest.raises(yoco.YocoError, match="do not match"):
+        yoco.global_kv_write(cache, rows(2), rows(2), 0, 0)
+    with pytest.raises(yoco.YocoError, match="device tensor"):
+        yoco.global_kv_write(cache, rows(3), rows(3), 0, 0)
