@@ -154,6 +154,11 @@ void check_query(const yoco_kv_cache& c, const at::Tensor& q) {
 }
 bool same_rows(const at::Tensor& t, int64_t n, const yoco_kv_cache& c) { return t.dim() == 3 && t.size(0) == n && t.size(1) == c.Hkv && t.size(2) == c.d; }
 
+int64_t rows(const at::Tensor& k) {
+  if (!k.dim()) fail("k/v rows do not match the cache");
+  return k.size(0);
+}
+
 // q, k, v, window, scale, out
 PyObject* swa_prefill(PyObject* const* a) {
   const at::Tensor &q = tensor(a[0], "q"), &k = tensor(a[1], "k"), &v = tensor(a[2], "v");
@@ -173,7 +178,7 @@ PyObject* swa_prefill(PyObject* const* a) {
 PyObject* global_kv_write(PyObject* const* a) {
   const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &k = tensor(a[1], "k"), &v = tensor(a[2], "v");
-  const int64_t n = k.dim() ? k.size(0) : 0;
+  const int64_t n = rows(k);
   if (n && (!same_rows(k, n, c) || v.sizes() != k.sizes() || v.scalar_type() != k.scalar_type())) fail("k/v rows do not match the cache");
   const void* rs = nullptr;
   if (!none(a[3])) {
@@ -192,7 +197,7 @@ PyObject* global_kv_write(PyObject* const* a) {
 PyObject* swa_cache_write(PyObject* const* a) {
   const yoco_kv_cache c = cache(a[0]);
   const at::Tensor &k = tensor(a[1], "k"), &v = tensor(a[2], "v");
-  const int64_t n = k.dim() ? k.size(0) : 0;
+  const int64_t n = rows(k);
   if (n && (!same_rows(k, n, c) || v.sizes() != k.sizes() || v.scalar_type() != k.scalar_type())) fail("k/v rows do not match the cache");
   const int64_t b = integer(a[3]), pos0 = integer(a[4]);
   void *kp = n ? dev(k, "k") : nullptr, *vp = n ? dev(v, "v") : nullptr;

@@ -320,3 +320,11 @@ def test_calls_see_the_descriptor_that_a_cache_has_now():
         yoco.global_kv_write(cache, rows(2), rows(2), 0, 0)
     with pytest.raises(yoco.YocoError, match="device tensor"):
         yoco.global_kv_write(cache, rows(3), rows(3), 0, 0)
+
+
+def test_a_scalar_is_no_empty_set_of_rows():
+    import torch
+    one = torch.zeros((), dtype=torch.bfloat16)
+    for write in (yoco.global_kv_write, yoco.swa_cache_write, lambda c, k, v, b, p: yoco.global_kv_write_scaled(c, k, v, torch.zeros(0), b, p)):
+        with pytest.raises(yoco.YocoError, match="do not match"):
+            write(bare_cache(), one, one, 0, 0)
