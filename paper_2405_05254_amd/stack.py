@@ -39,7 +39,7 @@ def _swiglu(x, L):
 
 
 def _plain(X):
-    """Rows as the row-wise kernels read them: contiguous and 16-byte aligned (a copy where they are not)."""
+    """A tensor as libyoco reads it: contiguous and 16-byte aligned (a copy where it is not)."""
     X = X.contiguous()
     return X if X.data_ptr() % 16 == 0 else X.clone()
 
@@ -100,6 +100,7 @@ class YocoStack:
         def describe(layers, names):
             out = (yb._Layer * len(layers))()
             for s, L in zip(out, layers):
+                L["ln1"], L["ln2"] = _plain(L["ln1"]), _plain(L["ln2"])
                 L["w_in"], L["w_o"], L["w_gu"], L["w_2"] = join(L, *names), join(L, "W_O"), join(L, "W_G", "W_1"), join(L, "W_2")
                 for n in ("ln1", "w_in", "w_o", "ln2", "w_gu", "w_2"):
                     setattr(s, n, L[n].data_ptr())
@@ -108,6 +109,7 @@ class YocoStack:
         st = yb._Stack()
         self._self_desc, self._cross_desc = describe(self.self_layers, into), describe(self.cross_layers, ("W_Q",))
         st.self, st.cross = self._self_desc, self._cross_desc
+        self.kv["ln"], self.final_ln = _plain(self.kv["ln"]), _plain(self.final_ln)
         self.kv["w_kv"] = join(self.kv, "W_K", "W_V")
         out = {"W_out": self.W_out}
         self.w_out = join(out, "W_out")

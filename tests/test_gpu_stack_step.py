@@ -128,3 +128,56 @@ def test_rows_that_do_not_fit_the_stack_are_refused():
             st.write_cache(bad)
     again = st.write_cache(X[:, None])                               # rows with a dim of 1 between: as torch ops take them
     assert torch.allclose(again.planes()[0].float(), cache.planes()[0].float(), rtol=2 ** -6, atol=1e-3)
+
+
+def weights_on_device(kind="swa"):
+    """The small stack's weights as bf16 GPU tensors, which a stack takes as they are."""
+    w = ys.stack_weights(3, stack_config(2, 2, 2, 256, 704, 200, kind), "bf16")
+
+    def dev(x):
+        return torch.as_tensor(x).to("cuda", torch.bfloat16)
+    for holder in w["self"] + w["cross"] + [w["kv"], w]:
+        for n, x in holder.items():
+            if isinstance(x, np.ndarray):
+                holder[n] = dev(x)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for holder, names in [(L, ("ln1", "ln2")) for L in w["self"] + w["cross"]] + [(w["kv"], ("ln",)), (w, ("final_ln",))]:
+        for n in names:
+            holder[n] = (1 + 0.2 * torch.randn(256, device="cuda", generator=gen)).bfloat16()
+    return w
+
+
+def request(st, toks):
+    """Logits of a prompt's last row, of four token steps and of the early exit over all of it."""
+    state = st.new_generation_state(48)
+    out = [st.prefill(toks[:30], state)] + [st.decode_step(t, state) for t in toks[30:34]]
+    return torch.cat(out + [st.forward_early_exit(toks[:34])[0]]).float()
+
+
+def as_torch_ops(w):
+    """The same stack in torch ops, on weights of its own."""
+    import copy
+
+    from paper_2405_05254_amd.stack import YocoStack
+    st = YocoStack(copy.deepcopy(w), torch.bfloat16, glue_dtype=torch.bfloat16)
+    st._native = None
+    return st
+
+
+def close(got, ref):
+    return ((got - ref).norm() / ref.norm()).item() < 1.5e-2          # as in test_bf16_stack_matches_the_torch_ops
+
+
+@pytest.mark.parametrize("how", ["strided", "misaligned"])
+def test_gains_of_any_stride_and_alignment(how):
+    from paper_2405_05254_amd.stack import YocoStack
+    w = weights_on_device()
+    toks = torch.from_numpy(ys.tokens(1, 40, 200)).cuda()
+    ref = request(as_torch_ops(w), toks)
+    for holder, names in [(L, ("ln1", "ln2")) for L in w["self"] + w["cross"]] + [(w["kv"], ("ln",)), (w, ("final_ln",))]:
+        for n in names:
+            room = torch.zeros(256 * 2 + 1, dtype=torch.bfloat16, device="cuda")
+            view = room[0:512:2] if how == "strided" else room[1:257]
+            holder[n] = view.copy_(holder[n])
+    st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+    assert st._native is not None and close(request(st, toks), ref)
