@@ -77,13 +77,31 @@ class YocoStack:
 
     def _lay_out(self):
         """The stack as libyoco sees it: every weight with a row per output, matrices that read the same input joined.
-        None when a width has no kernel (a torch step serves it)."""
+        None when a shape has no kernel or a weight is not the plain matrix or row that the kernels read (torch ops serve such a
+        stack, and say what they miss)."""
         layers = self.self_layers + self.cross_layers
         if not self.cross_layers or self.embed.device.type != "cuda":
             return None
-        dm, ffn, vocab = self.embed.shape[1], layers[0]["W_2"].shape[0], self.W_out.shape[1]
-        if dm % 8 or ffn % 8 or max(dm, ffn, self.Hq * self.d) > 16384 or any(L["W_2"].shape[0] != ffn for L in layers):
+        gret = self.self_kind == "gret"
+        into = ("W_Q", "W_K", "W_V") + (("W_gate", "W_gamma") if gret else ())
+        dm, ffn, vocab = self.embed.shape[1], layers[0]["W_2"].shape[0], self.W_out.shape[-1]
+        qd, kd, ckd = (h * self.d for h in (self.Hq, self.Hkv_self, self.Hkv))
+        if dm % 8 or ffn % 8 or max(dm, ffn, qd) > 16384 or min(dm, ffn, vocab, qd, kd, ckd) < 1 or not self.tau > 0:
             return None
+        if self.Hq % self.Hkv or (self.self_layers and (self.Hq != self.Hkv_self if gret else self.Hq % self.Hkv_self)):
+            return None
+        shapes = dict(ln=(dm,), ln1=(dm,), ln2=(dm,), W_Q=(dm, qd), W_K=(dm, kd), W_V=(dm, kd), W_gate=(dm, qd), W_gamma=(dm, self.Hq), W_O=(qd, dm),
+                      W_G=(dm, ffn), W_1=(dm, ffn), W_2=(ffn, dm))
+        rest = ("ln1", "ln2", "W_O", "W_G", "W_1", "W_2")
+        wanted = [(L.get(n), shapes[n]) for L in self.self_layers for n in into + rest]
+        wanted += [(L.get(n), shapes[n]) for L in self.cross_layers for n in ("W_Q",) + rest]
+        wanted += [(self.kv.get("ln"), (dm,)), (self.kv.get("W_K"), (dm, ckd)), (self.kv.get("W_V"), (dm, ckd)), (self.final_ln, (dm,)), (self.W_out, (dm, vocab))]
+        if any(t is None or t.shape != shape or t.dtype != torch.bfloat16 or t.device != self.embed.device for t, shape in wanted):
+            return None
+        st = yb._Stack()
+        st.n_self, st.n_cross, st.d_model, st.ffn, st.vocab = len(self.self_layers), len(self.cross_layers), dm, ffn, vocab
+        st.Hq, st.Hkv_self, st.Hkv, st.d, st.gret = self.Hq, self.Hkv_self, self.Hkv, self.d, int(gret)
+        st.scale, st.eps, st.tau = self.scale, self.eps, self.tau
 
         def join(L, *names):
             rows = torch.cat([L[n].t() for n in names])
@@ -94,9 +112,6 @@ class YocoStack:
                 at += m
             return rows
 
-        gret = self.self_kind == "gret"
-        into = ("W_Q", "W_K", "W_V") + (("W_gate", "W_gamma") if gret else ())
-
         def describe(layers, names):
             out = (yb._Layer * len(layers))()
             for s, L in zip(out, layers):
@@ -106,7 +121,6 @@ class YocoStack:
                     setattr(s, n, L[n].data_ptr())
             return out
 
-        st = yb._Stack()
         self._self_desc, self._cross_desc = describe(self.self_layers, into), describe(self.cross_layers, ("W_Q",))
         st.self, st.cross = self._self_desc, self._cross_desc
         self.kv["ln"], self.final_ln = _plain(self.kv["ln"]), _plain(self.final_ln)
@@ -115,9 +129,6 @@ class YocoStack:
         self.w_out = join(out, "W_out")
         self.W_out = out["W_out"]
         st.kv_ln, st.w_kv, st.final_ln, st.w_out = (t.data_ptr() for t in (self.kv["ln"], self.kv["w_kv"], self.final_ln, self.w_out))
-        st.n_self, st.n_cross, st.d_model, st.ffn, st.vocab = len(self.self_layers), len(self.cross_layers), dm, ffn, vocab
-        st.Hq, st.Hkv_self, st.Hkv, st.d, st.gret = self.Hq, self.Hkv_self, self.Hkv, self.d, int(gret)
-        st.scale, st.eps, st.tau = self.scale, self.eps, self.tau
         self._scratch_bytes = yb.stack_step_scratch(st)
         return st
 

@@ -181,3 +181,26 @@ def test_gains_of_any_stride_and_alignment(how):
             holder[n] = view.copy_(holder[n])
     st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
     assert st._native is not None and close(request(st, toks), ref)
+
+
+def test_stacks_without_a_native_step_run_as_torch_ops():
+    """What torch ops take, or refuse only where it is used, does not keep a stack from being made or served."""
+    from paper_2405_05254_amd.stack import YocoStack
+    toks = torch.from_numpy(ys.tokens(1, 40, 200)).cuda()
+    w = weights_on_device()
+    w["cross"][1]["ln2"] = torch.full((1,), 1.25, dtype=torch.bfloat16, device="cuda")        # one gain for every column
+    w["self"][0]["ln1"] = w["self"][0]["ln1"][None]
+    st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+    got = request(st, toks)
+    w["cross"][1]["ln2"], w["self"][0]["ln1"] = w["cross"][1]["ln2"].expand(256), w["self"][0]["ln1"][0]
+    assert close(request(YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16), toks), got)
+    w = weights_on_device()
+    w["Hkv"] = 1                                                     # fewer heads than W_K of Eq. 2 has columns for
+    st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+    X = st.self_decoder(toks)                                        # the self-decoder does not mind
+    with pytest.raises(RuntimeError):
+        st.write_cache(X)
+    w["Hkv"], w["kv"]["W_K"] = 2, w["kv"]["W_K"][:, :128].contiguous()    # a matrix that is too small for the native step to read
+    st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+    with pytest.raises(RuntimeError):
+        st.decode_step(toks[0], st.new_generation_state(8))
