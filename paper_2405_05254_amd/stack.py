@@ -6,7 +6,7 @@ A bf16 stack (kernel dtype and glue bf16, head_dim 128) runs its token steps who
 call enqueues every launch of the token; as torch ops a step was bound by the host, 2.3 ms for 4 + 4 layers whose
 weights stream in 0.13 ms) and its prompts with torch GEMMs and libyoco's row-wise passes between them. Its weights
 are laid out once, a row per output, which is the order a matrix-vector product reads them in; the tensors in the
-layer dicts are views of that.
+layer dicts are views of that, and what a program puts in their place is laid out when it is next used.
 
 Precision: the attention operands (Q, K, V, the global cache, O) have the
 kernel dtype; the residual stream and the glue GEMMs run in `glue_dtype`
@@ -15,6 +15,7 @@ on the path are the ones at the attention boundary.
 """
 import ctypes
 import math
+import threading
 
 import torch
 
@@ -73,7 +74,31 @@ class YocoStack:
             self.kv["gW_V"] = (self.kv["ln"].float()[:, None] * self.kv["W_V"].float()).to(glue_dtype)
         self.cross_layers = [layer(L) for L in w["cross"]]
         self.final_ln, self.W_out = dev(w["final_ln"]), dev(w["W_out"])
+        self._lock = threading.Lock()
         self._native = self._lay_out() if dtype == glue_dtype == torch.bfloat16 and self.d == 128 else None
+
+    def _settings(self):
+        return (self.Hq, self.Hkv_self, self.Hkv, self.d, self.self_kind, self.scale, self.eps, self.tau, len(self.self_layers), len(self.cross_layers))
+
+    def _is_laid(self, native):
+        """Whether the weights and settings are those that were laid out: the same tensors at the same addresses."""
+        return self._settings() == native.settings and all(a is b for a, b in zip(self.self_layers + self.cross_layers, native.layers)) and \
+            self.kv is native.kv and all(holder.get(name) is t and t.data_ptr() == at for holder, name, t, at in native.weights)
+
+    def _current(self):
+        """The layout for the native calls, None where torch ops serve. What a program has replaced since is laid out anew;
+        the wait is for callers on other streams. (A capture would record the layout and not do it: torch ops.)"""
+        native = self._native
+        if native is None or self._is_laid(native):
+            return native
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        with self._lock:
+            if self._native is not None and not self._is_laid(self._native):
+                native = self._lay_out()
+                torch.cuda.current_stream(self.embed.device).synchronize()
+                self._native = native
+            return self._native
 
     def _lay_out(self):
         """The stack as libyoco sees it: every weight with a row per output, matrices that read the same input joined.
@@ -103,46 +128,56 @@ class YocoStack:
         st.Hq, st.Hkv_self, st.Hkv, st.d, st.gret = self.Hq, self.Hkv_self, self.Hkv, self.d, int(gret)
         st.scale, st.eps, st.tau = self.scale, self.eps, self.tau
 
-        def join(L, *names):
-            rows = torch.cat([L[n].t() for n in names])
-            at = 0
+        weights = []                 # what was laid out: holder, name, tensor, its address
+
+        def place(L, n, t):
+            L[n] = t
+            weights.append((L, n, t, t.data_ptr()))
+            return t.data_ptr()
+
+        def join(L, rows_name, *names):
+            """L[rows_name]: the named matrices, a row per output; they become views of it (and stay, where they are)."""
+            rows, width, at, views = L.get(rows_name), L[names[0]].shape[0], 0, []
+            total = sum(L[n].shape[1] for n in names)
+            kept = torch.is_tensor(rows) and rows.shape == (total, width) and rows.dtype == torch.bfloat16 and rows.is_contiguous() and rows.data_ptr() % 16 == 0
             for n in names:
-                m = L[n].shape[1]
-                L[n] = rows[at:at + m].t()
-                at += m
-            return rows
+                end = at + L[n].shape[1]
+                kept = kept and L[n].data_ptr() == rows[at:end].data_ptr() and L[n].stride() == rows[at:end].t().stride()
+                views.append((n, at, end))
+                at = end
+            if not kept:
+                rows = torch.cat([L[n].t() for n in names])
+            for n, at, end in views:
+                place(L, n, L[n] if kept else rows[at:end].t())
+            return place(L, rows_name, rows)
 
         def describe(layers, names):
             out = (yb._Layer * len(layers))()
             for s, L in zip(out, layers):
-                L["ln1"], L["ln2"] = _plain(L["ln1"]), _plain(L["ln2"])
-                L["w_in"], L["w_o"], L["w_gu"], L["w_2"] = join(L, *names), join(L, "W_O"), join(L, "W_G", "W_1"), join(L, "W_2")
-                for n in ("ln1", "w_in", "w_o", "ln2", "w_gu", "w_2"):
-                    setattr(s, n, L[n].data_ptr())
+                s.ln1, s.ln2 = place(L, "ln1", _plain(L["ln1"])), place(L, "ln2", _plain(L["ln2"]))
+                s.w_in, s.w_o = join(L, "w_in", *names), join(L, "w_o", "W_O")
+                s.w_gu, s.w_2 = join(L, "w_gu", "W_G", "W_1"), join(L, "w_2", "W_2")
             return out
 
-        self._self_desc, self._cross_desc = describe(self.self_layers, into), describe(self.cross_layers, ("W_Q",))
-        st.self, st.cross = self._self_desc, self._cross_desc
-        self.kv["ln"], self.final_ln = _plain(self.kv["ln"]), _plain(self.final_ln)
-        self.kv["w_kv"] = join(self.kv, "W_K", "W_V")
-        out = {"W_out": self.W_out}
-        self.w_out = join(out, "W_out")
-        self.W_out = out["W_out"]
-        st.kv_ln, st.w_kv, st.final_ln, st.w_out = (t.data_ptr() for t in (self.kv["ln"], self.kv["w_kv"], self.final_ln, self.w_out))
-        self._scratch_bytes = yb.stack_step_scratch(st)
+        own = self.__dict__
+        st.self, st.cross = describe(self.self_layers, into), describe(self.cross_layers, ("W_Q",))
+        st.kv_ln, st.w_kv = place(self.kv, "ln", _plain(self.kv["ln"])), join(self.kv, "w_kv", "W_K", "W_V")
+        st.final_ln, st.w_out = place(own, "final_ln", _plain(self.final_ln)), join(own, "w_out", "W_out")
+        st.scratch_bytes = yb.stack_step_scratch(st)
+        st.weights, st.layers, st.kv, st.settings = weights, layers, self.kv, self._settings()
         return st
 
-    def _scratch(self):
-        return torch.empty(self._scratch_bytes, dtype=torch.uint8, device=self.device)
+    def _scratch(self, native):
+        return torch.empty(native.scratch_bytes, dtype=torch.uint8, device=self.device)
 
-    def _norm(self, X, gain):
-        if self._native is None or X.dtype != torch.bfloat16 or X.dim() != 2 or X.shape[1] != gain.shape[0]:
+    def _norm(self, X, gain, native):
+        if native is None or X.dtype != torch.bfloat16 or X.dim() != 2 or X.shape[1] != gain.shape[0]:
             return _rmsnorm(X, gain, self.eps)
         return yb.norm_rows(_plain(X), gain, self.eps)
 
-    def _after_attention(self, a, X, L):
+    def _after_attention(self, a, X, L, native):
         """W_O, the residual and the SwiGLU half of Eq. 1 for the rows of a prompt."""
-        if self._native is None:
+        if native is None:
             Y = a @ L["W_O"] + X
             return _rows(Y, lambda y: _swiglu(_rmsnorm(y, L["ln2"], self.eps), L) + y)
         Y, xn = yb.norm_rows(a @ L["W_O"], L["ln2"], self.eps, add=_plain(X))
@@ -156,10 +191,10 @@ class YocoStack:
     def self_decoder(self, tokens, rings=None):
         """rings: optional per-layer generation caches that receive what a later decode step needs: rolling
         caches (the last `window` K/V rows) for sliding-window attention, fp32 states for gated retention."""
-        X = self.embed[tokens]
+        X, native = self.embed[tokens], self._current()
         T = X.shape[0]
         for n, L in enumerate(self.self_layers):
-            xn = self._norm(X, L["ln1"])
+            xn = self._norm(X, L["ln1"], native)
             q = (xn @ L["W_Q"]).to(self.dtype).view(1, T, self.Hq, self.d)
             k = (xn @ L["W_K"]).to(self.dtype).view(1, T, self.Hkv_self, self.d)
             v = (xn @ L["W_V"]).to(self.dtype).view(1, T, self.Hkv_self, self.d)
@@ -183,7 +218,7 @@ class YocoStack:
             if self.capture is not None and self.self_kind != "gret" and ("self%d" % n) in self.capture:
                 self.capture["self%d" % n] = (q[0], k[0], v[0], o[0])
             del q, k, v, o, xn
-            X = self._after_attention(a, X, L)
+            X = self._after_attention(a, X, L, native)
             del a
         return X
 
@@ -199,22 +234,22 @@ class YocoStack:
             v = (X @ self.kv["gW_V"]).view(T, self.Hkv, self.d)
             yb.global_kv_write_scaled(cache, k, v, rs, 0, pos0)
             return cache
-        xn = self._norm(X, self.kv["ln"])
+        xn = self._norm(X, self.kv["ln"], self._current())
         k = (xn @ self.kv["W_K"]).to(self.dtype).view(T, self.Hkv, self.d)
         v = (xn @ self.kv["W_V"]).to(self.dtype).view(T, self.Hkv, self.d)
         yb.global_kv_write(cache, k, v, 0, pos0)
         return cache
 
     # -- cross-decoder: Eq. 3
-    def _cross_layer(self, X, L, attn):
+    def _cross_layer(self, X, L, attn, native=None):
         Tq = X.shape[0]
-        q = (self._norm(X, L["ln1"]) @ L["W_Q"]).to(self.dtype).view(Tq, self.Hq, self.d)
+        q = (self._norm(X, L["ln1"], native) @ L["W_Q"]).to(self.dtype).view(Tq, self.Hq, self.d)
         a = attn(q).view(Tq, self.Hq * self.d).to(self.glue)
         del q
-        return self._after_attention(a, X, L)
+        return self._after_attention(a, X, L, native)
 
     def cross_decoder_rows(self, X, cache, q_pos0):
-        ws = None
+        ws, native = None, self._current()
         if X.shape[0] <= 8:          # few rows: let the call split over the cache
             nbytes, _ = yb.cross_attn_decode_workspace(cache, self.Hq)
             ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
@@ -224,16 +259,17 @@ class YocoStack:
                 if self.capture is not None and ("cross%d" % n) in self.capture:
                     self.capture["cross%d" % n] = (q, o)
                 return o
-            X = self._cross_layer(X, L, attn)
+            X = self._cross_layer(X, L, attn, native)
         return X
 
     def cross_decoder_decode(self, x_last, cache, length):
         """One token through the cross-decoder with the split-KV decode kernel."""
         nbytes, _ = yb.cross_attn_decode_workspace(cache, self.Hq)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        if self._native is not None:
+        native = self._current()
+        if native is not None:
             X = torch.empty_like(x_last, memory_format=torch.contiguous_format)
-            yb.stack_step(self._native, _plain(x_last), None, None, cache, length - 1, self._scratch(), ws, x_out=X)
+            yb.stack_step(native, _plain(x_last), None, None, cache, length - 1, self._scratch(native), ws, x_out=X)
             return X
         lens = torch.tensor([length], dtype=torch.int64, device=self.device)
         X = x_last
@@ -278,19 +314,23 @@ class YocoStack:
             nbytes, _ = yb.cross_attn_decode_workspace(c, self.Hq)
             ws.append(torch.empty(nbytes, dtype=torch.uint8, device=self.device))
         state = dict(rings=rings, cache=cache, ws_ring=ws[0], ws_cache=ws[1], length=0)
-        if self._native is not None:
-            state["scratch"], state["ws"] = self._scratch(), max(ws, key=torch.numel)
+        native = self._current()
+        if native is not None:
+            state["scratch"] = self._scratch(native)
         return state
 
-    def _native_logits(self, x, state, pos, whole):
+    def _native_logits(self, native, x, state, pos, whole):
         """Logits [1,vocab] of one token at position pos; whole: through both decoders, else through the cross-decoder alone."""
-        logits = torch.empty((1, self._native.vocab), dtype=self.glue, device=self.device)
+        logits = torch.empty((1, native.vocab), dtype=self.glue, device=self.device)
+        if "scratch" not in state or state["scratch"].numel() < native.scratch_bytes:      # made for other layers, or for torch ops
+            state["scratch"] = self._scratch(native)
+        ws = max(state["ws_ring"], state["ws_cache"], key=torch.numel)
         rings, descs, states = state["rings"], None, None       # described anew: a caller may have put copies in their place
         if whole and self.self_kind == "gret":
             states = (ctypes.c_void_p * len(rings))(*(yb._state(r, "state", 1, self.Hq, self.d, self.d) for r in rings))
         elif whole:
             descs = (yb._Cache * len(rings))(*(r.desc for r in rings))
-        yb.stack_step(self._native, _plain(x), descs, states, state["cache"], pos, state["scratch"], state["ws"], logits=logits)
+        yb.stack_step(native, _plain(x), descs, states, state["cache"], pos, state["scratch"], ws, logits=logits)
         return logits
 
     def prefill(self, tokens, state):
@@ -300,8 +340,9 @@ class YocoStack:
         T = X.shape[0]
         self.write_cache(X, state["cache"], 0)
         state["length"] = T
-        if self._native is not None:
-            return self._native_logits(X[T - 1:T], state, T - 1, False)
+        native = self._current()
+        if native is not None:
+            return self._native_logits(native, X[T - 1:T], state, T - 1, False)
         lens = torch.tensor([T], dtype=torch.int64, device=self.device)
         x = X[T - 1:T].contiguous()
         for L in self.cross_layers:
@@ -311,8 +352,9 @@ class YocoStack:
     def decode_step(self, token, state):
         """One new token through both decoders; returns its logits [1,vocab]."""
         p = state["length"]
-        if self._native is not None:
-            logits = self._native_logits(self.embed[torch.as_tensor(token, device=self.device).view(1)], state, p, True)
+        native = self._current()
+        if native is not None:
+            logits = self._native_logits(native, self.embed[torch.as_tensor(token, device=self.device).view(1)], state, p, True)
             state["length"] = p + 1
             return logits
         pos = torch.tensor([p], dtype=torch.int64, device=self.device)

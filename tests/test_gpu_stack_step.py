@@ -204,3 +204,65 @@ def test_stacks_without_a_native_step_run_as_torch_ops():
     st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
     with pytest.raises(RuntimeError):
         st.decode_step(toks[0], st.new_generation_state(8))
+
+
+def replaced(w, st, how):
+    """Something else in the place of a weight or setting, in a stack and in the dict that its reference is made from."""
+    gen = torch.Generator(device="cuda").manual_seed(9)
+
+    def like(t, scale=1.0, shift=0.0):
+        return (shift + scale * torch.randn(t.shape, device="cuda", generator=gen)).bfloat16()
+    if how == "matrices":
+        for mine, theirs, names in ((st.self_layers[0], w["self"][0], ("W_Q", "W_2")), (st.cross_layers[1], w["cross"][1], ("W_G",)), (st.kv, w["kv"], ("W_V",))):
+            for n in names:
+                mine[n] = theirs[n] = like(mine[n], 0.0625)
+        st.W_out = w["W_out"] = like(st.W_out, 0.0625)
+    elif how == "gains":
+        for mine, theirs, n in ((st.self_layers[1], w["self"][1], "ln1"), (st.cross_layers[0], w["cross"][0], "ln2"), (st.kv, w["kv"], "ln")):
+            mine[n] = theirs[n] = like(mine[n], 0.3, 1.0)
+        st.final_ln = w["final_ln"] = like(st.final_ln, 0.3, 1.0)
+    elif how == "transposed":                                        # the same memory, read the other way
+        st.self_layers[1]["W_O"] = st.self_layers[1]["W_O"].t()
+        w["self"][1]["W_O"] = w["self"][1]["W_O"].t()
+    elif how == "data":                                              # the same tensor, other memory
+        st.cross_layers[0]["W_Q"].data = w["cross"][0]["W_Q"] = like(st.cross_layers[0]["W_Q"], 0.0625)
+    elif how == "layer":
+        st.cross_layers[0] = dict(st.cross_layers[0], W_1=like(st.cross_layers[0]["W_1"], 0.0625))
+        w["cross"][0] = dict(w["cross"][0], W_1=st.cross_layers[0]["W_1"].clone())
+    elif how == "fewer layers":
+        del st.cross_layers[0], w["cross"][0]
+    elif how == "wider":
+        for mine, theirs in zip(st.self_layers + st.cross_layers, w["self"] + w["cross"]):
+            for n, shape in (("W_G", (256, 1408)), ("W_1", (256, 1408)), ("W_2", (1408, 256))):
+                mine[n] = theirs[n] = like(torch.empty(shape), 0.0442)
+    else:
+        st.scale = 0.02
+
+
+@pytest.mark.parametrize("how", ["matrices", "gains", "transposed", "data", "layer", "fewer layers", "wider", "setting"])
+def test_what_was_replaced_after_construction_counts(how):
+    """In prompts and token steps alike, also between the steps of a request."""
+    from paper_2405_05254_amd.stack import YocoStack
+    w = weights_on_device()
+    toks = torch.from_numpy(ys.tokens(1, 40, 200)).cuda()
+    st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+    first = request(st, toks)
+    replaced(w, st, how)
+    other = as_torch_ops(w)
+    if how == "setting":
+        other.scale = st.scale
+    ref = request(other, toks)
+    assert not close(first, ref)                                     # it matters
+    assert close(request(st, toks), ref) and st._native is not None
+    w = weights_on_device()
+    st, other = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16), as_torch_ops(w)
+    steps = []
+    for s in (st, other):
+        state = s.new_generation_state(48)
+        s.prefill(toks[:30], state)
+        w2 = weights_on_device()
+        replaced(w2, s, how)
+        if how == "data":
+            s.cross_layers[0]["W_Q"].data = s.cross_layers[0]["W_Q"].data.clone()
+        steps.append(torch.cat([s.decode_step(t, state) for t in toks[30:34]]).float())
+    assert close(*steps)
