@@ -77,6 +77,13 @@ class YocoStack:
         self._lock = threading.Lock()
         self._native = self._lay_out() if dtype == glue_dtype == torch.bfloat16 and self.d == 128 else None
 
+    def __getstate__(self):          # addresses are this process's and this object's own
+        return dict(self.__dict__, _lock=None, _native=self._native is not None)
+
+    def __setstate__(self, state):
+        self.__dict__.update(state, _lock=threading.Lock(), _native=None)
+        self._native = self._lay_out() if state["_native"] else None
+
     def _settings(self):
         return (self.Hq, self.Hkv_self, self.Hkv, self.d, self.self_kind, self.scale, self.eps, self.tau, len(self.self_layers), len(self.cross_layers))
 

@@ -266,3 +266,22 @@ def test_what_was_replaced_after_construction_counts(how):
             s.cross_layers[0]["W_Q"].data = s.cross_layers[0]["W_Q"].data.clone()
         steps.append(torch.cat([s.decode_step(t, state) for t in toks[30:34]]).float())
     assert close(*steps)
+
+
+@pytest.mark.parametrize("how", ["deepcopy", "pickle", "copy"])
+def test_a_stack_can_be_copied(how):
+    import copy
+    import pickle
+    st = small_stack("swa")
+    toks = torch.from_numpy(ys.tokens(1, 40, 200)).cuda()
+    ref = request(st, toks)
+    other = dict(deepcopy=copy.deepcopy, pickle=lambda x: pickle.loads(pickle.dumps(x)), copy=copy.copy)[how](st)
+    assert other._native is not None and torch.equal(request(other, toks), ref)
+    L = other.self_layers[0]
+    assert L["W_Q"].data_ptr() == L["w_in"].data_ptr()               # one copy of each weight, here too
+    if how != "copy":                                                # which shares the layers
+        L["W_Q"].zero_()
+    other.final_ln = other.final_ln * 2
+    assert not close(request(other, toks), ref) and torch.equal(request(st, toks), ref)
+    st._native = None                                                # torch ops stay torch ops
+    assert copy.copy(st)._native is None and copy.deepcopy(st)._native is None
