@@ -274,7 +274,7 @@ class YocoStack:
         nbytes, _ = yb.cross_attn_decode_workspace(cache, self.Hq)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         native = self._current()
-        if native is not None:
+        if native is not None and length > 0:                # nothing cached: the torch ops, on zeros from the attention
             X = torch.empty_like(x_last, memory_format=torch.contiguous_format)
             yb.stack_step(native, _plain(x_last), None, None, cache, length - 1, self._scratch(native), ws, x_out=X)
             return X

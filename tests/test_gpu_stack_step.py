@@ -285,3 +285,13 @@ def test_a_stack_can_be_copied(how):
     assert not close(request(other, toks), ref) and torch.equal(request(st, toks), ref)
     st._native = None                                                # torch ops stay torch ops
     assert copy.copy(st)._native is None and copy.deepcopy(st)._native is None
+
+
+def test_a_cache_without_rows_is_attended_to():
+    """Attention over no rows is zero; the rest of the layer runs."""
+    st = small_stack("swa")
+    X = st.self_decoder(torch.from_numpy(ys.tokens(1, 40, 200)).cuda())
+    cache = st.write_cache(X)
+    got = st.cross_decoder_decode(X[39:], cache, 0)
+    st._native = None
+    assert close(got.float(), st.cross_decoder_decode(X[39:], cache, 0).float())
