@@ -587,8 +587,11 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
   if (rc) return rc;
   const bool self = rings || states;
   if (self && (st->gret ? !states : !rings)) return fail(YOCO_ERR_INVALID_ARG, "the self-decoder's caches do not match its kind");
+  if (self && (!st->kv_ln || !st->w_kv)) return fail(YOCO_ERR_INVALID_ARG, "stack: missing weights of the global cache");
   if (cache->B != 1 || cache->Hkv != st->Hkv || cache->d != st->d || io_dtype(*cache) != YOCO_BF16)
     return fail(YOCO_ERR_INVALID_ARG, "the cache does not match the stack");
+  if (cache->dtype == YOCO_INT8 && !yoco::decode_i8_supported(*cache, st->Hq))
+    return fail(YOCO_ERR_UNSUPPORTED, "an 8-bit cache serves up to 16 query heads per KV head, not %d", st->Hq / cache->Hkv);
   if (pos < 0) return fail(YOCO_ERR_INVALID_ARG, "negative position %lld", (long long)pos);
   if (!aligned16(x) || !aligned16(x_out) || !aligned16(logits) || !aligned16(scratch) || !aligned16(workspace))
     return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned");
@@ -599,7 +602,15 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
   rc = yoco_cross_attn_decode_workspace(cache, st->Hq, &need, &splits);
   if (rc) return rc;
   if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
-  if (self && !st->gret) {
+  const bool in_rings = self && !st->gret && st->n_self > 0;
+  if (self && st->gret) {
+    if (!(st->eps >= 0.f)) return fail(YOCO_ERR_INVALID_ARG, "negative eps");
+    for (int i = 0; i < st->n_self; ++i) {
+      if (!states[i]) return fail(YOCO_ERR_INVALID_ARG, "state %d is null", i);
+      if (!aligned16(states[i])) return fail(YOCO_ERR_ALIGNMENT, "state %d is not 16-byte aligned", i);
+    }
+  }
+  if (in_rings) {
     for (int i = 0; i < st->n_self; ++i) {
       rc = check_cache(rings + i);
       if (rc) return rc;
@@ -612,7 +623,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
     if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
   }
 
-  const Splits plan = decode_splits(cache, st->Hq), ring_plan = decode_splits(self && !st->gret ? rings : cache, st->Hq);
+  const Splits plan = decode_splits(cache, st->Hq), ring_plan = decode_splits(in_rings ? rings : cache, st->Hq);
   hipStream_t s = (hipStream_t)stream;
   const int dm = st->d_model, qd = st->Hq * st->d, kd = st->Hkv_self * st->d, ckd = st->Hkv * st->d;
   hipError_t e = hipSuccess;

@@ -328,3 +328,28 @@ def test_a_scalar_is_no_empty_set_of_rows():
     for write in (yoco.global_kv_write, yoco.swa_cache_write, lambda c, k, v, b, p: yoco.global_kv_write_scaled(c, k, v, torch.zeros(0), b, p)):
         with pytest.raises(yoco.YocoError, match="do not match"):
             write(bare_cache(), one, one, 0, 0)
+
+
+def test_a_refused_stack_step_has_launched_nothing():
+    """What a later part of the step would refuse is refused before its first launch (which without a device is error -5)."""
+    L = yoco.lib()
+    p = 0x7f0000000000
+    layers = (yb._Layer * 2)(*(yb._Layer(*[p] * 6) for _ in range(2)))
+
+    def cache(Hkv, dtype=yoco.BF16):
+        c = yb._Cache()
+        assert L.yoco_kv_cache_init(p, yoco.kv_cache_bytes(1, Hkv, 128, 64, dtype), 1, Hkv, 128, 64, dtype, C.byref(c)) == 0
+        return c
+
+    def step(c, rings=None, states=None, **fields):
+        fields = dict(dict(kv_ln=p, w_kv=p, n_self=2, Hq=17, Hkv_self=17, Hkv=c.Hkv, eps=1e-6), **fields)
+        st = yb._Stack(self=layers, cross=layers, final_ln=p, w_out=p, n_cross=2, d_model=256, d=128, ffn=512, vocab=100, scale=0.1, tau=16.0, **fields)
+        return L.yoco_stack_step(C.byref(st), p, rings, states, C.byref(c), 3, None, p, p, 1 << 20, p, 1 << 30, None)
+    two = (yb._Cache * 2)(cache(17), cache(17))
+    assert step(cache(1, yoco.INT8), rings=two) == -2                        # 17 heads read each row of the codes
+    assert step(cache(1, yoco.INT8)) == -2                                   # also when only the cross-decoder runs
+    assert step(cache(17), states=(C.c_void_p * 2)(p, None), gret=1) == -1   # the second layer has no state
+    assert step(cache(17), states=(C.c_void_p * 2)(p, p + 4), gret=1) == -3
+    assert step(cache(17), states=(C.c_void_p * 2)(p, p), gret=1, eps=-1.0) == -1
+    for missing in (dict(kv_ln=None), dict(w_kv=None)):                      # the row of the cache is projected without layers too
+        assert step(cache(17), rings=(yb._Cache * 0)(), n_self=0, **missing) == -1
