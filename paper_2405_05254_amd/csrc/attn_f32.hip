@@ -186,13 +186,17 @@ __global__ void __launch_bounds__(64 * kWaves, QB == 1 ? 3 : 2) attn_f32_kernel(
   }
 
   // Keys that a query of these rows does not see were weighed with 0, and 0 * inf is NaN: where anything came out infinite
-  // or NaN, the rows are done again over the keys that each of them sees.
+  // or NaN, the rows are done again over the keys that each of them sees. Q comes from registers: o may be its memory.
   if (!__syncthreads_or(bad)) return;
   float* const q_s = &red_o[wave][0][0];
   float* const p_s = q_s + D;
   for (int row = wave; row < kRows && i0 + row < a.Tq; row += kWaves) {
-    const T* q = qb0 + (i0 + row) * a.q_stride_t;
-    for (int e = lane; e < D; e += 64) q_s[e] = Elem<T>::load(q + e);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+      if (row == qb * 16 + n) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) *(f32x4*)(q_s + qg * 4 + 16 * i) = qf[qb][i];
+      }
     lds_wave_sync();
     const int64_t pos = a.q_pos0 + i0 + row, j_lo = pos - a.window + 1 > 0 ? pos - a.window + 1 : 0;
     float m1 = -INFINITY, l1 = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};

@@ -57,3 +57,15 @@ def test_values_that_a_query_does_not_see_do_not_reach_it(d, T, H, value):
     assert not np.isfinite(o[sees]).any()
     st = ys.error_stats(o[~sees], ref[~sees])
     assert np.isfinite(o[~sees]).all() and st["max_abs"] <= ys.TOL["f32"]["max_abs"] and st["mean_rel"] <= ys.TOL["f32"]["mean_rel"], st
+
+
+@pytest.mark.parametrize("dtype,d,T,H", [("f32", 128, 70, 2), ("bf16", 64, 70, 3), ("f32", 64, 2065, 8)])     # 16- and 32-row workgroups
+def test_outputs_in_the_place_of_the_queries(dtype, d, T, H):
+    """Also where an infinite value has rows done again: bit for bit what a fresh output gets."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + d)
+    q, k, v = (torch.randn(1, T, H, d, device="cuda", generator=g).to(torch.float32 if dtype == "f32" else torch.bfloat16) for _ in range(3))
+    v[0, 37, :, 3] = float("inf")
+    ref = yoco.swa_prefill(q, k, v, 24, 0.1)
+    got = yoco.swa_prefill(q, k, v, 24, 0.1, out=q)
+    assert got is q and torch.equal(got.nan_to_num(nan=7.0), ref.nan_to_num(nan=7.0))
