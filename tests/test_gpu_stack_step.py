@@ -295,3 +295,29 @@ def test_a_cache_without_rows_is_attended_to():
     got = st.cross_decoder_decode(X[39:], cache, 0)
     st._native = None
     assert close(got.float(), st.cross_decoder_decode(X[39:], cache, 0).float())
+
+
+@pytest.mark.parametrize("kind", ["swa", "gret"])
+def test_errors_against_64_bits_are_those_of_the_torch_ops(kind):
+    """Both chains round the same thirty or so intermediates to bf16, so their errors against the fp64 oracle are two draws
+    of one size: over three stacks here, and over single rows of larger ones, they differ by 7 % at most. One rounding more
+    in each layer half would add an eighth to it, so a quarter more is too much."""
+    import oracle
+    from paper_2405_05254_amd.stack import YocoStack
+    errors = np.zeros(2)
+    for seed in (3, 4, 5):
+        w = ys.stack_weights(seed, stack_config(4, 4, 4, 512, 1408, 1001, kind), "bf16")
+        if kind == "gret":
+            for L in w["self"]:
+                L["W_gamma"] = ys.round_to(L["W_gamma"] * 0.05, "bf16")
+        toks = ys.tokens(seed, 76, 1001)
+        ref = torch.from_numpy(oracle.yoco_stack(toks, w)[69:])
+        for i in range(2):
+            st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+            if i:
+                st._native = None
+            state, on_gpu = st.new_generation_state(76), torch.from_numpy(toks).cuda()
+            got = torch.cat([st.prefill(on_gpu[:70], state)] + [st.decode_step(t, state) for t in on_gpu[70:]]).cpu().double()
+            errors[i] += ((got - ref).norm() / ref.norm()).item() ** 2
+    print("error against fp64: %.3e, torch ops %.3e" % tuple((errors / 3) ** 0.5))
+    assert errors[0] < 1.25 ** 2 * errors[1]
