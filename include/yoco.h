@@ -194,9 +194,16 @@ int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* byt
  * int64 [B]; sequence b attends to cache rows [0, lens[b]) -- its own row has
  * been written before the call (Eq. 2 precedes Eq. 3, the mask is j <= i).
  * lens[b] is clamped to [0, N_cap]; a sequence with lens[b] == 0 gets zeros.
- * Pass 1 reduces each split of the cache to (max, sum, vector) for all query
- * heads of a KV head in one read; pass 2 merges the splits by log-sum-exp in
- * a fixed order (no atomics: results are bit-reproducible).
+ * Each split of the cache is reduced to (max, sum, vector) for all query heads
+ * of a KV head in one read, and the splits are merged by log-sum-exp in a fixed
+ * order: results are bit-reproducible. For d = 128 and up to 16 query heads per
+ * KV head (bf16 and 8-bit caches) that is one launch: a split is published in
+ * the workspace under a tag of the call, with device-scope stores, and whoever
+ * finds every split published merges; nothing waits. Other shapes take a second
+ * launch. How many splits a sequence gets depends on the lengths of the whole
+ * batch, so that the same sequence in another batch may differ by the order of
+ * fp32 sums. The workspace needs no clearing; calls that overlap in time must
+ * not share one.
  */
 int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const int64_t* lens, int Hq,
                            float scale, void* workspace, size_t workspace_bytes, void* stream);
@@ -212,8 +219,8 @@ int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const
  * array is refused with YOCO_ERR_WORKSPACE before anything is launched.
  * All calls on one GPU share that GPU's array: two calls that overlap in time
  * on one GPU (different streams or threads) race; calls on one stream are
- * ordered. Nothing in the array needs clearing between calls (pass 1 writes
- * every partial the merge reads).
+ * ordered. Nothing in the array needs clearing between calls (a merge reads
+ * only what the same call has published there).
  */
 #define YOCO_NOALLOC_SCRATCH_BYTES ((size_t)4 << 20)
 int yoco_cross_attn_decode_noalloc(const yoco_kv_cache* c, const void* q, void* o, const int64_t* lens, int Hq,
@@ -261,9 +268,10 @@ int yoco_kv_cache_append(const yoco_kv_cache* c, const void* k, const void* v, c
  * the rows have been appended already (yoco_kv_cache_append). The row attends to
  * the min(lens[b], N_cap) rows the ring holds, which are exactly positions
  * lens[b]-N_cap .. lens[b]-1; the order of the slots is irrelevant to a
- * softmax-weighted sum. Same two passes, workspace
+ * softmax-weighted sum. Same splits, workspace
  * (yoco_cross_attn_decode_workspace on this ring) and reproducibility as
- * yoco_cross_attn_decode.
+ * yoco_cross_attn_decode; with more than 16 query heads per KV head, or d other
+ * than 128, the rows are stored by a launch of their own.
  */
 int yoco_swa_decode(const yoco_kv_cache* ring, const void* q, const void* k_new, const void* v_new, void* o,
                     const int64_t* lens, int Hq, float scale, void* workspace, size_t workspace_bytes, void* stream);
@@ -285,10 +293,10 @@ int yoco_swa_decode(const yoco_kv_cache* ring, const void* q, const void* k_new,
  * S is stored transposed so that its rows run along the key dimension.
  * state_in: the state before row 0 (NULL = zeros); state_out: receives the
  * state after the last row (NULL = not stored); they may be the same memory.
- * Domain of the chunkwise bf16 path: its products run on fp16 operands, so
- * |k|, |v| and |scale * q.k| must stay below 65504 (magnitudes under 2^-14
- * lose low bits or flush, an absolute error below 2^-25); the recurrent
- * kernel computes in fp32 and has no such limit.
+ * The chunkwise bf16 path's products take q, k and v as they are and every other
+ * operand (scores times decay, v times decay, the state) as a bf16 high and low
+ * part: 16 significant bits over the exponent range of fp32. The recurrent
+ * kernel computes in fp32.
  */
 
 /* Scratch bytes yoco_gret_prefill needs for its chunkwise path on this shape
@@ -301,7 +309,10 @@ int yoco_gret_prefill_workspace(int B, int64_t T, int H, int dk, int dv, int chu
  * of 128 runs chunkwise on the matrix cores when `workspace` holds at least
  * yoco_gret_prefill_workspace() bytes (device memory, 256-byte aligned); every
  * other case runs the recurrence, which computes the same function (dk, dv <=
- * 128). T == 0 copies state_in to state_out.
+ * 128). The chunkwise path works in chunks of its own; `chunk` sizes the
+ * workspace, which is more than that path now touches, and through it bounds
+ * the segments a sequence is cut into (another order of fp32 sums, no more).
+ * T == 0 copies state_in to state_out.
  */
 int yoco_gret_prefill(const void* q, const void* k, const void* v, const float* log_gamma, const void* gate, void* o,
                       const float* state_in, float* state_out, int B, int64_t T, int H, int dk, int dv, int chunk,
@@ -350,10 +361,12 @@ int yoco_stack_step_scratch(const yoco_stack* st, size_t* bytes);
  * x: [d_model], the token's embedding. rings: n_self rolling caches of one sequence (host array; NULL for gated
  * retention), states: n_self fp32 states [1,Hq,d,d] (host array of device pointers; NULL for sliding windows).
  * The token is at position pos: its rows are stored in the rings (or states) and in row pos of the cache before they
- * are attended to (past the cache's capacity nothing is stored, as in yoco_kv_cache_append). With rings == states == NULL only the cross-decoder runs (the exit row of an early-exit prefill,
- * Fig. 3: x is the self-decoder's last row, whose cache row has been written). logits: [vocab] or NULL; x_out:
- * [d_model], the residual stream after the last layer, or NULL. workspace: yoco_cross_attn_decode_workspace of the
- * larger of the ring and the cache. d must be 128, widths multiples of 8 and at most 16384.
+ * are attended to (past the cache's capacity nothing is stored, as in yoco_kv_cache_append). With rings == states ==
+ * NULL only the cross-decoder runs (the exit row of an early-exit prefill, Fig. 3: x is the self-decoder's last row,
+ * whose cache row has been written). logits: [vocab] or NULL; x_out: [d_model], the residual stream after the last
+ * layer, or NULL. workspace: yoco_cross_attn_decode_workspace of the larger of the ring and the cache. d must be 128,
+ * widths multiples of 8 and at most 16384; an 8-bit cache serves up to 16 query heads per KV head. What a later part
+ * of the step would refuse is refused before its first launch.
  */
 int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* rings, float* const* states, const yoco_kv_cache* cache,
                     int64_t pos, void* x_out, void* logits, void* scratch, size_t scratch_bytes, void* workspace,

@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(256) kv_code_i8_block_kernel(yoco_kv_cache c, 
   if (part == 0) *(float*)(blk + kI8ScaleOffset + 4 * rho) = scale;
 }
 
-// ---------------------------------------------------------------- decode pass 1 over the coded cache
+// ---------------------------------------------------------------- decode over the coded cache
 // Both contractions run on the matrix cores, whose operands are exactly what the block layout delivers:
 //   scores  S^T[row][head] = K[row][dim] . q[head][dim]      v_mfma_i32_16x16x64_i8, K codes as loaded (no conversion);
 //           q is split into two int8 parts per head, q = s1 * hi + (s1 / 254) * lo, which keeps 16 bits below max|q|
@@ -293,16 +293,16 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
   const u32x4* vp = (const u32x4*)c.v + plane;
 
   Block nx;
-      auto load = [&](int64_t row0) {                       // row0 is a multiple of 64
-        const int64_t base = (row0 >> 6) * (kI8BlockBytes / 16);
-  #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          nx.k[u] = __builtin_nontemporal_load(kp + base + u * 64 + lane);
-          nx.v[u] = __builtin_nontemporal_load(vp + base + u * 64 + lane);
-        }
-        nx.ks = __builtin_nontemporal_load((const float*)(kp + base + kI8ScaleOffset / 16) + lane);
-        nx.vs = __builtin_nontemporal_load((const float*)(vp + base + kI8ScaleOffset / 16) + lane);
-      };
+  auto load = [&](int64_t row0) {                         // row0 is a multiple of 64
+    const int64_t base = (row0 >> 6) * (kI8BlockBytes / 16);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      nx.k[u] = __builtin_nontemporal_load(kp + base + u * 64 + lane);
+      nx.v[u] = __builtin_nontemporal_load(vp + base + u * 64 + lane);
+    }
+    nx.ks = __builtin_nontemporal_load((const float*)(kp + base + kI8ScaleOffset / 16) + lane);
+    nx.vs = __builtin_nontemporal_load((const float*)(vp + base + kI8ScaleOffset / 16) + lane);
+  };
   load(w_lo < j_hi ? w_lo : 0);                           // in flight while the query is coded; a wavefront without rows loads block 0
   // (unconditional: behind a branch the compiler waits for all of it before the first use of the query. 8 heads x 32768
   // rows 18.7 -> 17.6 us a layer, 8 ragged sequences of up to 3000 rows 13.2 -> 11.9 us)

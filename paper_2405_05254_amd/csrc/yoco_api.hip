@@ -61,9 +61,10 @@ int check_heads(int Hq, int Hkv) {
 
 // Splits of the decode pass. Streaming reads on MI355X are fastest with few, long, contiguous streams: one workgroup per
 // CU (measured: 6.9 TB/s at 256 workgroups, 6.0 TB/s at 2048; 8 KV heads x 16384 rows 17.7 us at 256, 19.6 at 512).
-// `even`: the splits a sequence gets on average (a batch of equal lengths possibly fewer: inv_even). A split of a bf16 cache has at least 128 rows, one step of its four
-// wavefronts: a launch over few rows is latency, and a step more costs more than the workgroups saved (16 heads x 2016
-// rows: 13.4 us at 4 splits of 512 rows, 7.7 us at 16 of 128). Of an 8-bit or fp32 cache it has at least 512.
+// `even`: the splits a sequence gets on average (a batch of equal lengths possibly fewer: inv_even). A split of a bf16
+// cache has at least 128 rows, one step of its four wavefronts: a launch over few rows is latency, and a step more costs
+// more than the workgroups saved (16 heads x 2016 rows: 13.4 us at 4 splits of 512 rows, 7.7 us at 16 of 128). Of an
+// 8-bit or fp32 cache it has at least 512.
 // `most`: what the workspace holds and the grid launches. Twice as many where a split of `even` has rows enough (2560)
 // to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
 // decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
@@ -479,8 +480,8 @@ int yoco_cross_attn_decode_noalloc(const yoco_kv_cache* c, const void* q, void* 
   void* ptr = nullptr;
   rc = scratch_of_current_device(&ptr);
   if (rc) return rc;
-  // Every partial the merge reads is written by pass 1 of the same call (empty splits included), so nothing in the
-  // array has to be cleared between calls.
+  // A merge reads only what the same call has put there (splits published under its tag, or every partial of the generic
+  // kernels' first launch), so nothing in the array has to be cleared between calls.
   return yoco_cross_attn_decode(c, q, o, lens, Hq, scale, ptr, kScratchBytes, stream);
 }
 

@@ -139,8 +139,8 @@ hipError_t launch_mfma_ceiling(const void* seed, void* sink, int iters, int work
 hipError_t launch_attn_loop_ceiling(const void* seed, void* sink, int iters, int workgroups, int mode, hipStream_t s);
 hipError_t launch_stream_read(const void* buf, size_t bytes, void* sink, int workgroups, hipStream_t s);
 
-// Partial result of one split, per (b, h, split): o[0..d), then the running max
-// m (natural-log units) and sum l, padded so every row starts 16-byte aligned.
+// Partial result of one split, per (b, h, split): o[0..d), then the running max m (log2 units in the fused decodes, whose
+// tag follows the sum; natural in the generic kernels) and the sum l, padded so every row starts 16-byte aligned.
 __host__ __device__ inline size_t partial_stride(int d) { return (size_t)d + 4; }
 
 }  // namespace yoco
