@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
       mfma_softmax_pv(st, s, vst, lane);
     };
     // A cache is read again by the next layer: what fits the 256 MB behind the L2s is read so that it stays there, more
-    // than that streams past it (8 x 8 x 1700 rows: 16.9 us instead of 20.2; 16 x 8 x 32768: 315 us instead of 371).
+    // than that streams past it (8 x 8 x 1700 rows: 14.3 us instead of 14.9; 16 x 8 x 32768: 300 us instead of 368).
     // A rolling cache belongs to one layer and streams.
     if (APPEND || part.total * (float)c.Hkv > (float)(kResidentBytes / (2 * kD * 2))) walk(std::true_type());
     else walk(std::false_type());

@@ -6,14 +6,17 @@
 //   O = scale * ((Q K^T * D) V + (Q S) * 2^(G_j)),   D(j,k) = 2^(G_j - G_k), k <= j
 //   S <- 2^(G_last) S + K^T (V * 2^(G_last - G_j))
 // The sequence is cut into segments, about two workgroups' worth per CU over all heads, and a segment into chunks of 64
-// rows (the caller's chunk size plays no part: the result does not depend on it). Launches:
+// rows. The caller's chunk size plays no part, but that it sizes the workspace and with it the most segments there can
+// be: another cut is another order of fp32 sums. Launches:
 //   1  what a segment adds to the state, for all segments but the last (reads K and V)
 //   2  the scan across segments, element-wise and in place: the state before each segment. Up to three earlier segments
 //      are folded by launch 3 itself.
 //   3  outputs: a workgroup walks its segment with the state in its MFMA accumulators, and hands over the final state.
-// Nothing but one state per segment touches memory in between: Q, gate and O move once, K and V twice (1.41 GB at
-// T = 32768 x 24 heads with the gate, against 2.1 GB of a form that wrote and read one state per 256-row chunk). Bound by
-// HBM: 1.01 GB algorithmic.
+// Nothing but one state per segment touches memory in between: Q, gate and O move once, K and V twice. Read and written
+// at T = 32768 x 24 heads without the gate, by the counters of HBM: 0.45, 0.06 and 0.85 GB in launches 1 to 3, 1.36 in
+// all of 0.81 algorithmic (a gate adds 0.2 to both; a form that wrote and read one state per 256-row chunk moved 2.1 GB
+// with it). Launch 3 does that at 4 TB/s in 214 us, below the 7.07 of a plain stream: its loads and its ten products per
+// chunk where four are asked for do not overlap fully.
 //
 // Partition: wavefront w owns dims 32 w .. 32 w + 31 of V, of the outputs and of the state, S[128 ek][32 ev] with ev
 // along the lanes. A state accumulator is then, rounded to bf16, the A operand of O^T = S^T Q^T as it stands (the rows of

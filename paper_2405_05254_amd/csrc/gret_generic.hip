@@ -206,8 +206,10 @@ __global__ void __launch_bounds__(32 * kStepGroups) gret_decode_kernel(GretView 
 template <typename T>
 void launch_step(const GretView& a, hipStream_t s) {
   // A layer's states are met again at the next token. Up to 16 MB of them, those of 16 layers fit the 256 MB behind the
-  // L2s and are left there; more than that is kept from displacing itself (13 layers: 8 x 24 heads 90 us against 102
-  // nontemporal, 12 x 24, just past the line, 136 against 145; 21 x 16 163 against 149, 16 x 24 182 against 156).
+  // L2s and are left there; more than that is kept from displacing itself. How many layers there are a call does not know,
+  // so the line is drawn for 16, where the two sides cross between 16.5 and 18 MB (16 layers: 8 x 24 heads 106 us against
+  // 120 nontemporal, 10 x 24 133 against 134, 11 x 24, 16.5 MB, 158 against 172, 12 x 24 182 against 176, 16 x 24 214
+  // against 189). Programs of fewer layers would gain past it: of 13, 12 x 24 heads 120 against 142, 14 x 24 154 against 148.
   if ((size_t)a.B * a.H * 128 * 128 * sizeof(float) <= ((size_t)16 << 20))
     hipLaunchKernelGGL((gret_decode_kernel<T, false>), dim3(a.H, a.B), dim3(32 * kStepGroups), 0, s, a);
   else

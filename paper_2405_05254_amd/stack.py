@@ -6,7 +6,9 @@ A bf16 stack (kernel dtype and glue bf16, head_dim 128) runs its token steps who
 call enqueues every launch of the token; as torch ops a step was bound by the host, 2.3 ms for 4 + 4 layers whose
 weights stream in 0.13 ms) and its prompts with torch GEMMs and libyoco's row-wise passes between them. Its weights
 are laid out once, a row per output, which is the order a matrix-vector product reads them in; the tensors in the
-layer dicts are views of that, and what a program puts in their place is laid out when it is next used.
+layer dicts are views of that, and what a program puts in their place is laid out when it is next used. So a stack made
+from bf16 tensors that are on the GPU already holds copies of them, where other stacks hold the tensors themselves
+(4 + 4 layers: 2.5 ms and 0.9 GB; asking at each call whether they are still the same: 9 us).
 
 Precision: the attention operands (Q, K, V, the global cache, O) have the
 kernel dtype; the residual stream and the glue GEMMs run in `glue_dtype`
