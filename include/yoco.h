@@ -196,11 +196,11 @@ int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* byt
  * lens[b] is clamped to [0, N_cap]; a sequence with lens[b] == 0 gets zeros.
  * Each split of the cache is reduced to (max, sum, vector) for all query heads
  * of a KV head in one read, and the splits are merged by log-sum-exp in a fixed
- * order: results are bit-reproducible. For d = 128 and up to 16 query heads per
- * KV head (bf16 and 8-bit caches) that is one launch: a split is published in
- * the workspace under a tag of the call, with device-scope stores, and whoever
- * finds every split published merges; nothing waits. Other shapes take a second
- * launch. How many splits a sequence gets depends on the lengths of the whole
+ * order: results are bit-reproducible. For d = 128 on bf16 and 8-bit caches, few
+ * splits of few heads (up to 16 splits of 4 heads per KV head, 8 of 8) merge in
+ * the same launch: a split is published in the workspace under a tag of the
+ * call, with device-scope stores, and whoever finds every split published
+ * merges; nothing waits. Otherwise a second launch merges. How many splits a sequence gets depends on the lengths of the whole
  * batch, so that the same sequence in another batch may differ by the order of
  * fp32 sums. The workspace needs no clearing; calls that overlap in time must
  * not share one.

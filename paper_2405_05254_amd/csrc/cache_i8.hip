@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
   const int n = lane & 15, qg = lane >> 4;
 
   const SplitRows part = split_rows<256>(out, c, lens, fixed_len, b, sp);
-  if (sp > 0 && sp >= part.splits) return;
+  if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * 64;                  // the wavefronts take turns at the split's blocks
 
@@ -436,7 +436,7 @@ hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;
   const int G = Hq / c.Hkv;
-  if (G < 1 || G > 16 || splits > kMaxFusedSplits) return hipErrorInvalidValue;
+  if (G < 1 || G > 16 || splits > kMaxDecodeSplits || (tag && !decode_meets_in_launch(G, splits))) return hipErrorInvalidValue;
   if (G <= 4)
     hipLaunchKernelGGL(decode_i8_kernel<4>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out);
   else

@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
   const int r = lane >> 4, seg = lane & 15;
 
   const SplitRows part = split_rows<128>(out, c, lens, fixed_len, b, sp);
-  if (sp > 0 && sp >= part.splits) return;
+  if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kRowsPerStep;        // the wavefronts take turns at the split's steps
   constexpr int kTurn = 4 * kRowsPerStep;
@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   unsigned char* vst = smem + wave * kStageBytes;
 
   const SplitRows part = split_rows<128>(out, c, lens, fixed_len, b, sp);
-  if (sp > 0 && sp >= part.splits) return;
+  if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
 
@@ -456,7 +456,7 @@ hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64
   const bf16_t* kn = (const bf16_t*)k_new;
   const bf16_t* vn = (const bf16_t*)v_new;
   const int G = Hq / c.Hkv;
-  if (G < 1 || G > kGMax || splits > kMaxFusedSplits) return hipErrorInvalidValue;
+  if (G < 1 || G > kGMax || splits > kMaxDecodeSplits || (tag && !decode_meets_in_launch(G, splits))) return hipErrorInvalidValue;
   if (!kn) {
     hipLaunchKernelGGL(decode_bf16_mfma_kernel<false>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
     return hipGetLastError();

@@ -1,7 +1,8 @@
-// The end of a split-KV decode workgroup: merge its wavefronts, publish the split's partial result, and let the
-// workgroup that finds every split of its (sequence, KV head) published merge them. One launch per decode step: a merge
-// launch of its own cost 3.9 us behind passes of 10 to 16 us on caches of a few thousand rows (and 3 us of host time);
-// the tail costs about 2 us.
+// The end of a split-KV decode workgroup: merge its wavefronts, publish the split's partial result, and, where splits
+// and heads are few (decode_meets_in_launch), let the workgroup that finds every split of its (sequence, KV head)
+// published merge them. One launch per decode step then, which saves up to a microsecond and 3 us of host time against
+// a merge launch. That one workgroup's reading is a serial chain that grows with splits and heads, so the others are left
+// for a merge launch, a workgroup per query head.
 //
 // Nothing has to be cleared beforehand. A split is published by writing the call's tag (64 bits, never used twice by a
 // process, drawn around a random start) into the spare words of its partial; whoever sees all tags merges, and puts
@@ -13,7 +14,8 @@
 
 namespace yoco {
 
-constexpr int kMaxFusedSplits = 256;
+constexpr int kMaxDecodeSplits = 256;
+constexpr float kLn2 = 0.6931471805599453f;
 
 struct SplitOut {
   float* ws;                 // [B][Hq][splits][128 + 4]: vector, max (log2 units), sum, tag
@@ -21,7 +23,7 @@ struct SplitOut {
   int splits;                // the most a sequence can be split into
   float inv_ragged;          // 1 / how many workgroups the whole batch should make, when its lengths differ
   float inv_even;            // ... and when they do not
-  unsigned long long tag;
+  unsigned long long tag;    // 0: the splits are left for a merge launch
 };
 
 // Which rows a workgroup takes. The batch's rows, times its KV heads, are shared out over `workgroups` workgroups: a
@@ -88,9 +90,9 @@ __device__ __forceinline__ void put_u64(void* p, unsigned long long x) {
 }
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// The merge of S published splits: o = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s. Each thread owns a head's pair of
-// dims and takes the splits' maxima and sums along with its part of their vectors: one trip to memory for every N splits,
-// no exchange between threads. Order and assignment are fixed: results are bit-reproducible whoever merges.
+// The merge of S <= N published splits: o = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s. Each thread owns a head's pair
+// of dims and takes the splits' maxima and sums along with its part of their vectors: one trip to memory, no exchange
+// between threads. Order and assignment are fixed: results are bit-reproducible whoever merges.
 template <int N>
 __device__ __forceinline__ void merge_splits(const SplitOut& out, int G, size_t head0, int S) {
   constexpr int kD = 128;
@@ -98,31 +100,24 @@ __device__ __forceinline__ void merge_splits(const SplitOut& out, int G, size_t 
   for (int t = threadIdx.x; t < G * (kD / 2); t += 256) {
     const int h = t / (kD / 2), e = (t % (kD / 2)) * 2;
     const float* const p = out.ws + (head0 + h) * per_head;
-    float M = -INFINITY, L = 0.f, a = 0.f, b = 0.f;
-    for (int s0 = 0; s0 < S; s0 += N) {
-      unsigned long long ml[N], x[N];
+    unsigned long long ml[N], x[N];
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const int s = s0 + i < S ? s0 + i : S - 1;
-        ml[i] = get_u64(p + s * stride + kD);
-        x[i] = get_u64(p + s * stride + e);
-      }
-      float m_new = M;
+    for (int i = 0; i < N; ++i) {
+      const int s = i < S ? i : S - 1;
+      ml[i] = get_u64(p + s * stride + kD);
+      x[i] = get_u64(p + s * stride + e);
+    }
+    float M = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < N; ++i) m_new = fmaxf(m_new, __uint_as_float((unsigned)ml[i]));
-      const float base = m_new == -INFINITY ? 0.f : m_new;                             // empty splits only, so far
-      const float alpha = __builtin_amdgcn_exp2f(M - base);
-      L *= alpha;
-      a *= alpha;
-      b *= alpha;
+    for (int i = 0; i < N; ++i) M = fmaxf(M, __uint_as_float((unsigned)ml[i]));
+    const float base = M == -INFINITY ? 0.f : M;                                       // empty splits only
+    float L = 0.f, a = 0.f, b = 0.f;
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const float f = s0 + i < S ? __builtin_amdgcn_exp2f(__uint_as_float((unsigned)ml[i]) - base) : 0.f;
-        L = fmaf(f, __uint_as_float((unsigned)(ml[i] >> 32)), L);
-        a = fmaf(f, __uint_as_float((unsigned)x[i]), a);
-        b = fmaf(f, __uint_as_float((unsigned)(x[i] >> 32)), b);
-      }
-      M = m_new;
+    for (int i = 0; i < N; ++i) {
+      const float f = i < S ? __builtin_amdgcn_exp2f(__uint_as_float((unsigned)ml[i]) - base) : 0.f;
+      L = fmaf(f, __uint_as_float((unsigned)(ml[i] >> 32)), L);
+      a = fmaf(f, __uint_as_float((unsigned)x[i]), a);
+      b = fmaf(f, __uint_as_float((unsigned)(x[i] >> 32)), b);
     }
     const float inv = L > 0.f ? 1.f / L : 0.f;                                         // no visible row -> zeros
     *(unsigned*)(out.o + (head0 + h) * kD + e) = (unsigned)f32_to_bf16(a * inv) | ((unsigned)f32_to_bf16(b * inv) << 16);
@@ -137,6 +132,7 @@ __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)
   constexpr int kD = 128;
   const size_t stride = partial_stride(kD);
   const size_t per_head = out.splits * stride;
+  const bool whole = out.tag ? S <= 1 : out.splits <= 1;     // a single split is the whole answer
   for (int t = threadIdx.x; t < G * kD; t += 256) {
     const int h = t / kD, e = t % kD;
     const float M = fmaxf(fmaxf(red_ml[0][h][0], red_ml[1][h][0]), fmaxf(red_ml[2][h][0], red_ml[3][h][0]));
@@ -147,18 +143,26 @@ __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)
       l = fmaf(f, red_ml[w][h][1], l);
       o = fmaf(f, red_o[w][h][e], o);
     }
-    if (S <= 1) {            // a single split is the whole answer
+    if (whole) {
       out.o[(head0 + h) * kD + e] = f32_to_bf16(l > 0.f ? o / l : 0.f);
       continue;
     }
     float* p = out.ws + (head0 + h) * per_head + sp * stride;
+    if (!out.tag) {
+      p[e] = o;
+      if (e == 0) {
+        p[kD] = l > 0.f ? M * kLn2 : -INFINITY;    // the merge launch works with natural exponents
+        p[kD + 1] = l;
+      }
+      continue;
+    }
     put_f32(p + e, o);
     if (e == 0) {
       put_f32(p + kD, l > 0.f ? M : -INFINITY);
       put_f32(p + kD + 1, l);
     }
   }
-  if (S <= 1) return;
+  if (whole || !out.tag) return;
   wait_stores();                                   // this wavefront's part is visible to the whole device
   __syncthreads();                                 // ... and everyone else's
   float* const tags = out.ws + head0 * per_head + kD + 2;                  // split s: tags + s * stride
@@ -166,15 +170,14 @@ __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)
   if (threadIdx.x < 64) {
     if (threadIdx.x == 0) put_u64(tags + sp * stride, out.tag);
     wait_stores();
-    for (int s = threadIdx.x; s < S; s += 64) seen &= get_u64(tags + s * stride) == out.tag;
+    if (threadIdx.x < S) seen = get_u64(tags + threadIdx.x * stride) == out.tag;
   }
   if (!__syncthreads_and(seen)) return;            // uniform over the workgroup
 
   if (S <= 4) merge_splits<4>(out, G, head0, S);
   else if (S <= 8) merge_splits<8>(out, G, head0, S);
-  else if (S <= 16) merge_splits<16>(out, G, head0, S);
-  else merge_splits<32>(out, G, head0, S);
-  for (int s = threadIdx.x; s < S; s += 256) put_u64(tags + s * stride, 0ull);
+  else merge_splits<kMeetSplits>(out, G, head0, S);
+  if (threadIdx.x < S) put_u64(tags + threadIdx.x * stride, 0ull);
 }
 
 }  // namespace yoco

@@ -138,7 +138,7 @@ unsigned long long next_tag() {
   return z;
 }
 
-// Split-KV attention of one query token per sequence of `c`: one launch, or pass 1 + merge (generic kernels).
+// Split-KV attention of one query token per sequence of `c`: one launch, or one for the splits and one for their merge.
 // `lens` (device) or, when it is null, `fixed_len` (host) gives the visible rows.
 // k_new / v_new (both null or both rows [B,Hkv,d] of the cache dtype): the new token's row is stored at slot
 // lens[b] - 1 (ring: modulo the capacity) by the same call and attended to.
@@ -146,13 +146,16 @@ int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* le
                float* ws, const Splits& sp, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
                int ring = 0) {
   hipError_t e;
+  const unsigned long long tag = yoco::decode_meets_in_launch(Hq / c.Hkv, sp.most) ? next_tag() : 0;
   if (c.dtype == YOCO_INT8) {
     if (!yoco::decode_i8_supported(c, Hq))
       return fail(YOCO_ERR_UNSUPPORTED, "%s: an 8-bit cache serves up to 16 query heads per KV head, not %d", what, Hq / c.Hkv);
     if (k_new) return fail(YOCO_ERR_UNSUPPORTED, "%s: no fused append into an 8-bit cache", what);
-    return hip_result(yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, next_tag(), o, s), what);
+    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, tag, o, s);
+    if (tag) return hip_result(e, what);
   } else if (yoco::decode_bf16_supported(c, Hq)) {
-    return hip_result(yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, next_tag(), o, k_new, v_new, ring, s), what);
+    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, tag, o, k_new, v_new, ring, s);
+    if (tag) return hip_result(e, what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend
       e = yoco::launch_kv_append(c, k_new, v_new, lens, lens ? -1 : fixed_len - 1, ring, c.dtype, s);

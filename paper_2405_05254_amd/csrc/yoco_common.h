@@ -88,7 +88,13 @@ hipError_t launch_gret_chunk(const GretView& a, int chunk, void* workspace, hipS
 bool swa_mfma_supported(const AttnView& a, int dtype);
 hipError_t launch_swa_mfma(const AttnView& a, hipStream_t s);
 bool decode_bf16_supported(const yoco_kv_cache& c, int Hq);
-// Both fused decode launches leave the merged output in o (the splits meet in ws under `tag`, see decode_tail.h).
+// Where one decode launch also merges its splits (decode_tail.h): a workgroup reads them all, G / 4 heads one after
+// another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (fused against a merge launch, us: 1 x 8 heads x 2048 rows
+// at 16 splits and 3 heads 8.1 and 8.2, 4 x 4096 rows at 16 and 2 9.9 and 10.7, at 8 and 8 11.6 and 11.6; 32 and 4 9.6 and
+// 8.3, 16 and 8 10.4 and 9.1, 2 and 16 12.5 and 11.6, 128 and 4 17.6 and 9.5, 256 and 16 73.8 and 15.5).
+constexpr int kMeetSplits = 16;
+inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G <= 8 && (G + 3) / 4 * splits <= kMeetSplits); }
+// Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.
 // k_new / v_new ([B,Hkv,128] bf16, or null): also store and attend to the new token's row at slot lens[b] - 1.
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
                               float* ws, int splits, float inv_ragged, float inv_even, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,

@@ -1,5 +1,5 @@
-"""The end of a split decode step: splits that meet in the caller's workspace without anything having been cleared, and
-ragged batches whose sequences get different numbers of splits, against the fp64 oracle."""
+"""The end of a split decode step: splits that meet in the caller's workspace without anything having been cleared or are
+left for a merge launch, and ragged batches whose sequences get different numbers of splits, against the fp64 oracle."""
 import math
 
 import numpy as np
@@ -19,7 +19,14 @@ SCALE = 1.0 / math.sqrt(D)
 @pytest.mark.parametrize("dtype,Hq,Hkv,N_cap,lens", [
     ("bf16", 2, 1, 300, [300, 1, 129]),                     # 1 .. 3 splits of one step each
     ("bf16", 6, 2, 1100, [1100, 1024]),                     # 9 splits: the wider merge
-    ("bf16", 3, 1, 2300, [2300]),                           # 18 splits: two rounds of the widest merge
+    ("bf16", 4, 1, 2048, [2048]),                           # 16 splits of 4 heads: the most that meet in one launch
+    ("bf16", 3, 1, 2300, [2300]),                           # 18 splits: a merge launch
+    ("bf16", 16, 2, 1024, [1024, 130]),                     # 8 splits of 8 heads: one launch
+    ("bf16", 8, 1, 1100, [1100, 0, 900]),                   # 9 splits of 8 heads: a merge launch, an empty sequence
+    ("bf16", 9, 1, 500, [500, 1]),                          # 9 heads: a merge launch however few the splits
+    ("int8", 12, 3, 9000, [9000, 12, 0]),                   # 18 splits of 4 heads: a merge launch
+    ("int8", 5, 1, 4000, [4000, 2000]),                     # 8 splits of 5: one launch
+    ("int8", 8, 1, 5000, [5000, 513, 0]),                   # 10 splits of 8: a merge launch
     ("bf16", 16, 1, 9000, [9000, 0, 7, 4400, 128, 127]),    # 16 heads in one workgroup, an empty sequence among long ones
     ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
     ("bf16", 12, 12, 1100, [1100, 1100, 1090, 1100, 1100, 1100, 1100]),   # 84 units of equal lengths: 3 splits, not 4
@@ -71,3 +78,37 @@ def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
     ref = oracle.cross_attn_int8(q.float().cpu().numpy(), k.float().cpu().numpy(), v.float().cpu().numpy(), 2599, SCALE)
     st = ys.error_stats(o.float().cpu().numpy(), ref)
     assert st["max_abs"] <= 2e-2 and st["mean_rel"] <= 2e-3, st
+
+
+@pytest.mark.parametrize("Hq,Hkv,N_cap,tokens", [
+    (1, 1, 2048, [5000, 3, 0]),       # the vector-ALU step, 16 splits in one launch
+    (2, 1, 2200, [2200, 9000]),       # ... 18, with a merge launch
+    (12, 4, 2048, [2048, 1]),         # the matrix-core step
+    (4, 1, 2200, [100000, 700, 0]),
+    (16, 1, 700, [699, 701]),         # more than 8 heads per KV head
+])
+def test_rings_that_are_split_store_the_new_row_and_attend_to_it(Hq, Hkv, N_cap, tokens):
+    B, rng = len(tokens), np.random.default_rng(N_cap)
+    rows = lambda n: torch.from_numpy(ys.normal(rng, (B, n, Hkv, D), 1.0, "bf16")).cuda().to(torch.bfloat16)  # noqa: E731
+    K, V, kn, vn = rows(N_cap), rows(N_cap), rows(1), rows(1)
+    fused, apart = (yoco.KVCache(B, Hkv, D, N_cap, torch.bfloat16) for _ in range(2))
+    for c in (fused, apart):
+        c.mem.zero_()
+        for b in range(B):
+            yoco.global_kv_write(c, K[b], V[b], b, 0)
+    q = torch.from_numpy(ys.normal(rng, (B, Hq, D), 1.0, "bf16")).cuda().to(torch.bfloat16)
+    ln = torch.tensor(tokens, dtype=torch.int64, device="cuda")
+    ws = torch.full((yoco.cross_attn_decode_workspace(fused, Hq)[0],), 0xFF, dtype=torch.uint8, device="cuda")
+    got = yoco.swa_decode(fused, q, ln, SCALE, ws, k_new=kn[:, 0], v_new=vn[:, 0])
+    yoco.kv_cache_append(apart, kn[:, 0], vn[:, 0], ln - 1, True)
+    ref = yoco.swa_decode(apart, q, ln, SCALE, ws)
+    assert torch.equal(fused.mem, apart.mem)
+    for b, n in enumerate(tokens):
+        if n == 0:
+            assert not got[b].any() and not ref[b].any()
+            continue
+        k, v = (p[b, :, :min(n, N_cap)].float().cpu().numpy().transpose(1, 0, 2) for p in apart.planes())
+        want = oracle.cross_attn(q[b:b + 1].float().cpu().numpy(), k, v, k.shape[0] - 1, SCALE)[0]
+        for o in (got, ref):
+            st = ys.error_stats(o[b].float().cpu().numpy(), want)
+            assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
