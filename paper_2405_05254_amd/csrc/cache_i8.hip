@@ -269,11 +269,12 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
   __shared__ float red_ml[4][GMAX][2];
   const int G = Hq / c.Hkv;
   __shared__ __attribute__((aligned(16))) float scales[4][2][64];
-  const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z;
+  const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, qg = lane >> 4;
 
-  const SplitRows part = split_rows<256>(out, c, lens, fixed_len, b, sp);
+  const SplitRows part = split_rows<256>(out, c, lens, fixed_len);
+  const int b = part.b, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * 64;                  // the wavefronts take turns at the split's blocks
@@ -430,8 +431,8 @@ hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* 
 }
 
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, float inv_ragged, float inv_even, unsigned long long tag, void* o, hipStream_t s) {
-  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, tag};
+                            float* ws, int splits, float inv_ragged, float inv_even, int places, unsigned long long tag, void* o, hipStream_t s) {
+  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, places, tag};
   dim3 grid(c.Hkv, c.B, splits), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;

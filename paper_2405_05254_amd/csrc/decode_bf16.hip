@@ -114,11 +114,12 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
   constexpr int kRowsPerStep = 4 * R;
   __shared__ float red_o[4][G][kD];
   __shared__ float red_ml[4][G][2];
-  const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z;
+  const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = lane >> 4, seg = lane & 15;
 
-  const SplitRows part = split_rows<128>(out, c, lens, fixed_len, b, sp);
+  const SplitRows part = split_rows<128>(out, c, lens, fixed_len);
+  const int b = part.b, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kRowsPerStep;        // the wavefronts take turns at the split's steps
@@ -319,12 +320,13 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   __shared__ float red_ml[4][kGMax][2];
   float (*red_o)[kGMax][kD] = (float (*)[kGMax][kD])smem;
   const int G = Hq / c.Hkv;
-  const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z;
+  const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, qg = lane >> 4;
   unsigned char* vst = smem + wave * kStageBytes;
 
-  const SplitRows part = split_rows<128>(out, c, lens, fixed_len, b, sp);
+  const SplitRows part = split_rows<128>(out, c, lens, fixed_len);
+  const int b = part.b, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
@@ -449,9 +451,9 @@ bool decode_bf16_supported(const yoco_kv_cache& c, int Hq) {
 // KV head keeps the vector-ALU kernel, whose shorter prologue and merge win there (16 x 24 heads x 1024 rows: 36.1 us
 // against 40.9; at 3 heads per KV head, 2 x 8 x 2048 rows, 11.6 against 10.2 the other way round).
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                              float* ws, int splits, float inv_ragged, float inv_even, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
+                              float* ws, int splits, float inv_ragged, float inv_even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
                               hipStream_t s) {
-  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, tag};
+  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, places, tag};
   dim3 grid(c.Hkv, c.B, splits), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;

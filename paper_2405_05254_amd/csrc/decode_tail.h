@@ -15,6 +15,13 @@
 namespace yoco {
 
 constexpr int kMaxDecodeSplits = 256;
+// Ragged batches get no more splits than CUs where a split has rows enough to pay for finding the shares (0.4 us) and the
+// sequences are few enough that this leaves no more than a third of the CUs' places unused (760 ragged batches of 2 to 48
+// sequences of 1500 to 44564 rows, 16 to 64 query heads, bf16 and 8-bit: a twentieth faster on the mean than shares of
+// rows / CUs, which made up to a tenth more workgroups than CUs and launched those with rows among those without: 2 x 16
+// heads x 44564 rows, lengths 0.88 of it, 147 us, now 103; 8 x 8 x 25000, 0.69, 136 and 93).
+constexpr int kLongSplit = 512;
+constexpr float kGoodFit = 1.5f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 struct SplitOut {
@@ -23,60 +30,129 @@ struct SplitOut {
   int splits;                // the most a sequence can be split into
   float inv_ragged;          // 1 / how many workgroups the whole batch should make, when its lengths differ
   float inv_even;            // ... and when they do not
+  int places;                // how many (sequence, split) pairs have a CU of their own for each KV head; 0: do not ask
   unsigned long long tag;    // 0: the splits are left for a merge launch
 };
 
-// Which rows a workgroup takes. The batch's rows, times its KV heads, are shared out over `workgroups` workgroups: a
-// sequence gets as many splits as its length asks for, so that a batch of ragged lengths ends together (8 sequences of
-// 375 to 3000 rows x 8 KV heads: the longest no longer runs on as many workgroups as the shortest). GRAIN: what a
-// split's rows are a multiple of (a step of each of its four wavefronts).
+// Which rows a workgroup takes. A sequence gets as many splits as its length asks for, so that a batch of ragged lengths
+// ends together (8 sequences of 375 to 3000 rows x 8 KV heads: the longest no longer runs on as many workgroups as the
+// shortest). GRAIN: what a split's rows are a multiple of (a step of each of its four wavefronts).
 struct SplitRows {
+  int b, sp;                 // sequence and split
   int64_t lo, hi;            // rows of this split, lo >= hi: nothing to do
   int splits;                // of this sequence; 0: the sequence is empty, split 0 stores zeros
   float total;               // rows of the whole batch (of its capacity where nothing is split)
 };
 
+// Inclusive scan over the wavefront with 0 as the neutral element: within rows of 16 lanes, then a row's last value into
+// the next one, then the lower half's into the upper half.
+template <int CTRL, int ROWS, typename F>
+__device__ __forceinline__ int dpp_step(int x, F f) { return f(x, __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false)); }
+template <typename F>
+__device__ __forceinline__ int lane_scan(int x, F f) {
+  x = dpp_step<0x111, 0xf>(x, f);    // row_shr:1
+  x = dpp_step<0x112, 0xf>(x, f);    // row_shr:2
+  x = dpp_step<0x114, 0xf>(x, f);    // row_shr:4
+  x = dpp_step<0x118, 0xf>(x, f);    // row_shr:8
+  x = dpp_step<0x142, 0xa>(x, f);    // row_bcast:15 into rows 1 and 3
+  return dpp_step<0x143, 0xc>(x, f);  // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, 63); }
+__device__ __forceinline__ int lanes_sum(int x) { return last_lane(lane_scan(x, [](int a, int b) { return a + b; })); }
+__device__ __forceinline__ float lanes_sum(float x) {
+  return __int_as_float(last_lane(lane_scan(__float_as_int(x), [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); })));
+}
+__device__ __forceinline__ float lanes_max(float x) {       // of values that are not negative
+  return __int_as_float(last_lane(lane_scan(__float_as_int(x), [](int a, int b) { return a > b ? a : b; })));
+}
+
+// How many splits `len` rows ask for at 1 / inv_share rows a split (a tenth over is no reason for one more).
+__device__ __forceinline__ int splits_for(float len, float inv_share, int most) {
+  const int n = (int)ceilf(len * inv_share - 0.1f);
+  return n < 1 ? 1 : n > most ? most : n;
+}
+// ceil(a / b), or one more, for positive whole numbers below 2^24.
+__device__ __forceinline__ int about_ceil_div(int a, int b) {
+  const int q = (int)((float)(a + b - 1) * __builtin_amdgcn_rcpf((float)b));
+  return q * b < a ? q + 1 : q;
+}
+// How many splits of `each` steps hold `steps`, no more than the n that `each` was made for.
+__device__ __forceinline__ int splits_of(int steps, int each, int n) {
+  const int s = about_ceil_div(steps, each);
+  return s < n ? s : n;
+}
+
 template <int GRAIN>
-__device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_kv_cache& c, const int64_t* lens, int64_t fixed_len, int b, int sp) {
+__device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_kv_cache& c, const int64_t* lens, int64_t fixed_len) {
   // 32-bit arithmetic: 2^31 rows of 132 bytes and more do not fit any GPU this runs on
-  auto clamp_len = [&](int64_t n) { return (unsigned)(n < 0 ? 0 : n > c.N_cap ? c.N_cap : n); };
-  const unsigned len = clamp_len(lens ? lens[b] : fixed_len);
-  unsigned n = 1;
-  float total = (float)c.B * (float)c.N_cap;         // unsplit: nothing depends on the other lengths
-  if (out.splits > 1) {
-    total = (float)len;
-    float inv = out.inv_even;
-    if (lens && c.B > 1) {                           // the same float arithmetic in every workgroup: all agree on every sequence's splits
-      total = 0.f;
-      if (out.inv_ragged == out.inv_even) {
-        for (int i = threadIdx.x & 63; i < c.B; i += 64) total += (float)clamp_len(lens[i]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o);
-      } else {
-        float longest = 0.f;
-        for (int i = threadIdx.x & 63; i < c.B; i += 64) {
-          const float n_i = (float)clamp_len(lens[i]);
-          total += n_i;
-          longest = fmaxf(longest, n_i);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-          total += __shfl_xor(total, o);
-          longest = fmaxf(longest, __shfl_xor(longest, o));
-        }
-        if (longest * (float)c.B * 16.f > total * 17.f) inv = out.inv_ragged;   // equal: the longest is within a sixteenth of the mean
-      }
-    }
-    const float share = fmaxf(total * (float)c.Hkv * inv, (float)GRAIN);
-    n = (unsigned)__builtin_amdgcn_readfirstlane((int)ceilf((float)len / share - 0.1f));
-    n = n < 1 ? 1 : n > (unsigned)out.splits ? (unsigned)out.splits : n;
-  }
+  auto clamp_len = [&](int64_t n) { return (int)(n < 0 ? 0 : n > c.N_cap ? c.N_cap : n); };
+  const int B = c.B;
   SplitRows r;
-  const unsigned rows = ((len + n * GRAIN - 1) / (n * GRAIN)) * GRAIN;          // even shares of this sequence
-  r.splits = rows ? (int)((len + rows - 1) / rows) : 0;
-  r.lo = (int64_t)sp * rows;
-  r.hi = r.lo + rows < len ? r.lo + rows : len;
-  r.total = total;
+  r.b = blockIdx.y;
+  r.sp = blockIdx.z;
+  int len, n = 1;
+  r.total = (float)B * (float)c.N_cap;               // unsplit: nothing depends on the other lengths
+  if (out.splits == 1 || !lens || B == 1) {
+    len = clamp_len(lens ? lens[r.b] : fixed_len);
+    if (out.splits > 1) {
+      r.total = (float)len * (float)B;
+      n = splits_for((float)len, 1.f / fmaxf(r.total * (float)c.Hkv * out.inv_even, (float)GRAIN), out.splits);
+    }
+  } else {
+    // The same float arithmetic in every workgroup: all agree on every sequence's splits.
+    const int lane = threadIdx.x & 63;
+    const int mine = lane < B ? clamp_len(lens[lane]) : 0;       // a lane per sequence, of the first 64
+    float sum = (float)mine, longest = (float)mine;
+    for (int i = lane + 64; i < B; i += 64) {
+      const float n_i = (float)clamp_len(lens[i]);
+      sum += n_i;
+      longest = fmaxf(longest, n_i);
+    }
+    r.total = lanes_sum(sum);
+    const bool ragged = lanes_max(longest) * (float)B * 16.f > r.total * 17.f;       // equal: the longest is within a sixteenth of the mean
+    float share = fmaxf(r.total * (float)c.Hkv * (ragged ? out.inv_ragged : out.inv_even), (float)GRAIN);
+    bool fits = false;
+    const float fl = (float)mine;
+    if (ragged && 2 * B <= out.places && B <= 64 && share >= (float)kLongSplit) {
+      // The smallest share, nearly, with which every split has a CU of its own, because a CU with two makes the launch wait.
+      float s = fmaxf(r.total / (float)out.places, (float)GRAIN);
+      for (int i = 0; i < 32 && !fits; ++i) {
+        const int over = lanes_sum(lane < B ? splits_for(fl, 1.f / s, out.splits) : 0) - out.places;
+        fits = over <= 0;
+        if (!fits) s *= 1.f + fmaxf(0.03f, 0.5f * (float)over / (float)out.places);
+      }
+      fits = fits && s * (float)out.places < kGoodFit * r.total;       // not where sequences too short to fill a place waste many
+      share = fits ? s : share;
+    }
+    const float inv_share = 1.f / share;
+    if (!fits) {
+      len = B <= 64 ? __builtin_amdgcn_readlane(mine, r.b) : clamp_len(lens[r.b]);
+      n = splits_for((float)len, inv_share, out.splits);
+    } else {
+      const int wanted = splits_for(fl, inv_share, out.splits), steps = (mine + GRAIN - 1) / GRAIN;
+      const int live = lane < B ? (steps ? splits_of(steps, about_ceil_div(steps, wanted), wanted) : 1) : 0;   // an empty sequence has one, which stores zeros
+      // Workgroups are dealt to the CUs in order, and those without rows leave at once: the ones with rows come first, so
+      // that no CU gets two while another gets none.
+      auto locate = [&](int count, int j) {          // the sequence that holds place j of all counts, and its place there
+        const int upto = lane_scan(count, [](int a, int b) { return a + b; });
+        r.b = __builtin_ctzll(__builtin_amdgcn_ballot_w64(j < upto) | (1ull << 63));
+        r.sp = j - __builtin_amdgcn_readlane(upto - count, r.b);
+      };
+      const int j = (int)blockIdx.y + B * (int)blockIdx.z, all = lanes_sum(live);
+      locate(live, j);
+      if (j >= all) {                                // one of those without rows
+        locate(lane < B ? out.splits - live : 0, j - all);
+        r.sp += __builtin_amdgcn_readlane(live, r.b);
+      }
+      len = __builtin_amdgcn_readlane(mine, r.b);
+      n = __builtin_amdgcn_readlane(wanted, r.b);
+    }
+  }
+  n = __builtin_amdgcn_readfirstlane(n);
+  const int steps = (len + GRAIN - 1) / GRAIN, each = about_ceil_div(steps, n);       // even shares of this sequence
+  r.splits = steps ? splits_of(steps, each, n) : 0;
+  r.lo = (int64_t)r.sp * (each * GRAIN);
+  r.hi = r.lo + each * GRAIN < len ? r.lo + each * GRAIN : len;
   return r;
 }
 

@@ -31,6 +31,11 @@ SCALE = 1.0 / math.sqrt(D)
     ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
     ("bf16", 12, 12, 1100, [1100, 1100, 1090, 1100, 1100, 1100, 1100]),   # 84 units of equal lengths: 3 splits, not 4
     ("bf16", 12, 12, 1100, [1100, 1100, 900, 1100, 1100, 1100, 1100]),    # ... just past what counts as equal
+    ("bf16", 16, 16, 9000, [9000, 1300, 0]),                # 16 places for the splits of three sequences: a CU for each
+    ("bf16", 8, 8, 9000, [0, 9000, 5, 8000, 2500, 127]),    # ... of 6, two of them without a split to spare
+    ("bf16", 32, 8, 2600, [2600, 1, 1900, 600, 2500, 0, 2570, 1200, 130, 2000, 700, 2599]),
+    ("int8", 8, 8, 9000, [9000, 513, 0, 7777]),
+    ("bf16", 2, 2, 900, [(i * 379) % 901 for i in range(70)]),            # more sequences than a wavefront has lanes
     ("bf16", 34, 17, 4200, [4200] * 8),                     # 136 units: three splits, on half as many CUs as two rounds have
     ("bf16", 17, 17, 1000, [1000] * 9),                     # 153 units: unsplit, in a workspace for two
     ("int8", 3, 3, 5700, [5700] * 8),                       # 24 units: 10 splits, not 11
