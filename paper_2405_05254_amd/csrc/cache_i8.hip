@@ -431,8 +431,8 @@ hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* 
 }
 
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, float inv_ragged, float inv_even, int places, unsigned long long tag, void* o, hipStream_t s) {
-  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, places, tag};
+                            float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, hipStream_t s) {
+  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, even, places, tag};
   dim3 grid(c.Hkv, c.B, splits), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;

@@ -451,9 +451,9 @@ bool decode_bf16_supported(const yoco_kv_cache& c, int Hq) {
 // KV head keeps the vector-ALU kernel, whose shorter prologue and merge win there (16 x 24 heads x 1024 rows: 36.1 us
 // against 40.9; at 3 heads per KV head, 2 x 8 x 2048 rows, 11.6 against 10.2 the other way round).
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                              float* ws, int splits, float inv_ragged, float inv_even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
+                              float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
                               hipStream_t s) {
-  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, places, tag};
+  const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, even, places, tag};
   dim3 grid(c.Hkv, c.B, splits), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;

@@ -30,6 +30,7 @@ struct SplitOut {
   int splits;                // the most a sequence can be split into
   float inv_ragged;          // 1 / how many workgroups the whole batch should make, when its lengths differ
   float inv_even;            // ... and when they do not
+  int even;                  // that many for each sequence
   int places;                // how many (sequence, split) pairs have a CU of their own for each KV head; 0: do not ask
   unsigned long long tag;    // 0: the splits are left for a merge launch
 };
@@ -96,7 +97,7 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
     len = clamp_len(lens ? lens[r.b] : fixed_len);
     if (out.splits > 1) {
       r.total = (float)len * (float)B;
-      n = splits_for((float)len, 1.f / fmaxf(r.total * (float)c.Hkv * out.inv_even, (float)GRAIN), out.splits);
+      n = splits_for((float)len, 1.f / (float)GRAIN, out.even < out.splits ? out.even : out.splits);
     }
   } else {
     // The same float arithmetic in every workgroup: all agree on every sequence's splits.
@@ -113,19 +114,19 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
     float share = fmaxf(r.total * (float)c.Hkv * (ragged ? out.inv_ragged : out.inv_even), (float)GRAIN);
     bool fits = false;
     const float fl = (float)mine;
-    if (ragged && 2 * B <= out.places && B <= 64 && share >= (float)kLongSplit) {
+    if (__builtin_expect(ragged && 2 * B <= out.places && B <= 64 && share >= (float)kLongSplit, 0)) {
       // The smallest share, nearly, with which every split has a CU of its own, because a CU with two makes the launch wait.
       float s = fmaxf(r.total / (float)out.places, (float)GRAIN);
       for (int i = 0; i < 32 && !fits; ++i) {
-        const int over = lanes_sum(lane < B ? splits_for(fl, 1.f / s, out.splits) : 0) - out.places;
+        const int over = lanes_sum(lane < B ? splits_for(fl, __builtin_amdgcn_rcpf(s), out.splits) : 0) - out.places;
         fits = over <= 0;
         if (!fits) s *= 1.f + fmaxf(0.03f, 0.5f * (float)over / (float)out.places);
       }
       fits = fits && s * (float)out.places < kGoodFit * r.total;       // not where sequences too short to fill a place waste many
       share = fits ? s : share;
     }
-    const float inv_share = 1.f / share;
-    if (!fits) {
+    const float inv_share = __builtin_amdgcn_rcpf(share);
+    if (__builtin_expect(!fits, 1)) {
       len = B <= 64 ? __builtin_amdgcn_readlane(mine, r.b) : clamp_len(lens[r.b]);
       n = splits_for((float)len, inv_share, out.splits);
     } else {
@@ -149,8 +150,13 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
     }
   }
   n = __builtin_amdgcn_readfirstlane(n);
-  const int steps = (len + GRAIN - 1) / GRAIN, each = about_ceil_div(steps, n);       // even shares of this sequence
-  r.splits = steps ? splits_of(steps, each, n) : 0;
+  const int steps = (len + GRAIN - 1) / GRAIN;
+  int each = steps;                                  // even shares of this sequence
+  r.splits = steps ? 1 : 0;
+  if (n > 1) {
+    each = about_ceil_div(steps, n);
+    r.splits = steps ? splits_of(steps, each, n) : 0;
+  }
   r.lo = (int64_t)r.sp * (each * GRAIN);
   r.hi = r.lo + each * GRAIN < len ? r.lo + each * GRAIN : len;
   return r;

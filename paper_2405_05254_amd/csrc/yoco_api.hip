@@ -73,6 +73,7 @@ int check_heads(int Hq, int Hkv) {
 struct Splits {
   int even, most;
   float inv_ragged, inv_even;   // 1 / how many workgroups a batch of ragged, of equal lengths should make
+  int alike;                    // splits of each sequence of one length
   int places;                   // ragged: splits, over the batch, that have a CU of their own for each KV head; 0: not asked
 };
 
@@ -120,7 +121,7 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
     const int64_t twice = 2 * cus / units;
     if (c->dtype == YOCO_BF16 && 4 * units * n < 3 * cus && 2 * units * twice >= 3 * cus && twice <= most && c->N_cap / twice >= 1024) n = twice;
   }
-  return {(int)s, (int)most, 1.f / (float)(units * s), 1.f / (float)(units * n), units <= cus ? cus / c->Hkv : 0};
+  return {(int)s, (int)most, 1.f / (float)(units * s), 1.f / (float)(units * n), (int)n, units <= cus ? cus / c->Hkv : 0};
 }
 
 // The tag a decode launch marks its published splits with: never 0, never the same twice in a process (a bijection of a
@@ -152,10 +153,10 @@ int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* le
     if (!yoco::decode_i8_supported(c, Hq))
       return fail(YOCO_ERR_UNSUPPORTED, "%s: an 8-bit cache serves up to 16 query heads per KV head, not %d", what, Hq / c.Hkv);
     if (k_new) return fail(YOCO_ERR_UNSUPPORTED, "%s: no fused append into an 8-bit cache", what);
-    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.places, tag, o, s);
+    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, s);
     if (tag) return hip_result(e, what);
   } else if (yoco::decode_bf16_supported(c, Hq)) {
-    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.places, tag, o, k_new, v_new, ring, s);
+    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, k_new, v_new, ring, s);
     if (tag) return hip_result(e, what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend

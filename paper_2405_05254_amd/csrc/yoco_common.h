@@ -97,7 +97,7 @@ inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G
 // Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.
 // k_new / v_new ([B,Hkv,128] bf16, or null): also store and attend to the new token's row at slot lens[b] - 1.
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                              float* ws, int splits, float inv_ragged, float inv_even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
+                              float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
                               hipStream_t s);
 
 // 8-bit global cache (cache_i8.hip), head_dim 128: a plane per (sequence, KV head) is a run of 64-row blocks, each
@@ -119,7 +119,7 @@ bool decode_i8_supported(const yoco_kv_cache& c, int Hq);
 hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* v, const float* row_scale, int b, int64_t pos0, int64_t n,
                              const int64_t* pos, int src_dtype, hipStream_t s);
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, float inv_ragged, float inv_even, int places, unsigned long long tag, void* o, hipStream_t s);   // q, o bf16
+                            float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, hipStream_t s);   // q, o bf16
 
 // What stands between the attention calls of a whole bf16 stack (stack_glue.hip). One token: out = W x with W [N][K], the
 // input normalised first when gain != null; res: added behind the product; glu: W is [2 N][K] and output n is
