@@ -325,20 +325,26 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   const int n = lane & 15, qg = lane >> 4;
   unsigned char* vst = smem + wave * kStageBytes;
 
+  // lane (head n, dim group qg) holds dims 32 t + 8 qg .. + 7 of its head's query for t = 0..3; requested for the sequence
+  // that it mostly is before the lengths are there
+  u32x4 qraw[4] = {};
+  auto load_q = [&](int b) {
+    if (n < G) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) qraw[t] = *(const u32x4*)(q + ((int64_t)b * Hq + g * G + n) * kD + t * 32 + qg * 8);
+    }
+  };
+  load_q(blockIdx.y);
   const SplitRows part = split_rows<128>(out, c, lens, fixed_len);
   const int b = part.b, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
 
-  // lane (head n, dim group qg) holds dims 32 t + 8 qg .. + 7 of its head's query for t = 0..3
+  if (__builtin_expect(b != (int)blockIdx.y, 0)) load_q(b);
   bf16x8_t qf[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    u32x4 x = {0, 0, 0, 0};
-    if (n < G) x = *(const u32x4*)(q + ((int64_t)b * Hq + g * G + n) * kD + t * 32 + qg * 8);
-    qf[t] = __builtin_bit_cast(bf16x8_t, x);
-  }
+  for (int t = 0; t < 4; ++t) qf[t] = __builtin_bit_cast(bf16x8_t, qraw[t]);
 
   MState st;
   st.m = kNegBig;
