@@ -114,7 +114,7 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   // -> 31.1). Where that leaves a quarter of the CUs without one, two rounds' worth is better for a bf16 cache (160 units x
   // 16384: 160 workgroups 258 us, 320 268, 480 203; in 8 bits 107, 130, 108), if it makes at least one and a half (200 x 2
   // does not) of splits of 1024 rows or more. Ragged lengths keep the larger count, of which short sequences take less
-  // (200 units of 1000 to 8192 rows: 88 us, at 200 workgroups 137).
+  // (200 units of 1000 to 8192 rows: 88 us, at 200 workgroups 137), unless the kernel finds shares that fit (split_rows).
   int64_t n = s;
   if (units < cus && units * s > cus) {
     n = cus / units;
