@@ -172,8 +172,13 @@ int yoco_global_kv_write_scaled(const yoco_kv_cache* c, const void* k, const voi
  * workspace: optional device scratch (NULL = none), 16-byte aligned. With at
  * least yoco_cross_attn_decode_workspace(c, Hq) bytes, a call with Tq <= 8 rows
  * (the exit row of an early-exit prefill, Fig. 3) is split over the cache like
- * a decode step instead of walking it with one workgroup per head. The result
- * is the same operation either way.
+ * a decode step instead of walking it with one workgroup per head. On a bf16
+ * cache with d = 128 a call with more rows, but few enough that a workgroup per
+ * head and 128 rows does not fill the chip, shares the keys of such a tile out
+ * over several workgroups as far as the workspace holds their partial results
+ * (yoco_cross_attn_prefill_workspace); a second launch merges them in a fixed
+ * order. The result is the same operation either way, up to the order of fp32
+ * sums. Calls that overlap in time must not share a workspace.
  * A bf16 cache with d = 128 and more than 8 rows runs on the same matrix-core
  * path as yoco_swa_prefill, with the same domain: cached |v| below 65504, and
  * |v| under 2^-14 read with an absolute error below 2^-25.
@@ -181,6 +186,11 @@ int yoco_global_kv_write_scaled(const yoco_kv_cache* c, const void* k, const voi
 int yoco_cross_attn_prefill(const yoco_kv_cache* c, const void* q, void* o, int b, int64_t q_pos0,
                             int64_t Tq, int Hq, float scale, void* workspace, size_t workspace_bytes,
                             void* stream);
+
+/* How much workspace yoco_cross_attn_prefill can make use of for more than 8
+ * rows; 0: none. Less is used as far as it goes. Host only. */
+int yoco_cross_attn_prefill_workspace(const yoco_kv_cache* c, int64_t q_pos0, int64_t Tq, int Hq, float scale,
+                                      size_t* bytes);
 
 /* Workspace for yoco_cross_attn_decode on this cache with Hq query heads:
  * `splits` partial results (running max, sum, d-vector in fp32) per

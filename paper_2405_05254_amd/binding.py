@@ -56,6 +56,7 @@ def lib():
     L.yoco_global_kv_write.argtypes = [C.POINTER(_Cache), vp, vp, i32, i64, i64, i32, vp]
     L.yoco_global_kv_write_scaled.argtypes = [C.POINTER(_Cache), vp, vp, vp, i32, i64, i64, i32, vp]
     L.yoco_cross_attn_prefill.argtypes = [C.POINTER(_Cache), vp, vp, i32, i64, i64, i32, f32, vp, sz, vp]
+    L.yoco_cross_attn_prefill_workspace.argtypes = [C.POINTER(_Cache), i64, i64, i32, f32, C.POINTER(sz)]
     L.yoco_cross_attn_decode_workspace.argtypes = [C.POINTER(_Cache), i32, C.POINTER(sz), C.POINTER(i32)]
     L.yoco_cross_attn_decode.argtypes = [C.POINTER(_Cache), vp, vp, vp, i32, f32, vp, sz, vp]
     L.yoco_cross_attn_decode_noalloc.argtypes = [C.POINTER(_Cache), vp, vp, vp, i32, f32, vp]
@@ -73,7 +74,7 @@ def lib():
     L.yoco_ceiling_attn_loop.argtypes = [vp, vp, i32, i32, i32, vp]
     L.yoco_ceiling_stream_read.argtypes = [vp, sz, vp, i32, vp]
     for name in ("yoco_ceiling_mfma", "yoco_ceiling_attn_loop", "yoco_ceiling_stream_read", "yoco_kv_cache_bytes", "yoco_kv_cache_init", "yoco_swa_prefill", "yoco_global_kv_write", "yoco_global_kv_write_scaled",
-                 "yoco_cross_attn_prefill", "yoco_cross_attn_decode_workspace", "yoco_cross_attn_decode", "yoco_cross_attn_decode_noalloc",
+                 "yoco_cross_attn_prefill", "yoco_cross_attn_prefill_workspace", "yoco_cross_attn_decode_workspace", "yoco_cross_attn_decode", "yoco_cross_attn_decode_noalloc",
                  "yoco_swa_cache_write", "yoco_kv_cache_append", "yoco_swa_decode",
                  "yoco_gret_prefill_workspace", "yoco_gret_prefill", "yoco_gret_decode",
                  "yoco_stack_step_scratch", "yoco_stack_step", "yoco_norm_rows", "yoco_glu_rows"):
@@ -191,8 +192,16 @@ def global_kv_write_scaled(cache, k, v, row_scale, b, pos0):
 
 def cross_attn_prefill(cache, q, b, q_pos0, scale, out=None, workspace=None):
     """q [Tq,Hq,d] -> o [Tq,Hq,d], causal over the cache of sequence b (yoco_cross_attn_prefill).
-    workspace: optional device scratch tensor (see cross_attn_decode_workspace) for few-row calls."""
+    workspace: optional device scratch tensor (cross_attn_decode_workspace for up to 8 rows, cross_attn_prefill_workspace
+    for more, which take it from torch's allocator where none is given)."""
     return (_CALLS or _calls()).cross_attn_prefill(cache.address, q, b, q_pos0, scale, out, workspace)
+
+
+def cross_attn_prefill_workspace(cache, q_pos0, Tq, Hq, scale):
+    """Bytes of scratch that cross_attn_prefill can make use of for more than 8 rows; 0: none."""
+    n = C.c_size_t()
+    _check(lib().yoco_cross_attn_prefill_workspace(C.byref(cache.desc), q_pos0, Tq, Hq, scale, C.byref(n)))
+    return n.value
 
 
 def cross_attn_decode_workspace(cache, Hq):

@@ -8,6 +8,7 @@
 #include <Python.h>
 #include <ATen/ATen.h>
 #include <c10/hip/HIPFunctions.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
 #include <stdarg.h>
@@ -21,7 +22,7 @@ namespace {
 PyObject* g_error = nullptr;             // YocoError
 
 #define YOCO_CALLS(X)                                                                                                       \
-  X(yoco_last_error_string) X(yoco_swa_prefill) X(yoco_global_kv_write_scaled) X(yoco_cross_attn_prefill) X(yoco_cross_attn_decode) \
+  X(yoco_last_error_string) X(yoco_swa_prefill) X(yoco_global_kv_write_scaled) X(yoco_cross_attn_prefill) X(yoco_cross_attn_prefill_workspace) X(yoco_cross_attn_decode) \
   X(yoco_cross_attn_decode_noalloc) X(yoco_swa_cache_write) X(yoco_kv_cache_append) X(yoco_swa_decode) X(yoco_gret_prefill) X(yoco_gret_decode)
 #define X(name) decltype(&::name) p_##name = nullptr;
 YOCO_CALLS(X)
@@ -227,8 +228,21 @@ PyObject* cross_attn_prefill(PyObject* const* a) {
   const int64_t b = integer(a[2]), q_pos0 = integer(a[3]);
   const float scale = real(a[4]);
   const at::Tensor o = output(a[5], q);
-  const Workspace w = workspace(a[6]);
+  Workspace w = workspace(a[6]);
   void *qp = dev(q, "q"), *op = dev(o, "o");
+  // Without a workspace: scratch from torch's pool of this stream, to which it goes back when the call has been enqueued.
+  // The call does without where there is none to be had, and under capture, where the pool might have to ask the driver.
+  at::Tensor scratch;
+  size_t useful = 0;
+  if (!w.p && p_yoco_cross_attn_prefill_workspace(&c, q_pos0, q.size(0), (int)q.size(1), scale, &useful) == 0 && useful &&
+      c10::hip::currentStreamCaptureStatusMayInitCtx() == c10::hip::CaptureStatus::None) {
+    try {
+      scratch = at::empty({(int64_t)useful}, q.options().dtype(at::kByte));
+      w.p = scratch.data_ptr();
+      w.bytes = useful;
+    } catch (const c10::OutOfMemoryError&) {
+    }
+  }
   call([&] { return p_yoco_cross_attn_prefill(&c, qp, op, (int)b, q_pos0, q.size(0), (int)q.size(1), scale, w.p, w.bytes, stream()); });
   return wrap(o, a[5]);
 }

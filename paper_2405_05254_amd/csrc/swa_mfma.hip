@@ -44,6 +44,7 @@ constexpr int kStageRows = 1024 / kThreads;   // 16-byte chunks of a K (or V) ti
 constexpr int kStageStep = kThreads / 16;     // rows between a thread's chunks
 constexpr int kBM = kNQ * kWaves;
 constexpr int kTileBytes = kBN * kD * 2;     // 16 KiB
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLazyLog2 = 8.0f;            // rescale only when the max grows by more than 2^8
@@ -53,8 +54,32 @@ struct Args {
   int n_qtiles;       // query tiles per (sequence, head)
   int total;          // workgroups
   int64_t n_keys;     // keys that exist (rows beyond are never read)
+  int pieces;         // a query tile's key tiles are shared out over so many workgroups
+  float* part;        // pieces > 1: their partial results (kPieceFloats each), merged by a launch of its own
 };
 
+// Partial result of one piece: the accumulators of its 4 wavefronts as the lanes hold them, [wave][16][lane][4], then per
+// wavefront and query the maximum (raw scores) and the sum of the weights, [wave][32][2].
+constexpr int kPieceMl = kBM * kD;
+constexpr int kPieceFloats = kPieceMl + kBM * 2;
+constexpr int kMergeAhead = 4;
+
+// The key tiles that some row of query tile qt sees, and of n tiles the ones of piece p of `pieces` (none if hi < lo).
+struct Tiles {
+  int lo, hi;
+};
+__host__ __device__ __forceinline__ Tiles tiles_of(const AttnView& a, int qt) {
+  const int64_t i0 = (int64_t)qt * kBM, p0 = a.q_pos0 + i0;
+  const int64_t rows = a.Tq - i0 < kBM ? a.Tq - i0 : kBM;
+  const int64_t lo_key = p0 - a.window + 1 > 0 ? p0 - a.window + 1 : 0;
+  return {(int)(lo_key / kBN), (int)((p0 + rows - 1) / kBN)};
+}
+__host__ __device__ __forceinline__ Tiles piece_of(Tiles t, int p, int pieces) {
+  const int n = t.hi - t.lo + 1;
+  return {t.lo + (int)((int64_t)n * p / pieces), t.lo + (int)((int64_t)n * (p + 1) / pieces) - 1};
+}
+
+template <bool SPLIT>
 __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   // Two tile buffers as distinct arrays, so that the compiler can tell the
   // stores of the next tile from the operand reads of the current one.
@@ -76,18 +101,22 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   const int G = a.Hq / a.Hkv;
   const int hh = logical % G;
   const int qt = g.n_qtiles - 1 - (logical / G) % g.n_qtiles;
-  const int kvh = (logical / (G * g.n_qtiles)) % a.Hkv;
-  const int b = logical / (G * g.n_qtiles * a.Hkv);
+  const int outer = logical / (G * g.n_qtiles);
+  const int piece = SPLIT ? outer % g.pieces : 0;       // the same piece of all query tiles together: they share key tiles
+  const int kvh = (SPLIT ? outer / g.pieces : outer) % a.Hkv;
+  const int b = (SPLIT ? outer / g.pieces : outer) / a.Hkv;
   const int h = kvh * G + hh;
 
   const int64_t i0 = (int64_t)qt * kBM;                 // first query row of the workgroup
   const int64_t p0 = a.q_pos0 + i0;                     // its absolute position
   const int64_t win = a.window;
   // key tiles that intersect the window of some row of the workgroup
-  int64_t rows_here = a.Tq - i0 < kBM ? a.Tq - i0 : kBM;
-  const int64_t lo_key = p0 - win + 1 > 0 ? p0 - win + 1 : 0;
-  const int64_t hi_key = p0 + rows_here - 1;
-  const int jt_lo = (int)(lo_key / kBN), jt_hi = (int)(hi_key / kBN);
+  Tiles tiles = tiles_of(a, qt);
+  if (SPLIT) {
+    tiles = piece_of(tiles, piece, g.pieces);
+    if (tiles.hi < tiles.lo) return;                    // fewer tiles than pieces: the merge knows
+  }
+  const int jt_lo = tiles.lo, jt_hi = tiles.hi;
 
   const bf16_t* kg = (const bf16_t*)a.k + b * a.kv_stride_b + kvh * a.kv_stride_h;
   const bf16_t* vg = (const bf16_t*)a.v + b * a.kv_stride_b + kvh * a.kv_stride_h;
@@ -137,6 +166,7 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   const int64_t iw = i0 + wave * kNQ;                   // first row of the wavefront
   int64_t iq = iw + lq;
   const bool q_valid = iq < a.Tq;
+  const bool any_row = iw < a.Tq;                       // a wavefront without rows stages tiles and multiplies nothing
   if (!q_valid) iq = a.Tq - 1;
   const bf16_t* qg = (const bf16_t*)a.q + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD;
   bf16x8 qf[8];
@@ -189,7 +219,7 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
     const int jt = tile_of(st);
     const int j0r = (jt - jt_lo) * kBN;                 // tile's first key, relative origin
     // does some row of this wavefront see some key of the tile? / every row every key?
-    const bool need = (j0r <= pw_lo + kNQ - 1) && (j0r + kBN - 1 > pw_lo - win32);
+    const bool need = any_row && (j0r <= pw_lo + kNQ - 1) && (j0r + kBN - 1 > pw_lo - win32);
     const bool full = (j0r + kBN - 1 <= pw_lo) && (j0r > pw_lo + kNQ - 1 - win32);
     // the same for the two 32-key halves: on edge tiles a wavefront multiplies only the halves it needs
     const bool need0 = need && (j0r + 31 > pw_lo - win32);
@@ -309,8 +339,20 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
     step(st + 1, k_b, v_b, k_a, v_a);
   }
 
-  // ---- normalise and store O (bf16, rounded once)
+  if (!any_row) return;
   const float l_tot = l_lane + other_half(l_lane);
+  if (SPLIT) {                                           // unnormalised, in the order that the lanes hold it: 1 KiB a store
+    float* const part = g.part + ((((int64_t)b * a.Hq + h) * g.n_qtiles + qt) * g.pieces + piece) * kPieceFloats;
+    f32x4* const po = (f32x4*)part + wave * 1024 + lane;
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq)
+        __builtin_nontemporal_store(f32x4{acc_o[mb][rq * 4], acc_o[mb][rq * 4 + 1], acc_o[mb][rq * 4 + 2], acc_o[mb][rq * 4 + 3]}, po + (mb * 4 + rq) * 64);
+    if (hf == 0) *(f32x2*)(part + kPieceMl + (wave * kNQ + lq) * 2) = f32x2{m_used, l_tot};
+    return;
+  }
+  // ---- normalise and store O (bf16, rounded once)
   const float inv = 1.f / l_tot;
   if (q_valid) {
     bf16_t* og = (bf16_t*)a.o + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD;
@@ -325,6 +367,107 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   }
 }
 
+// ---- the merge of a query tile's pieces: o = sum_p 2^((m_p - M) c) o_p / sum_p 2^((m_p - M) c) l_p, in a fixed order.
+// A workgroup takes 32 dims of a query tile, its lanes what the attention kernel's lanes held. Bound by the partials, 66 KB
+// for each piece, which mostly come back from the memory behind the L2s.
+__global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
+  const AttnView& a = g.a;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, lq = lane & 31;
+  const int qt = blockIdx.x, mb = blockIdx.y, head = blockIdx.z, b = head / a.Hq, h = head % a.Hq;
+  const int64_t iq = (int64_t)qt * kBM + wave * kNQ + lq;
+  if ((int64_t)qt * kBM + wave * kNQ >= a.Tq) return;      // a wavefront without rows has stored nothing
+  const float c = a.scale * kLog2e;
+  const int n = tiles_of(a, qt).hi - tiles_of(a, qt).lo + 1, pieces = g.pieces;
+  const float* const first = g.part + ((int64_t)head * g.n_qtiles + qt) * pieces * kPieceFloats;
+  float M = kNegBig, L = 0.f;
+  f32x4 o[4] = {};
+  for (int p0 = 0; p0 < pieces; p0 += kMergeAhead) {       // a group's loads go out together
+    f32x2 ml[kMergeAhead];
+    f32x4 x[kMergeAhead][4];
+#pragma unroll
+    for (int i = 0; i < kMergeAhead; ++i) {
+      const int p = p0 + i < pieces ? p0 + i : pieces - 1;
+      const float* const part = first + (int64_t)p * kPieceFloats;
+      ml[i] = *(const f32x2*)(part + kPieceMl + (wave * kNQ + lq) * 2);
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) x[i][rq] = ((const f32x4*)part)[wave * 1024 + (mb * 4 + rq) * 64 + lane];
+    }
+    float m_new = M;
+    bool live[kMergeAhead];
+#pragma unroll
+    for (int i = 0; i < kMergeAhead; ++i) {                // a piece without tiles has stored nothing
+      const int p = p0 + i;
+      live[i] = p < pieces && (int64_t)n * (p + 1) / pieces > (int64_t)n * p / pieces;
+      m_new = live[i] ? fmaxf(m_new, ml[i][0]) : m_new;
+    }
+    const float alpha = __builtin_amdgcn_exp2f((M - m_new) * c);
+    M = m_new;
+    L *= alpha;
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) o[rq] *= alpha;
+#pragma unroll
+    for (int i = 0; i < kMergeAhead; ++i) {
+      if (!live[i]) continue;
+      const float f = __builtin_amdgcn_exp2f((ml[i][0] - M) * c);
+      L = fmaf(f, ml[i][1], L);
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[rq][e] = fmaf(f, x[i][rq][e], o[rq][e]);
+    }
+  }
+  if (iq >= a.Tq) return;
+  const float inv = 1.f / L;
+  bf16_t* const og = (bf16_t*)a.o + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD + mb * 32 + hf * 4;
+#pragma unroll
+  for (int rq = 0; rq < 4; ++rq)
+    *(u32x2*)(og + rq * 8) = u32x2{pack_bf16(o[rq][0] * inv, o[rq][1] * inv), pack_bf16(o[rq][2] * inv, o[rq][3] * inv)};
+}
+
+// How many pieces a call's query tiles are cut into. A workgroup's walk over the keys is serial, so a call with few
+// query tiles leaves the chip idle (64 rows x 16 heads over 24000 rows: 16 workgroups of 376 tiles each, 508 us; in 32 pieces
+// 46), and one whose workgroups are no multiple of the 512 places waits for the CUs that hold two (2000 rows x 24 heads over
+// 16000: 384 workgroups 457 us, in 4 pieces three full rounds, 423). The estimate is in us, from what was measured: a
+// 64-key tile takes 1.34 where a CU has one workgroup, 1.6 where some have two and 2.15 where all have; 5 for a launch and
+// the two ends of a walk; a merge 5 and 0.016 for each piece's way out and back. 30 shapes of 16 to 4096 rows are within a
+// tenth of their best count by it. A cut has to promise a twentieth, because it costs memory.
+constexpr int kMaxPieces = 32;
+constexpr int64_t kMaxPieceWgs = 1536;         // bounds the partials at 102 MB
+float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
+  constexpr int64_t kCus = 256, kPlaces = 512;
+  constexpr float kEnds = 5.f, kAlone = 1.34f, kSome = 1.6f, kAll = 2.15f, kMerge = 5.f, kPiece = 0.016f;
+  const int64_t wgs = items * pieces, full = wgs / kPlaces, rest = wgs % kPlaces;
+  auto tile = [&](int64_t n) { return n <= kCus ? kAlone : kSome + (kAll - kSome) * (float)(n - kCus) / (float)(kPlaces - kCus); };
+  const float longest = ceilf((float)n_max / (float)pieces), mean = n_mean / (float)pieces;
+  float t = (float)full * (mean * kAll + kEnds) + (rest ? mean * tile(rest) + kEnds : 0.f);
+  const float least = longest * tile(wgs < kPlaces ? wgs : kPlaces) + kEnds;
+  if (t < least) t = least;
+  return pieces > 1 ? t + kMerge + kPiece * (float)wgs : t;
+}
+int pieces_for(const AttnView& a, int64_t room) {
+  const int n_qtiles = (int)((a.Tq + kBM - 1) / kBM);
+  const int64_t items = (int64_t)n_qtiles * a.Hq * a.B;
+  if (2 * items > kMaxPieceWgs) return 1;
+  int n_max = 0;
+  int64_t sum = 0;
+  for (int qt = 0; qt < n_qtiles; ++qt) {
+    const Tiles t = tiles_of(a, qt);
+    sum += t.hi - t.lo + 1;
+    if (t.hi - t.lo + 1 > n_max) n_max = t.hi - t.lo + 1;
+  }
+  const float mean = (float)sum / (float)n_qtiles;
+  int best = 1;
+  float us = 0.95f * estimate_us(items, n_max, mean, 1);
+  for (int p = 2; p <= kMaxPieces && p <= n_max && items * p <= kMaxPieceWgs && items * p <= room; ++p) {
+    const float t = estimate_us(items, n_max, mean, p);
+    if (t < us) {
+      us = t;
+      best = p;
+    }
+  }
+  return best;
+}
+
 }  // namespace
 
 bool swa_mfma_supported(const AttnView& a, int dtype) {
@@ -336,13 +479,25 @@ bool swa_mfma_supported(const AttnView& a, int dtype) {
   return total < (1LL << 31);
 }
 
-hipError_t launch_swa_mfma(const AttnView& a, hipStream_t s) {
+size_t swa_mfma_workspace(const AttnView& a) {
+  const int pieces = pieces_for(a, kMaxPieceWgs);
+  return pieces > 1 ? (size_t)((a.Tq + kBM - 1) / kBM) * a.Hq * a.B * pieces * kPieceFloats * sizeof(float) : 0;
+}
+
+hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s) {
   Args g;
   g.a = a;
   g.n_qtiles = (int)((a.Tq + kBM - 1) / kBM);
-  g.total = g.n_qtiles * a.Hq * a.B;
   g.n_keys = a.q_pos0 + a.Tq;
-  hipLaunchKernelGGL(swa_mfma_kernel, dim3(g.total), dim3(kThreads), 0, s, g);
+  g.part = (float*)workspace;
+  g.pieces = workspace ? pieces_for(a, (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float)))) : 1;
+  g.total = g.n_qtiles * a.Hq * a.B * g.pieces;
+  if (g.pieces == 1) {
+    hipLaunchKernelGGL(swa_mfma_kernel<false>, dim3(g.total), dim3(kThreads), 0, s, g);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(swa_mfma_kernel<true>, dim3(g.total), dim3(kThreads), 0, s, g);
+  hipLaunchKernelGGL(swa_merge_kernel, dim3(g.n_qtiles, 4, a.Hq * a.B), dim3(kThreads), 0, s, g);
   return hipGetLastError();
 }
 

@@ -253,6 +253,18 @@ int scratch_of_current_device(void** out) {
 
 constexpr int64_t kFewRows = 8;   // query rows up to which the prefill call splits over the cache like decode
 
+// Tq query rows over one sequence of a cache, without the tensors.
+yoco::AttnView cross_view(const yoco_kv_cache& c, int64_t q_pos0, int64_t Tq, int Hq, float scale) {
+  yoco::AttnView a = {};
+  a.q_stride_t = (int64_t)Hq * c.d;
+  a.kv_stride_n = c.d;
+  a.kv_stride_h = c.N_cap * c.d;
+  a.Tq = Tq; a.q_pos0 = q_pos0;
+  a.window = q_pos0 + Tq;          // every earlier row is visible
+  a.Hq = Hq; a.Hkv = c.Hkv; a.d = c.d; a.B = 1; a.scale = scale;
+  return a;
+}
+
 }  // namespace
 
 #pragma GCC visibility push(default)
@@ -317,7 +329,7 @@ int yoco_swa_prefill(const void* q, const void* k, const void* v, void* o, int B
   a.Tq = T; a.q_pos0 = 0;
   a.window = window > T ? T : window;
   a.Hq = Hq; a.Hkv = Hkv; a.d = d; a.B = B; a.scale = scale;
-  if (yoco::swa_mfma_supported(a, dtype)) return hip_result(yoco::launch_swa_mfma(a, (hipStream_t)stream), "swa_prefill");
+  if (yoco::swa_mfma_supported(a, dtype)) return hip_result(yoco::launch_swa_mfma(a, nullptr, 0, (hipStream_t)stream), "swa_prefill");
   if (yoco::attn_f32_supported(a)) return hip_result(yoco::launch_attn_f32(a, dtype, (hipStream_t)stream), "swa_prefill");
   return hip_result(yoco::launch_attn_generic(a, dtype, (hipStream_t)stream), "swa_prefill");
 }
@@ -422,22 +434,26 @@ int yoco_cross_attn_prefill(const yoco_kv_cache* c, const void* q, void* o, int 
   if (c->dtype == YOCO_INT8)
     return fail(YOCO_ERR_UNSUPPORTED, "cross_attn_prefill over an 8-bit cache serves up to %d rows and needs the decode workspace",
                 (int)kFewRows);
-  yoco::AttnView a;
+  yoco::AttnView a = cross_view(*c, q_pos0, Tq, Hq, scale);
   a.q = q; a.o = o;
   a.k = (const char*)c->k + (size_t)b * seq_bytes;
   a.v = (const char*)c->v + (size_t)b * seq_bytes;
-  a.q_stride_t = (int64_t)Hq * c->d;
-  a.q_stride_b = 0;
-  a.kv_stride_n = c->d;
-  a.kv_stride_h = c->N_cap * c->d;
-  a.kv_stride_b = 0;
-  a.Tq = Tq; a.q_pos0 = q_pos0;
-  a.window = q_pos0 + Tq;          // every earlier row is visible
-  a.Hq = Hq; a.Hkv = c->Hkv; a.d = c->d; a.B = 1; a.scale = scale;
   if (yoco::swa_mfma_supported(a, c->dtype))
-    return hip_result(yoco::launch_swa_mfma(a, (hipStream_t)stream), "cross_attn_prefill");
+    return hip_result(yoco::launch_swa_mfma(a, workspace, workspace_bytes, (hipStream_t)stream), "cross_attn_prefill");
   if (yoco::attn_f32_supported(a)) return hip_result(yoco::launch_attn_f32(a, c->dtype, (hipStream_t)stream), "cross_attn_prefill");
   return hip_result(yoco::launch_attn_generic(a, c->dtype, (hipStream_t)stream), "cross_attn_prefill");
+}
+
+int yoco_cross_attn_prefill_workspace(const yoco_kv_cache* c, int64_t q_pos0, int64_t Tq, int Hq, float scale, size_t* bytes) {
+  if (!c || !bytes) return fail(YOCO_ERR_INVALID_ARG, "null argument");
+  if (c->B <= 0 || c->Hkv <= 0 || c->N_cap <= 0 || c->d <= 0) return fail(YOCO_ERR_INVALID_ARG, "cache has a non-positive size");
+  int rc = check_heads(Hq, c->Hkv);
+  if (rc) return rc;
+  if (Tq <= 0 || q_pos0 < 0 || Tq > c->N_cap || q_pos0 > c->N_cap - Tq)
+    return fail(YOCO_ERR_INVALID_ARG, "query positions outside the cache capacity %lld", (long long)c->N_cap);
+  const yoco::AttnView a = cross_view(*c, q_pos0, Tq, Hq, scale);
+  *bytes = Tq > kFewRows && yoco::swa_mfma_supported(a, c->dtype) ? yoco::swa_mfma_workspace(a) : 0;
+  return YOCO_OK;
 }
 
 int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* bytes, int* splits) {

@@ -86,7 +86,10 @@ hipError_t launch_gret_chunk(const GretView& a, int chunk, void* workspace, hipS
 
 // bf16, d = 128 fast paths. `supported` functions are host-side predicates.
 bool swa_mfma_supported(const AttnView& a, int dtype);
-hipError_t launch_swa_mfma(const AttnView& a, hipStream_t s);
+// workspace (or null): where it holds the partial results, the key tiles of few query tiles are shared out over several
+// workgroups; swa_mfma_workspace says how much such a call makes use of (0: none).
+size_t swa_mfma_workspace(const AttnView& a);
+hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s);
 bool decode_bf16_supported(const yoco_kv_cache& c, int Hq);
 // Where one decode launch also merges its splits (decode_tail.h): a workgroup reads them all, G / 4 heads one after
 // another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (fused against a merge launch, us: 1 x 8 heads x 2048 rows

@@ -1,0 +1,104 @@
+"""Prefill over a cache with the keys of a query tile shared out over several workgroups, whose partial results a second
+launch merges, against the fp64 oracle."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_2405_05254_amd as yoco  # noqa: E402
+import yoco_synth as ys  # noqa: E402
+
+D = 128
+SCALE = 1.0 / math.sqrt(D)
+PIECE = (128 * 128 + 2 * 128) * 4          # bytes of one piece's partial result
+
+
+def plan(cache, q_pos0, Tq, Hq):
+    """Pieces that a call is cut into: what it can make use of, in partial results of its query tiles."""
+    return yoco.cross_attn_prefill_workspace(cache, q_pos0, Tq, Hq, SCALE) // (PIECE * Hq * ((Tq + 127) // 128)) or 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,q_pos0,Tq,pieces", [
+    (24, 8, 1482, 23, 8),        # one query tile, three of its wavefronts without rows
+    (2, 2, 3000, 129, 0),        # the last tile has one row
+    (1, 1, 0, 1000, 0),          # the first query tiles see fewer key tiles than there are pieces
+    (3, 1, 64 * 60 - 9, 9, 0),   # the fewest rows that are not a decode step
+    (16, 2, 5000, 256, 0),       # whole tiles
+    (4, 4, 1, 1600, 0),
+    (24, 8, 10, 30, 1),          # too short to cut
+])
+def test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, pieces):
+    N, rng = q_pos0 + Tq, np.random.default_rng(Tq)
+    cache = yoco.KVCache(2, Hkv, D, N + 3, torch.bfloat16)
+    cache.mem.fill_(0xFF)                                       # NaN wherever nothing is written
+    K, V = (ys.normal(rng, (N, Hkv, D), 1.0, "bf16") for _ in range(2))
+    q = ys.normal(rng, (Tq, Hq, D), 1.0, "bf16")
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    yoco.global_kv_write(cache, dev(K), dev(V), 1, 0)
+    n = plan(cache, q_pos0, Tq, Hq)
+    assert n == pieces or (pieces == 0 and n > 1)
+    nbytes = yoco.cross_attn_prefill_workspace(cache, q_pos0, Tq, Hq, SCALE)
+    own = yoco.cross_attn_prefill(cache, dev(q), 1, q_pos0, SCALE)
+    ref = oracle.cross_attn(q, K, V, q_pos0, SCALE)
+    tol = ys.TOL["bf16"]
+    st = ys.error_stats(own.float().cpu().numpy(), ref)
+    assert st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], st
+    if n == 1:
+        return
+    ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    given = yoco.cross_attn_prefill(cache, dev(q), 1, q_pos0, SCALE, workspace=ws)
+    assert torch.equal(own, given)                              # whatever the scratch held before
+    for part in (nbytes // 2, 1024):                            # fewer pieces, and no room for two
+        ws = torch.full((part // 4 + 64,), float("nan"), dtype=torch.float32, device="cuda")
+        o = yoco.cross_attn_prefill(cache, dev(q), 1, q_pos0, SCALE, workspace=ws[:part // 4])
+        assert torch.isnan(ws[part // 4:]).all()
+        st = ys.error_stats(o.float().cpu().numpy(), ref)
+        assert st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], (part, st)
+
+
+@pytest.mark.gpu
+def test_under_capture_a_call_takes_no_scratch_of_its_own():
+    cache = yoco.KVCache(1, 2, D, 2000, torch.bfloat16)
+    for i, p in enumerate(cache.planes()):
+        p.copy_(ys.device_normal(p.shape, i, 1.0, torch.bfloat16, "cuda"))
+    q = ys.device_normal((40, 4, D), 2, 1.0, torch.bfloat16, "cuda")
+    o, ws = torch.empty_like(q), torch.empty(yoco.cross_attn_prefill_workspace(cache, 1960, 40, 4, SCALE), dtype=torch.uint8, device="cuda")
+    eager = yoco.cross_attn_prefill(cache, q, 0, 1960, SCALE)
+    for given in (None, ws):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            yoco.cross_attn_prefill(cache, q, 0, 1960, SCALE, out=o, workspace=given)
+        for _ in range(3):
+            o.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.allclose(o.float(), eager.float(), atol=2e-2) and (given is None or torch.equal(o, eager))
+
+
+def _desc(dtype, Hkv, N, d=D):
+    import ctypes as C
+
+    from paper_2405_05254_amd import binding as yb
+    c = yb._Cache()
+    assert yoco.lib().yoco_kv_cache_init(0x7f0000000000, yoco.kv_cache_bytes(1, Hkv, d, N, dtype), 1, Hkv, d, N, dtype, C.byref(c)) == 0
+    return c, C
+
+
+def test_scratch_is_asked_for_where_it_is_of_use_and_bounded():
+    L = yoco.lib()
+    for dtype, d, Hkv, Hq, pos0, Tq, want in [
+            (yoco.BF16, D, 8, 24, 14000, 2000, True), (yoco.BF16, D, 8, 24, 24000, 4096, True), (yoco.BF16, D, 1, 1, 500000, 9, True),
+            (yoco.BF16, D, 8, 24, 14000, 8, False),             # few rows use the decode workspace
+            (yoco.BF16, D, 8, 24, 0, 300, False), (yoco.BF16, D, 8, 64, 20000, 8192, False),
+            (yoco.F32, D, 8, 24, 14000, 2000, False), (yoco.BF16, 64, 8, 24, 14000, 2000, False), (yoco.INT8, D, 8, 24, 14000, 2000, False)]:
+        c, C = _desc(dtype, Hkv, pos0 + Tq, d)
+        n = C.c_size_t(1)
+        assert L.yoco_cross_attn_prefill_workspace(C.byref(c), pos0, Tq, Hq, SCALE, C.byref(n)) == 0
+        assert (n.value > 0) == want and n.value <= 1536 * PIECE, (pos0, Tq, n.value)
+    assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 14001, 2000, 24, SCALE, C.byref(n)) != 0
+    assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 9, SCALE, C.byref(n)) != 0
+    assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 24, SCALE, None) != 0
