@@ -83,6 +83,15 @@ __device__ __forceinline__ int splits_of(int steps, int each, int n) {
   return s < n ? s : n;
 }
 
+// One length alone: a step a split as far as there are splits, or none where that saves fewer than three steps (of 256 rows:
+// two), because a meeting costs more (a merge launch there is in any case). us, 16 heads in bf16, a cache of 3000 rows: 200
+// rows (2 steps) 6.8 in two, 5.7 whole; 260 (3 steps) 8.0 in two, 6.5 whole; 520 (5 steps) 8.0 in four, 6.6 in five.
+template <int GRAIN>
+__device__ __forceinline__ int one_length_splits(int len, int most, bool meets) {
+  const int steps = (len + GRAIN - 1) / GRAIN, n = steps < most ? steps : most;
+  return n > 1 && (!meets || steps - about_ceil_div(steps, n) >= (GRAIN < 256 ? 3 : 2)) ? n : 1;
+}
+
 template <int GRAIN>
 __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_kv_cache& c, const int64_t* lens, int64_t fixed_len) {
   // 32-bit arithmetic: 2^31 rows of 132 bytes and more do not fit any GPU this runs on
@@ -97,7 +106,7 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
     len = clamp_len(lens ? lens[r.b] : fixed_len);
     if (out.splits > 1) {
       r.total = (float)len * (float)B;
-      n = splits_for((float)len, 1.f / (float)GRAIN, out.even < out.splits ? out.even : out.splits);
+      n = one_length_splits<GRAIN>(len, out.even < out.splits ? out.even : out.splits, out.tag != 0);
     }
   } else {
     // The same float arithmetic in every workgroup: all agree on every sequence's splits.
@@ -163,103 +172,107 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
 }
 
 // Device-coherent accesses (they bypass the per-XCD L2s).
-__device__ __forceinline__ void put_f32(float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ unsigned long long get_u64(const void* p) {
   return __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void put_u64(void* p, unsigned long long x) {
   __hip_atomic_store((unsigned long long*)p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void put_pair(float* p, float x, float y) {
+  put_u64(p, (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32));
+}
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// The merge of S <= N published splits: o = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s. Each thread owns a head's pair
-// of dims and takes the splits' maxima and sums along with its part of their vectors: one trip to memory, no exchange
-// between threads. Order and assignment are fixed: results are bit-reproducible whoever merges.
+// The merge of a head's S <= N published splits by one wavefront: o = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s. Each
+// lane owns a pair of dims and takes the splits' maxima and sums along with its part of their vectors: one trip to memory, no
+// exchange between lanes. Order and assignment are fixed: results are bit-reproducible whoever merges.
 template <int N>
-__device__ __forceinline__ void merge_splits(const SplitOut& out, int G, size_t head0, int S) {
-  constexpr int kD = 128;
-  const size_t stride = partial_stride(kD), per_head = out.splits * stride;
-  for (int t = threadIdx.x; t < G * (kD / 2); t += 256) {
-    const int h = t / (kD / 2), e = (t % (kD / 2)) * 2;
-    const float* const p = out.ws + (head0 + h) * per_head;
-    unsigned long long ml[N], x[N];
+__device__ __forceinline__ void merge_head(const float* p, size_t stride, int S, bf16_t* o) {
+  const int e = (threadIdx.x & 63) * 2;
+  unsigned long long ml[N], x[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int s = i < S ? i : S - 1;
-      ml[i] = get_u64(p + s * stride + kD);
-      x[i] = get_u64(p + s * stride + e);
-    }
-    float M = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < N; ++i) M = fmaxf(M, __uint_as_float((unsigned)ml[i]));
-    const float base = M == -INFINITY ? 0.f : M;                                       // empty splits only
-    float L = 0.f, a = 0.f, b = 0.f;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const float f = i < S ? __builtin_amdgcn_exp2f(__uint_as_float((unsigned)ml[i]) - base) : 0.f;
-      L = fmaf(f, __uint_as_float((unsigned)(ml[i] >> 32)), L);
-      a = fmaf(f, __uint_as_float((unsigned)x[i]), a);
-      b = fmaf(f, __uint_as_float((unsigned)(x[i] >> 32)), b);
-    }
-    const float inv = L > 0.f ? 1.f / L : 0.f;                                         // no visible row -> zeros
-    *(unsigned*)(out.o + (head0 + h) * kD + e) = (unsigned)f32_to_bf16(a * inv) | ((unsigned)f32_to_bf16(b * inv) << 16);
+  for (int i = 0; i < N; ++i) {
+    const int s = i < S ? i : S - 1;
+    ml[i] = get_u64(p + s * stride + 128);
+    x[i] = get_u64(p + s * stride + e);
   }
+  float M = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < N; ++i) M = fmaxf(M, __uint_as_float((unsigned)ml[i]));
+  const float base = M == -INFINITY ? 0.f : M;                                         // empty splits only
+  float L = 0.f, a = 0.f, b = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float f = i < S ? __builtin_amdgcn_exp2f(__uint_as_float((unsigned)ml[i]) - base) : 0.f;
+    L = fmaf(f, __uint_as_float((unsigned)(ml[i] >> 32)), L);
+    a = fmaf(f, __uint_as_float((unsigned)x[i]), a);
+    b = fmaf(f, __uint_as_float((unsigned)(x[i] >> 32)), b);
+  }
+  const float inv = L > 0.f ? 1.f / L : 0.f;                                           // no visible row -> zeros
+  *(unsigned*)(o + e) = (unsigned)f32_to_bf16(a * inv) | ((unsigned)f32_to_bf16(b * inv) << 16);
 }
 
 // 256 threads, head_dim 128. red_o [4][GS][128] and red_ml [4][GS][2] (max in log2 units, sum) hold the wavefronts'
-// states in LDS, complete behind a barrier; head0 = first query head of the KV head, in rows of o.
+// states in LDS, complete behind a barrier; head0 = first query head of the KV head, in rows of o. From here on a
+// wavefront has its heads to itself (every fourth): no barrier stands between the trips to memory, of which a meeting takes
+// four, one after another (the partial's way out, the tag's, all tags back, all partials back).
 template <int GS>
 __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)[GS][128], float (*red_ml)[GS][2], int G, size_t head0, int sp,
                                              int S) {
-  constexpr int kD = 128;
+  constexpr int kD = 128, kHeads = (GS + 3) / 4;             // heads of a wavefront
   const size_t stride = partial_stride(kD);
   const size_t per_head = out.splits * stride;
   const bool whole = out.tag ? S <= 1 : out.splits <= 1;     // a single split is the whole answer
-  for (int t = threadIdx.x; t < G * kD; t += 256) {
-    const int h = t / kD, e = t % kD;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, e = lane * 2;
+#pragma unroll
+  for (int i = 0; i < kHeads; ++i) {
+    const int h = wave + 4 * i;
+    if (h >= G) break;
     const float M = fmaxf(fmaxf(red_ml[0][h][0], red_ml[1][h][0]), fmaxf(red_ml[2][h][0], red_ml[3][h][0]));
-    float l = 0.f, o = 0.f;
+    float l = 0.f, o0 = 0.f, o1 = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const float f = __builtin_amdgcn_exp2f(red_ml[w][h][0] - M);
       l = fmaf(f, red_ml[w][h][1], l);
-      o = fmaf(f, red_o[w][h][e], o);
+      o0 = fmaf(f, red_o[w][h][e], o0);
+      o1 = fmaf(f, red_o[w][h][e + 1], o1);
     }
     if (whole) {
-      out.o[(head0 + h) * kD + e] = f32_to_bf16(l > 0.f ? o / l : 0.f);
+      *(unsigned*)(out.o + (head0 + h) * kD + e) =
+          (unsigned)f32_to_bf16(l > 0.f ? o0 / l : 0.f) | ((unsigned)f32_to_bf16(l > 0.f ? o1 / l : 0.f) << 16);
       continue;
     }
-    float* p = out.ws + (head0 + h) * per_head + sp * stride;
+    float* const p = out.ws + (head0 + h) * per_head + sp * stride;
+    const float m = l > 0.f ? M : -INFINITY;
     if (!out.tag) {
-      p[e] = o;
-      if (e == 0) {
-        p[kD] = l > 0.f ? M * kLn2 : -INFINITY;    // the merge launch works with natural exponents
+      p[e] = o0;
+      p[e + 1] = o1;
+      if (lane == 0) {
+        p[kD] = m * kLn2;                            // the merge launch works with natural exponents
         p[kD + 1] = l;
       }
       continue;
     }
-    put_f32(p + e, o);
-    if (e == 0) {
-      put_f32(p + kD, l > 0.f ? M : -INFINITY);
-      put_f32(p + kD + 1, l);
-    }
+    put_pair(p + e, o0, o1);
+    if (lane == 0) put_pair(p + kD, m, l);
   }
   if (whole || !out.tag) return;
-  wait_stores();                                   // this wavefront's part is visible to the whole device
-  __syncthreads();                                 // ... and everyone else's
-  float* const tags = out.ws + head0 * per_head + kD + 2;                  // split s: tags + s * stride
-  int seen = 1;
-  if (threadIdx.x < 64) {
-    if (threadIdx.x == 0) put_u64(tags + sp * stride, out.tag);
-    wait_stores();
-    if (threadIdx.x < S) seen = get_u64(tags + threadIdx.x * stride) == out.tag;
+  wait_stores();                                             // this wavefront's heads are visible to the whole device
+  float* const tags = out.ws + (head0 + wave) * per_head + kD + 2;           // head i, split s: tags + 4 i * per_head + s * stride
+  if (lane < kHeads && wave + 4 * lane < G) put_u64(tags + 4 * lane * per_head + sp * stride, out.tag);
+  wait_stores();
+#pragma unroll
+  for (int i = 0; i < kHeads; ++i) {
+    if (wave + 4 * i >= G) break;
+    float* const t = tags + 4 * i * per_head;
+    if (__builtin_amdgcn_ballot_w64(lane < S && get_u64(t + lane * stride) != out.tag)) continue;
+    const float* const p = t - (kD + 2);
+    bf16_t* const o = out.o + (head0 + wave + 4 * i) * kD;
+    if (S <= 4) merge_head<4>(p, stride, S, o);
+    else if (S <= 8) merge_head<8>(p, stride, S, o);
+    else merge_head<kMeetSplits>(p, stride, S, o);
+    if (lane < S) put_u64(t + lane * stride, 0ull);
   }
-  if (!__syncthreads_and(seen)) return;            // uniform over the workgroup
-
-  if (S <= 4) merge_splits<4>(out, G, head0, S);
-  else if (S <= 8) merge_splits<8>(out, G, head0, S);
-  else merge_splits<kMeetSplits>(out, G, head0, S);
-  if (threadIdx.x < S) put_u64(tags + threadIdx.x * stride, 0ull);
 }
 
 }  // namespace yoco

@@ -64,7 +64,8 @@ int check_heads(int Hq, int Hkv) {
 // `even`: the splits a sequence gets on average (a batch of equal lengths possibly fewer: inv_even). A split of a bf16
 // cache has at least 128 rows, one step of its four wavefronts: a launch over few rows is latency, and a step more costs
 // more than the workgroups saved (16 heads x 2016 rows: 13.4 us at 4 splits of 512 rows, 7.7 us at 16 of 128). Of an
-// 8-bit or fp32 cache it has at least 512.
+// 8-bit cache it has at least 256, a step again, where that many meet in the launch (4 x 4 heads: 1500 rows 8.6 us at 3
+// splits, 7.5 at 6; 4096 rows 9.2 at 8, 8.1 at 16), and else 512, as in fp32.
 // `most`: what the workspace holds and the grid launches. Twice as many where a split of `even` has rows enough (2560)
 // to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
 // decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
@@ -88,11 +89,14 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   const int64_t units = (int64_t)c->B * c->Hkv;
   auto clamp = [](int64_t s, int64_t hi) { return s > hi ? hi : s < 1 ? 1 : s; };
   const int64_t wanted = (cus + units - 1) / units;
-  const int min_rows = c->dtype == YOCO_BF16 ? 128 : 512;
+  const bool finer = c->dtype == YOCO_INT8 && yoco::decode_meets_in_launch(Hq / c->Hkv, (int)clamp(clamp(wanted, (c->N_cap + 255) / 256), 256));
+  const int min_rows = c->dtype == YOCO_BF16 ? 128 : finer ? 256 : 512;
   int64_t s = clamp(clamp(wanted, (c->N_cap + min_rows - 1) / min_rows), 256);
   // Splits of a bf16 cache have to save three steps of 128 rows to be worth the meeting at the end (240 units of 355 rows:
-  // 10.1 us unsplit, 12.0 in two; 16 units of 400: 9.2 unsplit, 7.6 in four).
-  if (c->dtype == YOCO_BF16 && (c->N_cap + 127) / 128 - (c->N_cap + 128 * s - 1) / (128 * s) < 3) s = 1;
+  // 10.1 us unsplit, 12.0 in two; 16 units of 400: 9.2 unsplit, 7.6 in four), of an 8-bit one two of 256 (32 units of 500
+  // rows: 6.9 unsplit, 7.5 in two; of 700 8.3 and 7.4 in three).
+  const int64_t least = c->dtype == YOCO_BF16 ? 3 : 2;
+  if ((c->dtype == YOCO_BF16 || finer) && (c->N_cap + min_rows - 1) / min_rows - (c->N_cap + min_rows * s - 1) / (min_rows * s) < least) s = 1;
   // More (sequence, KV head) units than CUs, and not a multiple of them: the workgroups of a ragged last round run
   // with part of the chip idle (384 units on 256 CUs measured 5.7 TB/s at 4096 rows). Two to four splits per unit
   // make the count a multiple again, as long as a split keeps at least 1024 rows (384 units of 1024 rows: 35.9 us

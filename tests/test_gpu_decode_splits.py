@@ -117,3 +117,25 @@ def test_rings_that_are_split_store_the_new_row_and_attend_to_it(Hq, Hkv, N_cap,
         for o in (got, ref):
             st = ys.error_stats(o[b].float().cpu().numpy(), want)
             assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,N_cap", [
+    ("bf16", 16, 16, 3000),           # 16 splits that meet in the launch
+    ("bf16", 12, 4, 3000),            # 24, with a merge launch
+    ("int8", 12, 4, 3000),            # 12 splits of a step of 256 rows
+    ("int8", 16, 2, 2000),            # 8 heads: 8 splits
+])
+def test_lengths_of_one_sequence_around_the_steps_of_its_splits(dtype, Hq, Hkv, N_cap):
+    rng = np.random.default_rng(N_cap + Hq)
+    cache = yoco.KVCache(1, Hkv, D, N_cap, torch.int8 if dtype == "int8" else torch.bfloat16)
+    cache.mem.zero_()
+    K, V = (ys.normal(rng, (N_cap, Hkv, D), 1.0, "bf16") for _ in range(2))
+    q = ys.normal(rng, (1, Hq, D), 1.0, "bf16")
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    yoco.global_kv_write(cache, dev(K), dev(V), 0, 0)
+    ws = torch.full((yoco.cross_attn_decode_workspace(cache, Hq)[0],), 0xFF, dtype=torch.uint8, device="cuda")
+    attend = oracle.cross_attn_int8 if dtype == "int8" else oracle.cross_attn
+    for n in (1, 127, 128, 129, 256, 257, 384, 385, 512, 513, 640, 641, 768, 769, 1025, 2000, N_cap):
+        o = yoco.cross_attn_decode(cache, dev(q), torch.tensor([n], dtype=torch.int64, device="cuda"), SCALE, ws)
+        st = ys.error_stats(o.float().cpu().numpy(), attend(q, K[:n], V[:n], n - 1, SCALE))
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (n, st)
