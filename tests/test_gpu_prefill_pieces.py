@@ -61,6 +61,25 @@ def test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, pieces):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("B,T,Hq,Hkv,window", [
+    (1, 700, 8, 8, 1024),        # a head per XCD
+    (4, 333, 6, 2, 200),         # grouped heads, windows shorter than the prompt
+    (8, 130, 3, 1, 4000),
+    (2, 129, 32, 4, 1),          # walks of one length: one KV head after another
+    (3, 260, 3, 1, 500),         # heads that eight XCDs do not share evenly
+])
+def test_window_prefill_whichever_tiles_go_first(B, T, Hq, Hkv, window):
+    rng = np.random.default_rng(T)
+    q = ys.normal(rng, (B, T, Hq, D), 1.0, "bf16")
+    k, v = (ys.normal(rng, (B, T, Hkv, D), 1.0, "bf16") for _ in range(2))
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    o = yoco.swa_prefill(dev(q), dev(k), dev(v), window, SCALE).float().cpu().numpy()
+    for b in range(B):
+        st = ys.error_stats(o[b], oracle.swa(q[b], k[b], v[b], window, SCALE))
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, st)
+
+
+@pytest.mark.gpu
 def test_under_capture_a_call_takes_no_scratch_of_its_own():
     cache = yoco.KVCache(1, 2, D, 2000, torch.bfloat16)
     for i, p in enumerate(cache.planes()):
