@@ -208,10 +208,12 @@ __global__ void __launch_bounds__(256, 2) gret_segment_kernel(SegArgs g) {
     load(x, c - 2 > c_lo ? c - 2 : c_lo);                              // in flight during the products of two chunks
     __syncthreads();
     u32x4 vh[4], vl[4];
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int t = 0; t < 4; ++t) weigh(tr_frag(v_d, vbase, wave, t), w_d, t, hf, vh[t], vl[t]);
 #pragma unroll
     for (int t = 0; t < 4; ++t) add_rows(S, k_d, kbase, vh[t], vl[t], t);
+    __builtin_amdgcn_s_setprio(0);
   };
   load(even, c_hi - 1);
   load(odd, c_hi - 2 > c_lo ? c_hi - 2 : c_lo);
@@ -394,6 +396,9 @@ __global__ void __launch_bounds__(256, 2) gret_output_kernel(SegArgs g) {
       for (int i = 0; i < 4; ++i) gr[i] = *(const u32x4*)(gg + (int64_t)c * kC * row_bytes + piece(i, end));
     }
     u32x4 q0[2], q1[2];
+    // Raised priority while a wavefront feeds the matrix pipe: the SIMD's other one fills in with its vector work (337 ->
+    // 329 us at T = 32768 x 24 heads with gate and state; nothing more from requesting the gate or V earlier).
+    __builtin_amdgcn_s_setprio(1);
     q0[0] = q_frag(0, 0);
     q1[0] = q_frag(1, 0);
     f32x16 o[2];
@@ -410,6 +415,7 @@ __global__ void __launch_bounds__(256, 2) gret_output_kernel(SegArgs g) {
       o[0] = mfma(sl[x], q0[x], o[0]);
       o[1] = mfma(sl[x], q1[x], o[1]);
     }
+    __builtin_amdgcn_s_setprio(0);
     {
       const float gq = g_t[sqb * 32 + lq];
 #pragma unroll
@@ -454,6 +460,7 @@ __global__ void __launch_bounds__(256, 2) gret_output_kernel(SegArgs g) {
     // ---- the chunk joins the state, and O^T += V^T P^T, 16 rows a step. K's operand of a step is requested behind the
     // state products of the step before, P's at the head of the step; either has eight or four products to arrive in.
     u32x4 vf[2], kt[4], pf[2][2], vh[2], vl[2];
+    __builtin_amdgcn_s_setprio(1);
     vf[0] = tr_frag(v_t, va, wave, 0);
 #pragma unroll
     for (int eb = 0; eb < 4; ++eb) kt[eb] = tr_frag(k_t, kta, eb, 0);
@@ -490,6 +497,7 @@ __global__ void __launch_bounds__(256, 2) gret_output_kernel(SegArgs g) {
       __builtin_amdgcn_sched_barrier(0);
     }
 
+    __builtin_amdgcn_s_setprio(0);
     if (c + 1 < c_hi) load_v(c + 1);                                         // here, because the products leave no registers for it
 
     // ---- GroupNorm over a query's 128 values: each wavefront's mean and sum of squares about it, combined over the four
