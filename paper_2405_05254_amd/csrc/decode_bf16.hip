@@ -308,17 +308,17 @@ __device__ __forceinline__ void mfma_softmax_pv(MState& st, const float (&s)[8],
   }
 }
 
-template <bool APPEND>
+template <bool APPEND, int GMAX>
 __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                                const int64_t* __restrict__ lens, int64_t fixed_len, int Hq,
                                                                float scale_log2, SplitOut out, const bf16_t* __restrict__ k_new,
                                                                const bf16_t* __restrict__ v_new, int ring) {
-  // V staging of the four wavefronts (4 x 32 rows x 288 B) during the stream, the merge buffers after it
+  // V staging of the four wavefronts (4 x 32 rows x 288 B), and the merge buffers beside it: a wavefront that is done writes
+  // its state without waiting for the others (13 layers over 16 ragged sequences of up to 1000 rows 145.6 -> 142.5 us)
   constexpr int kStageBytes = kMRows * kVStride;
-  constexpr int kRedBytes = 4 * kGMax * kD * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[(4 * kStageBytes > kRedBytes) ? 4 * kStageBytes : kRedBytes];
-  __shared__ float red_ml[4][kGMax][2];
-  float (*red_o)[kGMax][kD] = (float (*)[kGMax][kD])smem;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kStageBytes];
+  __shared__ __attribute__((aligned(16))) float red_o[4][GMAX][kD];
+  __shared__ float red_ml[4][GMAX][2];
   const int G = Hq / c.Hkv;
   const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -415,8 +415,8 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
         load_k(i + 1);
         mfma_softmax_pv(st, s, vst, lane);
       }
-      stage_v();
       mfma_scores<true>(s, qf, kr, scale_log2, qg, (int)(j_hi - w_lo) - i * (4 * kMRows));   // last step, 1 row or more
+      stage_v();
       mfma_softmax_pv(st, s, vst, lane);
     };
     // A cache is read again by the next layer: what fits the 256 MB behind the L2s is read so that it stays there, more
@@ -432,7 +432,6 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   float l = st.l;
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
-  __syncthreads();                                       // every wavefront is done with its staging rows
   if (n < G) {
 #pragma unroll
     for (int tt = 0; tt < 8; ++tt)
@@ -441,7 +440,7 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
     if (qg == 0) { red_ml[wave][n][0] = st.m; red_ml[wave][n][1] = l; }
   }
   __syncthreads();
-  finish_split<kGMax>(out, red_o, red_ml, G, (size_t)b * Hq + g * G, sp, part.splits);
+  finish_split<GMAX>(out, red_o, red_ml, G, (size_t)b * Hq + g * G, sp, part.splits);
 }
 
 }  // namespace
@@ -468,14 +467,16 @@ hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64
   const int G = Hq / c.Hkv;
   if (G < 1 || G > kGMax || splits > kMaxDecodeSplits || (tag && !decode_meets_in_launch(G, splits))) return hipErrorInvalidValue;
   if (!kn) {
-    hipLaunchKernelGGL(decode_bf16_mfma_kernel<false>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
+    if (G <= 4) hipLaunchKernelGGL((decode_bf16_mfma_kernel<false, 4>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
+    else hipLaunchKernelGGL((decode_bf16_mfma_kernel<false, kGMax>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
     return hipGetLastError();
   }
   switch (G) {
     case 1: hipLaunchKernelGGL((decode_bf16_kernel<1, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring); break;
     case 2: hipLaunchKernelGGL((decode_bf16_kernel<2, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring); break;
     default:
-      hipLaunchKernelGGL(decode_bf16_mfma_kernel<true>, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
+      if (G <= 4) hipLaunchKernelGGL((decode_bf16_mfma_kernel<true, 4>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
+      else hipLaunchKernelGGL((decode_bf16_mfma_kernel<true, kGMax>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
   }
   return hipGetLastError();
 }
