@@ -92,9 +92,9 @@ size_t swa_mfma_workspace(const AttnView& a);
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s);
 bool decode_bf16_supported(const yoco_kv_cache& c, int Hq);
 // Where one decode launch also merges its splits (decode_tail.h): a workgroup reads them all, G / 4 heads one after
-// another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (fused against a merge launch, us: 1 x 8 heads x 2048 rows
-// at 16 splits and 3 heads 8.1 and 8.2, 4 x 4096 rows at 16 and 2 9.9 and 10.7, at 8 and 8 11.6 and 11.6; 32 and 4 9.6 and
-// 8.3, 16 and 8 10.4 and 9.1, 2 and 16 12.5 and 11.6, 128 and 4 17.6 and 9.5, 256 and 16 73.8 and 15.5).
+// another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (in the launch
+// against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 7.3
+// and 7.5; 16 x 1 7.1 and 7.0; 32 x 4 8.4 and 7.6; 16 x 8 13.7 and 10.4), and a launch less on the host, 2.5 us.
 constexpr int kMeetSplits = 16;
 inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G <= 8 && (G + 3) / 4 * splits <= kMeetSplits); }
 // Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.

@@ -139,3 +139,25 @@ def test_lengths_of_one_sequence_around_the_steps_of_its_splits(dtype, Hq, Hkv, 
         o = yoco.cross_attn_decode(cache, dev(q), torch.tensor([n], dtype=torch.int64, device="cuda"), SCALE, ws)
         st = ys.error_stats(o.float().cpu().numpy(), attend(q, K[:n], V[:n], n - 1, SCALE))
         assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (n, st)
+
+
+@pytest.mark.parametrize("splits", [17, 32, 33, 64, 65, 256])
+def test_merge_launches_of_every_width(splits):
+    N, Hq = 128 * splits - 5, 3
+    cache = yoco.KVCache(1, 1, D, N, torch.bfloat16)
+    rng = np.random.default_rng(splits)
+    K, V = (ys.normal(rng, (N, 1, D), 1.0, "bf16") for _ in range(2))
+    q = ys.normal(rng, (1, Hq, D), 1.0, "bf16")
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    yoco.global_kv_write(cache, dev(K), dev(V), 0, 0)
+    nbytes, n = yoco.cross_attn_decode_workspace(cache, Hq)
+    assert n == splits
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    for length in (N, N // 2, 1, 0):                                     # splits without rows among them, and nothing but those
+        o = yoco.cross_attn_decode(cache, dev(q), torch.tensor([length], dtype=torch.int64, device="cuda"), SCALE, ws)
+        got = o.float().cpu().numpy()
+        if length == 0:
+            assert not got.any()
+            continue
+        st = ys.error_stats(got, oracle.cross_attn(q, K[:length], V[:length], length - 1, SCALE))
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (length, st)
