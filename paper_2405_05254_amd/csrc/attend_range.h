@@ -1,6 +1,7 @@
 // One wavefront's attention over a range of keys on the vector ALU: the whole of the generic kernels, and how the fp32
 // matrix-core kernel redoes a row that came out infinite or NaN.
 #pragma once
+#include "lanes.h"
 #include "yoco_common.h"
 
 namespace yoco {
@@ -12,14 +13,8 @@ __device__ __forceinline__ void lds_wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ float wave_max(float x) {
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
+__device__ __forceinline__ float wave_max(float x) { return over64<LaneMax>(x); }
+__device__ __forceinline__ float wave_sum(float x) { return over64<LaneSum>(x); }
 
 // Online softmax state of one wave over keys [j_lo, j_hi] of one KV head.
 // q_s: this wave's query in LDS (fp32, d entries). p_s: 64 floats of LDS.

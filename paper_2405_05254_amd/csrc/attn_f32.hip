@@ -121,8 +121,7 @@ __global__ void __launch_bounds__(64 * kWaves, QB == 1 ? 3 : 2) attn_f32_kernel(
         s[qb][i] = ahead - i >= 0 && ahead - i < a.window ? s[qb][i] * c : -INFINITY;
         mx = fmaxf(mx, s[qb][i]);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      mx = over_rows<LaneMax>(mx);
       const float base = finite_or_zero(mx), alpha = __builtin_amdgcn_exp2f(m[qb] - base);
       float sum = 0.f;
 #pragma unroll
@@ -152,8 +151,7 @@ __global__ void __launch_bounds__(64 * kWaves, QB == 1 ? 3 : 2) attn_f32_kernel(
 
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    l[qb] += __shfl_xor(l[qb], 16);
-    l[qb] += __shfl_xor(l[qb], 32);
+    l[qb] = over_rows<LaneSum>(l[qb]);
     const int row = qb * 16 + n;
 #pragma unroll
     for (int g = 0; g < kGroups; ++g)

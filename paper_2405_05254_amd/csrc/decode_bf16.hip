@@ -36,20 +36,6 @@ __device__ __forceinline__ float dot2_bf16(unsigned a, unsigned b, float c) {
 __device__ __forceinline__ float bf_lo(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float bf_hi(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
 
-// Sum over the 16 lanes of a DPP row; every lane ends with the total.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x) {
-  int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true);
-  return x + __int_as_float(y);
-}
-__device__ __forceinline__ float row16_sum(float x) {
-  x = dpp_add<0xB1>(x);    // quad_perm [1,0,3,2]
-  x = dpp_add<0x4E>(x);    // quad_perm [2,3,0,1]
-  x = dpp_add<0x141>(x);   // row_half_mirror: quads 0<->1, 2<->3
-  x = dpp_add<0x140>(x);   // row_mirror: halves 0<->1
-  return x;
-}
-
 template <int G>
 struct State {
   float m[G], l[G], o[G][8];
@@ -69,7 +55,7 @@ __device__ __forceinline__ void step(State<G>& st, const u32x4 (&kq)[G], const u
       a = dot2_bf16(kq[h][1], kr[u][1], a);
       a = dot2_bf16(kq[h][2], kr[u][2], a);
       a = dot2_bf16(kq[h][3], kr[u][3], a);
-      a = row16_sum(a) * scale_log2;
+      a = over16<LaneSum>(a) * scale_log2;
       if (TAIL && (u * 4 + r >= nvalid)) a = -INFINITY;
       s[u][h] = a;
     }
@@ -188,18 +174,14 @@ __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const
 #pragma unroll
   for (int h = 0; h < G; ++h) {
     float M = st.m[h];
-    M = fmaxf(M, __shfl_xor(M, 16));
-    M = fmaxf(M, __shfl_xor(M, 32));
+    M = over_rows<LaneMax>(M);
     const float f = __builtin_amdgcn_exp2f(st.m[h] - M);
     float l = st.l[h] * f;
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
+    l = over_rows<LaneSum>(l);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float x = st.o[h][i] * f;
-      x += __shfl_xor(x, 16);
-      x += __shfl_xor(x, 32);
-      st.o[h][i] = x;
+      const float x = st.o[h][i] * f;
+      st.o[h][i] = over_rows<LaneSum>(x);
     }
     if (lane < 16) {
 #pragma unroll
@@ -269,8 +251,7 @@ __device__ __forceinline__ void mfma_softmax_pv(MState& st, const float (&s)[8],
   float smax = s[0];
 #pragma unroll
   for (int i = 1; i < 8; ++i) smax = fmaxf(smax, s[i]);
-  smax = fmaxf(smax, __shfl_xor(smax, 16));     // the four lanes of a head hold 8 rows each
-  smax = fmaxf(smax, __shfl_xor(smax, 32));
+  smax = over_rows<LaneMax>(smax);              // the four lanes of a head hold 8 rows each
   const float m_new = fmaxf(st.m, smax);
   float p[8], psum = 0.f;
 #pragma unroll
@@ -429,9 +410,7 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   }
 
   // One state per head and wavefront: the four lanes of a head sum their row sums; then the merge over wavefronts.
-  float l = st.l;
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  const float l = over_rows<LaneSum>(st.l);
   if (n < G) {
 #pragma unroll
     for (int tt = 0; tt < 8; ++tt)

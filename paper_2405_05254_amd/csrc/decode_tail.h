@@ -10,6 +10,7 @@
 // device-coherent level, so the last one to publish sees all tags; two that see them both write the same bits. No
 // workgroup waits for another.
 #pragma once
+#include "lanes.h"
 #include "yoco_common.h"
 
 namespace yoco {

@@ -14,6 +14,7 @@
 // contiguous along the key dimension, so the 32 lanes of a half wavefront
 // read and write 512 contiguous bytes, and o[ev] = q . S^T[ev] is a butterfly
 // over those 32 lanes: no LDS and no barrier on the path without GroupNorm.
+#include "lanes.h"
 #include "yoco_common.h"
 
 namespace yoco {
@@ -36,13 +37,12 @@ template <> __device__ __forceinline__ f32x4 load4<bf16_t>(const bf16_t* p) {
 }
 
 __device__ __forceinline__ float half_wave_sum(float x) {      // over the 32 lanes that share tid / 32
-  for (int o = 16; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
+  return over32<LaneSum>(x);
 }
 
 // Sum of one value per thread over the workgroup; every thread gets the result.
 __device__ __forceinline__ float block_sum(float x, float* red) {
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  x = over64<LaneSum>(x);
   __syncthreads();                                  // the previous use of red[] is over
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
@@ -132,7 +132,8 @@ __global__ void __launch_bounds__(256) gret_recurrent_kernel(GretView a) {
 // a thread are reduced together (at the first two exchanges a lane keeps half of its rows), after which the eight lanes
 // kk / 8 of a half wavefront hold row rr + 32 (kk / 8). Measured against 4 wavefronts of 16 rows a thread, 13 layers:
 // 1 x 24 heads 94 -> 59 us, 8 x 24 113 -> 86, 16 x 24 174 -> 155 (4.2 TB/s of 50 MB a layer), 32 x 24 272 -> 248;
-// 8 wavefronts of 8 rows 67, 95, 168, 260. NT: nontemporal accesses, see launch_step.
+// 8 wavefronts of 8 rows 67, 95, 168, 260. With the sums over lanes in registers instead of shuffles (lanes.h) 49, 79 and 150
+// at 1, 8 and 16 x 24. NT: nontemporal accesses, see launch_step.
 constexpr int kStepRows = 4, kStepGroups = 128 / kStepRows;
 
 template <typename T, bool NT>
@@ -167,22 +168,19 @@ __global__ void __launch_bounds__(32 * kStepGroups) gret_decode_kernel(GretView 
     else st[r * kStride] = S[r];
     part[r] = qf[0] * S[r][0] + qf[1] * S[r][1] + qf[2] * S[r][2] + qf[3] * S[r][3];
   }
-  // reduce-scatter over the 32 lanes of the half wavefront: bit o of kk chooses the half of the rows at exchange o
+  // reduce-scatter over the 32 lanes of the half wavefront: bits 4 and 3 of kk choose a half of the rows each
+  static_assert(kR == 4, "two exchanges");
 #pragma unroll
-  for (int w = kR / 2, o = 16; w >= 1; w >>= 1, o >>= 1) {  // w rows stay per lane after the exchange with lane ^ o
-    const bool upper = (kk & o) != 0;
-#pragma unroll
-    for (int i = 0; i < w; ++i) {
-      const float send = upper ? part[i] : part[i + w];
-      const float keep = upper ? part[i + w] : part[i];
-      part[i] = keep + __shfl_xor(send, o);
-    }
+  for (int i = 0; i < 2; ++i) {                               // with lane ^ 16: rows i and i + 2, whose odd and even rows of lanes change places
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(part[i]), __float_as_uint(part[i + 2]), false, false);
+    part[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
-#pragma unroll
-  for (int o = kSame / 2; o >= 1; o >>= 1) part[0] += __shfl_xor(part[0], o);
+  const bool upper = (kk & 8) != 0;
+  part[0] = (upper ? part[1] : part[0]) + dpp_mov<0x128>(upper ? part[0] : part[1]);   // row_ror:8, lane ^ 8
+  part[0] = over8<LaneSum>(part[0]);
   float out = a.scale * part[0];
   auto total = [&](float x, float* sums) {                    // over the workgroup
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    x = over64<LaneSum>(x);
     if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = x;
     __syncthreads();
     float s = 0.f;

@@ -7,6 +7,7 @@
 // everything around it folded in (the norm before, the residual or the SwiGLU product behind), the first weights
 // requested before the norm of the input is formed, and enough wavefronts that the whole matrix is in flight at once.
 // The roundings are those of the unfused chain: every named intermediate is rounded to bf16 where it used to be stored.
+#include "lanes.h"
 #include "mfma_util.h"
 #include "yoco_common.h"
 
@@ -21,13 +22,8 @@ __device__ __forceinline__ float lo_f(unsigned x) { return __uint_as_float(x << 
 __device__ __forceinline__ float hi_f(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
 __device__ __forceinline__ float round_bf16(float x) { return bf16_to_f32(f32_to_bf16(x)); }
 
-__device__ __forceinline__ float wave_total(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
 __device__ __forceinline__ float block_total(float x, float* red) {     // 256 threads; red: 4 floats, used once
-  x = wave_total(x);
+  x = over64<LaneSum>(x);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
   return (red[0] + red[1]) + (red[2] + red[3]);
@@ -131,7 +127,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs g) {
     }
   }
 #pragma unroll
-  for (int r = 0; r < NR; ++r) acc[r] = wave_total(acc[r]);
+  for (int r = 0; r < NR; ++r) acc[r] = over64<LaneSum>(acc[r]);
   bf16_t* out = (bf16_t*)g.out;
 #pragma unroll
   for (int r = 0; r < ROWS; ++r) {
