@@ -7,6 +7,8 @@
 // everything around it folded in (the norm before, the residual or the SwiGLU product behind), the first weights
 // requested before the norm of the input is formed, and enough wavefronts that the whole matrix is in flight at once.
 // The roundings are those of the unfused chain: every named intermediate is rounded to bf16 where it used to be stored.
+#include <type_traits>
+
 #include "lanes.h"
 #include "mfma_util.h"
 #include "yoco_common.h"
@@ -35,13 +37,27 @@ __device__ __forceinline__ float swish(float g) { return g / (1.f + __expf(-g));
 enum Epilogue { kPlain, kResidual, kGlu };
 constexpr int kStep = 2048;                       // elements of K per trip: 4 loads of 16 bytes per lane and row
 
-template <int ROWS, bool NORM, Epilogue EPI>
-__global__ void __launch_bounds__(256) gemv_kernel(GemvArgs g) {
+// Args: GemvArgs, or GemvPair for two matrices, the second's workgroups behind the first's (N is a multiple of a workgroup's
+// outputs).
+template <int ROWS, bool NORM, Epilogue EPI, typename Args>
+__global__ void __launch_bounds__(256) gemv_kernel(Args g) {
+  constexpr bool kPair = std::is_same<Args, GemvPair>::value;
   constexpr int NR = EPI == kGlu ? 2 * ROWS : ROWS;
   extern __shared__ __attribute__((aligned(16))) unsigned char x_lds[];      // the input row (normalised), bf16
   __shared__ float red[4];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int row0 = (blockIdx.x * 4 + (tid >> 6)) * ROWS;
+  int row0 = (blockIdx.x * 4 + (tid >> 6)) * ROWS;
+  bool second = false;
+  if constexpr (kPair) {
+    second = (int)blockIdx.x * 4 * ROWS >= g.N;
+    if (second) {
+      row0 -= g.N;
+      g.gain = g.gain2;
+      g.W = g.W2;
+      g.out = g.out2;
+      g.n_plain = g.N = g.N2;
+    }
+  }
   const bf16_t* wp[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -141,7 +157,12 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs g) {
       const float a = acc[r];
       g.log_gamma[n - g.n_plain] = (fminf(a, 0.f) - log1pf(__expf(-fabsf(a)))) * g.inv_tau;
     } else {
-      out[n] = f32_to_bf16(acc[r]);
+      bf16_t* to = out + n;
+      if constexpr (kPair) {
+        const int heads = g.N >> 8, head = n >> 7;
+        if (!second && g.k_row) to = (bf16_t*)(head < heads ? g.k_row : g.v_row) + (head < heads ? head : head - heads) * g.head_stride + (n & 127);
+      }
+      *to = f32_to_bf16(acc[r]);
     }
   }
 }
@@ -195,10 +216,10 @@ __global__ void __launch_bounds__(256) glu_rows_kernel(const u32x4* __restrict__
   }
 }
 
-template <int ROWS, bool NORM, Epilogue EPI>
-hipError_t launch(const GemvArgs& g, hipStream_t s) {
+template <int ROWS, bool NORM, Epilogue EPI, typename Args>
+hipError_t launch(const Args& g, int rows, hipStream_t s) {
   const int per_wg = 4 * ROWS;
-  hipLaunchKernelGGL((gemv_kernel<ROWS, NORM, EPI>), dim3((unsigned)((g.N + per_wg - 1) / per_wg)), dim3(256), (unsigned)g.K * 2u, s, g);
+  hipLaunchKernelGGL((gemv_kernel<ROWS, NORM, EPI, Args>), dim3((unsigned)((rows + per_wg - 1) / per_wg)), dim3(256), (unsigned)g.K * 2u, s, g);
   return hipGetLastError();
 }
 
@@ -210,10 +231,17 @@ hipError_t launch(const GemvArgs& g, hipStream_t s) {
 // launch plus the bytes at 6.1 TB/s.
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
   if (g.K % 8 || g.K > kGemvMaxK || g.K <= 0 || g.N <= 0) return hipErrorInvalidValue;
-  if (g.glu) return launch<1, true, kGlu>(g, s);
-  if (g.res) return launch<1, false, kResidual>(g, s);
-  if (g.N >= 16384) return launch<2, true, kPlain>(g, s);
-  return launch<1, true, kPlain>(g, s);
+  if (g.glu) return launch<1, true, kGlu>(g, g.N, s);
+  if (g.res) return launch<1, false, kResidual>(g, g.N, s);
+  if (g.N >= 16384) return launch<2, true, kPlain>(g, g.N, s);
+  return launch<1, true, kPlain>(g, g.N, s);
+}
+
+// A token's row of the global cache and the first cross-decoder layer's queries: 43 launches of a step become 41 (one of the
+// two stored the row), 4 us of 303.
+hipError_t launch_gemv_pair(const GemvPair& g, hipStream_t s) {
+  if (g.K % 8 || g.K > kGemvMaxK || g.K <= 0 || g.N <= 0 || g.N % 256 || g.n_plain != g.N || g.N2 <= 0 || g.res || g.glu) return hipErrorInvalidValue;
+  return launch<1, true, kPlain>(g, g.N + g.N2, s);
 }
 
 hipError_t launch_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, hipStream_t s) {

@@ -685,16 +685,27 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
       if (rc) return rc;
       finish_layer(L, t.x);
     }
-    gemv(cur, st->kv_ln, st->w_kv, 2 * ckd, dm, nullptr, 0, t.in, 2 * ckd);
+    // Eq. 2 for the new row and the first cross-decoder layer's queries read the same input: one launch, which stores the row
+    // in a bf16 cache itself (past the capacity nothing is stored, as in yoco_kv_cache_append)
+    yoco::GemvPair g = {};
+    g.x = cur; g.K = dm; g.eps = st->eps;
+    g.gain = st->kv_ln; g.W = st->w_kv; g.N = g.n_plain = 2 * ckd; g.out = t.in + qd;
+    g.gain2 = st->cross[0].ln1; g.W2 = st->cross[0].w_in; g.N2 = qd; g.out2 = t.in;
+    if (cache->dtype == YOCO_BF16 && pos < cache->N_cap) {
+      g.k_row = (bf16_raw*)cache->k + pos * st->d;
+      g.v_row = (bf16_raw*)cache->v + pos * st->d;
+      g.head_stride = cache->N_cap * st->d;
+    }
+    if (e == hipSuccess) e = yoco::launch_gemv_pair(g, s);
     if (e != hipSuccess) return hip_result(e, "stack_step");
-    if (pos < cache->N_cap) {                 // past the capacity nothing is stored, as in yoco_kv_cache_append
-      rc = yoco_global_kv_write(cache, t.in, t.in + ckd, 0, pos, 1, YOCO_BF16, stream);
+    if (!g.k_row && pos < cache->N_cap) {
+      rc = yoco_global_kv_write(cache, t.in + qd, t.in + qd + ckd, 0, pos, 1, YOCO_BF16, stream);
       if (rc) return rc;
     }
   }
   for (int i = 0; i < st->n_cross; ++i) {
     const yoco_stack_layer& L = st->cross[i];
-    gemv(cur, L.ln1, L.w_in, qd, dm, nullptr, 0, t.in, qd);
+    if (i > 0 || !self) gemv(cur, L.ln1, L.w_in, qd, dm, nullptr, 0, t.in, qd);
     if (e != hipSuccess) return hip_result(e, "stack_step");
     rc = run_decode(*cache, t.in, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, plan, s, "stack_step");
     if (rc) return rc;

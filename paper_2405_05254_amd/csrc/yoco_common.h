@@ -137,8 +137,20 @@ struct GemvArgs {
   int N, K, n_plain, glu;
   float eps, inv_tau;
 };
+// Two matrices over the same input in one launch: the second is W2 [N2][K] behind a norm of its own (gain2), into out2; the
+// first one's outputs are a cache row's K heads and V heads of 128, head i at k_row (v_row) + i * head_stride, or go to out
+// where k_row is null. No res, no glu, no log-decays.
+struct GemvPair : GemvArgs {
+  const void* gain2;
+  const void* W2;
+  void* out2;
+  int N2;
+  void *k_row, *v_row;
+  int64_t head_stride;
+};
 constexpr int kGemvMaxK = 16384;      // the input row is held in LDS
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s);
+hipError_t launch_gemv_pair(const GemvPair& g, hipStream_t s);
 // xn = RMSNorm(x + add) * gain row by row (x + add is stored in y; add == null: no addition, y unused)
 hipError_t launch_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, hipStream_t s);
 hipError_t launch_glu_rows(const void* gu, void* h, int64_t rows, int ffn, hipStream_t s);
