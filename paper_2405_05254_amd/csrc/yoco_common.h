@@ -93,8 +93,8 @@ hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_
 bool decode_bf16_supported(const yoco_kv_cache& c, int Hq);
 // Where one decode launch also merges its splits (decode_tail.h): a workgroup reads them all, G / 4 heads one after
 // another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (in the launch
-// against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 7.3
-// and 7.5; 16 x 1 7.1 and 7.0; 32 x 4 8.4 and 7.6; 16 x 8 13.7 and 10.4), and a launch less on the host, 2.5 us.
+// against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 6.7
+// and 7.2; 32 x 3 7.7 and 6.9; 32 x 4 7.9 and 6.8; 16 x 8 9.9 and 7.5), and a launch less on the host, 2.5 us.
 constexpr int kMeetSplits = 16;
 inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G <= 8 && (G + 3) / 4 * splits <= kMeetSplits); }
 // Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.
