@@ -65,7 +65,12 @@ int check_heads(int Hq, int Hkv) {
 // cache has at least 128 rows, one step of its four wavefronts: a launch over few rows is latency, and a step more costs
 // more than the workgroups saved (16 heads x 2016 rows: 13.4 us at 4 splits of 512 rows, 7.7 us at 16 of 128). Of an
 // 8-bit cache it has at least 256, a step again, where that many meet in the launch (4 x 4 heads: 1500 rows 8.6 us at 3
-// splits, 7.5 at 6; 4096 rows 9.2 at 8, 8.1 at 16), and else 512, as in fp32.
+// splits, 7.5 at 6; 4096 rows 9.2 at 8, 8.1 at 16) or a merge launch is there in any case (16:4 heads x 16000 rows 9.6 us at
+// 32 splits, 8.2 at 63; 64:8 x 8000 9.7 at 16, 8.7 at 32; 16:1 x 700 9.7 at 2, 8.4 at 3) and has no more than 64 to read
+// for a head (6:2 x 30000 9.5 at 59, 10.1 at 118; 16:1 x 20000 10.1 at 40, 10.8 at 79). Else it has 512: a merge launch for finer
+// splits gains where the cache is full (24:8 x 8192 rows 9.3 us at 16, 8.0 at 32) and loses where it is not (300 rows of
+// them 6.3 and 7.5).
+// An fp32 cache has 512.
 // `most`: what the workspace holds and the grid launches. Twice as many where a split of `even` has rows enough (2560)
 // to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
 // decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
@@ -89,7 +94,9 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   const int64_t units = (int64_t)c->B * c->Hkv;
   auto clamp = [](int64_t s, int64_t hi) { return s > hi ? hi : s < 1 ? 1 : s; };
   const int64_t wanted = (cus + units - 1) / units;
-  const bool finer = c->dtype == YOCO_INT8 && yoco::decode_meets_in_launch(Hq / c->Hkv, (int)clamp(clamp(wanted, (c->N_cap + 255) / 256), 256));
+  auto count = [&](int64_t rows) { return (int)clamp(clamp(wanted, (c->N_cap + rows - 1) / rows), 256); };
+  auto meets = [&](int splits) { return yoco::decode_meets_in_launch(Hq / c->Hkv, splits); };
+  const bool finer = c->dtype == YOCO_INT8 && (meets(count(256)) || (!meets(count(512)) && count(256) <= 64));
   const int min_rows = c->dtype == YOCO_BF16 ? 128 : finer ? 256 : 512;
   int64_t s = clamp(clamp(wanted, (c->N_cap + min_rows - 1) / min_rows), 256);
   // Splits of a bf16 cache have to save three steps of 128 rows to be worth the meeting at the end (240 units of 355 rows:

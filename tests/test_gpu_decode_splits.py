@@ -24,9 +24,15 @@ SCALE = 1.0 / math.sqrt(D)
     ("bf16", 16, 2, 1024, [1024, 130]),                     # 8 splits of 8 heads: one launch
     ("bf16", 8, 1, 1100, [1100, 0, 900]),                   # 9 splits of 8 heads: a merge launch, an empty sequence
     ("bf16", 9, 1, 500, [500, 1]),                          # 9 heads: a merge launch however few the splits
-    ("int8", 12, 3, 9000, [9000, 12, 0]),                   # 18 splits of 4 heads: a merge launch
+    ("int8", 12, 3, 9000, [9000, 12, 0]),                   # 18 splits of 512 rows would need a merge launch: as many of 256 as fill the chip
     ("int8", 5, 1, 4000, [4000, 2000]),                     # 8 splits of 5: one launch
-    ("int8", 8, 1, 5000, [5000, 513, 0]),                   # 10 splits of 8: a merge launch
+    ("int8", 8, 1, 5000, [5000, 513, 0]),                   # 10 splits of 8, a merge launch: 20 of 256 rows
+    ("int8", 16, 1, 513, [513, 512]),                       # 3 splits of 16 heads for a merge launch; one row less is one split
+    ("int8", 16, 1, 512, [512, 257]),
+    ("int8", 4, 1, 8192, [8192, 300]),                      # 16 splits of 512 rows meet: no finer
+    ("int8", 4, 1, 8193, [8193, 300]),                      # 33 of 256
+    ("int8", 4, 1, 16384, [16384]),                         # 64 of 256
+    ("int8", 4, 1, 16385, [16385]),                         # 33 of 512, not 65
     ("bf16", 16, 1, 9000, [9000, 0, 7, 4400, 128, 127]),    # 16 heads in one workgroup, an empty sequence among long ones
     ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
     ("bf16", 12, 12, 1100, [1100, 1100, 1090, 1100, 1100, 1100, 1100]),   # 84 units of equal lengths: 3 splits, not 4
