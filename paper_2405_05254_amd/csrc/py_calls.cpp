@@ -231,10 +231,12 @@ PyObject* cross_attn_prefill(PyObject* const* a) {
   Workspace w = workspace(a[6]);
   void *qp = dev(q, "q"), *op = dev(o, "o");
   // Without a workspace: scratch from torch's pool of this stream, to which it goes back when the call has been enqueued.
-  // The call does without where there is none to be had, and under capture, where the pool might have to ask the driver.
+  // The call does without where there is none to be had, under capture, where the pool might have to ask the driver, and for
+  // queries of another device, whose pool knows nothing of the stream that the launches go to.
   at::Tensor scratch;
   size_t useful = 0;
   if (!w.p && p_yoco_cross_attn_prefill_workspace(&c, q_pos0, q.size(0), (int)q.size(1), scale, &useful) == 0 && useful &&
+      q.get_device() == c10::hip::current_device() &&
       c10::hip::currentStreamCaptureStatusMayInitCtx() == c10::hip::CaptureStatus::None) {
     try {
       scratch = at::empty({(int64_t)useful}, q.options().dtype(at::kByte));
