@@ -476,12 +476,23 @@ int pieces_for(const AttnView& a, int64_t room) {
   return best;
 }
 
-// Where walks differ much (their mean is under three quarters of the longest: batches of prompts up to twice the window), the
-// heavier query tiles go first over all heads of an XCD, so that the launch ends in short walks everywhere: 8 x 1000 rows x
-// 16 heads 70.8 -> 57.2 us, 4 x 1500 x 24:8 77.1 -> 75.6. Elsewhere one KV head follows another, whose key tiles then stay
-// in the L2 (32768 rows x 24 heads 553 us, heavier first 558; 2 x 4000, window 512, 81.8 and 84.2).
+// Where walks differ much (their mean is under three quarters of the longest: causal attention over up to twice the window)
+// and the launch is a few rounds of the chip's places, the heavier query tiles go first over all heads of an XCD, so that it
+// ends in short walks everywhere: 8 x 1000 rows x 16 heads 74.1 -> 57.6 us, 4 x 1500 x 24:8 78.4 -> 74.7, 4096 rows x 24 heads
+// without a window 145 -> 127. But all of the XCD's KV heads are walked side by side then, and the fewer workgroups of one
+// are in flight, the less of its key tiles comes from the L2: 59 x 1900 x 24 heads 1551 us one KV head after another,
+// 2174 heavier first; 12 x 700 x 24 89 and 89, 20 x 700 137 and 151 (two rounds gain all the same: 9 x 500 46.4 and 40.3);
+// 16 x 4096 x 24 without a window 2051 and 2343. In a long launch the end matters less, too (40 heads x 16384 rows, ten
+// rounds, 2901 and 2958; 24 x 24576, nine, 4008 and 3977).
+// Where two or three query heads share a KV head that share is smaller already (24:8: 8 x 1000 rows 91.6 and 83.3, 18 x
+// 1000 188 and 188, 12 x 1500 223 and 228, 28 x 300 59.2 and 61.9), and of four and more as much is lost as is won (32:8: 4 x
+// 1000 62.9 and 56.9, 8 x 1000 108 and 112, 9 x 1900 297 and 312).
+// Elsewhere one KV head follows another (32768 rows x 24 heads 553 us, heavier first 558; 2 x 4000, window 512, 81.8 and 84.2).
 int heavy_heads_for(const AttnView& a, int n_qtiles) {
-  if (n_qtiles > 256 || (int64_t)a.B * a.Hkv % 8) return 0;
+  const int64_t kv_heads = (int64_t)a.B * a.Hkv, wgs = (int64_t)n_qtiles * a.B * a.Hq;
+  const int group = a.Hq / a.Hkv;
+  if (kv_heads % 8 || group > 3 || n_qtiles > 256) return 0;
+  if (group == 1 ? wgs > 4608 || (kv_heads > 192 && wgs > 1024) : wgs > 2048 || kv_heads > 128) return 0;
   int64_t sum = 0, longest = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {
     const Tiles t = tiles_of(a, qt);

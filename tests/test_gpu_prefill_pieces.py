@@ -67,6 +67,12 @@ def test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, pieces):
     (8, 130, 3, 1, 4000),
     (2, 129, 32, 4, 1),          # walks of one length: one KV head after another
     (3, 260, 3, 1, 500),         # heads that eight XCDs do not share evenly
+    (1, 2500, 8, 8, 3000),       # long walks
+    (9, 300, 24, 24, 1024),      # more KV heads than stay side by side, in two rounds; in more than two rounds
+    (26, 260, 16, 16, 1024),
+    (5, 900, 12, 6, 1024),       # 30 KV heads: not shared evenly; two query heads on each of 32
+    (4, 900, 16, 8, 1024),
+    (2, 800, 32, 8, 1024),       # four on each: one KV head after another
 ])
 def test_window_prefill_whichever_tiles_go_first(B, T, Hq, Hkv, window):
     rng = np.random.default_rng(T)
@@ -121,3 +127,23 @@ def test_scratch_is_asked_for_where_it_is_of_use_and_bounded():
     assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 14001, 2000, 24, SCALE, C.byref(n)) != 0
     assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 9, SCALE, C.byref(n)) != 0
     assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 24, SCALE, None) != 0
+
+
+@pytest.mark.gpu
+def test_a_large_batch_takes_no_longer_a_prompt_than_a_small_one():
+    """Prompts of 1900 rows x 24 heads, window 1024: the key tiles of a head stay in the L2 for its query tiles also where a
+    launch has 59 of them (26 us a prompt and 28 at four of them; walked side by side 37)."""
+    def us_a_prompt(B):
+        q, k, v = (torch.zeros(B, 1900, 24, D, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+        o, best = torch.empty_like(q), float("inf")
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(4):
+                yoco.swa_prefill(q, k, v, 1024, SCALE, out=o)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 1e3 / (4 * B))
+        return best
+
+    assert us_a_prompt(59) < 1.2 * us_a_prompt(4)
