@@ -193,7 +193,9 @@ def global_kv_write_scaled(cache, k, v, row_scale, b, pos0):
 def cross_attn_prefill(cache, q, b, q_pos0, scale, out=None, workspace=None):
     """q [Tq,Hq,d] -> o [Tq,Hq,d], causal over the cache of sequence b (yoco_cross_attn_prefill).
     workspace: optional device scratch tensor (cross_attn_decode_workspace for up to 8 rows, cross_attn_prefill_workspace
-    for more, which take it from torch's allocator where none is given)."""
+    for more). Without one, a call of more rows that is not given its output either takes both from torch's allocator.
+    It does without scratch under stream capture and where memory is short, and so does every call that is given its
+    output: slower where query tiles are few, and with other low-order bits (yoco_cross_attn_prefill)."""
     return (_CALLS or _calls()).cross_attn_prefill(cache.address, q, b, q_pos0, scale, out, workspace)
 
 

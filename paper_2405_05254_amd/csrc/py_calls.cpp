@@ -7,6 +7,7 @@
 // address of its descriptor. The library is the one binding.py has loaded, found by path.
 #include <Python.h>
 #include <ATen/ATen.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
@@ -220,6 +221,32 @@ PyObject* kv_cache_append(PyObject* const* a) {
   return nothing();
 }
 
+// Scratch from torch's pool of the current stream, to which it goes back when the call has been enqueued; undefined where it
+// could cost the program more than the call gains. A request that the device cannot serve makes torch's allocator wait for
+// the device and give its cached blocks back, so memory has to be there with room to spare (asking takes 3 us). Under
+// capture the pool's blocks would be in use by the graph long after they went back. A capture of another thread or stream
+// is not touched: in relaxed mode this thread may ask the driver.
+at::Tensor spare_scratch(size_t bytes, const at::TensorOptions& on) {
+  if (c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) return {};
+  const c10::DeviceIndex device = c10::hip::current_device();
+  const double wanted = 2. * (double)bytes + (64 << 20);                  // the pool rounds up and takes whole segments
+  try {
+    c10::hip::HIPStreamCaptureModeGuard relaxed(hipStreamCaptureModeRelaxed);
+    size_t free = 0, total = 0;
+    if (hipMemGetInfo(&free, &total) != hipSuccess) {
+      (void)hipGetLastError();
+      return {};
+    }
+    if ((double)free < wanted) return {};
+    const double share = c10::hip::HIPCachingAllocator::getMemoryFraction(device);       // what the program has allowed itself
+    if (share < 1. && (double)c10::hip::HIPCachingAllocator::getDeviceStats(device).reserved_bytes[0].current + wanted > share * (double)total)
+      return {};
+    return at::empty({(int64_t)bytes}, on.dtype(at::kByte));
+  } catch (const c10::Error&) {                                           // another allocator, without these questions or this memory
+    return {};
+  }
+}
+
 // cache, q, b, q_pos0, scale, out, workspace
 PyObject* cross_attn_prefill(PyObject* const* a) {
   const yoco_kv_cache c = cache(a[0]);
@@ -230,19 +257,16 @@ PyObject* cross_attn_prefill(PyObject* const* a) {
   const at::Tensor o = output(a[5], q);
   Workspace w = workspace(a[6]);
   void *qp = dev(q, "q"), *op = dev(o, "o");
-  // Without a workspace: scratch from torch's pool of this stream, to which it goes back when the call has been enqueued.
-  // The call does without where there is none to be had, under capture, where the pool might have to ask the driver, and for
-  // queries of another device, whose pool knows nothing of the stream that the launches go to.
+  // Without a workspace a call that takes its output from torch's allocator takes scratch there, too, where that is to be had
+  // and the queries live where the launches go. One that is given its output allocates nothing.
   at::Tensor scratch;
   size_t useful = 0;
-  if (!w.p && p_yoco_cross_attn_prefill_workspace(&c, q_pos0, q.size(0), (int)q.size(1), scale, &useful) == 0 && useful &&
-      q.get_device() == c10::hip::current_device() &&
-      c10::hip::currentStreamCaptureStatusMayInitCtx() == c10::hip::CaptureStatus::None) {
-    try {
-      scratch = at::empty({(int64_t)useful}, q.options().dtype(at::kByte));
+  if (!w.p && none(a[5]) && q.get_device() == c10::hip::current_device() &&
+      p_yoco_cross_attn_prefill_workspace(&c, q_pos0, q.size(0), (int)q.size(1), scale, &useful) == 0 && useful) {
+    scratch = spare_scratch(useful, q.options());
+    if (scratch.defined()) {
       w.p = scratch.data_ptr();
       w.bytes = useful;
-    } catch (const c10::OutOfMemoryError&) {
     }
   }
   call([&] { return p_yoco_cross_attn_prefill(&c, qp, op, (int)b, q_pos0, q.size(0), (int)q.size(1), scale, w.p, w.bytes, stream()); });

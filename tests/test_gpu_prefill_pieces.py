@@ -1,6 +1,7 @@
 """Prefill over a cache with the keys of a query tile shared out over several workgroups, whose partial results a second
 launch merges, against the fp64 oracle."""
 import math
+import threading
 
 import numpy as np
 import pytest
@@ -127,6 +128,85 @@ def test_scratch_is_asked_for_where_it_is_of_use_and_bounded():
     assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 14001, 2000, 24, SCALE, C.byref(n)) != 0
     assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 9, SCALE, C.byref(n)) != 0
     assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 24, SCALE, None) != 0
+
+
+def _few_tiles(Tq=64, Hq=16, Hkv=2, N=4000):
+    """A call that is cut into pieces: cache, queries, their position and the scratch that the pieces take."""
+    cache = yoco.KVCache(1, Hkv, D, N, torch.bfloat16)
+    for i, p in enumerate(cache.planes()):
+        p.copy_(ys.device_normal(p.shape, i, 1.0, torch.bfloat16, "cuda"))
+    q = ys.device_normal((Tq, Hq, D), 2, 1.0, torch.bfloat16, "cuda")
+    nbytes = yoco.cross_attn_prefill_workspace(cache, N - Tq, Tq, Hq, SCALE)
+    assert plan(cache, N - Tq, Tq, Hq) > 1 and nbytes > 8 << 20
+    return cache, q, N - Tq, nbytes
+
+
+def _taken():
+    s = torch.cuda.memory_stats()
+    return s["allocation.all.allocated"], s["reserved_bytes.all.current"], s["num_ooms"], s["num_alloc_retries"]
+
+
+@pytest.mark.gpu
+def test_a_call_that_is_given_its_output_allocates_nothing():
+    cache, q, pos0, _ = _few_tiles()
+    o = torch.empty_like(q)
+    before = _taken()
+    assert yoco.cross_attn_prefill(cache, q, 0, pos0, SCALE, out=o) is o
+    assert _taken() == before
+    own = yoco.cross_attn_prefill(cache, q, 0, pos0, SCALE)
+    assert _taken()[0] == before[0] + 2                         # the output and the scratch
+    assert torch.allclose(o.float(), own.float(), atol=2e-3, rtol=2e-2)
+
+
+@pytest.mark.gpu
+def test_short_memory_costs_a_call_its_scratch_and_nothing_else():
+    cache, q, pos0, nbytes = _few_tiles()
+    whole = yoco.cross_attn_prefill(cache, q, 0, pos0, SCALE, out=torch.empty_like(q))
+    torch.cuda.empty_cache()
+    blocks = [torch.empty(512 << 10, dtype=torch.uint8, device="cuda") for _ in range(64)]
+    del blocks                                                  # cached in a pool of small blocks, where the scratch does not fit
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + nbytes // 2) / total)
+    try:
+        before = _taken()
+        o = yoco.cross_attn_prefill(cache, q, 0, pos0, SCALE)
+        after = _taken()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert after == (before[0] + 1,) + before[1:]               # the output alone; the cached blocks are still there
+    assert torch.equal(o, whole)
+
+
+@pytest.mark.gpu
+def test_scratch_leaves_the_capture_of_another_thread_alone():
+    cache, q, pos0, _ = _few_tiles()
+    side, own, x = torch.cuda.Stream(), [], torch.ones(1000, device="cuda")
+    with torch.cuda.stream(side):
+        ref = yoco.cross_attn_prefill(cache, q, 0, pos0, SCALE)
+        kept = ref.clone()
+        del ref
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()                                    # the next scratch is the driver's to give
+
+    def other():
+        with torch.cuda.stream(side):
+            own.append(yoco.cross_attn_prefill(cache, q, 0, pos0, SCALE))
+
+    with torch.cuda.stream(side):
+        room = torch.empty_like(q)                              # the next output is not
+    del room
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="global"):
+        y = x * 2
+        t = threading.Thread(target=other)
+        t.start()
+        t.join()
+        y = y + 1
+    for _ in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, torch.full_like(y, 3.0)) and torch.equal(own[0], kept)
 
 
 @pytest.mark.gpu
