@@ -177,8 +177,13 @@ int yoco_global_kv_write_scaled(const yoco_kv_cache* c, const void* k, const voi
  * head and 128 rows does not fill the chip, shares the keys of such a tile out
  * over several workgroups as far as the workspace holds their partial results
  * (yoco_cross_attn_prefill_workspace); a second launch merges them in a fixed
- * order. The result is the same operation either way, up to the order of fp32
- * sums. Calls that overlap in time must not share a workspace.
+ * order. The result is the same operation either way, and as far from exact
+ * arithmetic (1.67e-3 relative after the rounding to bf16), but not the same
+ * bits: softmax weights are rounded to fp16 against the largest score of a
+ * workgroup's keys, so that another number of workgroups takes other roundings
+ * (1e-3 apart as bf16). How many there are follows from the shape, the device
+ * and workspace_bytes alone; with those the same, a call repeats itself bit for
+ * bit. Calls that overlap in time must not share a workspace.
  * A bf16 cache with d = 128 and more than 8 rows runs on the same matrix-core
  * path as yoco_swa_prefill, with the same domain: cached |v| below 65504, and
  * |v| under 2^-14 read with an absolute error below 2^-25.

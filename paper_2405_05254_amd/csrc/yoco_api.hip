@@ -450,7 +450,7 @@ int yoco_cross_attn_prefill(const yoco_kv_cache* c, const void* q, void* o, int 
   a.k = (const char*)c->k + (size_t)b * seq_bytes;
   a.v = (const char*)c->v + (size_t)b * seq_bytes;
   if (yoco::swa_mfma_supported(a, c->dtype))
-    return hip_result(yoco::launch_swa_mfma(a, workspace, workspace_bytes, (hipStream_t)stream), "cross_attn_prefill");
+    return hip_result(yoco::launch_swa_mfma(a, Tq > kFewRows ? workspace : nullptr, workspace_bytes, (hipStream_t)stream), "cross_attn_prefill");
   if (yoco::attn_f32_supported(a)) return hip_result(yoco::launch_attn_f32(a, c->dtype, (hipStream_t)stream), "cross_attn_prefill");
   return hip_result(yoco::launch_attn_generic(a, c->dtype, (hipStream_t)stream), "cross_attn_prefill");
 }
