@@ -434,21 +434,21 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
 
 // How many pieces a call's query tiles are cut into. A workgroup's walk over the keys is serial, so a call with few
 // query tiles leaves the chip idle (64 rows x 16 heads over 24000 rows: 16 workgroups of 376 tiles each, 508 us; in 32 pieces
-// 46), and one whose workgroups are no multiple of the 512 places waits for the CUs that hold two (2000 rows x 24 heads over
-// 16000: 384 workgroups 457 us, in 4 pieces three full rounds, 423). The estimate is in us, from what was measured: a
+// 46), and one whose workgroups are no multiple of the places (two a CU) waits for the CUs that hold two (2000 rows x 24
+// heads over 16000: 384 workgroups 457 us, in 4 pieces three full rounds, 423). The estimate is in us, from what was measured: a
 // 64-key tile takes 1.34 where a CU has one workgroup, 1.6 where some have two and 2.15 where all have; 5 for a launch and
 // the two ends of a walk; a merge 5 and 0.016 for each piece's way out and back. 30 shapes of 16 to 4096 rows are within a
 // tenth of their best count by it. A cut has to promise a twentieth, because it costs memory.
 constexpr int kMaxPieces = 32;
 constexpr int64_t kMaxPieceWgs = 1536;         // bounds the partials at 102 MB
 float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
-  constexpr int64_t kCus = 256, kPlaces = 512;
+  const int64_t cus = compute_units(), places = 2 * cus;
   constexpr float kEnds = 5.f, kAlone = 1.34f, kSome = 1.6f, kAll = 2.15f, kMerge = 5.f, kPiece = 0.016f;
-  const int64_t wgs = items * pieces, full = wgs / kPlaces, rest = wgs % kPlaces;
-  auto tile = [&](int64_t n) { return n <= kCus ? kAlone : kSome + (kAll - kSome) * (float)(n - kCus) / (float)(kPlaces - kCus); };
+  const int64_t wgs = items * pieces, full = wgs / places, rest = wgs % places;
+  auto tile = [&](int64_t n) { return n <= cus ? kAlone : kSome + (kAll - kSome) * (float)(n - cus) / (float)(places - cus); };
   const float longest = ceilf((float)n_max / (float)pieces), mean = n_mean / (float)pieces;
   float t = (float)full * (mean * kAll + kEnds) + (rest ? mean * tile(rest) + kEnds : 0.f);
-  const float least = longest * tile(wgs < kPlaces ? wgs : kPlaces) + kEnds;
+  const float least = longest * tile(wgs < places ? wgs : places) + kEnds;
   if (t < least) t = least;
   return pieces > 1 ? t + kMerge + kPiece * (float)wgs : t;
 }

@@ -11,6 +11,17 @@
 
 #include "yoco_common.h"
 
+int yoco::compute_units() {
+  static const int cus = [] {                     // initialised once, thread-safe
+    int dev = 0, n = 0;
+    const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0;
+    (void)hipGetLastError();
+    return ok ? n : 256;                          // no device visible (host-only sizing): MI355X has 256 CUs
+  }();
+  return cus;
+}
+
 namespace {
 
 thread_local char g_err[256] = "";
@@ -84,13 +95,7 @@ struct Splits {
 };
 
 Splits decode_splits(const yoco_kv_cache* c, int Hq) {
-  static const int cus = [] {                     // initialised once, thread-safe
-    int dev = 0, n = 0;
-    const bool ok = hipGetDevice(&dev) == hipSuccess &&
-                    hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0;
-    (void)hipGetLastError();
-    return ok ? n : 256;                          // no device visible (host-only sizing): MI355X has 256 CUs
-  }();
+  const int cus = yoco::compute_units();
   const int64_t units = (int64_t)c->B * c->Hkv;
   auto clamp = [](int64_t s, int64_t hi) { return s > hi ? hi : s < 1 ? 1 : s; };
   const int64_t wanted = (cus + units - 1) / units;

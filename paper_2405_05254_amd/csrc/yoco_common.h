@@ -62,6 +62,8 @@ struct GretView {
   int group_norm;
 };
 
+int compute_units();      // CUs of the device that is current at the first call (a partition has a part of the chip's 256)
+
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_attn_generic(const AttnView& a, int dtype, hipStream_t s);
 // fp32 arithmetic on the matrix cores, head_dim 64 or 128 (attn_f32.hip).

@@ -5,6 +5,8 @@ before anything is launched."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -353,3 +355,21 @@ def test_a_refused_stack_step_has_launched_nothing():
     assert step(cache(17), states=(C.c_void_p * 2)(p, p), gret=1, eps=-1.0) == -1
     for missing in (dict(kv_ln=None), dict(w_kv=None)):                      # the row of the cache is projected without layers too
         assert step(cache(17), rings=(yb._Cache * 0)(), n_self=0, **missing) == -1
+
+
+def test_prefill_pieces_are_planned_for_the_device_there_is(tmp_path):
+    """128 query tiles leave half of a whole chip's 256 CUs idle and are cut; they fill a partition of 64 CUs, two each."""
+    src, shim = tmp_path / "partition.c", tmp_path / "partition.so"
+    src.write_text("int hipGetDevice(int* d) { *d = 0; return 0; }\n"
+                   "int hipDeviceGetAttribute(int* n, int attribute, int device) { *n = 64; return 0; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(shim), str(src)], check=True)
+    ask = """import ctypes as C, sys
+if sys.argv[1]: C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+from paper_2405_05254_amd import binding as yb
+c, n = yb._Cache(), C.c_size_t(1)
+assert yb.lib().yoco_kv_cache_init(1 << 40, 1 << 40, 1, 4, 128, 21024, 1, C.byref(c)) == 0
+assert yb.lib().yoco_cross_attn_prefill_workspace(C.byref(c), 20000, 1024, 16, 0.1, C.byref(n)) == 0
+print(n.value)"""
+    whole, part = (int(subprocess.run([sys.executable, "-c", ask, arg], cwd=ROOT, check=True, capture_output=True, text=True).stdout.split()[-1])
+                   for arg in ("", str(shim)))
+    assert whole > 0 and part == 0
