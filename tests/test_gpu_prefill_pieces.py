@@ -109,6 +109,31 @@ def test_under_capture_a_call_takes_no_scratch_of_its_own():
             assert torch.equal(o, want)
 
 
+def _desc(dtype, Hkv, N, d=D):
+    import ctypes as C
+
+    from paper_2405_05254_amd import binding as yb
+    c = yb._Cache()
+    assert yoco.lib().yoco_kv_cache_init(0x7f0000000000, yoco.kv_cache_bytes(1, Hkv, d, N, dtype), 1, Hkv, d, N, dtype, C.byref(c)) == 0
+    return c, C
+
+
+def test_scratch_is_asked_for_where_it_is_of_use_and_bounded():
+    L = yoco.lib()
+    for dtype, d, Hkv, Hq, pos0, Tq, want in [
+            (yoco.BF16, D, 8, 24, 14000, 2000, True), (yoco.BF16, D, 8, 24, 24000, 4096, True), (yoco.BF16, D, 1, 1, 500000, 9, True),
+            (yoco.BF16, D, 8, 24, 14000, 8, False),             # few rows use the decode workspace
+            (yoco.BF16, D, 8, 24, 0, 300, False), (yoco.BF16, D, 8, 64, 20000, 8192, False),
+            (yoco.F32, D, 8, 24, 14000, 2000, False), (yoco.BF16, 64, 8, 24, 14000, 2000, False), (yoco.INT8, D, 8, 24, 14000, 2000, False)]:
+        c, C = _desc(dtype, Hkv, pos0 + Tq, d)
+        n = C.c_size_t(1)
+        assert L.yoco_cross_attn_prefill_workspace(C.byref(c), pos0, Tq, Hq, SCALE, C.byref(n)) == 0
+        assert (n.value > 0) == want and n.value <= 1536 * PIECE, (pos0, Tq, n.value)
+    assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 14001, 2000, 24, SCALE, C.byref(n)) != 0
+    assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 9, SCALE, C.byref(n)) != 0
+    assert L.yoco_cross_attn_prefill_workspace(C.byref(c), 0, 2000, 24, SCALE, None) != 0
+
+
 def _few_tiles(Tq=64, Hq=16, Hkv=2, N=4000):
     """A call that is cut into pieces: cache, queries, their position and the scratch that the pieces take."""
     cache = yoco.KVCache(1, Hkv, D, N, torch.bfloat16)
