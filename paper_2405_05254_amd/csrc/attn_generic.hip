@@ -95,7 +95,7 @@ hipError_t launch_decode_generic(const yoco_kv_cache& c, const void* q, const in
 // thread (sl, dl) add splits sl, sl+nsl, ... for dimensions 4dl..4dl+3 with
 // independent 128-bit loads; the nsl partial sums are then added in order.
 // Assignment and order are fixed (no atomics): results are bit-reproducible.
-constexpr int kMaxSplits = 1024;
+constexpr int kMaxSplits = 256;        // no plan makes more
 
 template <typename T>
 __global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restrict__ ws, T* __restrict__ o, int d,
@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restri
   }
 }
 
-// The same, operation for operation, for d = 128 and up to 256 splits: one trip to memory. Every thread requests its share of
+// The same, operation for operation, for d = 128: one trip to memory. Every thread requests its share of
 // the vectors (8 N >= splits) together with the maxima and sums, which each wavefront reduces for itself; one barrier. The
 // launch is latency: 24 heads of 32 splits 3.9 -> 3.2 us in a chain of launches.
 template <typename T, int N>
@@ -204,7 +204,7 @@ __global__ void __launch_bounds__(256) decode_merge128_kernel(const float* __res
 
 template <typename T>
 void merge_launch(const float* ws, T* o, int d, int splits, dim3 grid, hipStream_t s) {
-  if (d != 128 || splits > 256) hipLaunchKernelGGL(decode_merge_kernel<T>, grid, dim3(256), 0, s, ws, o, d, splits);
+  if (d != 128) hipLaunchKernelGGL(decode_merge_kernel<T>, grid, dim3(256), 0, s, ws, o, d, splits);
   else if (splits <= 32) hipLaunchKernelGGL((decode_merge128_kernel<T, 4>), grid, dim3(256), 0, s, ws, o, splits);
   else if (splits <= 64) hipLaunchKernelGGL((decode_merge128_kernel<T, 8>), grid, dim3(256), 0, s, ws, o, splits);
   else hipLaunchKernelGGL((decode_merge128_kernel<T, 32>), grid, dim3(256), 0, s, ws, o, splits);

@@ -1,14 +1,14 @@
-// The end of a split-KV decode workgroup: merge its wavefronts, publish the split's partial result, and, where splits
-// and heads are few (decode_meets_in_launch), let the workgroup that finds every split of its (sequence, KV head)
-// published merge them. One launch per decode step then, which saves up to a microsecond and 3 us of host time against
-// a merge launch. That one workgroup's reading is a serial chain that grows with splits and heads, so the others are left
-// for a merge launch, a workgroup per query head.
+// The end of a split-KV decode workgroup: merge its wavefronts, publish the split's partial results, and, where splits
+// and heads are few (decode_meets_in_launch), merge the splits. A wavefront has every fourth head of the KV head to itself:
+// it publishes its split of them, and merges those of which it finds every split published. One launch per decode step
+// then, which saves up to a microsecond and 2.4 us of host time against a merge launch. That one wavefront's reading is
+// a serial chain that grows with splits and heads, so the others are left for a merge launch, a workgroup per query head.
 //
 // Nothing has to be cleared beforehand. A split is published by writing the call's tag (64 bits, never used twice by a
 // process, drawn around a random start) into the spare words of its partial; whoever sees all tags merges, and puts
-// zeros back, so that a captured launch can be replayed. A workgroup publishes before it looks, and both go to the
-// device-coherent level, so the last one to publish sees all tags; two that see them both write the same bits. No
-// workgroup waits for another.
+// zeros back, so that a captured launch can be replayed. A wavefront publishes before it looks, and both go to the
+// device-coherent level, so the last one to publish sees all tags; two that see them both write the same bits. None
+// waits for another.
 #pragma once
 #include "lanes.h"
 #include "yoco_common.h"
@@ -219,6 +219,7 @@ template <int GS>
 __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)[GS][128], float (*red_ml)[GS][2], int G, size_t head0, int sp,
                                              int S) {
   constexpr int kD = 128, kHeads = (GS + 3) / 4;             // heads of a wavefront
+  constexpr int kMeetHeads = kHeads < 2 ? kHeads : 2;        // where splits meet: at most 8 heads, of more than 4 at most 8 splits
   const size_t stride = partial_stride(kD);
   const size_t per_head = out.splits * stride;
   const bool whole = out.tag ? S <= 1 : out.splits <= 1;     // a single split is the whole answer
@@ -258,21 +259,21 @@ __device__ __forceinline__ void finish_split(const SplitOut& out, float (*red_o)
   if (whole || !out.tag) return;
   wait_stores();                                             // this wavefront's heads are visible to the whole device
   float* const tags = out.ws + (head0 + wave) * per_head + kD + 2;           // head i, split s: tags + 4 i * per_head + s * stride
-  if (lane < kHeads && wave + 4 * lane < G) put_u64(tags + 4 * lane * per_head + sp * stride, out.tag);
+  if (lane < kMeetHeads && wave + 4 * lane < G) put_u64(tags + 4 * lane * per_head + sp * stride, out.tag);
   wait_stores();
-  unsigned long long seen[kHeads];                           // of all of its heads in one trip
+  unsigned long long seen[kMeetHeads];                       // of all of its heads in one trip
 #pragma unroll
-  for (int i = 0; i < kHeads; ++i)
+  for (int i = 0; i < kMeetHeads; ++i)
     seen[i] = wave + 4 * i < G ? get_u64(tags + 4 * i * per_head + (lane < S ? lane : S - 1) * stride) : 0ull;
 #pragma unroll
-  for (int i = 0; i < kHeads; ++i) {
+  for (int i = 0; i < kMeetHeads; ++i) {
     if (wave + 4 * i >= G) break;
     if (__builtin_amdgcn_ballot_w64(seen[i] != out.tag)) continue;
     float* const t = tags + 4 * i * per_head;
     const float* const p = t - (kD + 2);
     bf16_t* const o = out.o + (head0 + wave + 4 * i) * kD;
     if (S <= 4) merge_head<4>(p, stride, S, o);
-    else if (S <= 8) merge_head<8>(p, stride, S, o);
+    else if (kMeetHeads > 1 || S <= 8) merge_head<8>(p, stride, S, o);
     else merge_head<kMeetSplits>(p, stride, S, o);
     if (lane < S) put_u64(t + lane * stride, 0ull);
   }

@@ -93,10 +93,9 @@ bool swa_mfma_supported(const AttnView& a, int dtype);
 size_t swa_mfma_workspace(const AttnView& a);
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s);
 bool decode_bf16_supported(const yoco_kv_cache& c, int Hq);
-// Where one decode launch also merges its splits (decode_tail.h): a workgroup reads them all, G / 4 heads one after
-// another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (in the launch
-// against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 6.7
-// and 7.2; 32 x 3 7.7 and 6.9; 32 x 4 7.9 and 6.8; 16 x 8 9.9 and 7.5), and a launch less on the host, 2.5 us.
+// Where one decode launch also merges its splits (decode_tail.h): a wavefront reads all splits of its G / 4 heads, one head
+// after another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (in the launch against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 6.7
+// and 7.2; 32 x 3 7.7 and 6.9; 32 x 4 7.9 and 6.8; 16 x 8 9.9 and 7.5), and a launch less on the host, 2.4 us.
 constexpr int kMeetSplits = 16;
 inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G <= 8 && (G + 3) / 4 * splits <= kMeetSplits); }
 // Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.
