@@ -297,6 +297,46 @@ def test_a_cache_without_rows_is_attended_to():
     assert close(got.float(), st.cross_decoder_decode(X[39:], cache, 0).float())
 
 
+@pytest.mark.parametrize("cap", [40, 64])
+@pytest.mark.parametrize("cache", ["bf16", "int8"])
+def test_steps_at_and_past_the_end_of_the_cache(cache, cap):
+    """The last row of the cache is stored; past it nothing is, and the rows there are attended to."""
+    import ctypes as C
+    st = small_stack("swa")
+    st.cache_dtype = torch.int8 if cache == "int8" else torch.bfloat16
+    toks = torch.from_numpy(ys.tokens(1, cap + 2, 200)).cuda()
+    logits, stored = [], []
+    for native in (True, False):
+        if not native:
+            st._native = None
+        assert (st._current() is not None) == native
+        state = st.new_generation_state(cap)
+        kv = state["cache"]
+        guarded = torch.full((kv.bytes + 8192,), 0xA5, dtype=torch.uint8, device="cuda")
+        kv.mem = guarded[4096:4096 + kv.bytes]
+        kv.mem.zero_()
+        assert yoco.lib().yoco_kv_cache_init(kv.mem.data_ptr(), kv.bytes, 1, 2, 128, cap, yoco.INT8 if cache == "int8" else yoco.BF16,
+                                             C.byref(kv.desc)) == 0
+        out = [st.prefill(toks[:cap - 1], state)]
+        before = kv.mem.clone()
+        for t in toks[cap - 1:]:
+            out.append(st.decode_step(t, state))
+            assert (guarded[:4096] == 0xA5).all() and (guarded[4096 + kv.bytes:] == 0xA5).all()
+            if len(out) == 2:
+                held = kv.mem.clone()
+                assert not torch.equal(held, before)
+            assert torch.equal(kv.mem, held)
+        if cache == "bf16":
+            rows = [p[:, :, :cap - 1] for p in kv.planes()]
+            kv.mem = before
+            assert all(torch.equal(a, b[:, :, :cap - 1]) for a, b in zip(rows, kv.planes()))
+        logits.append(torch.cat(out).double())
+        stored.append(held)
+    assert logits[0].shape == (4, 200) and close(*logits)
+    if cache == "bf16":
+        assert close(*(h.view(torch.bfloat16).double() for h in stored))
+
+
 @pytest.mark.parametrize("kind", ["swa", "gret"])
 def test_errors_against_64_bits_are_those_of_the_torch_ops(kind):
     """Both chains round the same thirty or so intermediates to bf16, so their errors against the fp64 oracle are two draws
