@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   const int64_t iw = i0 + wave * kNQ;                   // first row of the wavefront
   int64_t iq = iw + lq;
   const bool q_valid = iq < a.Tq;
-  const bool any_row = iw < a.Tq;                       // a wavefront without rows stages tiles and multiplies nothing
+  const bool any_row = iw < a.Tq;
   if (!q_valid) iq = a.Tq - 1;
   const bf16_t* qg = (const bf16_t*)a.q + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD;
   bf16x8 qf[8];
@@ -200,7 +200,9 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_o[mb][r] = 0.f;
 
-  const int pw_lo = (int)(p0 + wave * kNQ - (int64_t)jt_lo * kBN);      // wave's first position, relative to tile jt_lo
+  // wave's first position, relative to tile jt_lo; a wavefront without rows lies before all keys, so that it stages tiles and
+  // multiplies nothing
+  const int pw_lo = any_row ? (int)(p0 + wave * kNQ - (int64_t)jt_lo * kBN) : -(1 << 29);
   const int pq_rel0 = pw_lo + lq;                                        // this lane's query, same origin
   const int win32 = win > (1 << 30) ? (1 << 30) : (int)win;
 
@@ -227,7 +229,7 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
     const int jt = tile_of(st);
     const int j0r = (jt - jt_lo) * kBN;                 // tile's first key, relative origin
     // does some row of this wavefront see some key of the tile? / every row every key?
-    const bool need = any_row && (j0r <= pw_lo + kNQ - 1) && (j0r + kBN - 1 > pw_lo - win32);
+    const bool need = (j0r <= pw_lo + kNQ - 1) && (j0r + kBN - 1 > pw_lo - win32);
     const bool full = (j0r + kBN - 1 <= pw_lo) && (j0r > pw_lo + kNQ - 1 - win32);
     // the same for the two 32-key halves: on edge tiles a wavefront multiplies only the halves it needs
     const bool need0 = need && (j0r + 31 > pw_lo - win32);
