@@ -480,21 +480,31 @@ int pieces_for(const AttnView& a, int64_t room) {
 
 // Where walks differ much (their mean is under three quarters of the longest: causal attention over up to twice the window)
 // and the launch is a few rounds of the chip's places, the heavier query tiles go first over all heads of an XCD, so that it
-// ends in short walks everywhere: 8 x 1000 rows x 16 heads 74.1 -> 57.6 us, 4 x 1500 x 24:8 78.4 -> 74.7, 4096 rows x 24 heads
-// without a window 145 -> 127. But all of the XCD's KV heads are walked side by side then, and the fewer workgroups of one
-// are in flight, the less of its key tiles comes from the L2: 59 x 1900 x 24 heads 1551 us one KV head after another,
-// 2174 heavier first; 12 x 700 x 24 89 and 89, 20 x 700 137 and 151 (two rounds gain all the same: 9 x 500 46.4 and 40.3);
-// 16 x 4096 x 24 without a window 2051 and 2343. In a long launch the end matters less, too (40 heads x 16384 rows, ten
-// rounds, 2901 and 2958; 24 x 24576, nine, 4008 and 3977).
-// Where two or three query heads share a KV head that share is smaller already (24:8: 8 x 1000 rows 91.6 and 83.3, 18 x
-// 1000 188 and 188, 12 x 1500 223 and 228, 28 x 300 59.2 and 61.9), and of four and more as much is lost as is won (32:8: 4 x
-// 1000 62.9 and 56.9, 8 x 1000 108 and 112, 9 x 1900 297 and 312).
+// ends in short walks everywhere: 8 x 1000 rows x 16 heads 69.4 -> 56.4 us, 4 x 1500 x 24:8 77.1 -> 74.3, 4096 rows x 24 heads
+// without a window 145 -> 127, 3 x 1300 x 32:8 73.3 -> 63.8. But all of the XCD's KV heads are walked side by side then, and
+// the fewer workgroups of one are in flight, the less of its key tiles comes from the L2 (one KV head after another, heavier
+// first, us): 59 x 1900 x 24 heads 1551 and 2174, 12 x 700 x 24 77 and 83, 14 x 1100 x 40 277 and 342, 16 x 4096 x 24 without a
+// window 2051 and 2343. In a longer launch the end matters less, too: 8 x 3000 x 24, nine rounds, 503 and 524. Query tiles in
+// fours gain for longer (12 x 500 x 24 61.3 and 52.7, 6 x 1000 x 40 118 and 109): dealt out head after head, the heavier ones
+// of all heads meet on the same CUs.
+// Where two or three query heads share a KV head more of its workgroups are in flight already: 24:8, 8 x 1000 86.3 and 79.1,
+// 10 x 1000, four rounds, 104 and 101, but 12 x 700, three and a half, 72.5 and 75.3. From four on there is a gain in the first
+// round, where the order says which two share a CU (64:8, 2 x 300 16.5 and 14.5; nine and more heads: none), and in a second
+// one of several KV heads an XCD (32:8: 4 x 1000 60.1 and 53.6, 8 x 1000, four rounds, 103 and 106; 16:4, 4 x 1500, two KV heads,
+// 49.5 and 51.7).
+// A head of three query tiles is left alone where it fills one and a half rounds (12 x 300 x 24 29.6 and 33.0) or nearly one
+// (6 x 300 x 24 17.2 and 18.6; 8 x 300, one and an eighth, 26.0 and 24.5), and so is a launch whose workgroups have a CU each.
 // Elsewhere one KV head follows another (32768 rows x 24 heads 553 us, heavier first 558; 2 x 4000, window 512, 81.8 and 84.2).
 int heavy_heads_for(const AttnView& a, int n_qtiles) {
-  const int64_t kv_heads = (int64_t)a.B * a.Hkv, wgs = (int64_t)n_qtiles * a.B * a.Hq;
+  const int64_t kv_heads = (int64_t)a.B * a.Hkv, wgs = (int64_t)n_qtiles * a.B * a.Hq, places = 2 * compute_units();
   const int group = a.Hq / a.Hkv;
-  if (kv_heads % 8 || group > 3 || n_qtiles > 256) return 0;
-  if (group == 1 ? wgs > 4608 || (kv_heads > 192 && wgs > 1024) : wgs > 2048 || kv_heads > 128) return 0;
+  if (kv_heads % 8 || n_qtiles > 256 || 2 * wgs <= places) return 0;
+  if (n_qtiles <= 3 && (2 * wgs > 3 * places || (16 * wgs > 13 * places && wgs <= places))) return 0;
+  const bool few = group == 1    ? wgs <= 2 * places || (kv_heads <= 192 && wgs <= 7 * places) || (n_qtiles % 4 == 0 && wgs <= 3 * places)
+                   : group <= 3  ? kv_heads <= 128 && (wgs <= 3 * places || (n_qtiles >= 8 && wgs <= 4 * places))
+                   : wgs <= places ? group <= 8 && kv_heads >= 16
+                                   : group <= 7 && kv_heads >= 24 && kv_heads <= 64 && 8 * wgs <= 17 * places;
+  if (!few) return 0;
   int64_t sum = 0, longest = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {
     const Tiles t = tiles_of(a, qt);

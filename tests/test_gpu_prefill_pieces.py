@@ -63,7 +63,7 @@ def test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, pieces):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,T,Hq,Hkv,window", [
-    (1, 700, 8, 8, 1024),        # a head per XCD
+    (1, 700, 8, 8, 1024),        # a head per XCD, a CU per query tile
     (4, 333, 6, 2, 200),         # grouped heads, windows shorter than the prompt
     (8, 130, 3, 1, 4000),
     (2, 129, 32, 4, 1),          # walks of one length: one KV head after another
@@ -74,6 +74,9 @@ def test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, pieces):
     (5, 900, 12, 6, 1024),       # 30 KV heads: not shared evenly; two query heads on each of 32
     (4, 900, 16, 8, 1024),
     (2, 800, 32, 8, 1024),       # four on each: one KV head after another
+    (3, 700, 32, 8, 1024),       # ... but not where an XCD has three KV heads
+    (2, 2500, 16, 16, 3000),     # long walks, more of them than CUs
+    (6, 300, 24, 24, 1024),      # three query tiles a head that fill nearly a round
 ])
 def test_window_prefill_whichever_tiles_go_first(B, T, Hq, Hkv, window):
     rng = np.random.default_rng(T)
