@@ -149,9 +149,10 @@ __global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restri
   }
 }
 
-// The same, operation for operation, for d = 128: one trip to memory. Every thread requests its share of
-// the vectors (8 N >= splits) together with the maxima and sums, which each wavefront reduces for itself; one barrier. The
-// launch is latency: 24 heads of 32 splits 3.9 -> 3.2 us in a chain of launches.
+// The same, operation for operation, for d = 128: one trip to memory. Every thread requests its share of the vectors (8 N >=
+// splits) together with the maxima and sums, which each wavefront reduces for itself; one barrier. The launch is latency: 24
+// heads of 32 splits take 3.2 us of a chain of launches, 3.9 with the kernel above (a kernel trace, which counts the start and
+// the end that a chain overlaps, has 4.7).
 template <typename T, int N>
 __global__ void __launch_bounds__(256) decode_merge128_kernel(const float* __restrict__ ws, T* __restrict__ o, int splits) {
   constexpr int kD = 128, kRounds = (8 * N + 63) / 64;
