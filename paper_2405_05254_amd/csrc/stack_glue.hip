@@ -32,40 +32,148 @@ __device__ __forceinline__ float block_total(float x, float* red) {     // 256 t
 }
 __device__ __forceinline__ float swish(float g) { return g / (1.f + __expf(-g)); }
 
-// ---- y = W x for one row x. W is [N][K] (a row per output), so a wavefront owns kRows outputs and its lanes run along
+// ---- y = W x for one row x. W is [N][K] (a row per output), so a wavefront owns ROWS outputs and its lanes run along
 // K with 128-bit loads. GLU: output n takes rows n and N + n (the two halves of W): swish(first) * second.
-enum Epilogue { kPlain, kResidual, kGlu };
-constexpr int kStep = 2048;                       // elements of K per trip: 4 loads of 16 bytes per lane and row
-
 // Args: GemvArgs, or GemvPair for two matrices, the second's workgroups behind the first's (N is a multiple of a workgroup's
 // outputs).
+enum Epilogue { kPlain, kResidual, kGlu };
+
+// The rows of W that a wavefront takes; `g` becomes the matrix that its workgroup belongs to.
+template <int ROWS, Epilogue EPI, typename Args>
+struct OwnRows {
+  static constexpr bool kPair = std::is_same<Args, GemvPair>::value;
+  static constexpr int NR = EPI == kGlu ? 2 * ROWS : ROWS;
+  const bf16_t* w[NR];
+  int row0;
+  bool second;
+  __device__ __forceinline__ explicit OwnRows(Args& g) {
+    row0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * ROWS;
+    second = false;
+    if constexpr (kPair) {
+      second = (int)blockIdx.x * 4 * ROWS >= g.N;
+      if (second) {
+        row0 -= g.N;
+        g.gain = g.gain2;
+        g.W = g.W2;
+        g.out = g.out2;
+        g.n_plain = g.N = g.N2;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      int row = row0 + (EPI == kGlu ? r >> 1 : r);
+      row = row < g.N ? row : g.N - 1;                                       // surplus rows repeat the last one, nothing is stored
+      if (EPI == kGlu && (r & 1)) row += g.N;
+      w[r] = (const bf16_t*)g.W + (int64_t)row * g.K;
+    }
+  }
+  // Stores the outputs; acc: the rows' products, summed over the wavefront here. res: of this lane's output, where one is added.
+  __device__ __forceinline__ void store(const Args& g, float (&acc)[NR], float res) const {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[r] = over64<LaneSum>(acc[r]);
+    bf16_t* out = (bf16_t*)g.out;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const int n = row0 + r;
+      if (lane != r || n >= g.N) continue;
+      if (EPI == kGlu) {
+        out[n] = f32_to_bf16(round_bf16(swish(round_bf16(acc[2 * r]))) * round_bf16(acc[2 * r + 1]));
+      } else if (EPI == kResidual) {
+        out[n] = f32_to_bf16(round_bf16(acc[r]) + res);
+      } else if (n >= g.n_plain) {                                           // ln(gamma) of Eq. 4: logsigmoid(x W_gamma) / tau, fp32
+        const float a = acc[r];
+        g.log_gamma[n - g.n_plain] = (fminf(a, 0.f) - log1pf(__expf(-fabsf(a)))) * g.inv_tau;
+      } else {
+        bf16_t* to = out + n;
+        if constexpr (kPair) {
+          const int heads = g.N >> 8, head = n >> 7;
+          if (!second && g.k_row) to = (bf16_t*)(head < heads ? g.k_row : g.v_row) + (head < heads ? head : head - heads) * g.head_stride + (n & 127);
+        }
+        *to = f32_to_bf16(acc[r]);
+      }
+    }
+  }
+  __device__ __forceinline__ float residual(const Args& g) const {
+    const int lane = threadIdx.x & 63;
+    return EPI == kResidual && lane < ROWS && row0 + lane < g.N ? bf16_to_f32(((const bf16_t*)g.res)[row0 + lane]) : 0.f;
+  }
+};
+
+__device__ __forceinline__ float square(const u32x4& v, float ss) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ss = fmaf(lo_f(v[i]), lo_f(v[i]), fmaf(hi_f(v[i]), hi_f(v[i]), ss));
+  return ss;
+}
+__device__ __forceinline__ u32x4 normed(const u32x4& v, float rstd, const u32x4& gain) {
+  u32x4 y;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) y[i] = pack_bf16(lo_f(v[i]) * rstd * lo_f(gain[i]), hi_f(v[i]) * rstd * hi_f(gain[i]));
+  return y;
+}
+__device__ __forceinline__ float dot(const u32x4& w, const u32x4& x, float acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc = dot2(w[i], x[i], acc);
+  return acc;
+}
+
+// 16 bytes of a row in memory that every lane reads from, zeros behind its end; AUX: cache policy of the load.
+constexpr int kNontemporal = 2;
+template <int AUX>
+__device__ __forceinline__ u32x4 row_load(const void* row, unsigned bytes, int at) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)row, 0, bytes, 0x00027000);
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, AUX));
+}
+
+// Rows of up to CH * 512 elements: every wavefront holds the input row itself, a lane the 8 CH elements that its weights
+// meet, and norms it itself. With the row in LDS (below) the workgroup's wavefronts wait for one another twice between the first
+// load and the first product, in a launch that is over in a few microseconds. The input is requested before the weights (loads
+// return in order), all of them at once.
+template <int CH, int ROWS, bool NORM, Epilogue EPI, typename Args>
+__global__ void __launch_bounds__(256) gemv_short_kernel(Args g) {
+  const OwnRows<ROWS, EPI, Args> own(g);
+  constexpr int NR = OwnRows<ROWS, EPI, Args>::NR;
+  const int at = (threadIdx.x & 63) * 16;
+  const unsigned bytes = (unsigned)g.K * 2u;
+  u32x4 x[CH], gain[NORM ? CH : 1], w[NR][CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) x[c] = row_load<0>(g.x, bytes, at + c * 1024);
+  if (NORM)
+#pragma unroll
+    for (int c = 0; c < CH; ++c) gain[c] = row_load<0>(g.gain, bytes, at + c * 1024);
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int c = 0; c < CH; ++c) w[r][c] = row_load<kNontemporal>(own.w[r], bytes, at + c * 1024);
+  const float res = own.residual(g);
+  if (NORM) {
+    float ss = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) ss = square(x[c], ss);
+    const float rstd = rsqrtf(over64<LaneSum>(ss) / (float)g.K + g.eps);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) x[c] = normed(x[c], rstd, gain[c]);
+  }
+  float acc[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    acc[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) acc[r] = dot(w[r][c], x[c], acc[r]);
+  }
+  own.store(g, acc, res);
+}
+
+constexpr int kStep = 2048;                       // elements of K per trip: 4 loads of 16 bytes per lane and row
+
+// Longer rows: the input row lies in LDS, and the weights come in trips, the next one in flight.
 template <int ROWS, bool NORM, Epilogue EPI, typename Args>
 __global__ void __launch_bounds__(256) gemv_kernel(Args g) {
-  constexpr bool kPair = std::is_same<Args, GemvPair>::value;
-  constexpr int NR = EPI == kGlu ? 2 * ROWS : ROWS;
+  constexpr int NR = OwnRows<ROWS, EPI, Args>::NR;
   extern __shared__ __attribute__((aligned(16))) unsigned char x_lds[];      // the input row (normalised), bf16
   __shared__ float red[4];
   const int tid = threadIdx.x, lane = tid & 63;
-  int row0 = (blockIdx.x * 4 + (tid >> 6)) * ROWS;
-  bool second = false;
-  if constexpr (kPair) {
-    second = (int)blockIdx.x * 4 * ROWS >= g.N;
-    if (second) {
-      row0 -= g.N;
-      g.gain = g.gain2;
-      g.W = g.W2;
-      g.out = g.out2;
-      g.n_plain = g.N = g.N2;
-    }
-  }
-  const bf16_t* wp[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    int row = row0 + (EPI == kGlu ? r >> 1 : r);
-    row = row < g.N ? row : g.N - 1;                                         // surplus rows repeat the last one, nothing is stored
-    if (EPI == kGlu && (r & 1)) row += g.N;
-    wp[r] = (const bf16_t*)g.W + (int64_t)row * g.K;
-  }
+  const OwnRows<ROWS, EPI, Args> own(g);
   u32x4 w[NR][4];
   auto load = [&](int k0) {
 #pragma unroll
@@ -74,7 +182,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(Args g) {
       for (int c = 0; c < 4; ++c) {
         const int k = k0 + c * 512 + lane * 8;
         w[r][c] = u32x4{0, 0, 0, 0};
-        if (k < g.K) w[r][c] = __builtin_nontemporal_load((const u32x4*)(wp[r] + k));
+        if (k < g.K) w[r][c] = __builtin_nontemporal_load((const u32x4*)(own.w[r] + k));
       }
   };
   // The input row is requested before the weights (loads return in order): its norm is formed while they arrive.
@@ -93,11 +201,6 @@ __global__ void __launch_bounds__(256) gemv_kernel(Args g) {
   }
   load(0);
 
-  auto square = [](const u32x4& v, float ss) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ss = fmaf(lo_f(v[i]), lo_f(v[i]), fmaf(hi_f(v[i]), hi_f(v[i]), ss));
-    return ss;
-  };
   float rstd = 0.f;
   if (NORM) {
     float ss = 0.f;
@@ -106,14 +209,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(Args g) {
     for (int p = tid + kKeep * 256; p < pieces; p += 256) ss = square(xp[p], ss);
     rstd = rsqrtf(block_total(ss, red) / (float)g.K + g.eps);
   }
-  auto put = [&](int p, const u32x4& v, const u32x4& gn) {
-    u32x4 y = v;
-    if (NORM) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) y[i] = pack_bf16(lo_f(v[i]) * rstd * lo_f(gn[i]), hi_f(v[i]) * rstd * hi_f(gn[i]));
-    }
-    ((u32x4*)x_lds)[p] = y;
-  };
+  auto put = [&](int p, const u32x4& v, const u32x4& gn) { ((u32x4*)x_lds)[p] = NORM ? normed(v, rstd, gn) : v; };
 #pragma unroll
   for (int i = 0; i < kKeep; ++i)
     if (tid + i * 256 < pieces) put(tid + i * 256, xv[i], gv[i]);
@@ -136,35 +232,11 @@ __global__ void __launch_bounds__(256) gemv_kernel(Args g) {
       if (p < pieces) {
         const u32x4 x = ((const u32x4*)x_lds)[p];
 #pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[r] = dot2(cur[r][c][i], x[i], acc[r]);
+        for (int r = 0; r < NR; ++r) acc[r] = dot(cur[r][c], x, acc[r]);
       }
     }
   }
-#pragma unroll
-  for (int r = 0; r < NR; ++r) acc[r] = over64<LaneSum>(acc[r]);
-  bf16_t* out = (bf16_t*)g.out;
-#pragma unroll
-  for (int r = 0; r < ROWS; ++r) {
-    const int n = row0 + r;
-    if (lane != r || n >= g.N) continue;
-    if (EPI == kGlu) {
-      out[n] = f32_to_bf16(round_bf16(swish(round_bf16(acc[2 * r]))) * round_bf16(acc[2 * r + 1]));
-    } else if (EPI == kResidual) {
-      out[n] = f32_to_bf16(round_bf16(acc[r]) + bf16_to_f32(((const bf16_t*)g.res)[n]));
-    } else if (n >= g.n_plain) {                                             // ln(gamma) of Eq. 4: logsigmoid(x W_gamma) / tau, fp32
-      const float a = acc[r];
-      g.log_gamma[n - g.n_plain] = (fminf(a, 0.f) - log1pf(__expf(-fabsf(a)))) * g.inv_tau;
-    } else {
-      bf16_t* to = out + n;
-      if constexpr (kPair) {
-        const int heads = g.N >> 8, head = n >> 7;
-        if (!second && g.k_row) to = (bf16_t*)(head < heads ? g.k_row : g.v_row) + (head < heads ? head : head - heads) * g.head_stride + (n & 127);
-      }
-      *to = f32_to_bf16(acc[r]);
-    }
-  }
+  own.store(g, acc, own.residual(g));
 }
 
 // ---- prompts: the row-wise passes between the matrix products. One workgroup per row.
@@ -216,25 +288,41 @@ __global__ void __launch_bounds__(256) glu_rows_kernel(const u32x4* __restrict__
   }
 }
 
-template <int ROWS, bool NORM, Epilogue EPI, typename Args>
+template <int CH, int ROWS, bool NORM, Epilogue EPI, typename Args>
+hipError_t launch_short(const Args& g, dim3 grid, hipStream_t s) {
+  hipLaunchKernelGGL((gemv_short_kernel<CH, ROWS, NORM, EPI, Args>), grid, dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+// SHORT_ROWS, ROWS: outputs per wavefront where the input row is held in registers, and where it lies in LDS. Held in registers up
+// to 2048 elements behind a norm and up to 6144 without one; us, in LDS before and now:
+//   2048 x 2048 (8 MB) + residual 3.9 and 3.4, 2048 x 5632 6.2 and 6.0, 1024 x 5632 5.0 and 4.1; SwiGLU 2 x 5632 x 2048 (46 MB)
+//   9.7 and 9.2, 2 x 2816 x 1024 4.9 and 4.0; 6144 x 2048 6.5 and 6.0, 2048 x 2048 4.15 and 3.6; 32000 x 2048 (131 MB) 21.2 and
+//   20.9, 32000 x 1024 13.3 and 11.2. (A launch that does nothing takes 2.3, a plain read of 8, 23 and 46 MB 3.1, 5.0 and 8.3.)
+// Beyond: 3072 x 3072 5.5 and 6.0, SwiGLU 2 x 8448 x 3072 18.0 and 18.5; 2048 x 8192 + residual 8.2 and 8.3.
+template <int SHORT_ROWS, int ROWS, bool NORM, Epilogue EPI, typename Args>
 hipError_t launch(const Args& g, int rows, hipStream_t s) {
-  const int per_wg = 4 * ROWS;
-  hipLaunchKernelGGL((gemv_kernel<ROWS, NORM, EPI, Args>), dim3((unsigned)((rows + per_wg - 1) / per_wg)), dim3(256), (unsigned)g.K * 2u, s, g);
+  const dim3 grid((unsigned)((rows + 4 * SHORT_ROWS - 1) / (4 * SHORT_ROWS)));
+  if (g.K <= 1024) return launch_short<2, SHORT_ROWS, NORM, EPI>(g, grid, s);
+  if (g.K <= 2048) return launch_short<4, SHORT_ROWS, NORM, EPI>(g, grid, s);
+  if constexpr (!NORM) {
+    if (g.K <= 3072) return launch_short<6, SHORT_ROWS, NORM, EPI>(g, grid, s);
+    if (g.K <= 6144) return launch_short<12, SHORT_ROWS, NORM, EPI>(g, grid, s);
+  }
+  hipLaunchKernelGGL((gemv_kernel<ROWS, NORM, EPI, Args>), dim3((unsigned)((rows + 4 * ROWS - 1) / (4 * ROWS))), dim3(256), (unsigned)g.K * 2u, s, g);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// One output per wavefront (two for the classifier, whose outputs are tens of workgroups per CU anyway): more wavefronts
-// with less each measured faster down the line, with 2 / 1 outputs 6.9 / 6.3 us for 2048 x 5632 (23 MB), 4.3 / 4.0 us for
-// 2048 x 2048; 6144 x 2048 6.9 us, SwiGLU 2 x 5632 x 2048 (46 MB) 10.5 us, 32000 x 2048 (131 MB) 22.5 us: 3.2 us per
-// launch plus the bytes at 6.1 TB/s.
+// One output per wavefront where something is added or gated (two measured slower: 2048 x 5632 5.8 us and 5.7, SwiGLU 9.75 and
+// 9.4), else two where the row is short (6144 x 2048 6.2 and 6.65 with one) or the classifier's outputs are tens of
+// workgroups per CU anyway.
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
   if (g.K % 8 || g.K > kGemvMaxK || g.K <= 0 || g.N <= 0) return hipErrorInvalidValue;
-  if (g.glu) return launch<1, true, kGlu>(g, g.N, s);
-  if (g.res) return launch<1, false, kResidual>(g, g.N, s);
-  if (g.N >= 16384) return launch<2, true, kPlain>(g, g.N, s);
-  return launch<1, true, kPlain>(g, g.N, s);
+  if (g.glu) return launch<1, 1, true, kGlu>(g, g.N, s);
+  if (g.res) return launch<1, 1, false, kResidual>(g, g.N, s);
+  if (g.N >= 16384) return launch<2, 2, true, kPlain>(g, g.N, s);
+  return launch<2, 1, true, kPlain>(g, g.N, s);
 }
 
 // A token's row of the global cache and the first cross-decoder layer's queries. At 4 + 4 layers 43 launches of a step
@@ -242,7 +330,7 @@ hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
 // its own (42).
 hipError_t launch_gemv_pair(const GemvPair& g, hipStream_t s) {
   if (g.K % 8 || g.K > kGemvMaxK || g.K <= 0 || g.N <= 0 || g.N % 256 || g.n_plain != g.N || g.N2 <= 0 || g.res || g.glu) return hipErrorInvalidValue;
-  return launch<1, true, kPlain>(g, g.N + g.N2, s);
+  return launch<2, 1, true, kPlain>(g, g.N + g.N2, s);
 }
 
 hipError_t launch_norm_rows(const void* x, const void* add, void* y, const void* gain, void* xn, int64_t rows, int dim, float eps, hipStream_t s) {

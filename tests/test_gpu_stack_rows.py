@@ -1,0 +1,50 @@
+"""The token step's matrix-vector kernels where one form gives way to the next: input rows held in registers up to 1024, 2048, 3072
+and 6144 elements and in LDS beyond, outputs that are no multiple of a workgroup's, against the same stack as torch ops."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2405_05254_amd as yoco  # noqa: E402,F401
+
+pytestmark = pytest.mark.gpu
+
+
+def random_stack(Hq, dm, ffn, vocab):
+    gen = torch.Generator(device="cuda").manual_seed(dm + ffn)
+
+    def mat(*shape):
+        return (torch.randn(shape, device="cuda", generator=gen) / shape[0] ** 0.5).bfloat16()
+
+    def gain():
+        return (1 + 0.2 * torch.randn(dm, device="cuda", generator=gen)).bfloat16()
+    qd = 128 * Hq
+
+    def rest():
+        return dict(ln1=gain(), ln2=gain(), W_Q=mat(dm, qd), W_O=mat(qd, dm), W_G=mat(dm, ffn), W_1=mat(dm, ffn), W_2=mat(ffn, dm))
+    return dict(Hq=Hq, Hkv_self=Hq, Hkv=Hq, d=128, window=64, eps=1e-6, embed=mat(vocab, dm), final_ln=gain(), W_out=mat(dm, vocab),
+                self=[dict(W_K=mat(dm, qd), W_V=mat(dm, qd), **rest())], kv=dict(ln=gain(), W_K=mat(dm, qd), W_V=mat(dm, qd)), cross=[rest()])
+
+
+@pytest.mark.parametrize("Hq,dm,ffn,vocab", [
+    (1, 8, 8, 1),                  # one piece of a row, one output
+    (8, 1024, 3072, 1001),         # the last element that each form takes
+    (9, 1032, 3080, 1003),         # and one piece more
+    (16, 2048, 6144, 16387),
+    (17, 2056, 6152, 97),
+])
+def test_token_steps_where_the_kernels_change(Hq, dm, ffn, vocab):
+    import copy
+
+    from paper_2405_05254_amd.stack import YocoStack
+    w = random_stack(Hq, dm, ffn, vocab)
+    logits = []
+    for native in (True, False):
+        st = YocoStack(copy.deepcopy(w), torch.bfloat16, glue_dtype=torch.bfloat16)
+        assert st._native is not None
+        if not native:
+            st._native = None
+        state = st.new_generation_state(20)
+        toks = torch.arange(20, device="cuda") % vocab
+        logits.append(torch.cat([st.prefill(toks[:15], state)] + [st.decode_step(t, state) for t in toks[15:]]).double())
+    got, ref = logits
+    assert ((got - ref).norm() / ref.norm()).item() < 1.5e-2         # bf16 roundings that fall the other way, over four layer halves
