@@ -92,11 +92,12 @@ __device__ __forceinline__ void step(State<G>& st, const u32x4 (&kq)[G], const u
 // The call also stores the new token's K/V row (k_new, v_new: [B,Hkv,128]) at slot lens[b] - 1 (modulo
 // the capacity for a rolling cache) and attends to it. The row is taken from registers wherever the stream
 // meets its slot, so nothing is read back that this launch writes.
-template <int G, int R>
+template <int G, int R, typename... Ahead>
 __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                           const int64_t* __restrict__ lens, int64_t fixed_len, int Hq, float scale_log2,
                                                           SplitOut out, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
-                                                          int ring) {
+                                                          int ring, Ahead... ahead) {
+  if (has_read_ahead(out.splits, ahead...)) return;
   constexpr int kRowsPerStep = 4 * R;
   __shared__ float red_o[4][G][kD];
   __shared__ float red_ml[4][G][2];
@@ -289,11 +290,12 @@ __device__ __forceinline__ void mfma_softmax_pv(MState& st, const float (&s)[8],
   }
 }
 
-template <bool APPEND, int GMAX>
+template <bool APPEND, int GMAX, typename... Ahead>
 __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                                const int64_t* __restrict__ lens, int64_t fixed_len, int Hq,
                                                                float scale_log2, SplitOut out, const bf16_t* __restrict__ k_new,
-                                                               const bf16_t* __restrict__ v_new, int ring) {
+                                                               const bf16_t* __restrict__ v_new, int ring, Ahead... ahead) {
+  if (has_read_ahead(out.splits, ahead...)) return;
   // V staging of the four wavefronts (4 x 32 rows x 288 B), and the merge buffers beside it: a wavefront that is done writes
   // its state without waiting for the others (13 layers over 16 ragged sequences of up to 1000 rows 145.6 -> 142.5 us)
   constexpr int kStageBytes = kMRows * kVStride;
@@ -436,27 +438,27 @@ bool decode_bf16_supported(const yoco_kv_cache& c, int Hq) {
 // against 40.9; at 3 heads per KV head, 2 x 8 x 2048 rows, 11.6 against 10.2 the other way round).
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
                               float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
-                              hipStream_t s) {
+                              const ReadAhead& ahead, hipStream_t s) {
   const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, even, places, tag};
-  dim3 grid(c.Hkv, c.B, splits), block(256);
+  const dim3 grid(c.Hkv, c.B, splits + more_rows(c, ahead.workgroups)), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;
   const bf16_t* kn = (const bf16_t*)k_new;
   const bf16_t* vn = (const bf16_t*)v_new;
   const int G = Hq / c.Hkv;
   if (G < 1 || G > kGMax || splits > kMaxDecodeSplits || (tag && !decode_meets_in_launch(G, splits))) return hipErrorInvalidValue;
-  if (!kn) {
-    if (G <= 4) hipLaunchKernelGGL((decode_bf16_mfma_kernel<false, 4>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
-    else hipLaunchKernelGGL((decode_bf16_mfma_kernel<false, kGMax>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
-    return hipGetLastError();
-  }
-  switch (G) {
-    case 1: hipLaunchKernelGGL((decode_bf16_kernel<1, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring); break;
-    case 2: hipLaunchKernelGGL((decode_bf16_kernel<2, 8>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring); break;
-    default:
-      if (G <= 4) hipLaunchKernelGGL((decode_bf16_mfma_kernel<true, 4>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
-      else hipLaunchKernelGGL((decode_bf16_mfma_kernel<true, kGMax>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring);
-  }
+  auto launch = [&](auto... more) {
+    auto go = [&](auto* kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, kn, vn, ring, more...); };
+    if (!kn) {
+      if (G <= 4) go(&decode_bf16_mfma_kernel<false, 4, decltype(more)...>);
+      else go(&decode_bf16_mfma_kernel<false, kGMax, decltype(more)...>);
+    } else if (G == 1) go(&decode_bf16_kernel<1, 8, decltype(more)...>);
+    else if (G == 2) go(&decode_bf16_kernel<2, 8, decltype(more)...>);
+    else if (G <= 4) go(&decode_bf16_mfma_kernel<true, 4, decltype(more)...>);
+    else go(&decode_bf16_mfma_kernel<true, kGMax, decltype(more)...>);
+  };
+  if (ahead.workgroups) launch(ahead);
+  else launch();
   return hipGetLastError();
 }
 

@@ -211,6 +211,41 @@ __device__ __forceinline__ void merge_head(const float* p, size_t stride, int S,
   *(unsigned*)(o + e) = (unsigned)f32_to_bf16(a * inv) | ((unsigned)f32_to_bf16(b * inv) << 16);
 }
 
+// What the workgroups behind those of the splits do: read weights that the next launches will stream, so that these find them in
+// the L2 of their XCD. A decode step over a short cache is latency and leaves most of the bandwidth idle. Workgroups are dealt to
+// the 8 XCDs round robin, of this launch as of the next: piece i goes to an XCD that has workgroup i of the launch that reads it.
+__device__ __forceinline__ void read_ahead(const ReadAhead& w, int splits) {
+  const int before = gridDim.x * gridDim.y * splits, all = gridDim.x * gridDim.y * gridDim.z;
+  const int me = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  const int first = (me & 7) + 8 * ((me - before) >> 3), step = (all - before) & ~7;
+  for (int m = 0; m < 2; ++m)
+    for (int i = first; i < w.part[m].pieces; i += step)
+      for (int64_t at = (int64_t)i * w.part[m].bytes, half = 0; half < w.part[m].halves; ++half, at += w.part[m].to_second)
+        for (int e = threadIdx.x * 16; e < w.part[m].bytes; e += 4 * 256 * 16) {
+          unsigned x[4][4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int b = e + u * 256 * 16;
+            const uint4 v = *(const uint4*)((const char*)w.part[m].from + at + (b < w.part[m].bytes ? b : e));
+            x[u][0] = v.x; x[u][1] = v.y; x[u][2] = v.z; x[u][3] = v.w;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) asm volatile("" : : "v"(x[u][0]), "v"(x[u][1]), "v"(x[u][2]), "v"(x[u][3]));
+        }
+}
+
+// A decode kernel's last parameter, or none (as an argument that is never used it cost the other launches up to 2 %). True for a
+// workgroup that has read ahead and is done.
+template <typename... Ahead>
+__device__ __forceinline__ bool has_read_ahead(int splits, const Ahead&... ahead) {
+  if constexpr (sizeof...(Ahead) > 0) {
+    if ((int)blockIdx.z < splits) return false;
+    (read_ahead(ahead, splits), ...);
+    return true;
+  }
+  return false;
+}
+
 // 256 threads, head_dim 128. red_o [4][GS][128] and red_ml [4][GS][2] (max in log2 units, sum) hold the wavefronts'
 // states in LDS, complete behind a barrier; head0 = first query head of the KV head, in rows of o. From here on a
 // wavefront has its heads to itself (every fourth): no barrier stands between the trips to memory, of which a meeting takes

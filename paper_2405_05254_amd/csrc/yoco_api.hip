@@ -162,17 +162,17 @@ unsigned long long next_tag() {
 // lens[b] - 1 (ring: modulo the capacity) by the same call and attended to.
 int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
                float* ws, const Splits& sp, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
-               int ring = 0) {
+               int ring = 0, const yoco::ReadAhead& ahead = {}) {
   hipError_t e;
   const unsigned long long tag = yoco::decode_meets_in_launch(Hq / c.Hkv, sp.most) ? next_tag() : 0;
   if (c.dtype == YOCO_INT8) {
     if (!yoco::decode_i8_supported(c, Hq))
       return fail(YOCO_ERR_UNSUPPORTED, "%s: an 8-bit cache serves up to 16 query heads per KV head, not %d", what, Hq / c.Hkv);
     if (k_new) return fail(YOCO_ERR_UNSUPPORTED, "%s: no fused append into an 8-bit cache", what);
-    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, s);
+    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, ahead, s);
     if (tag) return hip_result(e, what);
   } else if (yoco::decode_bf16_supported(c, Hq)) {
-    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, k_new, v_new, ring, s);
+    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, k_new, v_new, ring, ahead, s);
     if (tag) return hip_result(e, what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend
@@ -238,6 +238,30 @@ struct StackScratch {
     bytes = (size_t)(p - p0);
   }
 };
+
+// The weights that the launches behind a layer's attention stream, as far as kAheadBytes go: W_O, then the SwiGLU pair (four rows of
+// either half for a workgroup of launch_gemv). A token step of 4 + 4 layers of 2048 over 2000 rows 283 us, 275 with it, over
+// 200 rows 275 and 266, of 1024-wide layers over 500 rows 172 and 164; with 9, 24 or 32 MB 277 to 278. Only for attention over no
+// more than the L2s hold, which would push the weights out again: over 3500 rows (28 MB) 288.5 and 287.5, over 12000 (98 MB) 327
+// either way.
+constexpr int64_t kAheadBytes = 16 << 20, kShortCache = 32 << 20;
+yoco::ReadAhead weights_ahead(const yoco_stack& st, const yoco_stack_layer& L, const yoco_kv_cache& c, int64_t rows) {
+  yoco::ReadAhead a = {};
+  if (rows > c.N_cap) rows = c.N_cap;
+  if (rows * c.Hkv * (c.dtype == YOCO_INT8 ? 264 : 512) > kShortCache) return a;
+  int64_t left = kAheadBytes;
+  auto part = [&](int m, const void* w, int64_t rows, int64_t width, int halves) {
+    const int64_t bytes = 4 * width * 2;
+    int64_t pieces = left / (bytes * halves);
+    if (pieces > rows / 4) pieces = rows / 4;
+    a.part[m] = {w, rows * width * 2, (int)bytes, (int)pieces, halves};
+    left -= pieces * bytes * halves;
+  };
+  part(0, L.w_o, st.d_model, (int64_t)st.Hq * st.d, 1);
+  part(1, L.w_gu, st.ffn, st.d_model, 2);
+  a.workgroups = yoco::compute_units();
+  return a;
+}
 
 // ---- static scratch for callers that cannot allocate (yoco_cross_attn_decode_noalloc). Every GPU the library
 // runs on holds its own copy of the array, at its own address, until the process ends. In host code the array's name is
@@ -692,7 +716,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
       if (st->gret) {
         rc = yoco_gret_decode(q, k, v, t.log_gamma, gate, t.o, states[i], 1, st->Hq, st->d, st->d, st->scale, 1, st->eps, YOCO_BF16, stream);
       } else {
-        rc = run_decode(rings[i], q, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, ring_plan, s, "stack_step", k, v, 1);
+        rc = run_decode(rings[i], q, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, ring_plan, s, "stack_step", k, v, 1, weights_ahead(*st, L, rings[i], pos + 1));
       }
       if (rc) return rc;
       finish_layer(L, t.x);
@@ -719,7 +743,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
     const yoco_stack_layer& L = st->cross[i];
     if (i > 0 || !self) gemv(cur, L.ln1, L.w_in, qd, dm, nullptr, 0, t.in, qd);
     if (e != hipSuccess) return hip_result(e, "stack_step");
-    rc = run_decode(*cache, t.in, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, plan, s, "stack_step");
+    rc = run_decode(*cache, t.in, t.o, nullptr, pos + 1, st->Hq, st->scale, (float*)workspace, plan, s, "stack_step", nullptr, nullptr, 0, weights_ahead(*st, L, *cache, pos + 1));
     if (rc) return rc;
     finish_layer(L, i + 1 == st->n_cross && x_out ? x_out : t.x);
   }

@@ -93,6 +93,12 @@ bool swa_mfma_supported(const AttnView& a, int dtype);
 size_t swa_mfma_workspace(const AttnView& a);
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s);
 bool decode_bf16_supported(const yoco_kv_cache& c, int Hq);
+// Weights that a decode launch reads ahead for the next launches (decode_tail.h), beside its own work: of up to two matrices, piece
+// i (a multiple of 16 bytes; with halves == 2 also the one to_second bytes on) is what workgroup i of the launch that uses it reads.
+struct ReadAhead {
+  struct { const void* from; int64_t to_second; int bytes, pieces, halves; } part[2];
+  int workgroups;               // 0: none
+};
 // Where one decode launch also merges its splits (decode_tail.h): a wavefront reads all splits of its G / 4 heads, one head
 // after another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (in the launch against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 6.7
 // and 7.2; 32 x 3 7.7 and 6.9; 32 x 4 7.9 and 6.8; 16 x 8 9.9 and 7.5), and a launch less on the host, 2.4 us.
@@ -102,7 +108,7 @@ inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G
 // k_new / v_new ([B,Hkv,128] bf16, or null): also store and attend to the new token's row at slot lens[b] - 1.
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
                               float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
-                              hipStream_t s);
+                              const ReadAhead& ahead, hipStream_t s);
 
 // 8-bit global cache (cache_i8.hip), head_dim 128: a plane per (sequence, KV head) is a run of 64-row blocks, each
 // 8192 code bytes followed by the rows' 64 fp32 scales in row order. Byte offsets of (block row rho, dim e) inside a block:
@@ -116,6 +122,12 @@ __host__ __device__ inline int i8_k_offset(int rho, int e) {      // K plane: si
 __host__ __device__ inline int i8_v_offset(int rho, int e) {      // V plane: bytes code + 128, transposed
   return (((e >> 4) * 64) + (rho >> 4) * 16 + (e & 15)) * 16 + (rho & 15);
 }
+// Rows of workgroups that `wanted` more of them take in a grid of c.Hkv x c.B, a multiple of the 8 XCDs in all.
+inline unsigned more_rows(const yoco_kv_cache& c, int wanted) {
+  const int64_t row = (int64_t)c.Hkv * c.B;
+  const int64_t unit = row % 8 == 0 ? 1 : row % 4 == 0 ? 2 : row % 2 == 0 ? 4 : 8;
+  return (unsigned)((wanted + row * unit - 1) / (row * unit) * unit);
+}
 bool cache_i8_supported(int d);
 bool decode_i8_supported(const yoco_kv_cache& c, int Hq);
 // pos == null: rows [n,Hkv,128] of sequence b to slots pos0 ..; pos != null: one row per sequence to slot pos[b].
@@ -123,7 +135,7 @@ bool decode_i8_supported(const yoco_kv_cache& c, int Hq);
 hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* v, const float* row_scale, int b, int64_t pos0, int64_t n,
                              const int64_t* pos, int src_dtype, hipStream_t s);
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, hipStream_t s);   // q, o bf16
+                            float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const ReadAhead& ahead, hipStream_t s);   // q, o bf16
 
 // What stands between the attention calls of a whole bf16 stack (stack_glue.hip). One token: out = W x with W [N][K], the
 // input normalised first when gain != null; res: added behind the product; glu: W is [2 N][K] and output n is
