@@ -133,13 +133,14 @@ __global__ void __launch_bounds__(256) gret_recurrent_kernel(GretView a) {
 // kk / 8 of a half wavefront hold row rr + 32 (kk / 8). Measured against 4 wavefronts of 16 rows a thread, 13 layers:
 // 1 x 24 heads 94 -> 59 us, 8 x 24 113 -> 86, 16 x 24 174 -> 155 (4.2 TB/s of 50 MB a layer), 32 x 24 272 -> 248;
 // 8 wavefronts of 8 rows 67, 95, 168, 260. With the sums over lanes in registers instead of shuffles (lanes.h) 49, 79 and 150
-// at 1, 8 and 16 x 24. NT: nontemporal accesses, see launch_step.
+// at 1, 8 and 16 x 24; with one wavefront finishing the outputs instead of sixteen 143 at 16 x 24 (without any outputs 137,
+// and a launch that only scales as much memory 130). NT: nontemporal accesses, see launch_step.
 constexpr int kStepRows = 4, kStepGroups = 128 / kStepRows;
 
 template <typename T, bool NT>
 __global__ void __launch_bounds__(32 * kStepGroups) gret_decode_kernel(GretView a) {
   constexpr int kDim = 128, kR = kStepRows, kSame = 32 / kR;
-  __shared__ float red[2][kStepGroups / 2];
+  __shared__ float outs[kDim];
   const int h = blockIdx.x, b = blockIdx.y;
   const int kk = threadIdx.x & 31, rr = threadIdx.x >> 5;
   const int ek = kk * 4;
@@ -158,7 +159,11 @@ __global__ void __launch_bounds__(32 * kStepGroups) gret_decode_kernel(GretView 
   f32x4 S[kR];
 #pragma unroll
   for (int r = 0; r < kR; ++r) S[r] = NT ? __builtin_nontemporal_load(st + r * kStride) : st[r * kStride];
-  const float gate = a.gate && first ? Elem<T>::load((const T*)a.gate + bh * kDim + ev) : 0.f;
+  // Of the rows 2 lane and 2 lane + 1, which the first wavefront finishes; raw and in every wavefront, from V where there is no
+  // gate: behind a branch, or converted there, it is waited for at once, and with it everything requested before it.
+  struct __attribute__((aligned(2 * sizeof(T)))) Pair { T x[2]; };
+  const int lane = threadIdx.x & 63;
+  const Pair gate = ((const Pair*)((const T*)(a.gate ? a.gate : a.v) + bh * kDim))[lane];
 
   float part[kR];
 #pragma unroll
@@ -178,27 +183,27 @@ __global__ void __launch_bounds__(32 * kStepGroups) gret_decode_kernel(GretView 
   const bool upper = (kk & 8) != 0;
   part[0] = (upper ? part[1] : part[0]) + dpp_mov<0x128>(upper ? part[0] : part[1]);   // row_ror:8, lane ^ 8
   part[0] = over8<LaneSum>(part[0]);
-  float out = a.scale * part[0];
-  auto total = [&](float x, float* sums) {                    // over the workgroup
-    x = over64<LaneSum>(x);
-    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = x;
-    __syncthreads();
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < kStepGroups / 2; ++w) s += sums[w];
-    return s;
-  };
+  // One wavefront finishes the 128 outputs: two sums over the workgroup in all sixteen are more instructions than the state takes.
+  if (first) outs[ev] = a.scale * part[0];
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  float y[2] = {outs[2 * lane], outs[2 * lane + 1]};
   if (a.group_norm) {
-    const float inv_dv = 1.f / (float)kDim;
-    const float mean = total(first ? out : 0.f, red[0]) * inv_dv;
-    const float dlt = out - mean;
-    const float var = total(first ? dlt * dlt : 0.f, red[1]) * inv_dv;
-    out = dlt * rsqrtf(var + a.eps);
+    const float mean = over64<LaneSum>(y[0] + y[1]) * (1.f / kDim);
+    y[0] -= mean;
+    y[1] -= mean;
+    const float rstd = rsqrtf(over64<LaneSum>(fmaf(y[0], y[0], y[1] * y[1])) * (1.f / kDim) + a.eps);
+    y[0] *= rstd;
+    y[1] *= rstd;
   }
-  if (first) {
-    if (a.gate) out *= gate / (1.f + __expf(-gate));         // swish gate of Eq. 7: y * g * sigmoid(g)
-    Elem<T>::store((T*)a.o + bh * kDim + ev, out);
+  Pair out;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float g = Elem<T>::load(&gate.x[i]);
+    if (a.gate) y[i] *= g / (1.f + __expf(-g));               // swish gate of Eq. 7: y * g * sigmoid(g)
+    Elem<T>::store(&out.x[i], y[i]);
   }
+  ((Pair*)((T*)a.o + bh * kDim))[lane] = out;
 }
 
 template <typename T>
