@@ -331,17 +331,20 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
       for (int wd = 0; wd < 4; ++wd) {
+        // Bytes code + 128, which one instruction puts into their place (|v| * inv1 is at most 127, what it leaves at most half a
+        // step): half the vector instructions of clamping, masking and shifting each code, of a launch that lasts 12 us (1 x 24:8
+        // heads x 32768 rows: 16.1 -> 15.9 us a layer).
         unsigned ph = 0, pl = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float v = x[half * 16 + wd * 4 + j];
-          const float h = fminf(fmaxf(rintf(v * inv1), -127.f), 127.f);
-          const float lo = fminf(fmaxf(rintf(fmaf(-h, s1, v) * inv2), -127.f), 127.f);
-          ph |= ((unsigned)(int)h & 0xffu) << (8 * j);
-          pl |= ((unsigned)(int)lo & 0xffu) << (8 * j);
+          const float h = rintf(fmaf(v, inv1, 128.f));
+          const float lo = rintf(fmaf(fmaf(128.f - h, s1, v), inv2, 128.f));
+          ph = __builtin_amdgcn_cvt_pk_u8_f32(h, j, ph);
+          pl = __builtin_amdgcn_cvt_pk_u8_f32(lo, j, pl);
         }
-        qhi[half][wd] = (int)ph;
-        qlo[half][wd] = (int)pl;
+        qhi[half][wd] = (int)(ph ^ 0x80808080u);
+        qlo[half][wd] = (int)(pl ^ 0x80808080u);
       }
     }
     qs = s2 * scale_log2;
