@@ -21,7 +21,10 @@ constexpr int kMaxDecodeSplits = 256;
 // sequences of 1500 to 44564 rows, 16 to 64 query heads, bf16 and 8-bit: a twentieth faster on the mean than shares of
 // rows / CUs, which made up to a tenth more workgroups than CUs and launched those with rows among those without: 2 x 16
 // heads x 44564 rows, lengths 0.88 of it, 147 us, now 103; 8 x 8 x 25000, 0.69, 136 and 93).
-constexpr int kLongSplit = 512;
+// From four sequences on 320 rows pay for it (5 x 8 heads x 5000 rows 16.3 us, now 14.7, 9 x 8 x 2833 17.3 and 15.8, 8 bits 14 x 8 x
+// 1963 13.5 and 11.2; at 256 rows 8 x 8 x 1500 9.4 and 9.6); of two or three the plain shares are about as good (3 x 16 x 2713
+// 11.9, 12.2 with the search).
+constexpr int kLongSplit = 512, kLongSplitOfMany = 320;
 constexpr float kGoodFit = 1.5f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -124,7 +127,7 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
     float share = fmaxf(r.total * (float)c.Hkv * (ragged ? out.inv_ragged : out.inv_even), (float)GRAIN);
     bool fits = false;
     const float fl = (float)mine;
-    if (__builtin_expect(ragged && 2 * B <= out.places && B <= 64 && share >= (float)kLongSplit, 0)) {
+    if (__builtin_expect(ragged && 2 * B <= out.places && B <= 64 && share >= (float)(B < kManySequences ? kLongSplit : kLongSplitOfMany), 0)) {
       // The smallest share, nearly, with which every split has a CU of its own, because a CU with two makes the launch wait.
       float s = fmaxf(r.total / (float)out.places, (float)GRAIN);
       for (int i = 0; i < 32 && !fits; ++i) {

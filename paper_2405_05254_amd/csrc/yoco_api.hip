@@ -85,10 +85,14 @@ int check_heads(int Hq, int Hkv) {
 // `most`: what the workspace holds and the grid launches. Twice as many where a split of `even` has rows enough (2560)
 // to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
 // decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
-// 21 instead of 17). A pure function of the cache shape, the query heads and the device: the workspace query and the
-// decode call agree.
+// 21 instead of 17). From four sequences on 700 rows are enough, up to three quarters as many units as CUs: there the long
+// sequences are what a launch waits for (21 x 8 heads x 600..4768 rows 54.8 us, now 43.7; 24 x 8 x 2000 24.5 and 22.7, 12 x 8 x
+// 3000 19.3 and 18.2; at 500 rows 30 x 8 x 1000 16.8 and 18.8; of 232 units x 3141 35.8 and 36.1; two sequences, 64:8 x 13668,
+// 15.1 and 16.4), unless the splits would then be too many to meet in the launch.
+// `least`: the same without that, which a workspace has to hold; one that holds no more gets no more. A pure function of the
+// cache shape, the query heads and the device: the workspace query and the decode call agree.
 struct Splits {
-  int even, most;
+  int even, most, least;
   float inv_ragged, inv_even;   // 1 / how many workgroups a batch of ragged, of equal lengths should make
   int alike;                    // splits of each sequence of one length
   int places;                   // ragged: splits, over the batch, that have a CU of their own for each KV head; 0: not asked
@@ -107,8 +111,8 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   // Splits of a bf16 cache have to save three steps of 128 rows to be worth the meeting at the end (240 units of 355 rows:
   // 10.1 us unsplit, 12.0 in two; 16 units of 400: 9.2 unsplit, 7.6 in four), of an 8-bit one two of 256 (32 units of 500
   // rows: 6.9 unsplit, 7.5 in two; of 700 8.3 and 7.4 in three).
-  const int64_t least = c->dtype == YOCO_BF16 ? 3 : 2;
-  if ((c->dtype == YOCO_BF16 || finer) && (c->N_cap + min_rows - 1) / min_rows - (c->N_cap + min_rows * s - 1) / (min_rows * s) < least) s = 1;
+  const int64_t saves = c->dtype == YOCO_BF16 ? 3 : 2;
+  if ((c->dtype == YOCO_BF16 || finer) && (c->N_cap + min_rows - 1) / min_rows - (c->N_cap + min_rows * s - 1) / (min_rows * s) < saves) s = 1;
   // More (sequence, KV head) units than CUs, and not a multiple of them: the workgroups of a ragged last round run
   // with part of the chip idle (384 units on 256 CUs measured 5.7 TB/s at 4096 rows). Two to four splits per unit
   // make the count a multiple again, as long as a split keeps at least 1024 rows (384 units of 1024 rows: 35.9 us
@@ -122,8 +126,12 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   const int64_t fits = (int64_t)(YOCO_NOALLOC_SCRATCH_BYTES / ((size_t)c->B * Hq * yoco::partial_stride(c->d) * sizeof(float)));
   auto bounded = [&](int64_t x) { return x > fits ? (fits > coarse ? fits : coarse) : x; };
   if (s > coarse) s = bounded(s);
-  int64_t most = s;
-  if (c->dtype == YOCO_BF16 && units <= cus && s > 1 && s <= 128 && c->N_cap / s >= 2560) most = bounded(2 * s) > s ? bounded(2 * s) : s;
+  int64_t most = s, least = s;
+  if (c->dtype == YOCO_BF16 && units <= cus && s > 1 && s <= 128) {
+    const int64_t twice = bounded(2 * s) > s ? bounded(2 * s) : s;
+    if (c->N_cap / s >= 2560) most = least = twice;
+    else if (c->N_cap / s >= 700 && c->B >= yoco::kManySequences && 4 * units <= 3 * cus && meets((int)twice) == meets((int)s)) most = twice;
+  }
   // Equal lengths: no more workgroups than CUs where the count is no multiple, because a workgroup or two too many share
   // a CU and the launch waits for them (24 units x 32768 rows: 264 workgroups 47.6 us in 8 bits and 87.4 in bf16, 240 36.2
   // and 64.1; 200 units x 8192: 400 workgroups 74.7 and 144, 200 63.6 and 136; rolling caches, 160 units x 2048: 36.9
@@ -135,9 +143,20 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   if (units < cus && units * s > cus) {
     n = cus / units;
     const int64_t twice = 2 * cus / units;
-    if (c->dtype == YOCO_BF16 && 4 * units * n < 3 * cus && 2 * units * twice >= 3 * cus && twice <= most && c->N_cap / twice >= 1024) n = twice;
+    if (c->dtype == YOCO_BF16 && 4 * units * n < 3 * cus && 2 * units * twice >= 3 * cus && twice <= least && c->N_cap / twice >= 1024) n = twice;
   }
-  return {(int)s, (int)most, 1.f / (float)(units * s), 1.f / (float)(units * n), (int)n, units <= cus ? cus / c->Hkv : 0};
+  return {(int)s, (int)most, (int)least, 1.f / (float)(units * s), 1.f / (float)(units * n), (int)n, units <= cus ? cus / c->Hkv : 0};
+}
+
+size_t partial_bytes(const yoco_kv_cache& c, int Hq, int splits) {
+  return (size_t)c.B * Hq * splits * yoco::partial_stride(c.d) * sizeof(float);
+}
+// The splits of a decode call with `held` bytes of workspace.
+int plan_decode(const yoco_kv_cache& c, int Hq, size_t held, Splits* plan) {
+  *plan = decode_splits(&c, Hq);
+  if (held < partial_bytes(c, Hq, plan->most)) plan->most = plan->least;
+  const size_t need = partial_bytes(c, Hq, plan->most);
+  return held < need ? fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", held, need) : YOCO_OK;
 }
 
 // The tag a decode launch marks its published splits with: never 0, never the same twice in a process (a bijection of a
@@ -459,7 +478,7 @@ int yoco_cross_attn_prefill(const yoco_kv_cache* c, const void* q, void* o, int 
     const size_t per_split = (size_t)Hq * yoco::partial_stride(c->d) * sizeof(float);
     Splits splits = decode_splits(&one, Hq);
     splits.most = splits.even;                                          // one sequence: nothing is ragged
-    const size_t whole = (size_t)c->B * decode_splits(c, Hq).most;      // what the documented workspace holds
+    const size_t whole = (size_t)c->B * decode_splits(c, Hq).least;     // what the documented workspace holds
     const size_t held = workspace_bytes / per_split;
     if (held >= (whole < (size_t)splits.even ? whole : (size_t)splits.even)) {
       if (held < (size_t)splits.most) splits.most = (int)held;
@@ -503,7 +522,7 @@ int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* byt
   if (rc) return rc;
   const int s = decode_splits(c, Hq).most;
   *splits = s;
-  *bytes = (size_t)c->B * Hq * s * yoco::partial_stride(c->d) * sizeof(float);
+  *bytes = partial_bytes(*c, Hq, s);
   return YOCO_OK;
 }
 
@@ -517,12 +536,10 @@ int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const
   if (!aligned16(q) || !aligned16(o) || !aligned16(workspace))
     return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned");
   if (c->B > 65535) return fail(YOCO_ERR_UNSUPPORTED, "B %d exceeds the grid limit", c->B);
-  size_t need = 0;
-  int splits = 0;
-  rc = yoco_cross_attn_decode_workspace(c, Hq, &need, &splits);
+  Splits plan;
+  rc = plan_decode(*c, Hq, workspace_bytes, &plan);
   if (rc) return rc;
-  if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
-  return run_decode(*c, q, o, lens, 0, Hq, scale, (float*)workspace, decode_splits(c, Hq), (hipStream_t)stream, "cross_attn_decode");
+  return run_decode(*c, q, o, lens, 0, Hq, scale, (float*)workspace, plan, (hipStream_t)stream, "cross_attn_decode");
 }
 
 int yoco_cross_attn_decode_noalloc(const yoco_kv_cache* c, const void* q, void* o, const int64_t* lens, int Hq, float scale,
@@ -531,10 +548,9 @@ int yoco_cross_attn_decode_noalloc(const yoco_kv_cache* c, const void* q, void* 
   int rc = check_cache(c);
   if (rc) return rc;
   if (!q || !o || !lens) return fail(YOCO_ERR_INVALID_ARG, "null pointer");
-  size_t need = 0;
-  int splits = 0;
-  rc = yoco_cross_attn_decode_workspace(c, Hq, &need, &splits);
+  rc = check_heads(Hq, c->Hkv);
   if (rc) return rc;
+  const size_t need = partial_bytes(*c, Hq, decode_splits(c, Hq).least);
   if (need > kScratchBytes)
     return fail(YOCO_ERR_WORKSPACE, "cross_attn_decode_noalloc: the partial results need %zu bytes, the static scratch holds %zu",
                 need, kScratchBytes);
@@ -562,12 +578,10 @@ int yoco_swa_decode(const yoco_kv_cache* ring, const void* q, const void* k_new,
   if (ring->B > 65535) return fail(YOCO_ERR_UNSUPPORTED, "B %d exceeds the grid limit", ring->B);
   if ((k_new == nullptr) != (v_new == nullptr)) return fail(YOCO_ERR_INVALID_ARG, "k_new and v_new must both be given or both be null");
   if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return fail(YOCO_ERR_ALIGNMENT, "new row pointer not 16-byte aligned");
-  size_t need = 0;
-  int splits = 0;
-  rc = yoco_cross_attn_decode_workspace(ring, Hq, &need, &splits);
+  Splits plan;
+  rc = plan_decode(*ring, Hq, workspace_bytes, &plan);
   if (rc) return rc;
-  if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
-  return run_decode(*ring, q, o, lens, 0, Hq, scale, (float*)workspace, decode_splits(ring, Hq), (hipStream_t)stream, "swa_decode", k_new, v_new, 1);
+  return run_decode(*ring, q, o, lens, 0, Hq, scale, (float*)workspace, plan, (hipStream_t)stream, "swa_decode", k_new, v_new, 1);
 }
 
 int yoco_gret_prefill_workspace(int B, int64_t T, int H, int dk, int dv, int chunk, int dtype, size_t* bytes) {
@@ -659,11 +673,9 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
     return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned");
   const StackScratch t(*st, (char*)scratch);
   if (scratch_bytes < t.bytes) return fail(YOCO_ERR_WORKSPACE, "scratch %zu < %zu bytes", scratch_bytes, t.bytes);
-  size_t need = 0;
-  int splits = 0;
-  rc = yoco_cross_attn_decode_workspace(cache, st->Hq, &need, &splits);
+  Splits plan, ring_plan;
+  rc = plan_decode(*cache, st->Hq, workspace_bytes, &plan);
   if (rc) return rc;
-  if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
   const bool in_rings = self && !st->gret && st->n_self > 0;
   if (self && st->gret) {
     if (!(st->eps >= 0.f)) return fail(YOCO_ERR_INVALID_ARG, "negative eps");
@@ -680,12 +692,10 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
           rings[i].N_cap != rings[0].N_cap)
         return fail(YOCO_ERR_INVALID_ARG, "ring %d does not match the stack", i);
     }
-    rc = yoco_cross_attn_decode_workspace(rings, st->Hq, &need, &splits);
+    rc = plan_decode(rings[0], st->Hq, workspace_bytes, &ring_plan);
     if (rc) return rc;
-    if (workspace_bytes < need) return fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, need);
   }
 
-  const Splits plan = decode_splits(cache, st->Hq), ring_plan = decode_splits(in_rings ? rings : cache, st->Hq);
   hipStream_t s = (hipStream_t)stream;
   const int dm = st->d_model, qd = st->Hq * st->d, kd = st->Hkv_self * st->d, ckd = st->Hkv * st->d;
   hipError_t e = hipSuccess;

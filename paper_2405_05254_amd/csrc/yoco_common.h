@@ -103,6 +103,9 @@ struct ReadAhead {
 // after another, so up to 16 splits of 4 heads per KV head, or 8 of 8 (in the launch against a merge launch, us: 3 splits of 4 heads, 8 bits, 7.3 and 9.4; 4 x 3 19.3 and 20.2; 8 x 2 15.3 and 16.0; 16 x 3 6.7
 // and 7.2; 32 x 3 7.7 and 6.9; 32 x 4 7.9 and 6.8; 16 x 8 9.9 and 7.5), and a launch less on the host, 2.4 us.
 constexpr int kMeetSplits = 16;
+// Sequences from which on a batch of ragged lengths is shared out finer: each sequence's last split is rounded up, so that the
+// splits that are too many for the CUs are about half as many as the sequences.
+constexpr int kManySequences = 4;
 inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G <= 8 && (G + 3) / 4 * splits <= kMeetSplits); }
 // Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.
 // k_new / v_new ([B,Hkv,128] bf16, or null): also store and attend to the new token's row at slot lens[b] - 1.

@@ -34,6 +34,11 @@ SCALE = 1.0 / math.sqrt(D)
     ("int8", 4, 1, 16384, [16384]),                         # 64 of 256
     ("int8", 4, 1, 16385, [16385]),                         # 33 of 512, not 65
     ("bf16", 16, 1, 9000, [9000, 0, 7, 4400, 128, 127]),    # 16 heads in one workgroup, an empty sequence among long ones
+    ("bf16", 9, 3, 1500, [1500, 1, 1499, 700, 0, 800, 129, 1400, 2]),     # many sequences and few units: every one in splits of a step
+    ("bf16", 24, 8, 3000, [3000, 375, 0, 2999, 1600, 128, 2100, 900]),    # ... splits to spare from 700 rows on, a CU for each
+    ("bf16", 16, 8, 1400, [1400, 200, 1300, 5, 1399, 700, 0, 1, 1200, 300, 1100, 128, 129, 256, 1024, 900, 640]),   # ... of two, at the line
+    ("bf16", 16, 8, 1399, [1399, 200, 1300, 5, 1398, 700, 0, 1, 1200, 300, 1100, 128, 129, 256, 1024, 900, 640]),   # ... below it
+    ("int8", 8, 8, 1963, [1963, 250, 1500, 0, 1000, 1900, 300, 512, 513, 1200, 800, 64, 1800, 1700]),
     ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
     ("bf16", 12, 12, 1100, [1100, 1100, 1090, 1100, 1100, 1100, 1100]),   # 84 units of equal lengths: 3 splits, not 4
     ("bf16", 12, 12, 1100, [1100, 1100, 900, 1100, 1100, 1100, 1100]),    # ... just past what counts as equal
@@ -73,6 +78,27 @@ def test_splits_meet_in_an_uncleared_workspace(dtype, Hq, Hkv, N_cap, lens, garb
             continue
         st = ys.error_stats(got, attend(q[b:b + 1], K[b, :n], V[b, :n], n - 1, SCALE)[0])
         assert st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], (b, n, splits, st)
+
+
+def test_a_workspace_without_splits_to_spare_is_enough():
+    """Splits to spare for a ragged batch of short sequences are used where the workspace holds them; half of it holds the others."""
+    B, Hkv, Hq, N = 8, 8, 24, 3000
+    rng = np.random.default_rng(5)
+    cache = yoco.KVCache(B, Hkv, D, N, torch.bfloat16)
+    for plane in cache.planes():
+        plane.copy_(torch.from_numpy(ys.normal(rng, tuple(plane.shape), 1.0, "bf16")))
+    q = torch.from_numpy(ys.normal(rng, (B, Hq, D), 1.0, "bf16")).cuda().to(torch.bfloat16)
+    lens = torch.tensor([3000, 375, 0, 2999, 1600, 128, 2100, 900], dtype=torch.int64, device="cuda")
+    nbytes, splits = yoco.cross_attn_decode_workspace(cache, Hq)
+    if splits % 2:
+        pytest.skip("no splits to spare on this many CUs")
+    whole, half = (yoco.cross_attn_decode(cache, q, lens, SCALE, torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda"))
+                   for n in (nbytes, nbytes // 2))
+    with pytest.raises(yoco.YocoError):
+        yoco.cross_attn_decode(cache, q, lens, SCALE, torch.empty(nbytes // 2 - 16, dtype=torch.uint8, device="cuda"))
+    a, b = whole.float().cpu().numpy(), half.float().cpu().numpy()
+    st = ys.error_stats(a, b)
+    assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], st
 
 
 def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
