@@ -86,9 +86,11 @@ int check_heads(int Hq, int Hkv) {
 // to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
 // decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
 // 21 instead of 17). From four sequences on 700 rows are enough, up to three quarters as many units as CUs: there the long
-// sequences are what a launch waits for (21 x 8 heads x 600..4768 rows 54.8 us, now 43.7; 24 x 8 x 2000 24.5 and 22.7, 12 x 8 x
-// 3000 19.3 and 18.2; at 500 rows 30 x 8 x 1000 16.8 and 18.8; of 232 units x 3141 35.8 and 36.1; two sequences, 64:8 x 13668,
-// 15.1 and 16.4), unless the splits would then be too many to meet in the launch.
+// sequences are what a launch waits for (us, lengths from an eighth of the capacity to all of it; bf16 21 x 8 heads x 4768 rows
+// 54.8, now 43.7, 24 x 8 x 2000 24.5 and 22.7, 12 x 8 x 3000 19.3 and 18.2; 8 bits, which had none to spare, 11 x 16 x 16614 91.9
+// and 71.4, 21 x 8 x 1818 18.0 and 15.5; three or four times as many give no more). At 500 rows 30 x 8 x 1000 takes 18.8 for 16.8, 232
+// units x 3141 36.1 for 35.8, and two sequences of 64:8 heads x 13668 16.4 for 15.1. Not where the splits are then too many
+// to meet in the launch.
 // `least`: the same without that, which a workspace has to hold; one that holds no more gets no more. A pure function of the
 // cache shape, the query heads and the device: the workspace query and the decode call agree.
 struct Splits {
@@ -127,9 +129,9 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   auto bounded = [&](int64_t x) { return x > fits ? (fits > coarse ? fits : coarse) : x; };
   if (s > coarse) s = bounded(s);
   int64_t most = s, least = s;
-  if (c->dtype == YOCO_BF16 && units <= cus && s > 1 && s <= 128) {
+  if ((c->dtype == YOCO_BF16 || finer) && units <= cus && s > 1 && s <= 128) {
     const int64_t twice = bounded(2 * s) > s ? bounded(2 * s) : s;
-    if (c->N_cap / s >= 2560) most = least = twice;
+    if (c->dtype == YOCO_BF16 && c->N_cap / s >= 2560) most = least = twice;
     else if (c->N_cap / s >= 700 && c->B >= yoco::kManySequences && 4 * units <= 3 * cus && meets((int)twice) == meets((int)s)) most = twice;
   }
   // Equal lengths: no more workgroups than CUs where the count is no multiple, because a workgroup or two too many share

@@ -38,6 +38,8 @@ SCALE = 1.0 / math.sqrt(D)
     ("bf16", 24, 8, 3000, [3000, 375, 0, 2999, 1600, 128, 2100, 900]),    # ... splits to spare from 700 rows on, a CU for each
     ("bf16", 16, 8, 1400, [1400, 200, 1300, 5, 1399, 700, 0, 1, 1200, 300, 1100, 128, 129, 256, 1024, 900, 640]),   # ... of two, at the line
     ("bf16", 16, 8, 1399, [1399, 200, 1300, 5, 1398, 700, 0, 1, 1200, 300, 1100, 128, 129, 256, 1024, 900, 640]),   # ... below it
+    ("int8", 24, 8, 3079, [3079, 400, 3000, 0, 257, 1900, 513, 2500, 256]),
+    ("int8", 64, 8, 4751, [4751, 600, 3000, 1]),
     ("int8", 8, 8, 1963, [1963, 250, 1500, 0, 1000, 1900, 300, 512, 513, 1200, 800, 64, 1800, 1700]),
     ("bf16", 8, 8, 21000, [20999, 2500, 300, 17, 9000]),    # splits to spare: the long sequences are cut finer than the short
     ("bf16", 12, 12, 1100, [1100, 1100, 1090, 1100, 1100, 1100, 1100]),   # 84 units of equal lengths: 3 splits, not 4
