@@ -88,8 +88,10 @@ int check_heads(int Hq, int Hkv) {
 // 21 instead of 17). From four sequences on 700 rows are enough, up to three quarters as many units as CUs: there the long
 // sequences are what a launch waits for (us, lengths from an eighth of the capacity to all of it; bf16 21 x 8 heads x 4768 rows
 // 54.8, now 43.7, 24 x 8 x 2000 24.5 and 22.7, 12 x 8 x 3000 19.3 and 18.2; 8 bits, which had none to spare, 11 x 16 x 16614 91.9
-// and 71.4, 21 x 8 x 1818 18.0 and 15.5; three or four times as many give no more). At 500 rows 30 x 8 x 1000 takes 18.8 for 16.8, 232
-// units x 3141 36.1 for 35.8, and two sequences of 64:8 heads x 13668 16.4 for 15.1. Not where the splits are then too many
+// and 71.4, 9 x 8 x 3079 12.2 and 11.1; three or four times as many give no more). At 500 rows 30 x 8 x 1000 takes 18.8 for 16.8, 232
+// units x 3141 36.1 for 35.8, and two sequences of 64:8 heads x 13668 16.4 for 15.1. In 8 bits only up to half as many units as CUs,
+// or from 3000 rows a split on, because the workgroups that a batch of equal lengths leaves without rows cost it (24 x 8 x 2000
+// 17.8 us, 18.7 with them, x 4000 31.6 and 32.2; x 6000 nothing). Not where the splits are then too many
 // to meet in the launch.
 // `least`: the same without that, which a workspace has to hold; one that holds no more gets no more. A pure function of the
 // cache shape, the query heads and the device: the workspace query and the decode call agree.
@@ -132,7 +134,8 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   if ((c->dtype == YOCO_BF16 || finer) && units <= cus && s > 1 && s <= 128) {
     const int64_t twice = bounded(2 * s) > s ? bounded(2 * s) : s;
     if (c->dtype == YOCO_BF16 && c->N_cap / s >= 2560) most = least = twice;
-    else if (c->N_cap / s >= 700 && c->B >= yoco::kManySequences && 4 * units <= 3 * cus && meets((int)twice) == meets((int)s)) most = twice;
+    const bool few = 4 * units <= 3 * cus && (c->dtype == YOCO_BF16 || 2 * units <= cus || c->N_cap / s >= 3000);
+    if (most == s && c->N_cap / s >= 700 && c->B >= yoco::kManySequences && few && meets((int)twice) == meets((int)s)) most = twice;
   }
   // Equal lengths: no more workgroups than CUs where the count is no multiple, because a workgroup or two too many share
   // a CU and the launch waits for them (24 units x 32768 rows: 264 workgroups 47.6 us in 8 bits and 87.4 in bf16, 240 36.2

@@ -124,6 +124,8 @@ def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
     (2, 1, 2200, [2200, 9000]),       # ... 18, with a merge launch
     (12, 4, 2048, [2048, 1]),         # the matrix-core step
     (4, 1, 2200, [100000, 700, 0]),
+    (16, 16, 1500, [5000, 3, 0, 700, 1499, 1500, 1501, 900]),       # splits to spare, the vector-ALU step
+    (24, 8, 3000, [2999, 3000, 3001, 1, 128, 1700, 375, 9000]),     # ... the matrix-core step
     (16, 1, 700, [699, 701]),         # more than 8 heads per KV head
 ])
 def test_rings_that_are_split_store_the_new_row_and_attend_to_it(Hq, Hkv, N_cap, tokens):
