@@ -128,7 +128,8 @@ __device__ __forceinline__ u32x4 row_load(const void* row, unsigned bytes, int a
 // Rows of up to CH * 512 elements: every wavefront holds the input row itself, a lane the 8 CH elements that its weights
 // meet, and norms it itself. With the row in LDS (below) the workgroup's wavefronts wait for one another twice between the first
 // load and the first product, in a launch that is over in a few microseconds. The input is requested before the weights (loads
-// return in order), all of them at once.
+// return in order), all of them at once. The sum of the norm is taken in the order of a workgroup's four wavefronts (block_total), so
+// that a row has the same norm here as in norm_rows_kernel, bit for bit: as a token and as a row of a prompt.
 template <int CH, int ROWS, bool NORM, Epilogue EPI, typename Args>
 __global__ void __launch_bounds__(256) gemv_short_kernel(Args g) {
   const OwnRows<ROWS, EPI, Args> own(g);
@@ -146,11 +147,12 @@ __global__ void __launch_bounds__(256) gemv_short_kernel(Args g) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) w[r][c] = row_load<kNontemporal>(own.w[r], bytes, at + c * 1024);
   const float res = own.residual(g);
-  if (NORM) {
-    float ss = 0.f;
+  if constexpr (NORM) {
+    static_assert(CH <= 4, "512 elements for each wavefront of block_total");
+    float part[4] = {};
 #pragma unroll
-    for (int c = 0; c < CH; ++c) ss = square(x[c], ss);
-    const float rstd = rsqrtf(over64<LaneSum>(ss) / (float)g.K + g.eps);
+    for (int c = 0; c < CH; ++c) part[c] = square(x[c], 0.f);
+    const float rstd = rsqrtf(sum_of_four_over64(part) / (float)g.K + g.eps);
 #pragma unroll
     for (int c = 0; c < CH; ++c) x[c] = normed(x[c], rstd, gain[c]);
   }

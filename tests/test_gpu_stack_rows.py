@@ -48,3 +48,36 @@ def test_token_steps_where_the_kernels_change(Hq, dm, ffn, vocab):
         logits.append(torch.cat([st.prefill(toks[:15], state)] + [st.decode_step(t, state) for t in toks[15:]]).double())
     got, ref = logits
     assert ((got - ref).norm() / ref.norm()).item() < 1.5e-2         # bf16 roundings that fall the other way, over four layer halves
+
+
+@pytest.mark.parametrize("Hq,dm,ffn,vocab", [
+    (1, 8, 8, 11),
+    (1, 520, 8, 524),
+    (2, 1024, 16, 1001),
+    (2, 1032, 16, 1033),
+    (2, 2048, 16, 16387),          # the classifier's two outputs a wavefront, three in its last workgroup
+    (2, 2056, 16, 16385),
+    (2, 4104, 16, 4110),
+])
+def test_a_token_is_normed_as_a_row_of_a_prompt(Hq, dm, ffn, vocab):
+    """Layers that add nothing and a classifier that copies: the logits are the normed row itself, every one of them, so that a
+    sum in another order (which moves 1 element in some 30000 by a bf16 step) and an output out of place both show."""
+    from paper_2405_05254_amd import binding as yb
+    from paper_2405_05254_amd.stack import YocoStack
+    w = random_stack(Hq, dm, ffn, vocab)
+    for L in w["self"] + w["cross"]:
+        for n in ("W_O", "W_2"):
+            L[n].zero_()
+    at = torch.arange(vocab, device="cuda") % dm
+    w["W_out"] = torch.zeros(dm, vocab, device="cuda").index_put_((at, torch.arange(vocab, device="cuda")), torch.ones((), device="cuda")).bfloat16()
+    gen = torch.Generator(device="cuda").manual_seed(dm)
+    steps = 400
+    w["embed"] = (torch.randn(steps, dm, device="cuda", generator=gen) * torch.randn(steps, dm, device="cuda", generator=gen).exp()).bfloat16()
+    st = YocoStack(w, torch.bfloat16, glue_dtype=torch.bfloat16)
+    assert st._native is not None
+    state = st.new_generation_state(steps)
+    toks = torch.arange(steps, device="cuda")
+    st.prefill(toks[:1], state)
+    got = torch.cat([st.decode_step(t, state) for t in toks[1:]])
+    want = yb.norm_rows(st.embed[1:], st.final_ln, st.eps)[:, at]
+    assert torch.equal(got, want), (got != want).sum().item()
