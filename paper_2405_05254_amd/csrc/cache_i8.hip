@@ -176,6 +176,19 @@ __device__ __forceinline__ unsigned pack_f16(float a, float b) {      // round t
   return __builtin_bit_cast(unsigned, (f16x2){(_Float16)a, (_Float16)b});
 }
 
+// rint(x * inv) as the low byte of a float's bits, |x * inv| <= 127 and a rounding: behind 1.5 * 2^23 a float has no fraction, so that
+// the sum's rounding is rint and its low bits are the whole number. Product and sum are rounded apart, as rint of the product is.
+constexpr float kWhole = 12582912.f;
+__device__ __forceinline__ float code_of(float x, float inv) {
+#pragma clang fp contract(off)
+  return x * inv + kWhole;
+}
+__device__ __forceinline__ int low_bytes(const float (&c)[4]) {
+  const unsigned even = __builtin_amdgcn_perm(__float_as_uint(c[2]), __float_as_uint(c[0]), 0x0c040c00u);
+  const unsigned odd = __builtin_amdgcn_perm(__float_as_uint(c[3]), __float_as_uint(c[1]), 0x040c000cu);
+  return (int)(even | odd);
+}
+
 struct Block {             // what a lane holds of one 64-row block
   u32x4 k[8];              // [tau * 2 + half]: K codes of row 16 (n / 4) + 4 tau + n % 4, dims 64 half + 16 qg ..
   u32x4 v[8];              // [t]: V codes of dim 16 t + n, rows 16 qg .. 16 qg + 15
@@ -331,20 +344,15 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
       for (int wd = 0; wd < 4; ++wd) {
-        // Bytes code + 128, which one instruction puts into their place (|v| * inv1 is at most 127, what it leaves at most half a
-        // step): half the vector instructions of clamping, masking and shifting each code, of a launch that lasts 12 us (1 x 24:8
-        // heads x 32768 rows: 16.1 -> 15.9 us a layer).
-        unsigned ph = 0, pl = 0;
+        float h[4], lo[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float v = x[half * 16 + wd * 4 + j];
-          const float h = rintf(fmaf(v, inv1, 128.f));
-          const float lo = rintf(fmaf(fmaf(128.f - h, s1, v), inv2, 128.f));
-          ph = __builtin_amdgcn_cvt_pk_u8_f32(h, j, ph);
-          pl = __builtin_amdgcn_cvt_pk_u8_f32(lo, j, pl);
+          h[j] = code_of(v, inv1);
+          lo[j] = code_of(fmaf(-(h[j] - kWhole), s1, v), inv2);
         }
-        qhi[half][wd] = (int)(ph ^ 0x80808080u);
-        qlo[half][wd] = (int)(pl ^ 0x80808080u);
+        qhi[half][wd] = low_bytes(h);
+        qlo[half][wd] = low_bytes(lo);
       }
     }
     qs = s2 * scale_log2;

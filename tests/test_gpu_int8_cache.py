@@ -203,6 +203,43 @@ def test_decode_over_codes_large_and_small_magnitudes(yoco):
     decode_case(yoco, 32, 2, 6, 2, 600, [600, 77], std=0.01)
 
 
+def test_query_codes_are_the_rounded_products(yoco):
+    """Every mantissa of a head's largest |q| against elements whose second code lies half-way between two whole numbers or
+    near it: codes are rint(x * inv) of the float32 product. One row of the cache sees the element alone, another the largest with
+    what balances the score, at a scale where a step of the second code is 1: the output is 0.5, and 0.27 or 0.73 a code off.
+    Its error: scores up to 46539 (log2 units) in float32, four roundings of half of 2^-8 each, a quarter of it 0.002, and bf16."""
+    B, H, f = 128, 8, np.float32
+    top = (1 + np.arange(B) / 128)[:, None]
+    ratio = np.array([-1 / 4, 1 / 4, -1 / 2, 1 / 2, -3 / 4, 1 / 8, -0.3701, 0.0123])
+    q = np.zeros((B, H, D))
+    q[:, :, 0], q[:, :, 5] = top, top * ratio
+    qt = dev(q, "bf16")
+    top, x = (host(qt)[:, :, n].astype(f) for n in (0, 5))
+    hi = np.rint(x * (f(127) / top))
+    left = (x.astype(np.float64) - hi.astype(np.float64) * (top / f(127))).astype(f)      # one rounding, as a fused multiply-add
+    lo = np.rint(left * (f(32258) / top))
+    assert hi.dtype == lo.dtype == f and np.abs(lo).max() > 63
+    cache = yoco.KVCache(B, H, D, 64, torch.int8)
+    k, v = np.zeros((B, 2, H, D), f), np.zeros((B, 2, H, D), f)
+    k[:, 0, :, 5] = v[:, 0] = v[:, 1, :, 0] = 1                                # of the second row of V only the last dims count: zeros
+    k[:, 1, :, 0] = (hi * 254 + lo) / 32258
+    for b in range(B):
+        yoco.global_kv_write(cache, dev(k[b], "f32"), dev(v[b], "f32"), b, 0)
+    (kc, ks), (vc, _) = read_cache(cache)
+    assert (kc[:, :, 0, 5] == 127).all() and (np.abs(kc[:, :, 1, 0]) == 127).all() and (vc[:, :, 0] == 127).all() and not vc[:, :, 1, 1:].any()
+    ws = torch.empty(yoco.cross_attn_decode_workspace(cache, H)[0], dtype=torch.uint8, device="cuda")
+    lens = torch.full((1,), 2, dtype=torch.int64, device="cuda")
+    for b in range(B):                                                          # a call a mantissa: the scale is one step of its code
+        one = yoco.KVCache(1, H, D, 64, torch.int8)
+        for mine, all_of in zip(one.blocks(), cache.blocks()):
+            mine.copy_(all_of[b:b + 1])
+        s2 = float(top[b, 0] / f(32258))
+        got = host(yoco.cross_attn_decode(one, qt[b:b + 1].contiguous(), lens, 1 / s2, ws))[0, :, 7]
+        w = [127 * ks[b, :, r].astype(np.float64) * m for r, m in ((0, hi[b] * 254 + lo[b]), (1, np.sign(x[b]) * 32258))]
+        want = 1 / (1 + np.exp(w[1] - w[0]))
+        assert np.abs(want - 0.5).max() < 0.01 and np.abs(got - want).max() < 0.02, (b, got, want)
+
+
 def test_decode_is_reproducible_and_does_not_touch_the_cache(yoco):
     scale = 1.0 / math.sqrt(D)
     rng = np.random.default_rng(5)
