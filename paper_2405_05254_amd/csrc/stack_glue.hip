@@ -128,7 +128,9 @@ __device__ __forceinline__ u32x4 row_load(const void* row, unsigned bytes, int a
 // Rows of up to CH * 512 elements: every wavefront holds the input row itself, a lane the 8 CH elements that its weights
 // meet, and norms it itself. With the row in LDS (below) the workgroup's wavefronts wait for one another twice between the first
 // load and the first product, in a launch that is over in a few microseconds. The input is requested before the weights (loads
-// return in order), all of them at once. The sum of the norm is taken in the order of a workgroup's four wavefronts (block_total), so
+// return in order), all of them at once: behind a norm the compiler has to be told, or it requests the weights when the norm is
+// formed, in two thirds of the registers (a token step, 4 + 4 layers of 2048: 274.1 us, 268.2 told; of 1024, two loads a row,
+// 165.1 and 165.6, so not there). The sum of the norm is taken in the order of a workgroup's four wavefronts (block_total), so
 // that a row has the same norm here as in norm_rows_kernel, bit for bit: as a token and as a row of a prompt.
 template <int CH, int ROWS, bool NORM, Epilogue EPI, typename Args>
 __global__ void __launch_bounds__(256) gemv_short_kernel(Args g) {
@@ -147,6 +149,7 @@ __global__ void __launch_bounds__(256) gemv_short_kernel(Args g) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) w[r][c] = row_load<kNontemporal>(own.w[r], bytes, at + c * 1024);
   const float res = own.residual(g);
+  if constexpr (NORM && CH > 2) __builtin_amdgcn_sched_barrier(0);
   if constexpr (NORM) {
     static_assert(CH <= 4, "512 elements for each wavefront of block_total");
     float part[4] = {};
