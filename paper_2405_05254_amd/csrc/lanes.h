@@ -61,18 +61,21 @@ __device__ __forceinline__ float over32(float x) {
 }
 template <typename F>
 __device__ __forceinline__ float over64(float x) { return over32<F>(with_other_half<F>(x)); }
-// (over64 of x[0] + of x[1]) + (of x[2] + of x[3]), with the same bits as from four of them: behind the first two exchanges a row of
-// lanes has one of the four to itself, so that the others run together.
-__device__ __forceinline__ float sum_of_four_over64(const float (&x)[4]) {
+// over64 of x[0] + of x[1], of four (x[0] + x[1]) + (x[2] + x[3]), with the same bits: behind the first exchanges a row of lanes has
+// one of them to itself, so that the others run together.
+template <int N>
+__device__ __forceinline__ float sum_over64(const float (&x)[N]) {
+  static_assert(N == 2 || N == 4, "a half or a row of lanes for each");
   float half[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i + 2]), false, false);
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i + N - 2]), false, false);
     half[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[0]), __float_as_uint(half[1]), false, false);
-  const float row = __uint_as_float(r[0]) + __uint_as_float(r[1]);            // row i: x[i]
-  return over_rows<LaneSum>(over8<LaneSum>(row + dpp_mov<0x128>(row)));       // row_ror:8
+  float row = __uint_as_float(r[0]) + __uint_as_float(r[1]);                  // row i: x[i % N]
+  row = with_next_row<LaneSum>(over8<LaneSum>(row + dpp_mov<0x128>(row)));    // row_ror:8
+  return N == 2 ? row : with_other_half<LaneSum>(row);
 }
 
 }  // namespace yoco

@@ -151,11 +151,10 @@ __global__ void __launch_bounds__(256) gemv_short_kernel(Args g) {
   const float res = own.residual(g);
   if constexpr (NORM && CH > 2) __builtin_amdgcn_sched_barrier(0);
   if constexpr (NORM) {
-    static_assert(CH <= 4, "512 elements for each wavefront of block_total");
-    float part[4] = {};
+    float part[CH];                                // of 512 elements, a wavefront's share of block_total
 #pragma unroll
     for (int c = 0; c < CH; ++c) part[c] = square(x[c], 0.f);
-    const float rstd = rsqrtf(sum_of_four_over64(part) / (float)g.K + g.eps);
+    const float rstd = rsqrtf(sum_over64(part) / (float)g.K + g.eps);
 #pragma unroll
     for (int c = 0; c < CH; ++c) x[c] = normed(x[c], rstd, gain[c]);
   }
