@@ -264,11 +264,13 @@ struct StackScratch {
 };
 
 // The weights that the launches behind a layer's attention stream, as far as kAheadBytes go: W_O, then the SwiGLU pair (four rows of
-// either half for a workgroup of launch_gemv). A token step of 4 + 4 layers of 2048 over 2000 rows 283 us, 275 with it, over
-// 200 rows 275 and 266, of 1024-wide layers over 500 rows 172 and 164; with 9, 24 or 32 MB 277 to 278. Only for attention over no
-// more than the L2s hold, which would push the weights out again: over 3500 rows (28 MB) 288.5 and 287.5, over 12000 (98 MB) 327
-// either way.
-constexpr int64_t kAheadBytes = 16 << 20, kShortCache = 32 << 20;
+// either half for a workgroup of launch_gemv). A token step of 4 + 4 layers of 2048 over 1900 rows 273.0 us, 268.0 with it, over
+// 200 rows 265.2 and 259.5, of 1024-wide layers over 500 rows 169.3 and 165.3; with 8, 24 or 32 MB 270, 270 and 277. Only for
+// attention over a short cache: a longer one pushes the weights out of the L2s (32 MB in all) again, and its launch has less
+// bandwidth to spare. The line lies behind where the two sides cross, the cross-decoder's launches not reading ahead and reading,
+// of 16 heads: 2200 rows (18 MB) 274.5 and 272.0, 2600 (21 MB) 274.7 and 274.7, 3000 (24.6 MB) 275.1 and 277.0, 3500 277.1 and
+// 280.7; of 8-bit rows 5500 (23.2 MB) 284.7 and 282.9.
+constexpr int64_t kAheadBytes = 16 << 20, kShortCache = 23 << 20;
 yoco::ReadAhead weights_ahead(const yoco_stack& st, const yoco_stack_layer& L, const yoco_kv_cache& c, int64_t rows) {
   yoco::ReadAhead a = {};
   if (rows > c.N_cap) rows = c.N_cap;

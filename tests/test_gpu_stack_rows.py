@@ -81,3 +81,27 @@ def test_a_token_is_normed_as_a_row_of_a_prompt(Hq, dm, ffn, vocab):
     got = torch.cat([st.decode_step(t, state) for t in toks[1:]])
     want = yb.norm_rows(st.embed[1:], st.final_ln, st.eps)[:, at]
     assert torch.equal(got, want), (got != want).sum().item()
+
+
+@pytest.mark.parametrize("cache,rows", [("bf16", 2944), ("bf16", 2945), ("int8", 5709), ("int8", 5710)])
+def test_token_steps_over_caches_around_what_counts_as_short(cache, rows):
+    """16 heads of up to 23 MB of rows: the cross-decoder's attention reads the weights behind it ahead; of a row more not."""
+    import copy
+
+    from paper_2405_05254_amd.stack import YocoStack
+    w = random_stack(16, 256, 264, 500)
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    K, V = (torch.randn(rows, 16, 128, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    logits = []
+    for native in (True, False):
+        st = YocoStack(copy.deepcopy(w), torch.bfloat16, glue_dtype=torch.bfloat16, cache_dtype=torch.int8 if cache == "int8" else torch.bfloat16)
+        if not native:
+            st._native = None
+        state = st.new_generation_state(rows)
+        for c in state["rings"]:
+            yoco.global_kv_write(c, K[:64], V[:64], 0, 0)
+        yoco.global_kv_write(state["cache"], K, V, 0, 0)
+        state["length"] = rows - 1                                     # the step stores the last row anew
+        logits.append(st.decode_step(torch.tensor(7, device="cuda"), state).double())
+    got, ref = logits
+    assert ((got - ref).norm() / ref.norm()).item() < 1.5e-2
