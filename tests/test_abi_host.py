@@ -16,6 +16,11 @@ from paper_2405_05254_amd import binding as yb
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+def torch_sees_a_gpu():
+    import torch
+    return torch.cuda.is_available()
+
+
 def declared_symbols():
     text = open(os.path.join(ROOT, "include", "yoco.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
@@ -119,6 +124,30 @@ def test_decode_splits_fill_the_chip():
         assert L.yoco_cross_attn_decode_workspace(C.byref(d), 24, C.byref(n), C.byref(s)) == 0
         assert B * 8 * s.value >= 256           # at least one workgroup per CU (256 CUs)
         assert n.value < 0.01 * 2 * B * 8 * N * 128 * 2   # partials cost < 1 % of the cache bytes
+
+
+def test_splits_to_spare_fit_the_static_scratch_as_the_others_do():
+    """yoco_cross_attn_decode_noalloc refuses what exceeds its scratch by the size query: splits to spare never push a shape past it,
+    and where they fit the call has them too (same bits as with a workspace of the queried size)."""
+    import random
+    L, rng, p, spare = yoco.lib(), random.Random(7), 0x7f0000000000, 0
+    n, s = C.c_size_t(), C.c_int()
+    for _ in range(4000):
+        G, Hkv, B = rng.choice([1, 2, 3, 4, 8, 9, 16, 17]), rng.choice([1, 2, 4, 8, 16]), rng.randint(1, 64)
+        d, dtype = rng.choice([(128, yoco.BF16)] * 2 + [(128, yoco.INT8), (64, yoco.BF16)])
+        c = yb._Cache()
+        c.k, c.v, c.B, c.Hkv, c.d, c.dtype, c.N_cap = p, p, B, Hkv, d, dtype, int(2 ** rng.uniform(8, 19))
+        assert L.yoco_cross_attn_decode_workspace(C.byref(c), G * Hkv, C.byref(n), C.byref(s)) == 0
+        a_split = B * G * Hkv * (d + 4) * 4
+        assert n.value == s.value * a_split
+        if n.value > yoco.NOALLOC_SCRATCH_BYTES:                                # returns before any device call
+            assert L.yoco_cross_attn_decode_noalloc(C.byref(c), p, p, p, G * Hkv, 1.0, None) == -4
+        least = s.value                                                         # sizes below the least are refused before anything is launched
+        while least > 1 and not torch_sees_a_gpu() and L.yoco_cross_attn_decode(C.byref(c), p, p, p, G * Hkv, 1.0, p, (least - 1) * a_split, None) != -4:
+            least -= 1
+        spare += least < s.value
+        assert 2 * least >= s.value and (least == s.value or (B >= 4 and c.N_cap >= 700 * least))
+    assert spare > 100 or torch_sees_a_gpu()
 
 
 def test_generation_calls_validate_before_launching():

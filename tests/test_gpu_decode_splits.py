@@ -83,24 +83,64 @@ def test_splits_meet_in_an_uncleared_workspace(dtype, Hq, Hkv, N_cap, lens, garb
 
 
 def test_a_workspace_without_splits_to_spare_is_enough():
-    """Splits to spare for a ragged batch of short sequences are used where the workspace holds them; half of it holds the others."""
+    """Splits to spare for a ragged batch of short sequences are used where the workspace holds them; half of it holds the others,
+    and nothing behind that half is touched."""
     B, Hkv, Hq, N = 8, 8, 24, 3000
     rng = np.random.default_rng(5)
     cache = yoco.KVCache(B, Hkv, D, N, torch.bfloat16)
     for plane in cache.planes():
         plane.copy_(torch.from_numpy(ys.normal(rng, tuple(plane.shape), 1.0, "bf16")))
     q = torch.from_numpy(ys.normal(rng, (B, Hq, D), 1.0, "bf16")).cuda().to(torch.bfloat16)
-    lens = torch.tensor([3000, 375, 0, 2999, 1600, 128, 2100, 900], dtype=torch.int64, device="cuda")
+    lens = [3000, 375, 0, 2999, 1600, 128, 2100, 900]
+    ln = torch.tensor(lens, dtype=torch.int64, device="cuda")
     nbytes, splits = yoco.cross_attn_decode_workspace(cache, Hq)
     if splits % 2:
         pytest.skip("no splits to spare on this many CUs")
-    whole, half = (yoco.cross_attn_decode(cache, q, lens, SCALE, torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda"))
-                   for n in (nbytes, nbytes // 2))
+    K, V = (p.float().cpu().numpy().transpose(0, 2, 1, 3) for p in cache.planes())
+    ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda")
+    for held in (nbytes // 2, nbytes):
+        o = yoco.cross_attn_decode(cache, q, ln, SCALE, ws[:held])
+        assert (ws[held:] == 0x5A).all()
+        for b, n in enumerate(lens):
+            if n == 0:
+                assert not o[b].any()
+                continue
+            st = ys.error_stats(o[b].float().cpu().numpy(), oracle.cross_attn(q[b:b + 1].float().cpu().numpy(), K[b, :n], V[b, :n], n - 1, SCALE)[0])
+            assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (held, b, n, st)
     with pytest.raises(yoco.YocoError):
-        yoco.cross_attn_decode(cache, q, lens, SCALE, torch.empty(nbytes // 2 - 16, dtype=torch.uint8, device="cuda"))
-    a, b = whole.float().cpu().numpy(), half.float().cpu().numpy()
-    st = ys.error_stats(a, b)
-    assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], st
+        yoco.cross_attn_decode(cache, q, ln, SCALE, ws[:nbytes // 2 - 16])
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,N_cap,splits,lens", [
+    ("int8", 24, 8, 128, 6000, 4, [5999, 6000, 3001] + [(i * 379) % 700 for i in range(14)]),    # 136 units of 8 bits: from 3000 rows a split on
+    ("int8", 24, 8, 128, 5999, 2, [5999, 3001] + [(i * 379) % 700 for i in range(15)]),          # ... a row less
+    ("bf16", 16, 1, 128, 22400, 62, [22400, 700, 0, 9000, 128, 1, 1400, 350]),                   # for a merge launch, which reads splits without rows too;
+    ("int8", 16, 1, 128, 22400, 62, [22400, 700, 0, 9000, 256, 1, 1400, 350]),                   # ... not 64: as many as the static scratch holds
+    ("bf16", 9, 1, 128, 22400, 64, [22400, 700, 0, 9000, 128, 1, 1400, 350]),
+    ("bf16", 24, 8, 64, 3000, 8, [3000, 0, 1, 2999, 129, 1500, 375, 8]),                         # kernels that cut every length alike
+])
+def test_splits_to_spare(dtype, Hq, Hkv, d, N_cap, splits, lens):
+    B, rng = len(lens), np.random.default_rng(N_cap + Hq)
+    cache = yoco.KVCache(B, Hkv, d, N_cap, torch.int8 if dtype == "int8" else torch.bfloat16)
+    cache.mem.zero_()
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    rows = [[ys.normal(rng, (n, Hkv, d), 1.0, "bf16") for _ in range(2)] for n in lens]
+    for b, (k, v) in enumerate(rows):
+        yoco.global_kv_write(cache, dev(k), dev(v), b, 0)
+    q = ys.normal(rng, (B, Hq, d), 1.0, "bf16")
+    nbytes, n_splits = yoco.cross_attn_decode_workspace(cache, Hq)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert n_splits == splits
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    o = yoco.cross_attn_decode(cache, dev(q), torch.tensor(lens, dtype=torch.int64, device="cuda"), 1 / math.sqrt(d), ws)
+    attend = oracle.cross_attn_int8 if dtype == "int8" else oracle.cross_attn
+    for b, n in enumerate(lens):
+        got = o[b].float().cpu().numpy()
+        if n == 0:
+            assert not got.any()
+            continue
+        st = ys.error_stats(got, attend(q[b:b + 1], *rows[b], n - 1, 1 / math.sqrt(d))[0])
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
 
 
 def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
