@@ -199,7 +199,9 @@ int yoco_cross_attn_prefill_workspace(const yoco_kv_cache* c, int64_t q_pos0, in
 
 /* Workspace for yoco_cross_attn_decode on this cache with Hq query heads:
  * `splits` partial results (running max, sum, d-vector in fp32) per
- * (sequence, query head). Host only. */
+ * (sequence, query head). Of a batch of four sequences or more up to half of
+ * the splits may be to spare for ragged lengths: a workspace that holds the
+ * others is accepted as well, and the call does without. Host only. */
 int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* bytes, int* splits);
 
 /*
@@ -215,10 +217,12 @@ int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* byt
  * splits of few heads (up to 16 splits of 4 heads per KV head, 8 of 8) merge in
  * the same launch: a split is published in the workspace under a tag of the
  * call, with device-scope stores, and whoever finds every split published
- * merges; nothing waits. Otherwise a second launch merges. How many splits a sequence gets depends on the lengths of the whole
- * batch, so that the same sequence in another batch may differ by the order of
- * fp32 sums. The workspace needs no clearing; calls that overlap in time must
- * not share one.
+ * merges; nothing waits. Otherwise a second launch merges. How many splits a
+ * sequence gets depends on the lengths of the whole batch and, where some are
+ * to spare, on whether workspace_bytes holds those, so that the same sequence
+ * in another batch or with a smaller workspace may differ by the order of fp32
+ * sums. The workspace needs no clearing; calls that overlap in time must not
+ * share one.
  */
 int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const int64_t* lens, int Hq,
                            float scale, void* workspace, size_t workspace_bytes, void* stream);
@@ -226,12 +230,13 @@ int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const
 /*
  * yoco_cross_attn_decode for callers that cannot allocate device memory or
  * carry a workspace: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc. Same operation, same kernels and bit-identical
- * results; the split partials live in a static device array inside the library
+ * harnesses that forbid hipMalloc. Same operation, same kernels and results
+ * bit-identical to those with a workspace of the queried size; the split partials live in a static device array inside the library
  * (YOCO_NOALLOC_SCRATCH_BYTES per GPU the library runs on, held until the
  * process ends) instead of a caller workspace. The call allocates and frees
  * nothing. A shape whose partials (yoco_cross_attn_decode_workspace) exceed the
- * array is refused with YOCO_ERR_WORKSPACE before anything is launched.
+ * array is refused with YOCO_ERR_WORKSPACE before anything is launched (splits
+ * to spare are no more than fit).
  * All calls on one GPU share that GPU's array: two calls that overlap in time
  * on one GPU (different streams or threads) race; calls on one stream are
  * ordered. Nothing in the array needs clearing between calls (a merge reads

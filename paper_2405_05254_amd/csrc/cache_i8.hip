@@ -321,7 +321,9 @@ __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, cons
   // (unconditional: behind a branch the compiler waits for all of it before the first use of the query. 8 heads x 32768
   // rows 18.7 -> 17.6 us a layer, 8 ragged sequences of up to 3000 rows 13.2 -> 11.9 us)
 
-  // The query of head n as two int8 operands: dims 64 half + 16 qg + j in byte j of half `half`.
+  // The query of head n as two int8 operands: dims 64 half + 16 qg + j in byte j of half `half`. Half the vector instructions of
+  // clamping, converting, masking and shifting each code, in a launch that lasts 12 us (1 x 24:8 heads x 32768 rows: 16.1 -> 15.9
+  // us a layer).
   i32x4 qhi[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, qlo[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   float qs = 0.f;
   {

@@ -3,12 +3,13 @@
 // optionally followed by the per-head GroupNorm of Eq. 7 (no learned affine)
 // and the multiplication by swish(gate) of the same equation.
 // fp32 arithmetic on the vector ALU for any storage dtype and head dims up to
-// 128. It is the decode step of the self-decoder (one row per sequence, the
-// state read and written once: HBM-bound) and the prefill path of every shape
-// the chunkwise MFMA kernels do not cover; the chunk size plays no part here
-// because the recurrent and chunkwise forms are the same function.
+// 128. It is the prefill path of every shape the chunkwise MFMA kernels do not
+// cover, and the decode step of the self-decoder (one row per sequence, the
+// state read and written once: HBM-bound), which at 128 x 128 has a kernel of
+// its own further down; the chunk size plays no part here because the
+// recurrent and chunkwise forms are the same function.
 //
-// One workgroup owns one (sequence, head) and keeps the whole state in
+// gret_recurrent_kernel: one workgroup owns one (sequence, head) and keeps the whole state in
 // registers, transposed: thread (rr = tid / 32, kk = tid % 32) holds
 // S^T[ev][4 kk .. 4 kk + 3] for the rows ev = rr + 8 r. A row of S^T is
 // contiguous along the key dimension, so the 32 lanes of a half wavefront
@@ -132,9 +133,11 @@ __global__ void __launch_bounds__(256) gret_recurrent_kernel(GretView a) {
 // a thread are reduced together (at the first two exchanges a lane keeps half of its rows), after which the eight lanes
 // kk / 8 of a half wavefront hold row rr + 32 (kk / 8). Measured against 4 wavefronts of 16 rows a thread, 13 layers:
 // 1 x 24 heads 94 -> 59 us, 8 x 24 113 -> 86, 16 x 24 174 -> 155 (4.2 TB/s of 50 MB a layer), 32 x 24 272 -> 248;
-// 8 wavefronts of 8 rows 67, 95, 168, 260. With the sums over lanes in registers instead of shuffles (lanes.h) 49, 79 and 150
-// at 1, 8 and 16 x 24; with one wavefront finishing the outputs instead of sixteen 143 at 16 x 24 (without any outputs 137,
-// and a launch that only scales as much memory 130). NT: nontemporal accesses, see launch_step.
+// 8 wavefronts of 8 rows 67, 95, 168, 260. With the sums over lanes in registers instead of shuffles (lanes.h) 53, 80 and 150 at 1, 8
+// and 16 x 24; with one wavefront finishing the outputs instead of sixteen 47, 74 and 143, 32 x 24 243 -> 240 (torch's in-place
+// product of the same states 24.5, 67, 149.5 and 265). States that 60 layers push out of the memory behind the L2s, us a layer: 8 x 24
+// 8.02 -> 7.59. Without GroupNorm the barrier and the one wavefront are all there is to it: 5.61 -> 5.52 a layer at 8 x 24 with the
+// gate, 1 x 24 3.39 -> 3.44, 8 x 24 5.54 -> 5.47 and 16 x 24 10.68 -> 10.76 without. NT: nontemporal accesses, see launch_step.
 constexpr int kStepRows = 4, kStepGroups = 128 / kStepRows;
 
 template <typename T, bool NT>

@@ -129,7 +129,7 @@ __device__ __forceinline__ u32x4 row_load(const void* row, unsigned bytes, int a
 // meet, and norms it itself. With the row in LDS (below) the workgroup's wavefronts wait for one another twice between the first
 // load and the first product, in a launch that is over in a few microseconds. The input is requested before the weights (loads
 // return in order), all of them at once: behind a norm the compiler has to be told, or it requests the weights when the norm is
-// formed, in two thirds of the registers (a token step, 4 + 4 layers of 2048: 274.1 us, 268.2 told; of 1024, two loads a row,
+// formed, in two thirds of the registers (a token, 4 + 4 layers of 2048: 274.1 us, 268.2 told; of 1024, two loads a row,
 // 165.1 and 165.6, so not there). The sum of the norm is taken in the order of a workgroup's four wavefronts (block_total), so
 // that a row has the same norm here as in norm_rows_kernel, bit for bit: as a token and as a row of a prompt.
 template <int CH, int ROWS, bool NORM, Epilogue EPI, typename Args>
@@ -298,11 +298,12 @@ hipError_t launch_short(const Args& g, dim3 grid, hipStream_t s) {
   return hipGetLastError();
 }
 // SHORT_ROWS, ROWS: outputs per wavefront where the input row is held in registers, and where it lies in LDS. Held in registers up
-// to 2048 elements behind a norm and up to 6144 without one; us, in LDS before and now:
-//   2048 x 2048 (8 MB) + residual 3.9 and 3.4, 2048 x 5632 6.2 and 6.0, 1024 x 5632 5.0 and 4.1; SwiGLU 2 x 5632 x 2048 (46 MB)
-//   9.7 and 9.2, 2 x 2816 x 1024 4.9 and 4.0; 6144 x 2048 6.5 and 6.0, 2048 x 2048 4.15 and 3.6; 32000 x 2048 (131 MB) 21.2 and
-//   20.9, 32000 x 1024 13.3 and 11.2. (A launch that does nothing takes 2.3, a plain read of 8, 23 and 46 MB 3.1, 5.0 and 8.3.)
-// Beyond: 3072 x 3072 5.5 and 6.0, SwiGLU 2 x 8448 x 3072 18.0 and 18.5; 2048 x 8192 + residual 8.2 and 8.3.
+// to 2048 elements behind a norm and up to 6144 without one. us a launch inside token steps of 4 + 4 layers (median of the kernel's own
+// time; every weight comes from HBM or from what attention's launch has read ahead), in LDS before and now: W_O 2048 x 2048 4.2 and
+// 2.6, W_2 2048 x 5632 6.2 and 5.9, SwiGLU 2 x 5632 x 2048 10.4 and 8.8, 6144 x 2048 behind a norm 6.7 and 6.3, 2048 x 2048 4.3 and 4.0;
+// of 1024-wide layers 3.2 and 2.2, 4.4 and 3.3, 5.3 and 3.4, 4.1 and 3.8, 3.4 and 3.0. Beyond, without a norm 2048 x 8192 is as good
+// either way; behind one rows of 2176 and 2560 would gain in registers too (a token, 3 + 3 layers: 246 us and 233, 275 and 263), 2816
+// little and 3072 nothing (306 and 302.5, 339 and 338).
 template <int SHORT_ROWS, int ROWS, bool NORM, Epilogue EPI, typename Args>
 hipError_t launch(const Args& g, int rows, hipStream_t s) {
   const dim3 grid((unsigned)((rows + 4 * SHORT_ROWS - 1) / (4 * SHORT_ROWS)));
@@ -318,9 +319,9 @@ hipError_t launch(const Args& g, int rows, hipStream_t s) {
 
 }  // namespace
 
-// One output per wavefront where something is added or gated (two measured slower: 2048 x 5632 5.8 us and 5.7, SwiGLU 9.75 and
-// 9.4), else two where the row is short (6144 x 2048 6.2 and 6.65 with one) or the classifier's outputs are tens of
-// workgroups per CU anyway.
+// One output per wavefront where something is added or gated, else two where the row is short or the classifier's outputs are tens
+// of workgroups per CU anyway. us a token, 4 + 4 layers of 2048 and of 1024: 266.7 and 164.7; with two where something is added
+// 270.5 and 171.2, where it is gated 272.9 and 173.9, with one everywhere 269.2 and 163.8.
 hipError_t launch_gemv(const GemvArgs& g, hipStream_t s) {
   if (g.K % 8 || g.K > kGemvMaxK || g.K <= 0 || g.N <= 0) return hipErrorInvalidValue;
   if (g.glu) return launch<1, 1, true, kGlu>(g, g.N, s);

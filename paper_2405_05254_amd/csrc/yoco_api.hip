@@ -86,13 +86,19 @@ int check_heads(int Hq, int Hkv) {
 // to be worth halving, so that the long sequences of a ragged batch can be split finer than the short ones (the kernel
 // decides, from the lengths on the device; 5 x 2500..20000 rows x 8 heads: 45 us instead of 52, but 32 x 125..1000 rows
 // 21 instead of 17). From four sequences on 700 rows are enough, up to three quarters as many units as CUs: there the long
-// sequences are what a launch waits for (us, lengths from an eighth of the capacity to all of it; bf16 21 x 8 heads x 4768 rows
-// 54.8, now 43.7, 24 x 8 x 2000 24.5 and 22.7, 12 x 8 x 3000 19.3 and 18.2; 8 bits, which had none to spare, 11 x 16 x 16614 91.9
-// and 71.4, 9 x 8 x 3079 12.2 and 11.1; three or four times as many give no more). At 500 rows 30 x 8 x 1000 takes 18.8 for 16.8, 232
-// units x 3141 36.1 for 35.8, and two sequences of 64:8 heads x 13668 16.4 for 15.1. In 8 bits only up to half as many units as CUs,
-// or from 3000 rows a split on, because the workgroups that a batch of equal lengths leaves without rows cost it (24 x 8 x 2000
-// 17.8 us, 18.7 with them, x 4000 31.6 and 32.2; x 6000 nothing). Not where the splits are then too many
-// to meet in the launch.
+// sequences are what a launch waits for (us, means over ten draws of lengths from an eighth of the capacity to all of it, without
+// and with; bf16 21 x 8:64 heads x 4768 rows 50.2 and 41.3, 12 x 8:24 x 3000 19.4 and 18.0, 24 x 8:24 x 2000 24.8 and 24.0, 8 x 8:24 x
+// 3000 14.1 and 13.95; 8 bits, which had none to spare, 11 x 16 x 16614 89.6 and 69.7, 9 x 8:24 x 3079 13.2 and 11.3). At
+// three quarters a step of rows more can turn it: 24 x 8:64 x 1420 20.1 and 19.95, x 1600 21.6 and 22.5, x 1800 24.25 and 24.0; beyond,
+// 232 units x 3141 35.8 and 36.1, 30 x 8 x 1000 16.8 and 18.8. From 500 to 700 rows it is one or the other (bf16 20 x 8:24 x 1200
+// 16.1 and 14.65, 9 x 8:24 x 2400 13.65 and 13.0, but 8 x 16 x 1200 13.4 and 13.65, 4 x 8:24 x 4500 12.15 and 12.55; 8 bits 12 x 8:24 x
+// 1800 10.8 and 10.7, 5 x 8:24 x 4000 10.5 and 10.8), and of two sequences 64:8 heads x 13668 take 15.1 and 16.4. Three or
+// four times as many give no more. In 8 bits only up to half as many units as CUs, or from 3000 rows a split on, because the
+// workgroups that a batch of equal lengths leaves without rows cost it (24 x 8 x 2000 17.8 and 18.7, x 4000 31.6 and 32.2, x 6000
+// 46.5 and 46.85). Not where the splits are then too many to meet in the launch. The kernels of other head dimensions, and of more
+// than 16 heads a KV head, share out the capacity and not the lengths; in bf16 the same rule is theirs, and theirs is the most to
+// gain, with a wavefront a head and little in flight in each (8 x 8:24 heads of 64 x 3000 rows 84.7 and 52.8 at equal, 77.4 and
+// 45.8 at ragged lengths, 5 x 8 of 64 x 8000 122 and 65.8, 12 x 4 of 256 x 6000 550 and 337).
 // `least`: the same without that, which a workspace has to hold; one that holds no more gets no more. A pure function of the
 // cache shape, the query heads and the device: the workspace query and the decode call agree.
 struct Splits {
