@@ -301,7 +301,8 @@ hipError_t launch_short(const Args& g, dim3 grid, hipStream_t s) {
 // to 2048 elements behind a norm and up to 6144 without one. us a launch inside token steps of 4 + 4 layers (median of the kernel's own
 // time; every weight comes from HBM or from what attention's launch has read ahead), in LDS before and now: W_O 2048 x 2048 4.2 and
 // 2.6, W_2 2048 x 5632 6.2 and 5.9, SwiGLU 2 x 5632 x 2048 10.4 and 8.8, 6144 x 2048 behind a norm 6.7 and 6.3, 2048 x 2048 4.3 and 4.0;
-// of 1024-wide layers 3.2 and 2.2, 4.4 and 3.3, 5.3 and 3.4, 4.1 and 3.8, 3.4 and 3.0. Beyond, without a norm 2048 x 8192 is as good
+// of 1024-wide layers 3.2 and 2.2, 4.4 and 3.3, 5.3 and 3.4, 4.1 and 3.8, 3.4 and 3.0. Over 131072 rows, where nothing is read ahead,
+// W_O and W_2 together 11.4 and 11.0, SwiGLU 9.7 and 9.0, 2048 x 2048 behind a norm 4.6 either way. Beyond, without a norm 2048 x 8192 is as good
 // either way; behind one rows of 2176 and 2560 would gain in registers too (a token, 3 + 3 layers: 246 us and 233, 275 and 263), 2816
 // little and 3072 nothing (306 and 302.5, 339 and 338).
 template <int SHORT_ROWS, int ROWS, bool NORM, Epilogue EPI, typename Args>
