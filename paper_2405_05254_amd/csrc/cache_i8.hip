@@ -273,21 +273,20 @@ __device__ __forceinline__ void step(State& st, const i32x4 (&qhi)[2], const i32
 // Workgroup = 4 wavefronts on one (sequence, KV head, split); the wavefronts take turns at its blocks,
 // the next block's loads in flight while the current one is reduced. q, o are bf16.
 // GMAX sizes the merge buffers (4 or 16 heads per KV head); G = Hq / Hkv <= GMAX is the real group size.
-template <int GMAX, typename... Ahead>
+template <int GMAX, typename... Last>
 __global__ void __launch_bounds__(256, 2) decode_i8_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                         const int64_t* __restrict__ lens, int64_t fixed_len, int Hq, float scale_log2,
-                                                        SplitOut out, Ahead... ahead) {
-  if (has_read_ahead(out.splits, ahead...)) return;
+                                                        SplitOut out, Last... last) {
+  if (has_read_ahead(out.splits, last...)) return;
   __shared__ float red_o[4][GMAX][kD];
   __shared__ float red_ml[4][GMAX][2];
   const int G = Hq / c.Hkv;
   __shared__ __attribute__((aligned(16))) float scales[4][2][64];
-  const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, qg = lane >> 4;
 
-  const SplitRows part = split_rows<256>(out, c, lens, fixed_len);
-  const int b = part.b, sp = part.sp;
+  const SplitRows part = split_rows<256>(out, c, lens, fixed_len, last...);
+  const int b = part.b, g = part.g, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * 64;                  // the wavefronts take turns at the split's blocks
@@ -442,9 +441,9 @@ hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* 
 }
 
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const ReadAhead& ahead, hipStream_t s) {
+                            float* ws, int splits, float inv_ragged, float inv_even, int even, int split, int places, unsigned long long tag, void* o, const ReadAhead& ahead, hipStream_t s) {
   const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, even, places, tag};
-  const dim3 grid(c.Hkv, c.B, splits + more_rows(c, ahead.workgroups)), block(256);
+  const dim3 grid = decode_grid(c, splits, split, ahead), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;
   const int G = Hq / c.Hkv;
@@ -453,7 +452,8 @@ hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t
     if (G <= 4) hipLaunchKernelGGL((decode_i8_kernel<4, decltype(more)...>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, more...);
     else hipLaunchKernelGGL((decode_i8_kernel<16, decltype(more)...>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, more...);
   };
-  if (ahead.workgroups) launch(ahead);
+  if (split) launch(SplitFirst{split});
+  else if (ahead.workgroups) launch(ahead);
   else launch();
   return hipGetLastError();
 }

@@ -92,21 +92,20 @@ __device__ __forceinline__ void step(State<G>& st, const u32x4 (&kq)[G], const u
 // The call also stores the new token's K/V row (k_new, v_new: [B,Hkv,128]) at slot lens[b] - 1 (modulo
 // the capacity for a rolling cache) and attends to it. The row is taken from registers wherever the stream
 // meets its slot, so nothing is read back that this launch writes.
-template <int G, int R, typename... Ahead>
+template <int G, int R, typename... Last>
 __global__ void __launch_bounds__(256) decode_bf16_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                           const int64_t* __restrict__ lens, int64_t fixed_len, int Hq, float scale_log2,
                                                           SplitOut out, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
-                                                          int ring, Ahead... ahead) {
-  if (has_read_ahead(out.splits, ahead...)) return;
+                                                          int ring, Last... last) {
+  if (has_read_ahead(out.splits, last...)) return;
   constexpr int kRowsPerStep = 4 * R;
   __shared__ float red_o[4][G][kD];
   __shared__ float red_ml[4][G][2];
-  const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = lane >> 4, seg = lane & 15;
 
-  const SplitRows part = split_rows<128>(out, c, lens, fixed_len);
-  const int b = part.b, sp = part.sp;
+  const SplitRows part = split_rows<128>(out, c, lens, fixed_len, last...);
+  const int b = part.b, g = part.g, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kRowsPerStep;        // the wavefronts take turns at the split's steps
@@ -290,12 +289,12 @@ __device__ __forceinline__ void mfma_softmax_pv(MState& st, const float (&s)[8],
   }
 }
 
-template <bool APPEND, int GMAX, typename... Ahead>
+template <bool APPEND, int GMAX, typename... Last>
 __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache c, const bf16_t* __restrict__ q,
                                                                const int64_t* __restrict__ lens, int64_t fixed_len, int Hq,
                                                                float scale_log2, SplitOut out, const bf16_t* __restrict__ k_new,
-                                                               const bf16_t* __restrict__ v_new, int ring, Ahead... ahead) {
-  if (has_read_ahead(out.splits, ahead...)) return;
+                                                               const bf16_t* __restrict__ v_new, int ring, Last... last) {
+  if (has_read_ahead(out.splits, last...)) return;
   // V staging of the four wavefronts (4 x 32 rows x 288 B), and the merge buffers beside it: a wavefront that is done writes
   // its state without waiting for the others (13 layers over 16 ragged sequences of up to 1000 rows 145.6 -> 142.5 us)
   constexpr int kStageBytes = kMRows * kVStride;
@@ -303,7 +302,6 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   __shared__ __attribute__((aligned(16))) float red_o[4][GMAX][kD];
   __shared__ float red_ml[4][GMAX][2];
   const int G = Hq / c.Hkv;
-  const int g = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = lane & 15, qg = lane >> 4;
   unsigned char* vst = smem + wave * kStageBytes;
@@ -311,20 +309,20 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
   // lane (head n, dim group qg) holds dims 32 t + 8 qg .. + 7 of its head's query for t = 0..3; requested for the sequence
   // that it mostly is before the lengths are there
   u32x4 qraw[4] = {};
-  auto load_q = [&](int b) {
+  auto load_q = [&](int b, int g) {
     if (n < G) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) qraw[t] = *(const u32x4*)(q + ((int64_t)b * Hq + g * G + n) * kD + t * 32 + qg * 8);
     }
   };
-  load_q(blockIdx.y);
-  const SplitRows part = split_rows<128>(out, c, lens, fixed_len);
-  const int b = part.b, sp = part.sp;
+  if constexpr (!kSplitsFirst<Last...>) load_q(blockIdx.y, blockIdx.x);
+  const SplitRows part = split_rows<128>(out, c, lens, fixed_len, last...);
+  const int b = part.b, g = part.g, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
 
-  if (__builtin_expect(b != (int)blockIdx.y, 0)) load_q(b);
+  if (kSplitsFirst<Last...> || __builtin_expect(b != (int)blockIdx.y, 0)) load_q(b, g);
   bf16x8_t qf[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) qf[t] = __builtin_bit_cast(bf16x8_t, qraw[t]);
@@ -437,10 +435,10 @@ bool decode_bf16_supported(const yoco_kv_cache& c, int Hq) {
 // KV head keeps the vector-ALU kernel, whose shorter prologue and merge win there (16 x 24 heads x 1024 rows: 36.1 us
 // against 40.9; at 3 heads per KV head, 2 x 8 x 2048 rows, 11.6 against 10.2 the other way round).
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                              float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
+                              float* ws, int splits, float inv_ragged, float inv_even, int even, int split, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
                               const ReadAhead& ahead, hipStream_t s) {
   const SplitOut out = {ws, (bf16_t*)o, splits, inv_ragged, inv_even, even, places, tag};
-  const dim3 grid(c.Hkv, c.B, splits + more_rows(c, ahead.workgroups)), block(256);
+  const dim3 grid = decode_grid(c, splits, split, ahead), block(256);
   const float sl2 = scale * kLog2e;
   const bf16_t* qp = (const bf16_t*)q;
   const bf16_t* kn = (const bf16_t*)k_new;
@@ -457,7 +455,8 @@ hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64
     else if (G <= 4) go(&decode_bf16_mfma_kernel<true, 4, decltype(more)...>);
     else go(&decode_bf16_mfma_kernel<true, kGMax, decltype(more)...>);
   };
-  if (ahead.workgroups) launch(ahead);
+  if (split) launch(SplitFirst{split});
+  else if (ahead.workgroups) launch(ahead);
   else launch();
   return hipGetLastError();
 }

@@ -10,6 +10,8 @@
 // device-coherent level, so the last one to publish sees all tags; two that see them both write the same bits. None
 // waits for another.
 #pragma once
+#include <type_traits>
+
 #include "lanes.h"
 #include "yoco_common.h"
 
@@ -43,7 +45,7 @@ struct SplitOut {
 // ends together (8 sequences of 375 to 3000 rows x 8 KV heads: the longest no longer runs on as many workgroups as the
 // shortest). GRAIN: what a split's rows are a multiple of (a step of each of its four wavefronts).
 struct SplitRows {
-  int b, sp;                 // sequence and split
+  int b, g, sp;              // sequence, KV head and split
   int64_t lo, hi;            // rows of this split, lo >= hi: nothing to do
   int splits;                // of this sequence; 0: the sequence is empty, split 0 stores zeros
   float total;               // rows of the whole batch (of its capacity where nothing is split)
@@ -96,17 +98,40 @@ __device__ __forceinline__ int one_length_splits(int len, int most, bool meets) 
   return n > 1 && (!meets || steps - about_ceil_div(steps, n) >= (GRAIN < 256 ? 3 : 2)) ? n : 1;
 }
 
-template <int GRAIN>
-__device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_kv_cache& c, const int64_t* lens, int64_t fixed_len) {
+// A decode kernel's last parameter, or none: ReadAhead, what the workgroups behind those of the splits read, or SplitFirst, that only
+// the first pairs of sequence and KV head are split. (A parameter, and a kernel, of its own: as an argument that is never used
+// either cost the others up to 3 %.)
+template <typename... Last>
+constexpr bool kSplitsFirst = (std::is_same<Last, SplitFirst>::value || ...);
+template <int GRAIN, typename... Last>
+__device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_kv_cache& c, const int64_t* lens, int64_t fixed_len, const Last&... last) {
   // 32-bit arithmetic: 2^31 rows of 132 bytes and more do not fit any GPU this runs on
   auto clamp_len = [&](int64_t n) { return (int)(n < 0 ? 0 : n > c.N_cap ? c.N_cap : n); };
   const int B = c.B;
   SplitRows r;
   r.b = blockIdx.y;
+  r.g = blockIdx.x;
   r.sp = blockIdx.z;
   int len, n = 1;
   r.total = (float)B * (float)c.N_cap;               // unsplit: nothing depends on the other lengths
-  if (out.splits == 1 || !lens || B == 1) {
+  if constexpr (kSplitsFirst<Last...>) {
+    // The splits come first: of a CU's two workgroups the first is the faster one, and theirs have a meeting before them (16 x 24 heads x
+    // 1024 rows, last, 35.9 us; first 34.3).
+    const int parts = (last.split, ...) * out.splits;
+    int unit = blockIdx.x;
+    const bool split = unit < parts;
+    if (split) {
+      const int u = __builtin_amdgcn_readfirstlane(unit / out.splits);
+      r.sp = unit - u * out.splits;
+      unit = u;
+    } else {
+      unit += (last.split, ...) - parts;
+    }
+    r.b = __builtin_amdgcn_readfirstlane(unit / c.Hkv);
+    r.g = unit - r.b * c.Hkv;
+    len = clamp_len(lens ? lens[r.b] : fixed_len);
+    if (split) n = one_length_splits<GRAIN>(len, out.splits, true);
+  } else if (out.splits == 1 || !lens || B == 1) {
     len = clamp_len(lens ? lens[r.b] : fixed_len);
     if (out.splits > 1) {
       r.total = (float)len * (float)B;
@@ -238,13 +263,12 @@ __device__ __forceinline__ void read_ahead(const ReadAhead& w, int splits) {
         }
 }
 
-// A decode kernel's last parameter, or none (as an argument that is never used it cost the other launches up to 2 %). True for a
-// workgroup that has read ahead and is done.
-template <typename... Ahead>
-__device__ __forceinline__ bool has_read_ahead(int splits, const Ahead&... ahead) {
-  if constexpr (sizeof...(Ahead) > 0) {
+// True for a workgroup that has read ahead and is done.
+template <typename... Last>
+__device__ __forceinline__ bool has_read_ahead(int splits, const Last&... last) {
+  if constexpr ((std::is_same<Last, ReadAhead>::value || ...)) {
     if ((int)blockIdx.z < splits) return false;
-    (read_ahead(ahead, splits), ...);
+    (read_ahead(last, splits), ...);
     return true;
   }
   return false;

@@ -105,8 +105,12 @@ struct Splits {
   int even, most, least;
   float inv_ragged, inv_even;   // 1 / how many workgroups a batch of ragged, of equal lengths should make
   int alike;                    // splits of each sequence of one length
+  int split, parts;             // the first `split` pairs of sequence and KV head are split into `parts`, where no other is
   int places;                   // ragged: splits, over the batch, that have a CU of their own for each KV head; 0: not asked
 };
+
+// Rows from which on the units that are over are split into more than two parts: window caches, whose rows seldom differ, and others.
+constexpr int64_t kRingPartRows = 512, kPartRows = 640;
 
 Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   const int cus = yoco::compute_units();
@@ -127,9 +131,22 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   // with part of the chip idle (384 units on 256 CUs measured 5.7 TB/s at 4096 rows). Two to four splits per unit
   // make the count a multiple again, as long as a split keeps at least 1024 rows (384 units of 1024 rows: 35.9 us
   // unsplit, 36.7 at two).
+  // Else, up to twice as many units as CUs, only the units that are over are split, into as many parts as give every CU one whole
+  // unit and at most one part, up to eight of 128 rows or more (us a layer, unsplit and so: window caches 12 x 24 heads x 1024 rows
+  // 33.2 and 27.2, 16 x 24 36.0 and 34.0, 12 x 24 x 512, ragged, 17.8 and 15.3; bf16 33 x 8:24 x 2000 65.5 and 44.7, 40 x 8:24 x 3000, ragged,
+  // 83.8 and 60.1; 8 bits 33 x 8:24 x 1024 20.7 and 16.2, 48 x 8 x 1024 22.2 and 20.8). Two parts of fewer than 512 rows lose (24 x 16 x 512
+  // 19.5 and 20.8), and so do 8 bits below 1024 rows (40 x 8 x 512 12.2 and 12.8) and more units (80 x 8 x 1024, 8 bits, 63 and 71). Of ragged
+  // batches it depends on which sequences are over; from 640 rows on it gains in the mean of eight draws for every count of
+  // units tried (17 x 16 x 700 2 %, 36 x 8 x 900 12, 20 x 16 x 2500 17), at 512 it is one or the other (33 x 8 +5 %, 75 x 4 -6 %).
+  int64_t split = 0, parts = 1;
   if (s == 1 && units > cus && units % cus != 0) {
     for (int64_t t = 2; t <= 4; ++t)
       if ((units * t) % cus == 0 && c->N_cap / t >= 1024) { s = t; break; }
+    if (s == 1 && units < 2 * cus && (c->dtype == YOCO_BF16 || c->dtype == YOCO_INT8) && c->d == 128 && Hq / c->Hkv <= 16) {
+      parts = clamp(clamp(cus / (units % cus), 8), c->N_cap / 128);
+      while (parts > 1 && !meets((int)parts)) --parts;
+      if (parts > 1 && c->N_cap >= (c->dtype == YOCO_BF16 && parts > 2 ? kRingPartRows : 1024)) split = units % cus;
+    }
   }
   // What fitted the static scratch with splits of 512 rows still does.
   const int64_t coarse = clamp(clamp(wanted, (c->N_cap + 511) / 512), 256);
@@ -156,16 +173,17 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
     const int64_t twice = 2 * cus / units;
     if (c->dtype == YOCO_BF16 && 4 * units * n < 3 * cus && 2 * units * twice >= 3 * cus && twice <= least && c->N_cap / twice >= 1024) n = twice;
   }
-  return {(int)s, (int)most, (int)least, 1.f / (float)(units * s), 1.f / (float)(units * n), (int)n, units <= cus ? cus / c->Hkv : 0};
+  return {(int)s, (int)most, (int)least, 1.f / (float)(units * s), 1.f / (float)(units * n), (int)n, (int)split, (int)parts, units <= cus ? cus / c->Hkv : 0};
 }
 
 size_t partial_bytes(const yoco_kv_cache& c, int Hq, int splits) {
   return (size_t)c.B * Hq * splits * yoco::partial_stride(c.d) * sizeof(float);
 }
 // The splits of a decode call with `held` bytes of workspace.
-int plan_decode(const yoco_kv_cache& c, int Hq, size_t held, Splits* plan) {
+int plan_decode(const yoco_kv_cache& c, int Hq, size_t held, Splits* plan, bool ring) {
   *plan = decode_splits(&c, Hq);
   if (held < partial_bytes(c, Hq, plan->most)) plan->most = plan->least;
+  if (!ring && c.N_cap < kPartRows) plan->split = 0;
   const size_t need = partial_bytes(c, Hq, plan->most);
   return held < need ? fail(YOCO_ERR_WORKSPACE, "workspace %zu < %zu bytes", held, need) : YOCO_OK;
 }
@@ -191,18 +209,20 @@ unsigned long long next_tag() {
 // k_new / v_new (both null or both rows [B,Hkv,d] of the cache dtype): the new token's row is stored at slot
 // lens[b] - 1 (ring: modulo the capacity) by the same call and attended to.
 int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-               float* ws, const Splits& sp, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
+               float* ws, Splits sp, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
                int ring = 0, const yoco::ReadAhead& ahead = {}) {
   hipError_t e;
+  if (ahead.workgroups) sp.split = 0;                // one or the other
+  if (sp.split) sp.most = sp.parts;                  // where every pair has room for one split: no more than CUs, which are fewer
   const unsigned long long tag = yoco::decode_meets_in_launch(Hq / c.Hkv, sp.most) ? next_tag() : 0;
   if (c.dtype == YOCO_INT8) {
     if (!yoco::decode_i8_supported(c, Hq))
       return fail(YOCO_ERR_UNSUPPORTED, "%s: an 8-bit cache serves up to 16 query heads per KV head, not %d", what, Hq / c.Hkv);
     if (k_new) return fail(YOCO_ERR_UNSUPPORTED, "%s: no fused append into an 8-bit cache", what);
-    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, ahead, s);
+    e = yoco::launch_decode_i8(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.split, sp.places, tag, o, ahead, s);
     if (tag) return hip_result(e, what);
   } else if (yoco::decode_bf16_supported(c, Hq)) {
-    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.places, tag, o, k_new, v_new, ring, ahead, s);
+    e = yoco::launch_decode_bf16(c, q, lens, fixed_len, Hq, scale, ws, sp.most, sp.inv_ragged, sp.inv_even, sp.alike, sp.split, sp.places, tag, o, k_new, v_new, ring, ahead, s);
     if (tag) return hip_result(e, what);
   } else {
     if (k_new) {                                      // no fused path for this shape: append, then attend
@@ -550,7 +570,7 @@ int yoco_cross_attn_decode(const yoco_kv_cache* c, const void* q, void* o, const
     return fail(YOCO_ERR_ALIGNMENT, "pointer not 16-byte aligned");
   if (c->B > 65535) return fail(YOCO_ERR_UNSUPPORTED, "B %d exceeds the grid limit", c->B);
   Splits plan;
-  rc = plan_decode(*c, Hq, workspace_bytes, &plan);
+  rc = plan_decode(*c, Hq, workspace_bytes, &plan, false);
   if (rc) return rc;
   return run_decode(*c, q, o, lens, 0, Hq, scale, (float*)workspace, plan, (hipStream_t)stream, "cross_attn_decode");
 }
@@ -592,7 +612,7 @@ int yoco_swa_decode(const yoco_kv_cache* ring, const void* q, const void* k_new,
   if ((k_new == nullptr) != (v_new == nullptr)) return fail(YOCO_ERR_INVALID_ARG, "k_new and v_new must both be given or both be null");
   if (k_new && (!aligned16(k_new) || !aligned16(v_new))) return fail(YOCO_ERR_ALIGNMENT, "new row pointer not 16-byte aligned");
   Splits plan;
-  rc = plan_decode(*ring, Hq, workspace_bytes, &plan);
+  rc = plan_decode(*ring, Hq, workspace_bytes, &plan, true);
   if (rc) return rc;
   return run_decode(*ring, q, o, lens, 0, Hq, scale, (float*)workspace, plan, (hipStream_t)stream, "swa_decode", k_new, v_new, 1);
 }
@@ -687,7 +707,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
   const StackScratch t(*st, (char*)scratch);
   if (scratch_bytes < t.bytes) return fail(YOCO_ERR_WORKSPACE, "scratch %zu < %zu bytes", scratch_bytes, t.bytes);
   Splits plan, ring_plan;
-  rc = plan_decode(*cache, st->Hq, workspace_bytes, &plan);
+  rc = plan_decode(*cache, st->Hq, workspace_bytes, &plan, false);
   if (rc) return rc;
   const bool in_rings = self && !st->gret && st->n_self > 0;
   if (self && st->gret) {
@@ -705,7 +725,7 @@ int yoco_stack_step(const yoco_stack* st, const void* x, const yoco_kv_cache* ri
           rings[i].N_cap != rings[0].N_cap)
         return fail(YOCO_ERR_INVALID_ARG, "ring %d does not match the stack", i);
     }
-    rc = plan_decode(rings[0], st->Hq, workspace_bytes, &ring_plan);
+    rc = plan_decode(rings[0], st->Hq, workspace_bytes, &ring_plan, true);
     if (rc) return rc;
   }
 

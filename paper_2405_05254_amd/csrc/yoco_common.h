@@ -110,7 +110,7 @@ inline bool decode_meets_in_launch(int G, int splits) { return splits <= 1 || (G
 // Both decode launches leave the merged output in o when `tag` is not 0, else partial results for launch_decode_merge.
 // k_new / v_new ([B,Hkv,128] bf16, or null): also store and attend to the new token's row at slot lens[b] - 1.
 hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                              float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
+                              float* ws, int splits, float inv_ragged, float inv_even, int even, int split, int places, unsigned long long tag, void* o, const void* k_new, const void* v_new, int ring,
                               const ReadAhead& ahead, hipStream_t s);
 
 // 8-bit global cache (cache_i8.hip), head_dim 128: a plane per (sequence, KV head) is a run of 64-row blocks, each
@@ -131,6 +131,15 @@ inline unsigned more_rows(const yoco_kv_cache& c, int wanted) {
   const int64_t unit = row % 8 == 0 ? 1 : row % 4 == 0 ? 2 : row % 2 == 0 ? 4 : 8;
   return (unsigned)((wanted + row * unit - 1) / (row * unit) * unit);
 }
+// The other last parameter of the decode kernels: the first `split` pairs of sequence and KV head are cut into `splits` parts each, the
+// others are whole, in a grid of one dimension.
+struct SplitFirst {
+  int split;
+};
+inline dim3 decode_grid(const yoco_kv_cache& c, int splits, int split, const ReadAhead& ahead) {
+  if (split) return dim3((unsigned)(c.Hkv * c.B + split * (splits - 1)));
+  return dim3(c.Hkv, c.B, splits + more_rows(c, ahead.workgroups));
+}
 bool cache_i8_supported(int d);
 bool decode_i8_supported(const yoco_kv_cache& c, int Hq);
 // pos == null: rows [n,Hkv,128] of sequence b to slots pos0 ..; pos != null: one row per sequence to slot pos[b].
@@ -138,7 +147,7 @@ bool decode_i8_supported(const yoco_kv_cache& c, int Hq);
 hipError_t launch_kv_code_i8(const yoco_kv_cache& c, const void* k, const void* v, const float* row_scale, int b, int64_t pos0, int64_t n,
                              const int64_t* pos, int src_dtype, hipStream_t s);
 hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t* lens, int64_t fixed_len, int Hq, float scale,
-                            float* ws, int splits, float inv_ragged, float inv_even, int even, int places, unsigned long long tag, void* o, const ReadAhead& ahead, hipStream_t s);   // q, o bf16
+                            float* ws, int splits, float inv_ragged, float inv_even, int even, int split, int places, unsigned long long tag, void* o, const ReadAhead& ahead, hipStream_t s);   // q, o bf16
 
 // What stands between the attention calls of a whole bf16 stack (stack_glue.hip). One token: out = W x with W [N][K], the
 // input normalised first when gain != null; res: added behind the product; glu: W is [2 N][K] and output n is

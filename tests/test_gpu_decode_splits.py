@@ -143,6 +143,48 @@ def test_splits_to_spare(dtype, Hq, Hkv, d, N_cap, splits, lens):
         assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,N_cap,lens", [
+    ("bf16", 33, 33, 640, [640] * 8),                                  # 264 units on 256 CUs: eight of them in five splits of a step
+    ("bf16", 33, 33, 640, [640, 1, 0, 639, 129, 384, 385, 640]),       # ... the sequences that are over have other lengths
+    ("bf16", 33, 33, 700, [0, 700, 1, 700, 128, 256, 257, 512]),       # ... the first, of which eight units are split, is empty
+    ("bf16", 86, 43, 1024, [1024] * 7 + [1023]),                       # 344 units: 88 in two
+    ("bf16", 86, 43, 1023, [1023] * 8),                                # ... a row less
+    ("bf16", 51, 17, 1000, [1000] * 15 + [3]),
+    ("bf16", 264, 33, 1100, [1100] * 8),                               # 8 query heads: as many splits as meet in the launch
+    ("bf16", 297, 33, 1100, [1100] * 8),                               # 9: none do
+    ("bf16", 4, 4, 700, [700 - i for i in range(70)]),                 # more sequences than a wavefront has lanes
+    ("int8", 36, 36, 1024, [1024] * 8),                                # 288 units in eighths, of which a length has as many as it has steps
+    ("int8", 36, 36, 1024, [257, 1024, 0, 513, 1, 256, 1000, 64]),
+    ("int8", 36, 36, 1023, [1023] * 8),
+    ("int8", 96, 48, 1100, [1100] * 8),                                # 384 units: half of what is over, each
+])
+def test_units_that_are_over_are_split(dtype, Hq, Hkv, N_cap, lens):
+    B, rng = len(lens), np.random.default_rng(N_cap + Hq)
+    cache = yoco.KVCache(B, Hkv, D, N_cap, torch.int8 if dtype == "int8" else torch.bfloat16)
+    cache.mem.zero_()
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    rows = [[ys.normal(rng, (n, Hkv, D), 1.0, "bf16") for _ in range(2)] for n in lens]
+    for b, (k, v) in enumerate(rows):
+        yoco.global_kv_write(cache, dev(k), dev(v), b, 0)
+    q = ys.normal(rng, (B, Hq, D), 1.0, "bf16")
+    ln = torch.tensor(lens, dtype=torch.int64, device="cuda")
+    nbytes, splits = yoco.cross_attn_decode_workspace(cache, Hq)
+    assert splits == 1 or torch.cuda.get_device_properties(0).multi_processor_count != 256      # the partials of a few units fit one split of all
+    ws = torch.full((nbytes + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    o = yoco.cross_attn_decode(cache, dev(q), ln, SCALE, ws[:nbytes])
+    assert torch.equal(o, yoco.cross_attn_decode(cache, dev(q), ln, SCALE, ws[:nbytes]))
+    assert torch.equal(o, yoco.cross_attn_decode_noalloc(cache, dev(q), ln, SCALE, torch.empty_like(o)))
+    assert (ws[nbytes:] == 0xFF).all()
+    attend = oracle.cross_attn_int8 if dtype == "int8" else oracle.cross_attn
+    for b, n in enumerate(lens):
+        got = o[b].float().cpu().numpy()
+        if n == 0:
+            assert not got.any()
+            continue
+        st = ys.error_stats(got, attend(q[b:b + 1], *rows[b], n - 1, SCALE)[0])
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
+
+
 def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
     """A batch of more (sequence, head) units than CUs has one split per unit: its workspace serves the few-row call of
     one sequence, whose own split count would be larger."""
@@ -167,6 +209,9 @@ def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
     (16, 16, 1500, [5000, 3, 0, 700, 1499, 1500, 1501, 900]),       # splits to spare, the vector-ALU step
     (24, 8, 3000, [2999, 3000, 3001, 1, 128, 1700, 375, 9000]),     # ... the matrix-core step
     (16, 1, 700, [699, 701]),         # more than 8 heads per KV head
+    (33, 33, 512, [512, 5000, 3, 0, 511, 513, 256, 700]),           # 264 units: the eight that are over in splits
+    (86, 43, 1024, [5000, 1024, 1023, 1, 2000, 0, 129, 1025]),      # ... 88 of 344 in two, two query heads each
+    (99, 33, 640, [640, 639, 641, 0, 1, 384, 385, 6400]),           # ... the matrix-core step
 ])
 def test_rings_that_are_split_store_the_new_row_and_attend_to_it(Hq, Hkv, N_cap, tokens):
     B, rng = len(tokens), np.random.default_rng(N_cap)
