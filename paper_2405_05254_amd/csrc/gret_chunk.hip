@@ -53,15 +53,11 @@ struct SegArgs {
 
 __device__ __forceinline__ float lo_f(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float hi_f(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
-// (x0, x1) = hi + lo in packed bf16; the remainders as dot products of hi with (-1, 0) and (0, -1), one instruction each.
-// (The constants pass through registers: as a literal, the compiler hands (-1, 0) to the instruction as (0, -1).)
+// (x0, x1) = hi + lo in packed bf16. The remainders are differences, not dot products of hi with (-1, 0) and (0, -1), which are an instruction
+// fewer each: those add to the register that holds x, so that a state's x has to be copied first, and what reads them waits.
 __device__ __forceinline__ void split_bf16(float x0, float x1, unsigned& hi, unsigned& lo) {
-  unsigned first = 0x0000bf80u, second = 0xbf800000u;
-  asm("" : "+s"(first), "+s"(second));
   hi = pack_bf16(x0, x1);
-  const bf16x2 h = __builtin_bit_cast(bf16x2, hi);
-  lo = pack_bf16(__builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, first), x0, false),
-                 __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, second), x1, false));
+  lo = pack_bf16(x0 - lo_f(hi), x1 - hi_f(hi));
 }
 __device__ __forceinline__ f32x16 mfma(const u32x4& a, const u32x4& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
