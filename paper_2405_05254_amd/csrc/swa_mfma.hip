@@ -63,7 +63,6 @@ struct Args {
 // wavefront and query the maximum (raw scores) and the sum of the weights, [wave][32][2].
 constexpr int kPieceMl = kBM * kD;
 constexpr int kPieceFloats = kPieceMl + kBM * 2;
-constexpr int kMergeAhead = 4;
 
 // The key tiles that some row of query tile qt sees, and of n tiles the ones of piece p of `pieces` (none if hi < lo).
 struct Tiles {
@@ -378,29 +377,34 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
 }
 
 // ---- the merge of a query tile's pieces: o = sum_p 2^((m_p - M) c) o_p / sum_p 2^((m_p - M) c) l_p, in a fixed order.
-// A workgroup takes 32 dims of a query tile, its lanes what the attention kernel's lanes held. Bound by the partials, 66 KB
-// for each piece, which mostly come back from the memory behind the L2s.
+// A workgroup takes 8 RQ dims of a query tile, its lanes what the attention kernel's lanes held. Bound by the partials, 66 KB
+// for each piece, which mostly come back from the memory behind the L2s; where query tiles are few, by the trips there: a group of
+// pieces each, of as many as 64 registers hold. 16 dims a workgroup are twice the workgroups and half the trips, and gain
+// up to as many query tiles as an eighth of the CUs (us a call, with 32 dims and with 16: 9 rows x 3:1 heads over 3831 18.8 and 17.4,
+// 38 x 24 over 20108 45.4 and 44.3, 128 x 24 over 16000 48.0 and 46.8; but 69 x 64 heads over 1741, 64 tiles, 25.4 and 27.1). 8 dims gain nothing more.
+template <int RQ>
 __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
   const AttnView& a = g.a;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, lq = lane & 31;
-  const int qt = blockIdx.x, mb = blockIdx.y, head = blockIdx.z, b = head / a.Hq, h = head % a.Hq;
+  const int qt = blockIdx.x, mb = blockIdx.y / (4 / RQ), rq0 = blockIdx.y % (4 / RQ) * RQ, head = blockIdx.z, b = head / a.Hq, h = head % a.Hq;
   const int64_t iq = (int64_t)qt * kBM + wave * kNQ + lq;
   if ((int64_t)qt * kBM + wave * kNQ >= a.Tq) return;      // a wavefront without rows has stored nothing
   const float c = a.scale * kLog2e;
   const int n = tiles_of(a, qt).hi - tiles_of(a, qt).lo + 1, pieces = g.pieces;
   const float* const first = g.part + ((int64_t)head * g.n_qtiles + qt) * pieces * kPieceFloats;
   float M = kNegBig, L = 0.f;
-  f32x4 o[4] = {};
+  constexpr int kMergeAhead = 16 / RQ;
+  f32x4 o[RQ] = {};
   for (int p0 = 0; p0 < pieces; p0 += kMergeAhead) {       // a group's loads go out together
     f32x2 ml[kMergeAhead];
-    f32x4 x[kMergeAhead][4];
+    f32x4 x[kMergeAhead][RQ];
 #pragma unroll
     for (int i = 0; i < kMergeAhead; ++i) {
       const int p = p0 + i < pieces ? p0 + i : pieces - 1;
       const float* const part = first + (int64_t)p * kPieceFloats;
       ml[i] = *(const f32x2*)(part + kPieceMl + (wave * kNQ + lq) * 2);
 #pragma unroll
-      for (int rq = 0; rq < 4; ++rq) x[i][rq] = ((const f32x4*)part)[wave * 1024 + (mb * 4 + rq) * 64 + lane];
+      for (int rq = 0; rq < RQ; ++rq) x[i][rq] = ((const f32x4*)part)[wave * 1024 + (mb * 4 + rq0 + rq) * 64 + lane];
     }
     float m_new = M;
     bool live[kMergeAhead];
@@ -414,14 +418,14 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
     M = m_new;
     L *= alpha;
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq) o[rq] *= alpha;
+    for (int rq = 0; rq < RQ; ++rq) o[rq] *= alpha;
 #pragma unroll
     for (int i = 0; i < kMergeAhead; ++i) {
       if (!live[i]) continue;
       const float f = __builtin_amdgcn_exp2f((ml[i][0] - M) * c);
       L = fmaf(f, ml[i][1], L);
 #pragma unroll
-      for (int rq = 0; rq < 4; ++rq)
+      for (int rq = 0; rq < RQ; ++rq)
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[rq][e] = fmaf(f, x[i][rq][e], o[rq][e]);
     }
@@ -430,8 +434,8 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
   const float inv = 1.f / L;
   bf16_t* const og = (bf16_t*)a.o + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD + mb * 32 + hf * 4;
 #pragma unroll
-  for (int rq = 0; rq < 4; ++rq)
-    *(u32x2*)(og + rq * 8) = u32x2{pack_bf16(o[rq][0] * inv, o[rq][1] * inv), pack_bf16(o[rq][2] * inv, o[rq][3] * inv)};
+  for (int rq = 0; rq < RQ; ++rq)
+    *(u32x2*)(og + (rq0 + rq) * 8) = u32x2{pack_bf16(o[rq][0] * inv, o[rq][1] * inv), pack_bf16(o[rq][2] * inv, o[rq][3] * inv)};
 }
 
 // How many pieces a call's query tiles are cut into. A workgroup's walk over the keys is serial, so a call with few
@@ -544,7 +548,9 @@ hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_
     return hipGetLastError();
   }
   hipLaunchKernelGGL(swa_mfma_kernel<true>, dim3(g.total), dim3(kThreads), 0, s, g);
-  hipLaunchKernelGGL(swa_merge_kernel, dim3(g.n_qtiles, 4, a.Hq * a.B), dim3(kThreads), 0, s, g);
+  const unsigned heads = (unsigned)(a.Hq * a.B);
+  if (8 * (int64_t)g.n_qtiles * heads <= compute_units()) hipLaunchKernelGGL(swa_merge_kernel<2>, dim3(g.n_qtiles, 8, heads), dim3(kThreads), 0, s, g);
+  else hipLaunchKernelGGL(swa_merge_kernel<4>, dim3(g.n_qtiles, 4, heads), dim3(kThreads), 0, s, g);
   return hipGetLastError();
 }
 
