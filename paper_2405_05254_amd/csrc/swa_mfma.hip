@@ -443,20 +443,24 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
 // 46), and one whose workgroups are no multiple of the places (two a CU) waits for the CUs that hold two (2000 rows x 24
 // heads over 16000: 384 workgroups 457 us, in 4 pieces three full rounds, 423). The estimate is in us, from what was measured: a
 // 64-key tile takes 1.34 where a CU has one workgroup, 1.6 where some have two and 2.15 where all have; 5 for a launch and
-// the two ends of a walk; a merge 5 and 0.016 for each piece's way out and back. 30 shapes of 16 to 4096 rows are within a
+// the two ends of a walk; a merge 5, 0.016 for each piece's way out and back and 0.35 for every trip after the first (1000 rows x 1 head
+// 15.7 us without it, in sixteen pieces, 14.0 with, in eight; by 0.6, 49 x 24 heads over 9521 would have ten for nineteen,
+// 33.5 for 31.0). 30 shapes of 16 to 4096 rows are within a
 // tenth of their best count by it. A cut has to promise a twentieth, because it costs memory.
 constexpr int kMaxPieces = 32;
+// How many pieces the merge of so many query tiles reads in a trip.
+int merge_ahead(int64_t items) { return 8 * items <= compute_units() ? 8 : 4; }
 constexpr int64_t kMaxPieceWgs = 1536;         // bounds the partials at 102 MB
 float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
   const int64_t cus = compute_units(), places = 2 * cus;
-  constexpr float kEnds = 5.f, kAlone = 1.34f, kSome = 1.6f, kAll = 2.15f, kMerge = 5.f, kPiece = 0.016f;
+  constexpr float kEnds = 5.f, kAlone = 1.34f, kSome = 1.6f, kAll = 2.15f, kMerge = 5.f, kPiece = 0.016f, kTrip = 0.35f;
   const int64_t wgs = items * pieces, full = wgs / places, rest = wgs % places;
   auto tile = [&](int64_t n) { return n <= cus ? kAlone : kSome + (kAll - kSome) * (float)(n - cus) / (float)(places - cus); };
   const float longest = ceilf((float)n_max / (float)pieces), mean = n_mean / (float)pieces;
   float t = (float)full * (mean * kAll + kEnds) + (rest ? mean * tile(rest) + kEnds : 0.f);
   const float least = longest * tile(wgs < places ? wgs : places) + kEnds;
   if (t < least) t = least;
-  return pieces > 1 ? t + kMerge + kPiece * (float)wgs : t;
+  return pieces > 1 ? t + kMerge + kPiece * (float)wgs + kTrip * (float)((pieces - 1) / merge_ahead(items)) : t;
 }
 int pieces_for(const AttnView& a, int64_t room) {
   const int n_qtiles = (int)((a.Tq + kBM - 1) / kBM);
@@ -549,7 +553,7 @@ hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_
   }
   hipLaunchKernelGGL(swa_mfma_kernel<true>, dim3(g.total), dim3(kThreads), 0, s, g);
   const unsigned heads = (unsigned)(a.Hq * a.B);
-  if (8 * (int64_t)g.n_qtiles * heads <= compute_units()) hipLaunchKernelGGL(swa_merge_kernel<2>, dim3(g.n_qtiles, 8, heads), dim3(kThreads), 0, s, g);
+  if (merge_ahead((int64_t)g.n_qtiles * heads) == 8) hipLaunchKernelGGL(swa_merge_kernel<2>, dim3(g.n_qtiles, 8, heads), dim3(kThreads), 0, s, g);
   else hipLaunchKernelGGL(swa_merge_kernel<4>, dim3(g.n_qtiles, 4, heads), dim3(kThreads), 0, s, g);
   return hipGetLastError();
 }
