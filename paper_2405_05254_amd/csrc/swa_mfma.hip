@@ -3,8 +3,9 @@
 // yoco_cross_attn_prefill (Eq. 3: causal over the global cache, GQA) through
 // one kernel: a query at absolute position p sees keys j with p - C < j <= p.
 //
-// Workgroup = 4 wavefronts, 128 query rows of one head; wavefront w owns rows
-// 32w .. 32w+31. Keys are walked in tiles of 64, only tiles that intersect
+// Workgroup = 4 wavefronts, 128 query columns; wavefront w owns columns
+// 32w .. 32w+31. Columns are the rows of one head or, where n query heads share
+// a KV head and it pays (heads_for), of all n, a row's heads side by side. Keys are walked in tiles of 64, only tiles that intersect
 // some row's window are visited, and a wavefront skips the tiles that none of
 // its own rows can see; the mask is applied only on the tiles that need it.
 //
@@ -49,9 +50,27 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLazyLog2 = 8.0f;            // rescale only when the max grows by more than 2^8
 
+// Columns of a query tile: the rows of one query head, or, PACKED, of the n query heads that share a KV head, one head after another
+// within a row. n * row <= column < 2^31, so that row = mulhi(column, mul) >> shift is exact (mul d = 2^(32 + shift) + e, 0 < e <= 2^(shift + 1)).
+struct Heads {
+  int n;
+  unsigned mul;
+  int shift;
+};
+template <bool PACKED>
+__host__ __device__ __forceinline__ int64_t row_of(const Heads& hs, int64_t col) {
+  if (!PACKED) return col;
+#ifdef __HIP_DEVICE_COMPILE__
+  return (int64_t)(__umulhi((unsigned)col, hs.mul) >> hs.shift);
+#else
+  return (unsigned)col / (unsigned)hs.n;
+#endif
+}
+
 struct Args {
   AttnView a;
-  int n_qtiles;       // query tiles per (sequence, head)
+  Heads heads;
+  int n_qtiles;       // query tiles per sequence and head, or KV head where its query heads are packed
   int total;          // workgroups
   int64_t n_keys;     // keys that exist (rows beyond are never read)
   int pieces;         // a query tile's key tiles are shared out over so many workgroups
@@ -68,18 +87,20 @@ constexpr int kPieceFloats = kPieceMl + kBM * 2;
 struct Tiles {
   int lo, hi;
 };
-__host__ __device__ __forceinline__ Tiles tiles_of(const AttnView& a, int qt) {
-  const int64_t i0 = (int64_t)qt * kBM, p0 = a.q_pos0 + i0;
-  const int64_t rows = a.Tq - i0 < kBM ? a.Tq - i0 : kBM;
+template <bool PACKED>
+__host__ __device__ __forceinline__ Tiles tiles_of(const AttnView& a, const Heads& hs, int qt) {
+  const int64_t c0 = (int64_t)qt * kBM, cols = PACKED ? a.Tq * hs.n : a.Tq;
+  const int64_t c1 = (c0 + kBM < cols ? c0 + kBM : cols) - 1;
+  const int64_t p0 = a.q_pos0 + row_of<PACKED>(hs, c0), p1 = a.q_pos0 + row_of<PACKED>(hs, c1);
   const int64_t lo_key = p0 - a.window + 1 > 0 ? p0 - a.window + 1 : 0;
-  return {(int)(lo_key / kBN), (int)((p0 + rows - 1) / kBN)};
+  return {(int)(lo_key / kBN), (int)(p1 / kBN)};
 }
 __host__ __device__ __forceinline__ Tiles piece_of(Tiles t, int p, int pieces) {
   const int n = t.hi - t.lo + 1;
   return {t.lo + (int)((int64_t)n * p / pieces), t.lo + (int)((int64_t)n * (p + 1) / pieces) - 1};
 }
 
-template <bool SPLIT>
+template <bool SPLIT, bool PACKED>
 __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   // Two tile buffers as distinct arrays, so that the compiler can tell the
   // stores of the next tile from the operand reads of the current one.
@@ -98,7 +119,7 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   const int bid = blockIdx.x;
   const int per = g.total >> 3, rem = g.total & 7, xcd = bid & 7;
   const int logical = xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
-  const int G = a.Hq / a.Hkv;
+  const int G = PACKED ? 1 : a.Hq / a.Hkv;
   int hh = logical % G;
   int qt = g.n_qtiles - 1 - (logical / G) % g.n_qtiles;
   int outer = logical / (G * g.n_qtiles);
@@ -112,13 +133,13 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   }
   const int kvh = outer % a.Hkv;
   const int b = outer / a.Hkv;
-  const int h = kvh * G + hh;
+  const int h = kvh * G + hh;                           // PACKED: the KV head
 
-  const int64_t i0 = (int64_t)qt * kBM;                 // first query row of the workgroup
-  const int64_t p0 = a.q_pos0 + i0;                     // its absolute position
+  const int64_t i0 = (int64_t)qt * kBM;                 // first column of the workgroup
+  const int64_t cols = PACKED ? a.Tq * g.heads.n : a.Tq;
   const int64_t win = a.window;
   // key tiles that intersect the window of some row of the workgroup
-  Tiles tiles = tiles_of(a, qt);
+  Tiles tiles = tiles_of<PACKED>(a, g.heads, qt);
   if (SPLIT) {
     tiles = piece_of(tiles, piece, g.pieces);
     if (tiles.hi < tiles.lo) return;                    // fewer tiles than pieces: the merge knows
@@ -170,12 +191,17 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   };
 
   // ---- Q^T fragments (B operand): lane holds query lq, dims ks*16 + hf*8 .. +8
-  const int64_t iw = i0 + wave * kNQ;                   // first row of the wavefront
-  int64_t iq = iw + lq;
-  const bool q_valid = iq < a.Tq;
-  const bool any_row = iw < a.Tq;
-  if (!q_valid) iq = a.Tq - 1;
-  const bf16_t* qg = (const bf16_t*)a.q + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD;
+  const int64_t iw = i0 + wave * kNQ;                   // first column of the wavefront
+  const bool any_row = iw < cols;
+  struct Place {
+    int64_t row, at;                                    // elements from the sequence's first query
+  };
+  auto place_of = [&](int lane_q) -> Place {            // columns past the end repeat the last one
+    const int64_t col = iw + lane_q < cols ? iw + lane_q : cols - 1, row = row_of<PACKED>(g.heads, col);
+    return {row, row * a.q_stride_t + (PACKED ? h * g.heads.n + (col - row * g.heads.n) : h) * kD};
+  };
+  const Place own = place_of(lq);
+  const bf16_t* qg = (const bf16_t*)a.q + b * a.q_stride_b + own.at;
   bf16x8 qf[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qg + ks * 16 + hf * 8));
@@ -199,10 +225,12 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_o[mb][r] = 0.f;
 
-  // wave's first position, relative to tile jt_lo; a wavefront without rows lies before all keys, so that it stages tiles and
-  // multiplies nothing
-  const int pw_lo = any_row ? (int)(p0 + wave * kNQ - (int64_t)jt_lo * kBN) : -(1 << 29);
-  const int pq_rel0 = pw_lo + lq;                                        // this lane's query, same origin
+  // the wavefront's first and last position, relative to tile jt_lo; one without rows lies before all keys, so that it stages tiles
+  // and multiplies nothing
+  const int64_t origin = (int64_t)jt_lo * kBN - a.q_pos0;
+  const int pw_lo = any_row ? (int)(row_of<PACKED>(g.heads, iw) - origin) : -(1 << 29);
+  const int pw_hi = !PACKED ? pw_lo + kNQ - 1 : any_row ? (int)(row_of<true>(g.heads, iw + kNQ < cols ? iw + kNQ - 1 : cols - 1) - origin) : -(1 << 29);
+  const int pq_rel0 = PACKED ? (int)(own.row - origin) : pw_lo + lq;      // this lane's query, same origin
   const int win32 = win > (1 << 30) ? (1 << 30) : (int)win;
 
   // ---- prologue: tile of step 0 into buffer a, tile of step 1 in flight
@@ -228,11 +256,11 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
     const int jt = tile_of(st);
     const int j0r = (jt - jt_lo) * kBN;                 // tile's first key, relative origin
     // does some row of this wavefront see some key of the tile? / every row every key?
-    const bool need = (j0r <= pw_lo + kNQ - 1) && (j0r + kBN - 1 > pw_lo - win32);
-    const bool full = (j0r + kBN - 1 <= pw_lo) && (j0r > pw_lo + kNQ - 1 - win32);
+    const bool need = (j0r <= pw_hi) && (j0r + kBN - 1 > pw_lo - win32);
+    const bool full = (j0r + kBN - 1 <= pw_lo) && (j0r > pw_hi - win32);
     // the same for the two 32-key halves: on edge tiles a wavefront multiplies only the halves it needs
     const bool need0 = need && (j0r + 31 > pw_lo - win32);
-    const bool need1 = need && (j0r + 32 <= pw_lo + kNQ - 1);
+    const bool need1 = need && (j0r + 32 <= pw_hi);
     const bool both = need0 && need1;
     const bool stage = st + 1 < n_t, prefetch = st + 2 < n_t;
     lds_char* kb = (lds_char*)k_cur;
@@ -351,7 +379,7 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   if (!any_row) return;
   const float l_tot = l_lane + other_half(l_lane);
   if (SPLIT) {                                           // unnormalised, in the order that the lanes hold it: 1 KiB a store
-    float* const part = g.part + ((((int64_t)b * a.Hq + h) * g.n_qtiles + qt) * g.pieces + piece) * kPieceFloats;
+    float* const part = g.part + ((((int64_t)b * (PACKED ? a.Hkv : a.Hq) + h) * g.n_qtiles + qt) * g.pieces + piece) * kPieceFloats;
     f32x4* const po = (f32x4*)part + wave * 1024 + lane;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
@@ -363,8 +391,10 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   }
   // ---- normalise and store O (bf16, rounded once)
   const float inv = 1.f / l_tot;
-  if (q_valid) {
-    bf16_t* og = (bf16_t*)a.o + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD;
+  if (iw + lq < cols) {
+    int again = lq;
+    if (PACKED) asm volatile("" : "+v"(again));          // keeps the place out of registers across the walk
+    bf16_t* og = (bf16_t*)a.o + b * a.q_stride_b + place_of(again).at;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -382,15 +412,16 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
 // pieces each, of as many as 64 registers hold. 16 dims a workgroup are twice the workgroups and half the trips, and gain
 // up to as many query tiles as an eighth of the CUs (us a call, with 32 dims and with 16: 9 rows x 3:1 heads over 3831 18.8 and 17.4,
 // 38 x 24 over 20108 45.4 and 44.3, 128 x 24 over 16000 48.0 and 46.8; but 69 x 64 heads over 1741, 64 tiles, 25.4 and 27.1). 8 dims gain nothing more.
-template <int RQ>
+template <bool PACKED, int RQ>
 __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
   const AttnView& a = g.a;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, lq = lane & 31;
-  const int qt = blockIdx.x, mb = blockIdx.y / (4 / RQ), rq0 = blockIdx.y % (4 / RQ) * RQ, head = blockIdx.z, b = head / a.Hq, h = head % a.Hq;
-  const int64_t iq = (int64_t)qt * kBM + wave * kNQ + lq;
-  if ((int64_t)qt * kBM + wave * kNQ >= a.Tq) return;      // a wavefront without rows has stored nothing
+  const int qt = blockIdx.x, mb = blockIdx.y / (4 / RQ), rq0 = blockIdx.y % (4 / RQ) * RQ, head = blockIdx.z, heads = PACKED ? a.Hkv : a.Hq, b = head / heads, h = head % heads;
+  const int64_t col = (int64_t)qt * kBM + wave * kNQ + lq, cols = PACKED ? a.Tq * g.heads.n : a.Tq;
+  if ((int64_t)qt * kBM + wave * kNQ >= cols) return;      // a wavefront without rows has stored nothing
   const float c = a.scale * kLog2e;
-  const int n = tiles_of(a, qt).hi - tiles_of(a, qt).lo + 1, pieces = g.pieces;
+  const Tiles tiles = tiles_of<PACKED>(a, g.heads, qt);
+  const int n = tiles.hi - tiles.lo + 1, pieces = g.pieces;
   const float* const first = g.part + ((int64_t)head * g.n_qtiles + qt) * pieces * kPieceFloats;
   float M = kNegBig, L = 0.f;
   constexpr int kMergeAhead = 16 / RQ;
@@ -430,12 +461,52 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
         for (int e = 0; e < 4; ++e) o[rq][e] = fmaf(f, x[i][rq][e], o[rq][e]);
     }
   }
-  if (iq >= a.Tq) return;
+  if (col >= cols) return;
   const float inv = 1.f / L;
-  bf16_t* const og = (bf16_t*)a.o + b * a.q_stride_b + iq * a.q_stride_t + (int64_t)h * kD + mb * 32 + hf * 4;
+  const int64_t row = row_of<PACKED>(g.heads, col), query_head = PACKED ? h * g.heads.n + (col - row * g.heads.n) : h;
+  bf16_t* const og = (bf16_t*)a.o + b * a.q_stride_b + row * a.q_stride_t + query_head * kD + mb * 32 + hf * 4;
 #pragma unroll
   for (int rq = 0; rq < RQ; ++rq)
     *(u32x2*)(og + (rq0 + rq) * 8) = u32x2{pack_bf16(o[rq][0] * inv, o[rq][1] * inv), pack_bf16(o[rq][2] * inv, o[rq][3] * inv)};
+}
+
+Tiles tiles_for(const AttnView& a, const Heads& hs, int qt) { return hs.n > 1 ? tiles_of<true>(a, hs, qt) : tiles_of<false>(a, hs, qt); }
+int qtiles_for(const AttnView& a, const Heads& hs) { return (int)((a.Tq * hs.n + kBM - 1) / kBM); }
+int64_t units_for(const AttnView& a, const Heads& hs) { return (int64_t)a.B * (a.Hq / hs.n); }
+
+// Whether the query heads of a KV head share its query tiles. A tile of 128 columns is then 128 / n rows: its walk over the keys is that
+// much shorter at the diagonal and at the window's end (24:8 heads, window 1024: 96 % of the key tiles, window 512: 91), fewer
+// columns lie idle behind the last row, and walks differ less. us, a head each and so: 4 x 1532 rows x 24:8 77.5 and 73.2, 2 x 1598,
+// window 512, 38.8 and 33.2, 12 x 204 22.6 and 15.1, 8 x 655 x 32:8 66.5 and 54.3, 32491 rows, window 2048, 928 and 907; over a
+// cache 151 rows x 64:8 over 22574 172 and 144, 1323 x 24:8 over 2102 82.2 and 80.5.
+// A call that leaves the chip idle lasts as long as its longest walk, 1.34 a key tile and 0.55 for each wavefront that has columns (its
+// queries, its outputs and its share of the CU): a head's last rows on one or two wavefronts of many CUs are then better than on four of a
+// few (25 rows x 64:8 over themselves 4.9 and 6.7, 290 x 16:4 11.9 and 12.4, 18 x 32:8 over 3383, cut into pieces, 20.4 and 22.7; the
+// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). From 2500 key tiles on, or where the work is nearly the same, that no longer counts.
+constexpr Heads kOneHead = {1, 0, 0};
+Heads heads_for(const AttnView& a) {
+  const int n = a.Hq / a.Hkv;
+  if (n == 1 || a.Tq * n >= (1LL << 31) - kBM) return kOneHead;
+  int bits = 1;
+  while ((1LL << bits) < n) ++bits;
+  const Heads packed = {n, (unsigned)((1ULL << (31 + bits)) / n + 1), bits - 1};
+  if (qtiles_for(a, kOneHead) * units_for(a, kOneHead) > 2 * compute_units()) return packed;
+  int64_t sum[2];
+  float longest[2];
+  for (int i = 0; i < 2; ++i) {
+    const Heads& hs = i ? packed : kOneHead;
+    sum[i] = 0;
+    longest[i] = 0.f;
+    for (int qt = 0, n_qtiles = qtiles_for(a, hs); qt < n_qtiles; ++qt) {
+      const Tiles t = tiles_for(a, hs, qt);
+      const int64_t left = a.Tq * hs.n - (int64_t)qt * kBM;
+      const float us = 1.34f * (float)(t.hi - t.lo + 1) + 0.55f * (float)(left < kBM ? (left + kNQ - 1) / kNQ : kWaves);
+      if (us > longest[i]) longest[i] = us;
+      sum[i] += (t.hi - t.lo + 1) * units_for(a, hs);
+      if (i == 0 && sum[0] >= 2500) return packed;
+    }
+  }
+  return 10 * sum[1] >= 9 * sum[0] || longest[1] <= longest[0] + 0.3f ? packed : kOneHead;
 }
 
 // How many pieces a call's query tiles are cut into. A workgroup's walk over the keys is serial, so a call with few
@@ -462,14 +533,14 @@ float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
   if (t < least) t = least;
   return pieces > 1 ? t + kMerge + kPiece * (float)wgs + kTrip * (float)((pieces - 1) / merge_ahead(items)) : t;
 }
-int pieces_for(const AttnView& a, int64_t room) {
-  const int n_qtiles = (int)((a.Tq + kBM - 1) / kBM);
-  const int64_t items = (int64_t)n_qtiles * a.Hq * a.B;
+int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
+  const int n_qtiles = qtiles_for(a, hs);
+  const int64_t items = n_qtiles * units_for(a, hs);
   if (2 * items > kMaxPieceWgs) return 1;
   int n_max = 0;
   int64_t sum = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {
-    const Tiles t = tiles_of(a, qt);
+    const Tiles t = tiles_for(a, hs, qt);
     sum += t.hi - t.lo + 1;
     if (t.hi - t.lo + 1 > n_max) n_max = t.hi - t.lo + 1;
   }
@@ -488,38 +559,38 @@ int pieces_for(const AttnView& a, int64_t room) {
 
 // Where walks differ much (their mean is under three quarters of the longest: causal attention over up to twice the window)
 // and the launch is a few rounds of the chip's places, the heavier query tiles go first over all heads of an XCD, so that it
-// ends in short walks everywhere: 8 x 1000 rows x 16 heads 69.4 -> 56.4 us, 4 x 1500 x 24:8 77.1 -> 74.3, 4096 rows x 24 heads
-// without a window 145 -> 127, 3 x 1300 x 32:8 73.3 -> 63.8. But all of the XCD's KV heads are walked side by side then, and
+// ends in short walks everywhere: 8 x 1000 rows x 16 heads 69.4 -> 56.4 us, 4096 rows x 24 heads
+// without a window 145 -> 127. But all of the XCD's KV heads are walked side by side then, and
 // the fewer workgroups of one are in flight, the less of its key tiles comes from the L2 (one KV head after another, heavier
 // first, us): 59 x 1900 x 24 heads 1551 and 2174, 12 x 700 x 24 77 and 83, 14 x 1100 x 40 277 and 342, 16 x 4096 x 24 without a
 // window 2051 and 2343. In a longer launch the end matters less, too: 8 x 3000 x 24, nine rounds, 503 and 524. Query tiles in
 // fours gain for longer (12 x 500 x 24 61.3 and 52.7, 6 x 1000 x 40 118 and 109): dealt out head after head, the heavier ones
 // of all heads meet on the same CUs.
-// Where two or three query heads share a KV head more of its workgroups are in flight already: 24:8, 8 x 1000 86.3 and 79.1,
-// 10 x 1000, four rounds, 104 and 101, but 12 x 700, three and a half, 72.5 and 75.3. From four on there is a gain in the first
-// round, where the order says which two share a CU (64:8, 2 x 300 16.5 and 14.5; nine and more heads: none), and in a second
-// one of several KV heads an XCD (32:8: 4 x 1000 60.1 and 53.6, 8 x 1000, four rounds, 103 and 106; 16:4, 4 x 1500, two KV heads,
-// 49.5 and 51.7).
+// Where query heads share their KV head's tiles, more of its workgroups are in flight already, and less is to be had: nothing beyond a
+// round with two KV heads an XCD (4 x 1500 x 16:4 47.7 and 50.8), up to four rounds with three or four (3 x 1300 x 32:8 64.8 and 59.0, 4 x 1532 x
+// 24:8 78.4 and 73.2, 4 x 2225 x 24:8 119.7 and 115.8), with five to eight where the last round is at most half full (8 x 512 x 24:8 38.0
+// and 31.0, 8 x 1000 85.0 and 79.0, 8 x 655 x 32:8 54.3 and 55.6), with more where it is nearly empty (12 x 1018 x 16:8 86.0 and 79.5, 12 x 700 x
+// 24:8 68.0 and 72.6). A grouped call of a head each has one round at most: 2 x 300 x 64:8 16.5 and 14.5, nine and more heads none.
 // A head of three query tiles is left alone where it fills one and a half rounds (12 x 300 x 24 29.6 and 33.0) or nearly one
 // (6 x 300 x 24 17.2 and 18.6; 8 x 300, one and an eighth, 26.0 and 24.5), and so is a launch whose workgroups have a CU each.
 // Elsewhere one KV head follows another (32768 rows x 24 heads 553 us, heavier first 558; 2 x 4000, window 512, 81.8 and 84.2).
-int heavy_heads_for(const AttnView& a, int n_qtiles) {
-  const int64_t kv_heads = (int64_t)a.B * a.Hkv, wgs = (int64_t)n_qtiles * a.B * a.Hq, places = 2 * compute_units();
+int heavy_heads_for(const AttnView& a, const Heads& hs, int n_qtiles) {
+  const int64_t kv_heads = (int64_t)a.B * a.Hkv, wgs = n_qtiles * units_for(a, hs), places = 2 * compute_units();
   const int group = a.Hq / a.Hkv;
   if (kv_heads % 8 || n_qtiles > 256 || 2 * wgs <= places) return 0;
   if (n_qtiles <= 3 && (2 * wgs > 3 * places || (16 * wgs > 13 * places && wgs <= places))) return 0;
-  const bool few = group == 1    ? wgs <= 2 * places || (kv_heads <= 192 && wgs <= 7 * places) || (n_qtiles % 4 == 0 && wgs <= 3 * places)
-                   : group <= 3  ? kv_heads <= 128 && (wgs <= 3 * places || (n_qtiles >= 8 && wgs <= 4 * places))
-                   : wgs <= places ? group <= 8 && kv_heads >= 16
-                                   : group <= 7 && kv_heads >= 24 && kv_heads <= 64 && 8 * wgs <= 17 * places;
+  const int64_t rest = wgs % places;
+  const bool few = hs.n > 1     ? wgs <= places || (kv_heads >= 24 && wgs <= 4 * places && (kv_heads <= 32 || 8 * rest <= places || (kv_heads <= 64 && 2 * rest <= places)))
+                   : group == 1 ? wgs <= 2 * places || (kv_heads <= 192 && wgs <= 7 * places) || (n_qtiles % 4 == 0 && wgs <= 3 * places)
+                                : group <= 3 ? kv_heads <= 128 : group <= 8 && kv_heads >= 16;
   if (!few) return 0;
   int64_t sum = 0, longest = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {
-    const Tiles t = tiles_of(a, qt);
+    const Tiles t = tiles_for(a, hs, qt);
     sum += t.hi - t.lo + 1;
     if (t.hi - t.lo + 1 > longest) longest = t.hi - t.lo + 1;
   }
-  return 4 * sum < 3 * longest * n_qtiles ? a.B * a.Hq / 8 : 0;
+  return 4 * sum < 3 * longest * n_qtiles ? (int)(units_for(a, hs) / 8) : 0;
 }
 
 }  // namespace
@@ -534,27 +605,35 @@ bool swa_mfma_supported(const AttnView& a, int dtype) {
 }
 
 size_t swa_mfma_workspace(const AttnView& a) {
-  const int pieces = pieces_for(a, kMaxPieceWgs);
-  return pieces > 1 ? (size_t)((a.Tq + kBM - 1) / kBM) * a.Hq * a.B * pieces * kPieceFloats * sizeof(float) : 0;
+  auto bytes = [&](const Heads& hs) {
+    const int pieces = pieces_for(a, hs, kMaxPieceWgs);
+    return pieces > 1 ? (size_t)qtiles_for(a, hs) * units_for(a, hs) * pieces * kPieceFloats * sizeof(float) : 0;
+  };
+  const Heads hs = heads_for(a);
+  const size_t one = bytes(kOneHead), own = hs.n > 1 ? bytes(hs) : 0;        // never less than for a head each
+  return one > own ? one : own;
 }
 
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s) {
   Args g;
   g.a = a;
-  g.n_qtiles = (int)((a.Tq + kBM - 1) / kBM);
+  g.heads = heads_for(a);
+  g.n_qtiles = qtiles_for(a, g.heads);
   g.n_keys = a.q_pos0 + a.Tq;
   g.part = (float*)workspace;
-  g.pieces = workspace ? pieces_for(a, (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float)))) : 1;
-  g.total = g.n_qtiles * a.Hq * a.B * g.pieces;
-  g.heavy_heads = g.pieces == 1 ? heavy_heads_for(a, g.n_qtiles) : 0;
+  g.pieces = workspace ? pieces_for(a, g.heads, (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float)))) : 1;
+  const int64_t units = units_for(a, g.heads);
+  g.total = (int)(g.n_qtiles * units * g.pieces);
+  g.heavy_heads = g.pieces == 1 ? heavy_heads_for(a, g.heads, g.n_qtiles) : 0;
+  auto go = [&](auto kernel, dim3 grid) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, g); };
+  const bool packed = g.heads.n > 1;
   if (g.pieces == 1) {
-    hipLaunchKernelGGL(swa_mfma_kernel<false>, dim3(g.total), dim3(kThreads), 0, s, g);
+    go(packed ? &swa_mfma_kernel<false, true> : &swa_mfma_kernel<false, false>, dim3(g.total));
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(swa_mfma_kernel<true>, dim3(g.total), dim3(kThreads), 0, s, g);
-  const unsigned heads = (unsigned)(a.Hq * a.B);
-  if (merge_ahead((int64_t)g.n_qtiles * heads) == 8) hipLaunchKernelGGL(swa_merge_kernel<2>, dim3(g.n_qtiles, 8, heads), dim3(kThreads), 0, s, g);
-  else hipLaunchKernelGGL(swa_merge_kernel<4>, dim3(g.n_qtiles, 4, heads), dim3(kThreads), 0, s, g);
+  go(packed ? &swa_mfma_kernel<true, true> : &swa_mfma_kernel<true, false>, dim3(g.total));
+  if (merge_ahead(g.n_qtiles * units) == 8) go(packed ? &swa_merge_kernel<true, 2> : &swa_merge_kernel<false, 2>, dim3(g.n_qtiles, 8, (unsigned)units));
+  else go(packed ? &swa_merge_kernel<true, 4> : &swa_merge_kernel<false, 4>, dim3(g.n_qtiles, 4, (unsigned)units));
   return hipGetLastError();
 }
 

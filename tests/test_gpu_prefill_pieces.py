@@ -90,6 +90,50 @@ def test_window_prefill_whichever_tiles_go_first(B, T, Hq, Hkv, window):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("B,T,Hq,Hkv,window", [
+    (1, 128, 3, 1, 1024),        # whole tiles: 384 columns
+    (2, 299, 3, 1, 64),          # a column behind one, windows of a key tile
+    (1, 213, 9, 3, 1),           # a column before one, rows that see themselves
+    (3, 77, 5, 1, 40),           # wavefronts that begin in a row's heads, one without columns
+    (12, 204, 24, 8, 512),       # more workgroups than places, which a head each would need two rounds of
+    (1, 131, 64, 1, 1000),       # two rows a tile
+    (1, 140, 387, 3, 100),       # 129 heads: a row is more than a tile
+    (4, 1500, 14, 2, 512),       # windows of whole tiles
+    (8, 331, 16, 8, 300),        # heavier tiles first
+    (1, 290, 16, 4, 1024),       # a head each: its last rows are on two wavefronts
+    (1, 1100, 32, 8, 2000),
+])
+def test_query_heads_that_share_a_tile_match_the_oracle(B, T, Hq, Hkv, window):
+    rng = np.random.default_rng(T + Hq)
+    q = ys.normal(rng, (B, T, Hq, D), 1.0, "bf16")
+    k, v = (ys.normal(rng, (B, T, Hkv, D), 1.0, "bf16") for _ in range(2))
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    out = torch.full((B * T * Hq * D + 4096,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    o = yoco.swa_prefill(dev(q), dev(k), dev(v), window, SCALE, out=out[:-4096].view(B, T, Hq, D)).float().cpu().numpy()
+    assert torch.isnan(out[-4096:]).all()
+    for b in range(B):
+        st = ys.error_stats(o[b], oracle.swa(q[b], k[b], v[b], window, SCALE))
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, st)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,q_pos0,Tq", [
+    (24, 8, 20000, 43),          # 129 columns: the second tile has one
+    (24, 8, 20000, 42),          # 126
+    (5, 1, 30000, 128),          # whole tiles, in as many pieces as there can be
+    (64, 8, 9000, 151),
+    (7, 1, 0, 700),              # the first tiles see fewer key tiles than there are pieces
+    (130, 1, 3000, 9),           # a row is more than a tile
+])
+def test_query_heads_that_share_a_tile_in_pieces(Hq, Hkv, q_pos0, Tq):
+    test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, 0 if plan_of(Hq, Hkv, q_pos0, Tq) > 1 else 1)
+
+
+def plan_of(Hq, Hkv, q_pos0, Tq):
+    return plan(yoco.KVCache(2, Hkv, D, q_pos0 + Tq + 3, torch.bfloat16), q_pos0, Tq, Hq)
+
+
+@pytest.mark.gpu
 def test_under_capture_a_call_takes_no_scratch_of_its_own():
     cache, q, pos0, nbytes = _few_tiles(Tq=40, Hq=8)
     kv = [p[0].transpose(0, 1).float().cpu().numpy() for p in cache.planes()]
