@@ -5,7 +5,7 @@
 // including j, a chunk of rows that finds the state S before it computes
 //   O = scale * ((Q K^T * D) V + (Q S) * 2^(G_j)),   D(j,k) = 2^(G_j - G_k), k <= j
 //   S <- 2^(G_last) S + K^T (V * 2^(G_last - G_j))
-// The sequence is cut into segments, about two workgroups' worth per CU over all heads, and a segment into chunks of 64
+// The sequence is cut into segments, one or two workgroups' worth per CU over all heads, and a segment into chunks of 64
 // rows. The caller's chunk size plays no part, but that it sizes the workspace and with it the most segments there can
 // be: another cut is another order of fp32 sums. Launches:
 //   1  what a segment adds to the state, for all segments but the last (reads K and V)
@@ -587,17 +587,44 @@ size_t gret_chunk_workspace(int B, int64_t T, int H, int chunk) {
          2 * align256(bh * nseg * kState * sizeof(float)) + align256(bh * nc * sizeof(float)) + align256(bh * nseg * sizeof(float));
 }
 
-// Chunks per segment: all segments resident at once at two workgroups per CU (512), each as long as that allows, because
-// a segment costs a state written, scanned and read; and no more segments than the workspace holds states for.
+// What `nseg` segments of `per` chunks take, in us, from what was measured: a launch of outputs 4.2 and one of segments 3.5; a chunk in both
+// 4.7 where the chip is nearly empty, 6.3 with a workgroup on every CU, 7.9 where the first CUs have two and 11.8 where all have, which is
+// what HBM and the vector units give; the scan, or each earlier segment that is folded; and the way out and back of a workgroup's state.
+float estimate_us(int64_t bh, int nseg, int per) {
+  constexpr float kOutputs = 4.2f, kSegments = 3.5f, kScan = 4.6f, kFolded = 1.5f, kStateUs = 0.02f, kCus = 256.f;
+  const float wgs = (float)(bh * nseg);
+  if (nseg == 1) return kOutputs + 4.7f * (float)per;
+  const float chunk = wgs <= kCus ? 4.7f + 1.6f * wgs / kCus : 7.9f + 3.9f * (wgs - kCus) / kCus;
+  const bool scanned = nseg - 1 > kFold;
+  return kOutputs + kSegments + (scanned ? kScan + kStateUs * wgs : kFolded * (float)(nseg - 1)) + kStateUs * wgs + chunk * (float)per;
+}
+// Chunks per segment: all segments resident at once, at most two workgroups per CU (512), and no more segments than the workspace
+// holds states for. Where that leaves a segment eight chunks there are as many (32768 rows x 24 heads, 10 segments 355 us, 21
+// segments 337; 4 x 5000 x 24, 4 and 5, 218 and 212). Of shorter ones a CU's second workgroup costs more in states than it
+// hides (us, two a CU and as here: 4000 rows x 16 heads 55.9 and 47.2, 2 x 3000 x 16 64.9 and 57.9, 4 x 1000 x 16 56.7 and 44.1,
+// 4 x 300 x 24, which one launch does then, 43.8 and 29.1), and the count is the one that the estimate finds, if it promises a
+// sixtieth (700 x 16 29.7 in 6 segments, 31.0 in 4).
 int gret_chunks_per_segment(int B, int64_t T, int H, int chunk) {
   const int64_t bh = (int64_t)B * H, n_chunks = (T + kC - 1) / kC;
   const int64_t nc = (T + chunk - 1) / chunk, old = gret_segment_chunks(B, H, (int)nc);
   const int64_t room = nc + 2 * ((nc + old - 1) / old);                      // states per head in the workspace: nseg - 1 and a copy of state_in
-  int64_t nseg = 512 / bh;
-  if (nseg > room) nseg = room;
-  if (nseg > n_chunks) nseg = n_chunks;
-  if (nseg < 1) nseg = 1;
-  return (int)((n_chunks + nseg - 1) / nseg);
+  int64_t most = 512 / bh;
+  if (most > room) most = room;
+  if (most > n_chunks) most = n_chunks;
+  if (most < 1) most = 1;
+  auto per_seg = [&](int64_t nseg) { return (int)((n_chunks + nseg - 1) / nseg); };
+  auto us_of = [&](int per) { return estimate_us(bh, (int)((n_chunks + per - 1) / per), per); };
+  int best = per_seg(most);
+  if (best >= 8) return best;
+  float us = 0.985f * us_of(best);
+  for (int64_t nseg = most - 1; nseg >= 1; --nseg) {
+    const float t = us_of(per_seg(nseg));
+    if (t < us) {
+      us = t;
+      best = per_seg(nseg);
+    }
+  }
+  return best;
 }
 
 hipError_t launch_gret_chunk(const GretView& a, int chunk, void* workspace, hipStream_t s) {

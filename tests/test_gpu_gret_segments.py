@@ -19,11 +19,15 @@ D = 128
     (1, 1, 1, 128, True, True, True),          # one row
     (3, 63, 2, 256, True, False, False),       # one chunk, one row short; one segment, no state before it
     (1, 64, 3, 128, False, True, True),
-    (2, 65, 1, 256, True, True, True),         # one row in the second chunk, two segments that launch 3 folds
+    (2, 65, 1, 256, True, True, True),         # one row in the second chunk
     (1, 257, 5, 128, False, False, True),      # four segments folded
     (1, 321, 2, 128, True, True, True),        # six chunks in six segments: the scan
     (1, 1100, 1, 1024, True, True, True),      # the workspace of large chunks holds few states: longer segments
     (2, 640, 130, 128, True, False, True),     # so many heads that a sequence is one segment
+    (1, 129, 2, 128, True, False, True),       # three chunks in three segments, of which launch 3 folds two
+    (4, 400, 24, 256, True, True, True),       # two segments of four chunks, the last of which is short of one
+    (4, 300, 24, 256, False, True, True),      # five chunks that one launch walks
+    (1, 700, 48, 256, True, True, False),      # a workgroup per CU for most of it
 ])
 def test_edges(B, T, H, chunk, norm, gate, carry):
     scale = 1.0 / math.sqrt(D)
