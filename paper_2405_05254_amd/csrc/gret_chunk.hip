@@ -603,7 +603,8 @@ float estimate_us(int64_t bh, int nseg, int per) {
 // segments 337; 4 x 5000 x 24, 4 and 5, 218 and 212). Of shorter ones a CU's second workgroup costs more in states than it
 // hides (us, two a CU and as here: 4000 rows x 16 heads 55.9 and 47.2, 2 x 3000 x 16 64.9 and 57.9, 4 x 1000 x 16 56.7 and 44.1,
 // 4 x 300 x 24, which one launch does then, 43.8 and 29.1), and the count is the one that the estimate finds, if it promises a
-// sixtieth (700 x 16 29.7 in 6 segments, 31.0 in 4).
+// sixtieth (700 x 16 29.7 in 6 segments, 31.0 in 4). With a CU for each workgroup anyway only the one launch is an alternative (4 x 250 x 24
+// 27.5 and 24.1; but 2 x 321 x 16 25.2 in 6 segments, 26.3 in 3).
 int gret_chunks_per_segment(int B, int64_t T, int H, int chunk) {
   const int64_t bh = (int64_t)B * H, n_chunks = (T + kC - 1) / kC;
   const int64_t nc = (T + chunk - 1) / chunk, old = gret_segment_chunks(B, H, (int)nc);
@@ -617,7 +618,8 @@ int gret_chunks_per_segment(int B, int64_t T, int H, int chunk) {
   int best = per_seg(most);
   if (best >= 8) return best;
   float us = 0.985f * us_of(best);
-  for (int64_t nseg = most - 1; nseg >= 1; --nseg) {
+  const bool second = bh * ((n_chunks + best - 1) / best) > 256;
+  for (int64_t nseg = second ? most - 1 : 1; nseg >= 1; --nseg) {
     const float t = us_of(per_seg(nseg));
     if (t < us) {
       us = t;
