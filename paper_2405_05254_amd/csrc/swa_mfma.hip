@@ -482,7 +482,8 @@ int64_t units_for(const AttnView& a, const Heads& hs) { return (int64_t)a.B * (a
 // A call that leaves the chip idle lasts as long as its longest walk, 1.34 a key tile and 0.55 for each wavefront that has columns (its
 // queries, its outputs and its share of the CU): a head's last rows on one or two wavefronts of many CUs are then better than on four of a
 // few (25 rows x 64:8 over themselves 4.9 and 6.7, 290 x 16:4 11.9 and 12.4, 18 x 32:8 over 3383, cut into pieces, 20.4 and 22.7; the
-// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). From 2500 key tiles on, or where the work is nearly the same, that no longer counts.
+// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). From 2500 key tiles on, or where the work is nearly the same, that no longer counts;
+// but in one round of the chip more than 512 rows have to save 3 % of them (4080 x 16:4 over 5932, 1 % saved, 298 and 306, 3939 x 16:4 95.5 and 98.0).
 constexpr Heads kOneHead = {1, 0, 0};
 Heads heads_for(const AttnView& a) {
   const int n = a.Hq / a.Hkv;
@@ -503,9 +504,10 @@ Heads heads_for(const AttnView& a) {
       const float us = 1.34f * (float)(t.hi - t.lo + 1) + 0.55f * (float)(left < kBM ? (left + kNQ - 1) / kNQ : kWaves);
       if (us > longest[i]) longest[i] = us;
       sum[i] += (t.hi - t.lo + 1) * units_for(a, hs);
-      if (i == 0 && sum[0] >= 2500) return packed;
+      if (i == 0 && sum[0] >= 2500 && a.Tq <= 4 * kBM) return packed;
     }
   }
+  if (sum[0] >= 2500) return a.Tq <= 4 * kBM || 100 * sum[1] < 97 * sum[0] ? packed : kOneHead;
   return 10 * sum[1] >= 9 * sum[0] || longest[1] <= longest[0] + 0.3f ? packed : kOneHead;
 }
 
