@@ -67,9 +67,13 @@ __host__ __device__ __forceinline__ int64_t row_of(const Heads& hs, int64_t col)
 #endif
 }
 
+// The kernels' last parameter where heads share tiles (PACKED), and no parameter where they do not: as one that is never used it cost a head
+// each 0.05 us a launch (18 rows x 64:8 heads 4.67 and 4.75, 43 x 24:8 5.57 and 5.63).
+__device__ __forceinline__ Heads heads_of() { return {1, 0, 0}; }
+__device__ __forceinline__ const Heads& heads_of(const Heads& shared) { return shared; }
+
 struct Args {
   AttnView a;
-  Heads heads;
   int n_qtiles;       // query tiles per sequence and head, or KV head where its query heads are packed
   int total;          // workgroups
   int64_t n_keys;     // keys that exist (rows beyond are never read)
@@ -100,13 +104,15 @@ __host__ __device__ __forceinline__ Tiles piece_of(Tiles t, int p, int pieces) {
   return {t.lo + (int)((int64_t)n * p / pieces), t.lo + (int)((int64_t)n * (p + 1) / pieces) - 1};
 }
 
-template <bool SPLIT, bool PACKED>
-__global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
+template <bool SPLIT, typename... Shared>
+__global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g, Shared... shared) {
+  constexpr bool PACKED = sizeof...(Shared) > 0;
   // Two tile buffers as distinct arrays, so that the compiler can tell the
   // stores of the next tile from the operand reads of the current one.
   __shared__ __attribute__((aligned(1024))) char k_a[kTileBytes], k_b[kTileBytes];
   __shared__ __attribute__((aligned(1024))) char v_a[kTileBytes], v_b[kTileBytes];
   const AttnView& a = g.a;
+  const Heads heads = heads_of(shared...);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wavefront-uniform: scalar branches below
   const int hf = lane >> 5, lq = lane & 31;
@@ -136,10 +142,10 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   const int h = kvh * G + hh;                           // PACKED: the KV head
 
   const int64_t i0 = (int64_t)qt * kBM;                 // first column of the workgroup
-  const int64_t cols = PACKED ? a.Tq * g.heads.n : a.Tq;
+  const int64_t cols = PACKED ? a.Tq * heads.n : a.Tq;
   const int64_t win = a.window;
   // key tiles that intersect the window of some row of the workgroup
-  Tiles tiles = tiles_of<PACKED>(a, g.heads, qt);
+  Tiles tiles = tiles_of<PACKED>(a, heads, qt);
   if (SPLIT) {
     tiles = piece_of(tiles, piece, g.pieces);
     if (tiles.hi < tiles.lo) return;                    // fewer tiles than pieces: the merge knows
@@ -197,8 +203,8 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
     int64_t row, at;                                    // elements from the sequence's first query
   };
   auto place_of = [&](int lane_q) -> Place {            // columns past the end repeat the last one
-    const int64_t col = iw + lane_q < cols ? iw + lane_q : cols - 1, row = row_of<PACKED>(g.heads, col);
-    return {row, row * a.q_stride_t + (PACKED ? h * g.heads.n + (col - row * g.heads.n) : h) * kD};
+    const int64_t col = iw + lane_q < cols ? iw + lane_q : cols - 1, row = row_of<PACKED>(heads, col);
+    return {row, row * a.q_stride_t + (PACKED ? h * heads.n + (col - row * heads.n) : h) * kD};
   };
   const Place own = place_of(lq);
   const bf16_t* qg = (const bf16_t*)a.q + b * a.q_stride_b + own.at;
@@ -228,8 +234,8 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
   // the wavefront's first and last position, relative to tile jt_lo; one without rows lies before all keys, so that it stages tiles
   // and multiplies nothing
   const int64_t origin = (int64_t)jt_lo * kBN - a.q_pos0;
-  const int pw_lo = any_row ? (int)(row_of<PACKED>(g.heads, iw) - origin) : -(1 << 29);
-  const int pw_hi = !PACKED ? pw_lo + kNQ - 1 : any_row ? (int)(row_of<true>(g.heads, iw + kNQ < cols ? iw + kNQ - 1 : cols - 1) - origin) : -(1 << 29);
+  const int pw_lo = any_row ? (int)(row_of<PACKED>(heads, iw) - origin) : -(1 << 29);
+  const int pw_hi = !PACKED ? pw_lo + kNQ - 1 : any_row ? (int)(row_of<true>(heads, iw + kNQ < cols ? iw + kNQ - 1 : cols - 1) - origin) : -(1 << 29);
   const int pq_rel0 = PACKED ? (int)(own.row - origin) : pw_lo + lq;      // this lane's query, same origin
   const int win32 = win > (1 << 30) ? (1 << 30) : (int)win;
 
@@ -412,15 +418,17 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g) {
 // pieces each, of as many as 64 registers hold. 16 dims a workgroup are twice the workgroups and half the trips, and gain
 // up to as many query tiles as an eighth of the CUs (us a call, with 32 dims and with 16: 9 rows x 3:1 heads over 3831 18.8 and 17.4,
 // 38 x 24 over 20108 45.4 and 44.3, 128 x 24 over 16000 48.0 and 46.8; but 69 x 64 heads over 1741, 64 tiles, 25.4 and 27.1). 8 dims gain nothing more.
-template <bool PACKED, int RQ>
-__global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
+template <int RQ, typename... Shared>
+__global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g, Shared... shared) {
+  constexpr bool PACKED = sizeof...(Shared) > 0;
   const AttnView& a = g.a;
+  const Heads shape = heads_of(shared...);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, lq = lane & 31;
   const int qt = blockIdx.x, mb = blockIdx.y / (4 / RQ), rq0 = blockIdx.y % (4 / RQ) * RQ, head = blockIdx.z, heads = PACKED ? a.Hkv : a.Hq, b = head / heads, h = head % heads;
-  const int64_t col = (int64_t)qt * kBM + wave * kNQ + lq, cols = PACKED ? a.Tq * g.heads.n : a.Tq;
+  const int64_t col = (int64_t)qt * kBM + wave * kNQ + lq, cols = PACKED ? a.Tq * shape.n : a.Tq;
   if ((int64_t)qt * kBM + wave * kNQ >= cols) return;      // a wavefront without rows has stored nothing
   const float c = a.scale * kLog2e;
-  const Tiles tiles = tiles_of<PACKED>(a, g.heads, qt);
+  const Tiles tiles = tiles_of<PACKED>(a, shape, qt);
   const int n = tiles.hi - tiles.lo + 1, pieces = g.pieces;
   const float* const first = g.part + ((int64_t)head * g.n_qtiles + qt) * pieces * kPieceFloats;
   float M = kNegBig, L = 0.f;
@@ -463,7 +471,7 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g) {
   }
   if (col >= cols) return;
   const float inv = 1.f / L;
-  const int64_t row = row_of<PACKED>(g.heads, col), query_head = PACKED ? h * g.heads.n + (col - row * g.heads.n) : h;
+  const int64_t row = row_of<PACKED>(shape, col), query_head = PACKED ? h * shape.n + (col - row * shape.n) : h;
   bf16_t* const og = (bf16_t*)a.o + b * a.q_stride_b + row * a.q_stride_t + query_head * kD + mb * 32 + hf * 4;
 #pragma unroll
   for (int rq = 0; rq < RQ; ++rq)
@@ -617,25 +625,29 @@ size_t swa_mfma_workspace(const AttnView& a) {
 }
 
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s) {
+  const Heads heads = heads_for(a);
   Args g;
   g.a = a;
-  g.heads = heads_for(a);
-  g.n_qtiles = qtiles_for(a, g.heads);
+  g.n_qtiles = qtiles_for(a, heads);
   g.n_keys = a.q_pos0 + a.Tq;
   g.part = (float*)workspace;
-  g.pieces = workspace ? pieces_for(a, g.heads, (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float)))) : 1;
-  const int64_t units = units_for(a, g.heads);
+  g.pieces = workspace ? pieces_for(a, heads, (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float)))) : 1;
+  const int64_t units = units_for(a, heads);
   g.total = (int)(g.n_qtiles * units * g.pieces);
-  g.heavy_heads = g.pieces == 1 ? heavy_heads_for(a, g.heads, g.n_qtiles) : 0;
-  auto go = [&](auto kernel, dim3 grid) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, g); };
-  const bool packed = g.heads.n > 1;
-  if (g.pieces == 1) {
-    go(packed ? &swa_mfma_kernel<false, true> : &swa_mfma_kernel<false, false>, dim3(g.total));
-    return hipGetLastError();
-  }
-  go(packed ? &swa_mfma_kernel<true, true> : &swa_mfma_kernel<true, false>, dim3(g.total));
-  if (merge_ahead(g.n_qtiles * units) == 8) go(packed ? &swa_merge_kernel<true, 2> : &swa_merge_kernel<false, 2>, dim3(g.n_qtiles, 8, (unsigned)units));
-  else go(packed ? &swa_merge_kernel<true, 4> : &swa_merge_kernel<false, 4>, dim3(g.n_qtiles, 4, (unsigned)units));
+  g.heavy_heads = g.pieces == 1 ? heavy_heads_for(a, heads, g.n_qtiles) : 0;
+  auto launch = [&](auto... shared) {
+    if (g.pieces == 1) {
+      hipLaunchKernelGGL((swa_mfma_kernel<false, decltype(shared)...>), dim3(g.total), dim3(kThreads), 0, s, g, shared...);
+      return;
+    }
+    hipLaunchKernelGGL((swa_mfma_kernel<true, decltype(shared)...>), dim3(g.total), dim3(kThreads), 0, s, g, shared...);
+    if (merge_ahead(g.n_qtiles * units) == 8)
+      hipLaunchKernelGGL((swa_merge_kernel<2, decltype(shared)...>), dim3(g.n_qtiles, 8, (unsigned)units), dim3(kThreads), 0, s, g, shared...);
+    else
+      hipLaunchKernelGGL((swa_merge_kernel<4, decltype(shared)...>), dim3(g.n_qtiles, 4, (unsigned)units), dim3(kThreads), 0, s, g, shared...);
+  };
+  if (heads.n > 1) launch(heads);
+  else launch();
   return hipGetLastError();
 }
 
