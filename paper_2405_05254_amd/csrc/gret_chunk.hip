@@ -55,7 +55,10 @@ __device__ __forceinline__ float lo_f(unsigned x) { return __uint_as_float(x << 
 __device__ __forceinline__ float hi_f(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
 // (x0, x1) = hi + lo in packed bf16. The remainders are differences, not dot products of hi with (-1, 0) and (0, -1), which are an instruction
 // fewer each: those add to the register that holds x, so that a state's x has to be copied first, and what reads them waits.
+// Differences of x as it is: where x is a product (weigh, scores times decay) the compiler would make them fused multiply-adds of the unrounded
+// product, whose low parts are others.
 __device__ __forceinline__ void split_bf16(float x0, float x1, unsigned& hi, unsigned& lo) {
+#pragma clang fp contract(off)
   hi = pack_bf16(x0, x1);
   lo = pack_bf16(x0 - lo_f(hi), x1 - hi_f(hi));
 }

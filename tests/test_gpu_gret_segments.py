@@ -53,3 +53,38 @@ def test_edges(B, T, H, chunk, norm, gate, carry):
             unit = max(1.0, float(np.abs(want).max()))
             st = ys.error_stats(got / unit, want / unit)
             assert np.isfinite(got).all() and st["max_abs"] <= most and st["mean_rel"] <= mean, (b, st)
+
+
+@pytest.mark.parametrize("T", [64, 129])         # the outputs' launch alone; the launch that adds up the first of three segments
+def test_what_is_split_is_the_rounded_product(T):
+    """Row j of the first chunk has a dim of K to itself, so that its row of the state is the high and the low part of v times its weight,
+    which is the same in all heads: there is one float32 weight by which all 128 x 16 of them are bf16(x) + bf16(x - bf16(x)) of the
+    rounded x = v w."""
+    H, rng = 16, np.random.default_rng(T)
+    bf16 = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.float32)).to(torch.bfloat16).float().numpy()  # noqa: E731
+    k, v = np.zeros((1, T, H, D), np.float32), bf16(rng.standard_normal((1, T, H, D)))
+    k[0, np.arange(64), :, np.arange(64)] = 1.0
+    lg = np.zeros((1, T, H), np.float32)
+    lg[0, :64] = -rng.exponential(0.04, (64, 1))
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    state = torch.empty((1, H, D, D), dtype=torch.float32, device="cuda")
+    ws = torch.empty(yoco.gret_prefill_workspace(1, T, H, D, D, 256, yoco.BF16), dtype=torch.uint8, device="cuda")
+    kd, vd = dev(k).to(torch.bfloat16), dev(v).to(torch.bfloat16)
+    yoco.gret_prefill(kd, kd, vd, dev(lg), 1.0, chunk=256, state_out=state, workspace=ws)
+    state = state.cpu().numpy()                                  # [.., dv, dk]
+    of_both = 0
+    for j in range(63):
+        got, x = state[0, :, :, j], v[0, j]
+        w0 = np.float32(np.exp(lg[0, j + 1:64, 0].astype(np.float64).sum()))
+        found = False
+        for ulps in sorted(range(-64, 65), key=abs):             # sums of 63 logarithms in fp32, below 8 in size: some 1e-6 of w
+            w = (w0.view(np.int32) + np.int32(ulps)).view(np.float32)
+            rounded, exact = x * w, x.astype(np.float64) * np.float64(w)
+            hi = bf16(rounded)
+            if np.array_equal(got, hi + bf16(rounded - hi)):
+                found = True
+                fused = (exact - hi).astype(np.float32)          # what a fused multiply-add gives
+                of_both += int((bf16(fused) != bf16(rounded - hi)).sum())
+                break
+        assert found, j
+    assert of_both > 20                                          # two formulas that agreed everywhere would prove nothing
