@@ -576,11 +576,15 @@ int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
 // window 2051 and 2343. In a longer launch the end matters less, too: 8 x 3000 x 24, nine rounds, 503 and 524. Query tiles in
 // fours gain for longer (12 x 500 x 24 61.3 and 52.7, 6 x 1000 x 40 118 and 109): dealt out head after head, the heavier ones
 // of all heads meet on the same CUs.
-// Where query heads share their KV head's tiles, more of its workgroups are in flight already, and less is to be had: nothing beyond a
-// round with two KV heads an XCD (4 x 1500 x 16:4 47.7 and 50.8), up to four rounds with three or four (3 x 1300 x 32:8 64.8 and 59.0, 4 x 1532 x
-// 24:8 78.4 and 73.2, 4 x 2225 x 24:8 119.7 and 115.8), with five to eight where the last round is at most half full (8 x 512 x 24:8 38.0
-// and 31.0, 8 x 1000 85.0 and 79.0, 8 x 655 x 32:8 54.3 and 55.6), with more where it is nearly empty (12 x 1018 x 16:8 86.0 and 79.5, 12 x 700 x
-// 24:8 68.0 and 72.6). A grouped call of a head each has one round at most: 2 x 300 x 64:8 16.5 and 14.5, nine and more heads none.
+// Where query heads share their KV head's tiles, more of its workgroups are in flight already, but their walks are as uneven (one KV head after
+// another and heavier first, us): one KV head an XCD gains nothing. Two up to 1.3 rounds (2 x 1464 x 24:8 42.0 and 38.8, 2 x 1367 x 32:8 41.8 and
+// 41.2; 1.44 rounds, 2 x 736 x 64:8, 29.7 and 32.3), of walks beyond 20 tiles up to 1.5 (2 x 1838 x 24:8, window 2048, 59.9 and 58.3) and where a later round
+// is nearly full (2.8 rounds, 3822 rows, 171 and 162; but 2.3, 3134 rows, 126 and 127). From three on up to 240 query heads two rounds (8 x 881 x
+// 16:8 51.9 and 42.5, 8 x 637 x 24:8 43.9 and 39.1, 10 x 430 x 24:8 34.8 and 33.0), up to 216 four (9 x 1257 x 16:8, window 2048, 91.3 and 82.6, 7 x 1150 x 24:8 86.0
+// and 81.0, 6 x 1805 x 24:8, window 2048, 156 and 154; but 10 x 557 x 24:8, 2.2 rounds, 43.2 and 44.8). More of them up to four rounds with three or four KV
+// heads an XCD (3 x 1300 x 32:8 64.8 and 59.0), with five to eight where the last round is at most half full (8 x 655 x 32:8, 2.6 rounds, 54.3
+// and 55.6), with more where it is nearly empty (12 x 1018 x 16:8 86.0 and 79.5). A grouped call of a head each has one round at
+// most: 2 x 300 x 64:8 16.5 and 14.5, nine and more heads none.
 // A head of three query tiles is left alone where it fills one and a half rounds (12 x 300 x 24 29.6 and 33.0) or nearly one
 // (6 x 300 x 24 17.2 and 18.6; 8 x 300, one and an eighth, 26.0 and 24.5), and so is a launch whose workgroups have a CU each.
 // Elsewhere one KV head follows another (32768 rows x 24 heads 553 us, heavier first 558; 2 x 4000, window 512, 81.8 and 84.2).
@@ -589,10 +593,20 @@ int heavy_heads_for(const AttnView& a, const Heads& hs, int n_qtiles) {
   const int group = a.Hq / a.Hkv;
   if (kv_heads % 8 || n_qtiles > 256 || 2 * wgs <= places) return 0;
   if (n_qtiles <= 3 && (2 * wgs > 3 * places || (16 * wgs > 13 * places && wgs <= places))) return 0;
-  const int64_t rest = wgs % places;
-  const bool few = hs.n > 1     ? wgs <= places || (kv_heads >= 24 && wgs <= 4 * places && (kv_heads <= 32 || 8 * rest <= places || (kv_heads <= 64 && 2 * rest <= places)))
-                   : group == 1 ? wgs <= 2 * places || (kv_heads <= 192 && wgs <= 7 * places) || (n_qtiles % 4 == 0 && wgs <= 3 * places)
-                                : group <= 3 ? kv_heads <= 128 : group <= 8 && kv_heads >= 16;
+  const int64_t rest = wgs % places, query_heads = (int64_t)a.B * a.Hq;
+  bool few;
+  if (hs.n == 1) {
+    few = group == 1 ? wgs <= 2 * places || (kv_heads <= 192 && wgs <= 7 * places) || (n_qtiles % 4 == 0 && wgs <= 3 * places)
+                     : group <= 3 || (group <= 8 && kv_heads >= 16);
+  } else if (wgs <= places) {
+    few = true;
+  } else if (kv_heads < 24) {
+    const bool long_walks = a.window > 20 * kBN && a.q_pos0 + a.Tq > 20 * kBN;
+    few = kv_heads >= 16 && (10 * wgs <= 13 * places || (long_walks && (2 * wgs <= 3 * places || (4 * rest >= 3 * places && wgs <= 3 * places))));
+  } else {
+    few = (query_heads <= 240 && wgs <= 2 * places) ||
+          (wgs <= 4 * places && (query_heads <= 216 || kv_heads <= 32 || 8 * rest <= places || (kv_heads <= 64 && 2 * rest <= places)));
+  }
   if (!few) return 0;
   int64_t sum = 0, longest = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {

@@ -77,6 +77,8 @@ def test_pieces_of_the_keys_match_the_oracle(Hq, Hkv, q_pos0, Tq, pieces):
     (3, 700, 32, 8, 1024),       # ... but not where an XCD has three KV heads
     (2, 2500, 16, 16, 3000),     # long walks, more of them than CUs
     (6, 300, 24, 24, 1024),      # three query tiles a head that fill nearly a round
+    (2, 1400, 24, 8, 1024),      # shared tiles of two KV heads an XCD, just over a round
+    (9, 480, 24, 8, 1024),       # ... of nine, in nearly two
 ])
 def test_window_prefill_whichever_tiles_go_first(B, T, Hq, Hkv, window):
     rng = np.random.default_rng(T)
