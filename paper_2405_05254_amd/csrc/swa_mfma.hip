@@ -490,8 +490,10 @@ int64_t units_for(const AttnView& a, const Heads& hs) { return (int64_t)a.B * (a
 // A call that leaves the chip idle lasts as long as its longest walk, 1.34 a key tile and 0.55 for each wavefront that has columns (its
 // queries, its outputs and its share of the CU): a head's last rows on one or two wavefronts of many CUs are then better than on four of a
 // few (25 rows x 64:8 over themselves 4.9 and 6.7, 290 x 16:4 11.9 and 12.4, 18 x 32:8 over 3383, cut into pieces, 20.4 and 22.7; the
-// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). From 2500 key tiles on, or where the work is nearly the same, that no longer counts;
-// but in one round of the chip more than 512 rows have to save 3 % of them (4080 x 16:4 over 5932, 1 % saved, 298 and 306, 3939 x 16:4 95.5 and 98.0).
+// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). From 2500 key tiles on, or where the work is nearly the same and a
+// head has more than one tile (but 96 x 24:8 over 1209, in pieces, 16.9 and 17.7), that no longer counts;
+// but in one round of the chip more than 512 rows have to save 3 % of them (4080 x 16:4 over 5932, 1 % saved, 298 and 306, 3939 x 16:4 95.5 and 98.0)
+// and lengthen no walk by a twentieth (656 x 64:8, 15.6 and 16.9, 22.8 and 23.7).
 constexpr Heads kOneHead = {1, 0, 0};
 Heads heads_for(const AttnView& a) {
   const int n = a.Hq / a.Hkv;
@@ -515,8 +517,8 @@ Heads heads_for(const AttnView& a) {
       if (i == 0 && sum[0] >= 2500 && a.Tq <= 4 * kBM) return packed;
     }
   }
-  if (sum[0] >= 2500) return a.Tq <= 4 * kBM || 100 * sum[1] < 97 * sum[0] ? packed : kOneHead;
-  return 10 * sum[1] >= 9 * sum[0] || longest[1] <= longest[0] + 0.3f ? packed : kOneHead;
+  if (sum[0] >= 2500) return 100 * sum[1] < 97 * sum[0] && longest[1] <= 1.05f * longest[0] ? packed : kOneHead;
+  return (a.Tq > kBM && 10 * sum[1] >= 9 * sum[0]) || longest[1] <= longest[0] + 0.3f ? packed : kOneHead;
 }
 
 // How many pieces a call's query tiles are cut into. A workgroup's walk over the keys is serial, so a call with few
@@ -546,7 +548,7 @@ float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
 int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
   const int n_qtiles = qtiles_for(a, hs);
   const int64_t items = n_qtiles * units_for(a, hs);
-  if (2 * items > kMaxPieceWgs) return 1;
+  if (2 * items > kMaxPieceWgs || 2 * items > room) return 1;
   int n_max = 0;
   int64_t sum = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {
@@ -639,13 +641,14 @@ size_t swa_mfma_workspace(const AttnView& a) {
 }
 
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s) {
+  const int64_t room = workspace ? (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float))) : 0;
   const Heads heads = heads_for(a);
   Args g;
   g.a = a;
   g.n_qtiles = qtiles_for(a, heads);
   g.n_keys = a.q_pos0 + a.Tq;
   g.part = (float*)workspace;
-  g.pieces = workspace ? pieces_for(a, heads, (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float)))) : 1;
+  g.pieces = pieces_for(a, heads, room);
   const int64_t units = units_for(a, heads);
   g.total = (int)(g.n_qtiles * units * g.pieces);
   g.heavy_heads = g.pieces == 1 ? heavy_heads_for(a, heads, g.n_qtiles) : 0;
