@@ -452,7 +452,7 @@ hipError_t launch_decode_i8(const yoco_kv_cache& c, const void* q, const int64_t
     if (G <= 4) hipLaunchKernelGGL((decode_i8_kernel<4, decltype(more)...>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, more...);
     else hipLaunchKernelGGL((decode_i8_kernel<16, decltype(more)...>), grid, block, 0, s, c, qp, lens, fixed_len, Hq, sl2, out, more...);
   };
-  if (split) launch(SplitFirst{split});
+  if (split) launch(split_first(c, split));
   else if (ahead.workgroups) launch(ahead);
   else launch();
   return hipGetLastError();

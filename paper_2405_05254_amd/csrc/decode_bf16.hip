@@ -315,14 +315,15 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
       for (int t = 0; t < 4; ++t) qraw[t] = *(const u32x4*)(q + ((int64_t)b * Hq + g * G + n) * kD + t * 32 + qg * 8);
     }
   };
-  if constexpr (!kSplitsFirst<Last...>) load_q(blockIdx.y, blockIdx.x);
+  const int mostly = kSplitsFirst<Last...> && (int)blockIdx.y >= c.B ? 0 : blockIdx.y;
+  load_q(mostly, blockIdx.x);
   const SplitRows part = split_rows<128>(out, c, lens, fixed_len, last...);
   const int b = part.b, g = part.g, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
 
-  if (kSplitsFirst<Last...> || __builtin_expect(b != (int)blockIdx.y, 0)) load_q(b, g);
+  if (__builtin_expect(b != mostly || (kSplitsFirst<Last...> && g != (int)blockIdx.x), 0)) load_q(b, g);
   bf16x8_t qf[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) qf[t] = __builtin_bit_cast(bf16x8_t, qraw[t]);
@@ -455,7 +456,7 @@ hipError_t launch_decode_bf16(const yoco_kv_cache& c, const void* q, const int64
     else if (G <= 4) go(&decode_bf16_mfma_kernel<true, 4, decltype(more)...>);
     else go(&decode_bf16_mfma_kernel<true, kGMax, decltype(more)...>);
   };
-  if (split) launch(SplitFirst{split});
+  if (split) launch(split_first(c, split));
   else if (ahead.workgroups) launch(ahead);
   else launch();
   return hipGetLastError();

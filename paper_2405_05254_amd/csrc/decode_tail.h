@@ -65,6 +65,9 @@ __device__ __forceinline__ int lane_scan(int x, F f) {
   return dpp_step<0x143, 0xc>(x, f);  // row_bcast:31 into rows 2 and 3
 }
 __device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, 63); }
+__device__ __forceinline__ int lanes_max(int x) {           // of values that are not negative
+  return last_lane(lane_scan(x, [](int a, int b) { return a > b ? a : b; }));
+}
 __device__ __forceinline__ int lanes_sum(int x) { return last_lane(lane_scan(x, [](int a, int b) { return a + b; })); }
 __device__ __forceinline__ float lanes_sum(float x) {
   return __int_as_float(last_lane(lane_scan(__float_as_int(x), [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); })));
@@ -115,21 +118,43 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
   int len, n = 1;
   r.total = (float)B * (float)c.N_cap;               // unsplit: nothing depends on the other lengths
   if constexpr (kSplitsFirst<Last...>) {
-    // The splits come first: of a CU's two workgroups the first is the faster one, and theirs have a meeting before them (16 x 24 heads x
-    // 1024 rows, last, 35.9 us; first 34.3).
-    const int parts = (last.split, ...) * out.splits;
-    int unit = blockIdx.x;
-    const bool split = unit < parts;
-    if (split) {
-      const int u = __builtin_amdgcn_readfirstlane(unit / out.splits);
-      r.sp = unit - u * out.splits;
-      unit = u;
-    } else {
-      unit += (last.split, ...) - parts;
+    // Whole, the launch lasts as long as the two units of a CU that has two, or as the longest sequence. Cut, it lasts as long as the longest
+    // and a part of the first, and a meeting's time, some 256 rows; what is too short for parts only waits for their workgroups. So the
+    // lengths decide, the same in all workgroups (us, whole, always cut, so: 12 x 24 heads of 128 to 1024 rows, the draws that are worst and
+    // best for a cut, 15.2, 17.4, 15.1 and 21.4, 16.1, 16.9; 33 x 8:24 x 500 to 4000 in 8 bits 30.1, 32.4, 30.2 and 44.4, 35.9, 35.9; 40 x 8:24 x
+    // 375 to 3000 56.6, 57.5, 57.0 and 88.4, 63.4, 63.4; all of 100 rows 5.4, 6.3, 5.8, where the 0.2 to 0.4 that it takes to look at the lengths
+    // show most).
+    const SplitFirst& f = (last, ...);
+    asm volatile("" : : "s"(f.split), "s"(f.apart), "s"(f.apart_most), "s"(out.splits));    // not a trip for the arguments behind the branch
+    int mine = 0, front = (int)c.N_cap;
+    bool worth = true;                               // of many sequences some pair is long
+    if (B <= 64) {                                   // a lane per sequence
+      const int i = threadIdx.x & 63;
+      const int64_t n_i = lens[i < B ? i : 0], n_x = lens[i + f.apart < B ? i + f.apart : 0], n_y = lens[i + f.apart_most < B ? i + f.apart_most : 0];
+      mine = i < B ? clamp_len(n_i) : 0;
+      const int x = clamp_len(n_x), y = i + f.apart_most < B ? clamp_len(n_y) : 0, first = i * c.Hkv < f.split ? mine : 0;
+      const int pair = lanes_max(first ? first + (x > y ? x : y) : 0), longest = lanes_max(mine);
+      front = lanes_max(first);
+      worth = (pair - longest - 256) * out.splits >= front;
     }
-    r.b = __builtin_amdgcn_readfirstlane(unit / c.Hkv);
-    r.g = unit - r.b * c.Hkv;
-    len = clamp_len(lens ? lens[r.b] : fixed_len);
+    const int id = r.b * c.Hkv + r.g, more = f.split * (out.splits - 1);
+    int unit = id;
+    bool split = false;
+    if (worth && one_length_splits<GRAIN>(front, out.splits, true) > 1) {
+      // The splits come first: of a CU's two workgroups the first is the faster one, and theirs have a meeting before them (16 x 24 heads x
+      // 1024 rows, last, 35.9 us; first 34.3).
+      auto quotient = [](int x, int by) { return __builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)by))); };   // exact: x < 2^20
+      split = id < f.split + more;
+      unit = split ? quotient(id, out.splits) : id - more;
+      r.b = quotient(unit, c.Hkv);
+      r.g = unit - r.b * c.Hkv;
+      if (split) r.sp = id - unit * out.splits;
+    }
+    if (unit >= B * c.Hkv) {                         // one to spare: a part of a sequence that has one
+      r.b = 0;
+      r.sp = 1;
+    }
+    len = B <= 64 ? __builtin_amdgcn_readlane(mine, r.b) : clamp_len(lens[r.b]);
     if (split) n = one_length_splits<GRAIN>(len, out.splits, true);
   } else if (out.splits == 1 || !lens || B == 1) {
     len = clamp_len(lens ? lens[r.b] : fixed_len);

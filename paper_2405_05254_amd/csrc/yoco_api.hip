@@ -135,9 +135,8 @@ Splits decode_splits(const yoco_kv_cache* c, int Hq) {
   // unit and at most one part, up to eight of 128 rows or more (us a layer, unsplit and so: window caches 12 x 24 heads x 1024 rows
   // 33.2 and 27.2, 16 x 24 36.0 and 34.0, 12 x 24 x 512, ragged, 17.8 and 15.3; bf16 33 x 8:24 x 2000 65.5 and 44.7, 40 x 8:24 x 3000, ragged,
   // 83.8 and 60.1; 8 bits 33 x 8:24 x 1024 20.7 and 16.2, 48 x 8 x 1024 22.2 and 20.8). Two parts of fewer than 512 rows lose (24 x 16 x 512
-  // 19.5 and 20.8), and so do 8 bits below 1024 rows (40 x 8 x 512 12.2 and 12.8) and more units (80 x 8 x 1024, 8 bits, 63 and 71). Of ragged
-  // batches it depends on which sequences are over; from 640 rows on it gains in the mean of eight draws for every count of
-  // units tried (17 x 16 x 700 2 %, 36 x 8 x 900 12, 20 x 16 x 2500 17), at 512 it is one or the other (33 x 8 +5 %, 75 x 4 -6 %).
+  // 19.5 and 20.8), and so do 8 bits below 1024 rows (40 x 8 x 512 12.2 and 12.8) and more units (80 x 8 x 1024, 8 bits, 63 and 71). Of a
+  // ragged batch the kernel looks at the lengths first (split_rows); caches below 640 rows have too little to gain for that.
   int64_t split = 0, parts = 1;
   if (s == 1 && units > cus && units % cus != 0) {
     for (int64_t t = 2; t <= 4; ++t)
@@ -212,7 +211,7 @@ int run_decode(const yoco_kv_cache& c, const void* q, void* o, const int64_t* le
                float* ws, Splits sp, hipStream_t s, const char* what, const void* k_new = nullptr, const void* v_new = nullptr,
                int ring = 0, const yoco::ReadAhead& ahead = {}) {
   hipError_t e;
-  if (ahead.workgroups) sp.split = 0;                // one or the other
+  if (!lens) sp.split = 0;                           // the kernel decides by the lengths
   if (sp.split) sp.most = sp.parts;                  // where every pair has room for one split: no more than CUs, which are fewer
   const unsigned long long tag = yoco::decode_meets_in_launch(Hq / c.Hkv, sp.most) ? next_tag() : 0;
   if (c.dtype == YOCO_INT8) {

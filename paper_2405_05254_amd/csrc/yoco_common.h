@@ -131,13 +131,18 @@ inline unsigned more_rows(const yoco_kv_cache& c, int wanted) {
   const int64_t unit = row % 8 == 0 ? 1 : row % 4 == 0 ? 2 : row % 2 == 0 ? 4 : 8;
   return (unsigned)((wanted + row * unit - 1) / (row * unit) * unit);
 }
-// The other last parameter of the decode kernels: the first `split` pairs of sequence and KV head are cut into `splits` parts each, the
-// others are whole, in a grid of one dimension.
+// The other last parameter of the decode kernels: where the lengths make it worth it, the first `split` pairs of sequence and KV head, as many
+// as there are more of them than CUs, are cut into `splits` parts each, and the others are whole. The grid has rows for that behind the
+// batch's own. A CU's second pair is the same head of the sequence `apart` or, where a CU's two are of other heads, `apart_most` further on.
 struct SplitFirst {
-  int split;
+  int split, apart, apart_most;
 };
+inline SplitFirst split_first(const yoco_kv_cache& c, int split) {
+  const int cus = c.B * c.Hkv - split;
+  return {split, cus / c.Hkv, (cus + c.Hkv - 1) / c.Hkv};
+}
 inline dim3 decode_grid(const yoco_kv_cache& c, int splits, int split, const ReadAhead& ahead) {
-  if (split) return dim3((unsigned)(c.Hkv * c.B + split * (splits - 1)));
+  if (split) return dim3(c.Hkv, c.B + (unsigned)((split * (splits - 1) + c.Hkv - 1) / c.Hkv));
   return dim3(c.Hkv, c.B, splits + more_rows(c, ahead.workgroups));
 }
 bool cache_i8_supported(int d);

@@ -185,6 +185,54 @@ def test_units_that_are_over_are_split(dtype, Hq, Hkv, N_cap, lens):
         assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,N_cap,lens,cut", [
+    ("bf16", 33, 33, 640, [640] * 8, True),                            # 264 units on 256 CUs, the eight that are over in five parts
+    ("bf16", 33, 33, 639, [639] * 8, False),
+    ("bf16", 33, 33, 700, [0] + [700] * 7, False),                     # what would be cut is empty
+    ("bf16", 33, 33, 700, [384] + [700] * 7, False),                   # ... saves two steps
+    ("bf16", 33, 33, 1000, [640] + [700] * 6 + [408], True),           # a CU's two units: 1048 rows, 92 more than 256 over the longest
+    ("bf16", 33, 33, 1000, [640] + [700] * 6 + [407], False),          # ... of which a seventh of 640 is more than 91
+    ("bf16", 33, 33, 1000, [1000] + [128] * 7, False),                 # the long one is the first
+    ("bf16", 24, 24, 1024, [1024] * 11 + [700], True),                 # 288 units: a CU's two are heads of sequences 10 or 11 apart
+    ("bf16", 86, 43, 1024, [1024] * 8, True),                          # two parts
+    ("bf16", 86, 43, 1023, [1023] * 8, False),
+    ("bf16", 32, 32, 1024, [1024] * 8, False),                         # a CU each
+    ("bf16", 4, 4, 700, [700 - i for i in range(70)], True),           # more sequences than a wavefront has lanes
+    ("bf16", 4, 4, 700, [100] * 70, False),
+    ("bf16", 264, 33, 1100, [1100] * 8, True),                         # 8 query heads: parts that meet in the launch
+    ("bf16", 297, 33, 1100, [1100] * 8, False),
+    ("int8", 36, 36, 1024, [1024] * 8, True),
+    ("int8", 36, 36, 1024, [512] * 8, False),                          # two steps of 256
+    ("int8", 36, 36, 1024, [1024, 300, 200, 400, 200, 200, 300, 300], False),
+])
+def test_the_lengths_say_whether_units_that_are_over_are_cut(dtype, Hq, Hkv, N_cap, lens, cut):
+    """Only parts write to the workspace."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the cases are made for 256 CUs")
+    B, rng = len(lens), np.random.default_rng(N_cap + Hq)
+    cache = yoco.KVCache(B, Hkv, D, N_cap, torch.int8 if dtype == "int8" else torch.bfloat16)
+    cache.mem.zero_()
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    rows = [[ys.normal(rng, (n, Hkv, D), 1.0, "bf16") for _ in range(2)] for n in lens]
+    for b, (k, v) in enumerate(rows):
+        yoco.global_kv_write(cache, dev(k), dev(v), b, 0)
+    q = ys.normal(rng, (B, Hq, D), 1.0, "bf16")
+    ln = torch.tensor(lens, dtype=torch.int64, device="cuda")
+    nbytes, splits = yoco.cross_attn_decode_workspace(cache, Hq)
+    assert splits == 1
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    o = yoco.cross_attn_decode(cache, dev(q), ln, SCALE, ws)
+    assert bool((ws != 0xFF).any()) == cut
+    attend = oracle.cross_attn_int8 if dtype == "int8" else oracle.cross_attn
+    for b, n in enumerate(lens):
+        got = o[b].float().cpu().numpy()
+        if n == 0:
+            assert not got.any()
+            continue
+        st = ys.error_stats(got, attend(q[b:b + 1], *rows[b], n - 1, SCALE)[0])
+        assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], (b, n, st)
+
+
 def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
     """A batch of more (sequence, head) units than CUs has one split per unit: its workspace serves the few-row call of
     one sequence, whose own split count would be larger."""
