@@ -87,3 +87,47 @@ def test_decode_step_replays_from_a_hip_graph():
         for s, w in zip(states, want_states):
             assert torch.equal(s, w), "a retention state differs on replay %d" % rep
     assert np.isfinite(want[0].float().cpu().numpy()).all()
+
+
+def test_units_that_are_over_replay_with_other_lengths():
+    """More (sequence, KV head) units than CUs: the lengths, which change between the replays, say whether some are cut into parts."""
+    import paper_2405_05254_amd as yoco
+    dev, bf, d, B = "cuda", torch.bfloat16, 128, 8
+    scale = 1.0 / math.sqrt(d)
+    ring, cache, cache8 = yoco.KVCache(B, 33, d, 640, bf), yoco.KVCache(B, 66, d, 1024, bf), yoco.KVCache(B, 36, d, 1024, torch.int8)
+    for i, kv in enumerate([ring, cache]):
+        for plane in kv.planes():
+            plane.copy_(ys.device_normal(plane.shape, 40 + i, 1.0, bf, dev))
+    for b in range(B):
+        yoco.global_kv_write(cache8, *(ys.device_normal((1024, 36, d), 50 + 2 * b + i, 1.0, bf, dev) for i in range(2)), b, 0)
+    calls = [(c, ys.device_normal((B, H, d), 70 + H, 1.0, bf, dev), torch.empty(B, H, d, dtype=bf, device=dev)) for c, H in [(ring, 33), (cache, 66), (cache8, 72)]]
+    ws = [torch.empty(yoco.cross_attn_decode_workspace(c, q.shape[1])[0], dtype=torch.uint8, device=dev) for c, q, _ in calls]
+    lens = torch.full((B,), 640, dtype=torch.int64, device=dev)
+
+    def step():
+        yoco.swa_decode(ring, calls[0][1], lens, scale, ws[0], out=calls[0][2])
+        for (c, q, o), w in list(zip(calls, ws))[1:]:
+            yoco.cross_attn_decode(c, q, lens, scale, w, out=o)
+
+    drawn = [[640] * B, [1024] * B, [1024] + [100] * 7, [0] + [1000] * 7, [700 - 8 * b for b in range(B)]]
+    want = []
+    for ns in drawn:
+        lens.copy_(torch.tensor(ns))
+        step()
+        torch.cuda.synchronize()
+        want.append([o.clone() for _, _, o in calls])
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            step()
+    torch.cuda.synchronize()
+    for rep in range(10):
+        lens.copy_(torch.tensor(drawn[rep % 5]))
+        for _, _, o in calls:
+            o.zero_()
+        assert math.isfinite(float(torch.randn(1 << 20, device=dev).sum()))          # eager work between the replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, (_, _, o) in enumerate(calls):
+            assert torch.equal(o, want[rep % 5][i]), (rep, i)
