@@ -417,7 +417,8 @@ __global__ void __launch_bounds__(kThreads, 2) swa_mfma_kernel(Args g, Shared...
 // for each piece, which mostly come back from the memory behind the L2s; where query tiles are few, by the trips there: a group of
 // pieces each, of as many as 64 registers hold. 16 dims a workgroup are twice the workgroups and half the trips, and gain
 // up to as many query tiles as an eighth of the CUs (us a call, with 32 dims and with 16: 9 rows x 3:1 heads over 3831 18.8 and 17.4,
-// 38 x 24 over 20108 45.4 and 44.3, 128 x 24 over 16000 48.0 and 46.8; but 69 x 64 heads over 1741, 64 tiles, 25.4 and 27.1). 8 dims gain nothing more.
+// 38 x 24 over 20108 45.4 and 44.3, 128 x 24 over 16000 48.0 and 46.8; but 69 x 64 heads over 1741, 64 tiles, 25.4 and 27.1),
+// where there are more than four pieces, one trip of the larger half (195 x 16:4 over 272, four, 14.2 and 14.9). 8 dims gain nothing more.
 template <int RQ, typename... Shared>
 __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g, Shared... shared) {
   constexpr bool PACKED = sizeof...(Shared) > 0;
@@ -527,12 +528,13 @@ Heads heads_for(const AttnView& a) {
 // heads over 16000: 384 workgroups 457 us, in 4 pieces three full rounds, 423). The estimate is in us, from what was measured: a
 // 64-key tile takes 1.34 where a CU has one workgroup, 1.6 where some have two and 2.15 where all have; 5 for a launch and
 // the two ends of a walk; a merge 5, 0.016 for each piece's way out and back and 0.35 for every trip after the first (1000 rows x 1 head
-// 15.7 us without it, in sixteen pieces, 14.0 with, in eight; by 0.6, 49 x 24 heads over 9521 would have ten for nineteen,
-// 33.5 for 31.0). 30 shapes of 16 to 4096 rows are within a
+// 15.7 us without it, in sixteen pieces, 14.0 with, in eight) as far as workgroups have a CU each: two on a CU take less than the
+// estimate has it, and beyond that no trip is counted (29 x 16:8 heads over 18145 in 32 pieces 31.0, in 16 35.1, 130 x 32:8 over 4554 in 7
+// 35.3, in 4 38.1, 255 x 24:8 over 4932 in 10 35.5, in 5 38.0). 30 shapes of 16 to 4096 rows are within a
 // tenth of their best count by it. A cut has to promise a twentieth, because it costs memory.
 constexpr int kMaxPieces = 32;
 // How many pieces the merge of so many query tiles reads in a trip.
-int merge_ahead(int64_t items) { return 8 * items <= compute_units() ? 8 : 4; }
+int merge_ahead(int64_t items, int64_t pieces) { return pieces > 4 && 8 * items <= compute_units() ? 8 : 4; }
 constexpr int64_t kMaxPieceWgs = 1536;         // bounds the partials at 102 MB
 float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
   const int64_t cus = compute_units(), places = 2 * cus;
@@ -543,7 +545,8 @@ float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
   float t = (float)full * (mean * kAll + kEnds) + (rest ? mean * tile(rest) + kEnds : 0.f);
   const float least = longest * tile(wgs < places ? wgs : places) + kEnds;
   if (t < least) t = least;
-  return pieces > 1 ? t + kMerge + kPiece * (float)wgs + kTrip * (float)((pieces - 1) / merge_ahead(items)) : t;
+  const int64_t alone = wgs <= cus ? pieces : cus / items;       // pieces at a CU for each workgroup
+  return pieces > 1 ? t + kMerge + kPiece * (float)wgs + kTrip * (float)(alone > 1 ? (alone - 1) / merge_ahead(items, alone) : 0) : t;
 }
 int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
   const int n_qtiles = qtiles_for(a, hs);
@@ -658,7 +661,7 @@ hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_
       return;
     }
     hipLaunchKernelGGL((swa_mfma_kernel<true, decltype(shared)...>), dim3(g.total), dim3(kThreads), 0, s, g, shared...);
-    if (merge_ahead(g.n_qtiles * units) == 8)
+    if (merge_ahead(g.n_qtiles * units, g.pieces) == 8)
       hipLaunchKernelGGL((swa_merge_kernel<2, decltype(shared)...>), dim3(g.n_qtiles, 8, (unsigned)units), dim3(kThreads), 0, s, g, shared...);
     else
       hipLaunchKernelGGL((swa_merge_kernel<4, decltype(shared)...>), dim3(g.n_qtiles, 4, (unsigned)units), dim3(kThreads), 0, s, g, shared...);

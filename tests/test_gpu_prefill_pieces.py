@@ -135,6 +135,38 @@ def plan_of(Hq, Hkv, q_pos0, Tq):
     return plan(yoco.KVCache(2, Hkv, D, q_pos0 + Tq + 3, torch.bfloat16), q_pos0, Tq, Hq)
 
 
+def on_256_cus():
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the counts are those of 256 CUs")
+
+
+def written(ws):
+    """Partial results that hold something."""
+    return int((~torch.isnan(ws.view(-1, PIECE // 4))).any(1).sum())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,q_pos0,Tq,parts", [
+    (24, 8, 1482, 23, 24 * 8),          # a tile a head: 23 rows on one wavefront
+    (24, 8, 20000, 42, 8 * 32),         # many key tiles: shared, 126 columns
+    (24, 8, 20000, 43, 16 * 32),        # ... 129
+    (64, 8, 9000, 151, 80 * 6),
+    (16, 16, 18145, 29, 16 * 32),       # two workgroups on a CU, whatever trips the merge takes
+    (24, 8, 14000, 2000, 384 * 4),
+])
+def test_which_tiles_a_call_is_cut_into(Hq, Hkv, q_pos0, Tq, parts):
+    on_256_cus()
+    cache = yoco.KVCache(1, Hkv, D, q_pos0 + Tq, torch.bfloat16)
+    cache.mem.zero_()
+    q = torch.zeros((Tq, Hq, D), dtype=torch.bfloat16, device="cuda")
+    nbytes = yoco.cross_attn_prefill_workspace(cache, q_pos0, Tq, Hq, SCALE)
+    assert nbytes >= parts * PIECE and (nbytes > 0) == (parts > 0)
+    if parts:
+        ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        yoco.cross_attn_prefill(cache, q, 0, q_pos0, SCALE, workspace=ws)
+        assert written(ws) == parts
+
+
 @pytest.mark.gpu
 def test_under_capture_a_call_takes_no_scratch_of_its_own():
     cache, q, pos0, nbytes = _few_tiles(Tq=40, Hq=8)
