@@ -480,47 +480,9 @@ __global__ void __launch_bounds__(kThreads) swa_merge_kernel(Args g, Shared... s
 }
 
 Tiles tiles_for(const AttnView& a, const Heads& hs, int qt) { return hs.n > 1 ? tiles_of<true>(a, hs, qt) : tiles_of<false>(a, hs, qt); }
+constexpr Heads kOneHead = {1, 0, 0};
 int qtiles_for(const AttnView& a, const Heads& hs) { return (int)((a.Tq * hs.n + kBM - 1) / kBM); }
 int64_t units_for(const AttnView& a, const Heads& hs) { return (int64_t)a.B * (a.Hq / hs.n); }
-
-// Whether the query heads of a KV head share its query tiles. A tile of 128 columns is then 128 / n rows: its walk over the keys is that
-// much shorter at the diagonal and at the window's end (24:8 heads, window 1024: 96 % of the key tiles, window 512: 91), fewer
-// columns lie idle behind the last row, and walks differ less. us, a head each and so: 4 x 1532 rows x 24:8 77.5 and 73.2, 2 x 1598,
-// window 512, 38.8 and 33.2, 12 x 204 22.6 and 15.1, 8 x 655 x 32:8 66.5 and 54.3, 32491 rows, window 2048, 928 and 907; over a
-// cache 151 rows x 64:8 over 22574 172 and 144, 1323 x 24:8 over 2102 82.2 and 80.5.
-// A call that leaves the chip idle lasts as long as its longest walk, 1.34 a key tile and 0.55 for each wavefront that has columns (its
-// queries, its outputs and its share of the CU): a head's last rows on one or two wavefronts of many CUs are then better than on four of a
-// few (25 rows x 64:8 over themselves 4.9 and 6.7, 290 x 16:4 11.9 and 12.4, 18 x 32:8 over 3383, cut into pieces, 20.4 and 22.7; the
-// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). From 2500 key tiles on, or where the work is nearly the same and a
-// head has more than one tile (but 96 x 24:8 over 1209, in pieces, 16.9 and 17.7), that no longer counts;
-// but in one round of the chip more than 512 rows have to save 3 % of them (4080 x 16:4 over 5932, 1 % saved, 298 and 306, 3939 x 16:4 95.5 and 98.0)
-// and lengthen no walk by a twentieth (656 x 64:8, 15.6 and 16.9, 22.8 and 23.7).
-constexpr Heads kOneHead = {1, 0, 0};
-Heads heads_for(const AttnView& a) {
-  const int n = a.Hq / a.Hkv;
-  if (n == 1 || a.Tq * n >= (1LL << 31) - kBM) return kOneHead;
-  int bits = 1;
-  while ((1LL << bits) < n) ++bits;
-  const Heads packed = {n, (unsigned)((1ULL << (31 + bits)) / n + 1), bits - 1};
-  if (qtiles_for(a, kOneHead) * units_for(a, kOneHead) > 2 * compute_units()) return packed;
-  int64_t sum[2];
-  float longest[2];
-  for (int i = 0; i < 2; ++i) {
-    const Heads& hs = i ? packed : kOneHead;
-    sum[i] = 0;
-    longest[i] = 0.f;
-    for (int qt = 0, n_qtiles = qtiles_for(a, hs); qt < n_qtiles; ++qt) {
-      const Tiles t = tiles_for(a, hs, qt);
-      const int64_t left = a.Tq * hs.n - (int64_t)qt * kBM;
-      const float us = 1.34f * (float)(t.hi - t.lo + 1) + 0.55f * (float)(left < kBM ? (left + kNQ - 1) / kNQ : kWaves);
-      if (us > longest[i]) longest[i] = us;
-      sum[i] += (t.hi - t.lo + 1) * units_for(a, hs);
-      if (i == 0 && sum[0] >= 2500 && a.Tq <= 4 * kBM) return packed;
-    }
-  }
-  if (sum[0] >= 2500) return 100 * sum[1] < 97 * sum[0] && longest[1] <= 1.05f * longest[0] ? packed : kOneHead;
-  return (a.Tq > kBM && 10 * sum[1] >= 9 * sum[0]) || longest[1] <= longest[0] + 0.3f ? packed : kOneHead;
-}
 
 // How many pieces a call's query tiles are cut into. A workgroup's walk over the keys is serial, so a call with few
 // query tiles leaves the chip idle (64 rows x 16 heads over 24000 rows: 16 workgroups of 376 tiles each, 508 us; in 32 pieces
@@ -548,10 +510,13 @@ float estimate_us(int64_t items, int n_max, float n_mean, int pieces) {
   const int64_t alone = wgs <= cus ? pieces : cus / items;       // pieces at a CU for each workgroup
   return pieces > 1 ? t + kMerge + kPiece * (float)wgs + kTrip * (float)(alone > 1 ? (alone - 1) / merge_ahead(items, alone) : 0) : t;
 }
-int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
+struct Cut {
+  int pieces;
+  float us;
+};
+Cut cut_for(const AttnView& a, const Heads& hs, int64_t room) {
   const int n_qtiles = qtiles_for(a, hs);
   const int64_t items = n_qtiles * units_for(a, hs);
-  if (2 * items > kMaxPieceWgs || 2 * items > room) return 1;
   int n_max = 0;
   int64_t sum = 0;
   for (int qt = 0; qt < n_qtiles; ++qt) {
@@ -560,16 +525,71 @@ int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
     if (t.hi - t.lo + 1 > n_max) n_max = t.hi - t.lo + 1;
   }
   const float mean = (float)sum / (float)n_qtiles;
-  int best = 1;
-  float us = 0.95f * estimate_us(items, n_max, mean, 1);
+  Cut best = {1, estimate_us(items, n_max, mean, 1)};
+  float us = 0.95f * best.us;
   for (int p = 2; p <= kMaxPieces && p <= n_max && items * p <= kMaxPieceWgs && items * p <= room; ++p) {
     const float t = estimate_us(items, n_max, mean, p);
     if (t < us) {
       us = t;
-      best = p;
+      best = {p, t};
     }
   }
   return best;
+}
+int pieces_for(const AttnView& a, const Heads& hs, int64_t room) {
+  const int64_t items = qtiles_for(a, hs) * units_for(a, hs);
+  return 2 * items > kMaxPieceWgs || 2 * items > room ? 1 : cut_for(a, hs, room).pieces;
+}
+
+// Whether the query heads of a KV head share its query tiles. A tile of 128 columns is then 128 / n rows: its walk over the keys is that
+// much shorter at the diagonal and at the window's end (24:8 heads, window 1024: 96 % of the key tiles, window 512: 91), fewer
+// columns lie idle behind the last row, and walks differ less. us, a head each and so: 4 x 1532 rows x 24:8 77.5 and 73.2, 2 x 1598,
+// window 512, 38.8 and 33.2, 12 x 204 22.6 and 15.1, 8 x 655 x 32:8 66.5 and 54.3, 32491 rows, window 2048, 928 and 907; over a
+// cache 151 rows x 64:8 over 22574 172 and 144, 1323 x 24:8 over 2102 82.2 and 80.5.
+// A call that leaves the chip idle lasts as long as its longest walk, 1.34 a key tile and 0.55 for each wavefront that has columns (its
+// queries, its outputs and its share of the CU): a head's last rows on one or two wavefronts of many CUs are then better than on four of a
+// few (25 rows x 64:8 over themselves 4.9 and 6.7, 290 x 16:4 11.9 and 12.4, 18 x 32:8 over 3383, cut into pieces, 20.4 and 22.7; the
+// other way round 69 x 16:4 7.8 and 7.0, 331 x 6:3 13.8 and 12.6). Rows of one tile a head, which are cut into pieces over a cache, are
+// asked the same with half of the key tiles, because the wavefronts' part is not cut (64 x 24:8 over 1031 14.1 and 15.9, 60 x 24:8 over 517 12.3 and 13.6).
+// From 2500 key tiles on, up to four tiles a head share always. More of them, in one round of the chip, where no walk comes near what
+// it was (window 512, 4 x 727 x 16:8, 25.2 and 23.2, window 1024, 3139 x 16:4, 43.2 and 40.9), or where the estimate promises a fourteenth (1321 x 16:4
+// over 13261 211 and 190, 1464 x 16:4 over 585 50.9 and 43.1); what promises less is one or the other (2447 x 16:4 over 154 63.3 and 69.1, 2581 x
+// 16:4 over 241 76.0 and 80.6, 2354 x 16:4 over 172 62.5 and 60.9). A cut in two on a CU against none there counts for nothing, the
+// estimate has that one too high (1965 x 32:8 over 368 73.0 and 81.1, 1615 x 24:8 over 530 61.3 and 62.8).
+// With one key tile there is no walk to shorten (16 x 16:8 over themselves 4.7 and 4.8).
+// Of 1768 drawn grouped calls of one round the mean is 3 % faster than a head each; 40 are more than 1 % slower, the worst 4.6 (68 x 24:8
+// over 1541 18.1 and 19.0), where two processes differ by up to 4.
+Heads heads_for(const AttnView& a, int64_t room) {
+  const int n = a.Hq / a.Hkv;
+  if (n == 1 || a.Tq * n >= (1LL << 31) - kBM) return kOneHead;
+  int bits = 1;
+  while ((1LL << bits) < n) ++bits;
+  const Heads packed = {n, (unsigned)((1ULL << (31 + bits)) / n + 1), bits - 1};
+  if (qtiles_for(a, kOneHead) * units_for(a, kOneHead) > 2 * compute_units()) return packed;
+  if (a.q_pos0 + a.Tq <= kBN) return kOneHead;
+  int64_t sum[2];
+  float longest[2], cut[2];                           // the longest walk, whole and with half its key tiles
+  for (int i = 0; i < 2; ++i) {
+    const Heads& hs = i ? packed : kOneHead;
+    sum[i] = 0;
+    longest[i] = cut[i] = 0.f;
+    for (int qt = 0, n_qtiles = qtiles_for(a, hs); qt < n_qtiles; ++qt) {
+      const Tiles t = tiles_for(a, hs, qt);
+      const int64_t left = a.Tq * hs.n - (int64_t)qt * kBM;
+      const float walk = 1.34f * (float)(t.hi - t.lo + 1), ends = 0.55f * (float)(left < kBM ? (left + kNQ - 1) / kNQ : kWaves);
+      if (walk + ends > longest[i]) longest[i] = walk + ends;
+      if (0.5f * walk + ends > cut[i]) cut[i] = 0.5f * walk + ends;
+      sum[i] += (t.hi - t.lo + 1) * units_for(a, hs);
+      if (i == 0 && sum[0] >= 2500 && a.Tq <= 4 * kBM) return packed;
+    }
+  }
+  if (sum[0] >= 2500) {
+    if (longest[1] <= 0.97f * longest[0]) return packed;
+    const Cut one = cut_for(a, kOneHead, room), shared = cut_for(a, packed, room);
+    const bool alike = one.pieces > 1 || shared.pieces == 1 || qtiles_for(a, packed) * units_for(a, packed) <= compute_units();
+    return alike && shared.us <= 0.93f * one.us ? packed : kOneHead;
+  }
+  return longest[1] <= longest[0] + 0.3f && (a.Tq > kBM || cut[1] <= cut[0] + 0.3f) ? packed : kOneHead;
 }
 
 // Where walks differ much (their mean is under three quarters of the longest: causal attention over up to twice the window)
@@ -638,14 +658,14 @@ size_t swa_mfma_workspace(const AttnView& a) {
     const int pieces = pieces_for(a, hs, kMaxPieceWgs);
     return pieces > 1 ? (size_t)qtiles_for(a, hs) * units_for(a, hs) * pieces * kPieceFloats * sizeof(float) : 0;
   };
-  const Heads hs = heads_for(a);
+  const Heads hs = heads_for(a, kMaxPieceWgs);
   const size_t one = bytes(kOneHead), own = hs.n > 1 ? bytes(hs) : 0;        // never less than for a head each
   return one > own ? one : own;
 }
 
 hipError_t launch_swa_mfma(const AttnView& a, void* workspace, size_t workspace_bytes, hipStream_t s) {
   const int64_t room = workspace ? (int64_t)(workspace_bytes / (kPieceFloats * sizeof(float))) : 0;
-  const Heads heads = heads_for(a);
+  const Heads heads = heads_for(a, room);
   Args g;
   g.a = a;
   g.n_qtiles = qtiles_for(a, heads);

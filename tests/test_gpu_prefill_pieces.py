@@ -148,10 +148,14 @@ def written(ws):
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,q_pos0,Tq,parts", [
     (24, 8, 1482, 23, 24 * 8),          # a tile a head: 23 rows on one wavefront
+    (24, 8, 517, 60, 24 * 5),           # 60 rows on two; of shared tiles one would have all four
     (24, 8, 20000, 42, 8 * 32),         # many key tiles: shared, 126 columns
     (24, 8, 20000, 43, 16 * 32),        # ... 129
     (64, 8, 9000, 151, 80 * 6),
     (16, 16, 18145, 29, 16 * 32),       # two workgroups on a CU, whatever trips the merge takes
+    (16, 4, 154, 2447, 320 * 3),        # as many pieces of a head each as of shared tiles, which save 4 %
+    (16, 4, 585, 1464, 184 * 4),        # shared, which a cut fits better
+    (32, 8, 368, 1965, 0),              # as good as uncut, and so it stays
     (24, 8, 14000, 2000, 384 * 4),
 ])
 def test_which_tiles_a_call_is_cut_into(Hq, Hkv, q_pos0, Tq, parts):
@@ -165,6 +169,32 @@ def test_which_tiles_a_call_is_cut_into(Hq, Hkv, q_pos0, Tq, parts):
         ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda")
         yoco.cross_attn_prefill(cache, q, 0, q_pos0, SCALE, workspace=ws)
         assert written(ws) == parts
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,Tq,tiles,pieces,parts,parts_of_half", [
+    (2, 1, 1000, 16, 8, 100, 58),       # rows over themselves: the first tile has one key tile, for one of its pieces
+    (3, 1, 513, 13, 9, 65, 35),         # the last tile has a row
+    (5, 1, 385, 16, 7, 61, 0),          # half as many pieces are not worth it
+    (12, 4, 770, 76, 3, 212, 0),
+])
+def test_shared_tiles_with_fewer_key_tiles_than_pieces(Hq, Hkv, Tq, tiles, pieces, parts, parts_of_half):
+    on_256_cus()
+    rng = np.random.default_rng(Tq)
+    cache = yoco.KVCache(2, Hkv, D, Tq + 3, torch.bfloat16)
+    cache.mem.fill_(0xFF)                                       # NaN wherever nothing is written
+    K, V = (ys.normal(rng, (Tq, Hkv, D), 1.0, "bf16") for _ in range(2))
+    q = ys.normal(rng, (Tq, Hq, D), 1.0, "bf16")
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    yoco.global_kv_write(cache, dev(K), dev(V), 1, 0)
+    ref, tol = oracle.cross_attn(q, K, V, 0, SCALE), ys.TOL["bf16"]
+    assert yoco.cross_attn_prefill_workspace(cache, 0, Tq, Hq, SCALE) >= tiles * pieces * PIECE
+    for held, expected in ((tiles * pieces, parts), (tiles * pieces // 2, parts_of_half), (2 * tiles - 1, 0)):
+        ws = torch.full((held * PIECE // 4 + 64,), float("nan"), dtype=torch.float32, device="cuda")
+        o = yoco.cross_attn_prefill(cache, dev(q), 1, 0, SCALE, workspace=ws[:-64])
+        assert written(ws[:-64]) == expected and torch.isnan(ws[-64:]).all()
+        st = ys.error_stats(o.float().cpu().numpy(), ref)
+        assert st["max_abs"] <= tol["max_abs"] and st["mean_rel"] <= tol["mean_rel"], (held, st)
 
 
 @pytest.mark.gpu
