@@ -594,14 +594,14 @@ size_t gret_chunk_workspace(int B, int64_t T, int H, int chunk) {
 // 4.7 where the chip is nearly empty, 6.3 with a workgroup on every CU, 7.9 where the first CUs have two and 11.8 where all have, which is
 // what HBM and the vector units give; the scan, or each earlier segment that is folded; and the way out and back of a workgroup's state.
 float estimate_us(int64_t bh, int nseg, int per) {
-  constexpr float kOutputs = 4.2f, kSegments = 3.5f, kScan = 4.6f, kFolded = 1.5f, kStateUs = 0.02f, kCus = 256.f;
-  const float wgs = (float)(bh * nseg);
+  constexpr float kOutputs = 4.2f, kSegments = 3.5f, kScan = 4.6f, kFolded = 1.5f, kStateUs = 0.02f;
+  const float wgs = (float)(bh * nseg), cus = (float)compute_units();
   if (nseg == 1) return kOutputs + 4.7f * (float)per;
-  const float chunk = wgs <= kCus ? 4.7f + 1.6f * wgs / kCus : 7.9f + 3.9f * (wgs - kCus) / kCus;
+  const float chunk = wgs <= cus ? 4.7f + 1.6f * wgs / cus : 7.9f + 3.9f * (wgs - cus) / cus;
   const bool scanned = nseg - 1 > kFold;
   return kOutputs + kSegments + (scanned ? kScan + kStateUs * wgs : kFolded * (float)(nseg - 1)) + kStateUs * wgs + chunk * (float)per;
 }
-// Chunks per segment: all segments resident at once, at most two workgroups per CU (512), and no more segments than the workspace
+// Chunks per segment: all segments resident at once, at most two workgroups per CU, and no more segments than the workspace
 // holds states for. Where that leaves a segment eight chunks there are as many (32768 rows x 24 heads, 10 segments 355 us, 21
 // segments 337; 4 x 5000 x 24, 4 and 5, 218 and 212). Of shorter ones a CU's second workgroup costs more in states than it
 // hides (us, two a CU and as here: 4000 rows x 16 heads 55.9 and 47.2, 2 x 3000 x 16 64.9 and 57.9, 4 x 1000 x 16 56.7 and 44.1,
@@ -612,7 +612,7 @@ int gret_chunks_per_segment(int B, int64_t T, int H, int chunk) {
   const int64_t bh = (int64_t)B * H, n_chunks = (T + kC - 1) / kC;
   const int64_t nc = (T + chunk - 1) / chunk, old = gret_segment_chunks(B, H, (int)nc);
   const int64_t room = nc + 2 * ((nc + old - 1) / old);                      // states per head in the workspace: nseg - 1 and a copy of state_in
-  int64_t most = 512 / bh;
+  int64_t most = 2 * compute_units() / bh;
   if (most > room) most = room;
   if (most > n_chunks) most = n_chunks;
   if (most < 1) most = 1;
@@ -621,7 +621,7 @@ int gret_chunks_per_segment(int B, int64_t T, int H, int chunk) {
   int best = per_seg(most);
   if (best >= 8) return best;
   float us = 0.985f * us_of(best);
-  const bool second = bh * ((n_chunks + best - 1) / best) > 256;
+  const bool second = bh * ((n_chunks + best - 1) / best) > compute_units();
   for (int64_t nseg = second ? most - 1 : 1; nseg >= 1; --nseg) {
     const float t = us_of(per_seg(nseg));
     if (t < us) {
