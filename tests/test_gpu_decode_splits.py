@@ -249,6 +249,25 @@ def test_few_rows_of_a_batch_use_what_the_documented_workspace_holds():
     assert st["max_abs"] <= 2e-2 and st["mean_rel"] <= 2e-3, st
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,N_cap", [("bf16", 264, 264, 1100), ("bf16", 600, 300, 600), ("int8", 288, 288, 1030)])
+def test_few_rows_over_more_heads_than_compute_units_are_whole(dtype, Hq, Hkv, N_cap):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the cases are made for 256 CUs")
+    cache = yoco.KVCache(2, Hkv, D, N_cap, torch.int8 if dtype == "int8" else torch.bfloat16)
+    cache.mem.zero_()
+    rng = np.random.default_rng(N_cap)
+    dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)  # noqa: E731
+    k, v = (ys.normal(rng, (N_cap, Hkv, D), 1.0, "bf16") for _ in range(2))
+    yoco.global_kv_write(cache, dev(k), dev(v), 1, 0)
+    q = ys.normal(rng, (3, Hq, D), 1.0, "bf16")
+    ws = torch.full((yoco.cross_attn_decode_workspace(cache, Hq)[0],), 0xFF, dtype=torch.uint8, device="cuda")
+    o = yoco.cross_attn_prefill(cache, dev(q), 1, N_cap - 3, SCALE, workspace=ws)
+    assert (ws == 0xFF).all()
+    attend = oracle.cross_attn_int8 if dtype == "int8" else oracle.cross_attn
+    st = ys.error_stats(o.float().cpu().numpy(), attend(q, k, v, N_cap - 3, SCALE))
+    assert st["max_abs"] <= ys.TOL["bf16"]["max_abs"] and st["mean_rel"] <= ys.TOL["bf16"]["mean_rel"], st
+
+
 @pytest.mark.parametrize("Hq,Hkv,N_cap,tokens", [
     (1, 1, 2048, [5000, 3, 0]),       # the vector-ALU step, 16 splits in one launch
     (2, 1, 2200, [2200, 9000]),       # ... 18, with a merge launch

@@ -119,6 +119,16 @@ def test_query_heads_that_share_a_tile_match_the_oracle(B, T, Hq, Hkv, window):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("B,T,Hq,Hkv,window", [
+    (5, 131, 64, 1, 1000),       # two rows a tile: 640 workgroups of a head each, more than a round
+    (52, 140, 5, 1, 40),         # wavefronts that begin in a row's heads, a last one with 28 columns
+    (65, 100, 7, 1, 1),          # rows that see themselves; the second tile begins in a row's third head
+])
+def test_heads_share_tiles_beyond_a_round(B, T, Hq, Hkv, window):
+    test_query_heads_that_share_a_tile_match_the_oracle(B, T, Hq, Hkv, window)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,q_pos0,Tq", [
     (24, 8, 20000, 43),          # 129 columns: the second tile has one
     (24, 8, 20000, 42),          # 126
