@@ -134,6 +134,10 @@ int yoco_kv_cache_init(void* mem, size_t bytes, int B, int Hkv, int d, int64_t N
  * or flushes to zero, an absolute error below 2^-25 per element. q and k have
  * no such limit (bf16 products, exact in fp32). fp32 inputs, other head
  * dimensions and scale <= 0 run on fp32 vector kernels without this limit.
+ * On that path the weights are rounded against the largest score that a query
+ * tile has met, and which rows and heads share a tile follows from all sizes of
+ * the call: it repeats itself bit for bit, but a sequence alone and in a batch
+ * may differ by those roundings (2e-4 of the norm as bf16).
  */
 int yoco_swa_prefill(const void* q, const void* k, const void* v, void* o, int B, int64_t T, int Hq,
                      int Hkv, int d, int64_t window, float scale, int dtype, void* stream);
@@ -174,16 +178,17 @@ int yoco_global_kv_write_scaled(const yoco_kv_cache* c, const void* k, const voi
  * (the exit row of an early-exit prefill, Fig. 3) is split over the cache like
  * a decode step instead of walking it with one workgroup per head. On a bf16
  * cache with d = 128 a call with more rows, but few enough that a workgroup per
- * head and 128 rows does not fill the chip, shares the keys of such a tile out
- * over several workgroups as far as the workspace holds their partial results
- * (yoco_cross_attn_prefill_workspace); a second launch merges them in a fixed
- * order. The result is the same operation either way, and as far from exact
+ * query tile (128 rows of a query head, or 128 pairs of a row and one of the
+ * query heads of a KV head) does not fill the chip, shares the keys of such a
+ * tile out over several workgroups as far as the workspace holds their partial
+ * results (yoco_cross_attn_prefill_workspace); a second launch merges them in a
+ * fixed order. The result is the same operation either way, and as far from exact
  * arithmetic (1.67e-3 relative after the rounding to bf16), but not the same
- * bits: softmax weights are rounded to fp16 against the largest score of a
- * workgroup's keys, so that another number of workgroups takes other roundings
- * (1e-3 apart as bf16). How many there are follows from the shape, the device
- * and workspace_bytes alone; with those the same, a call repeats itself bit for
- * bit. Calls that overlap in time must not share a workspace.
+ * bits: softmax weights are rounded to fp16 against the largest score that a
+ * tile has met, so that other tiles or another number of workgroups take other
+ * roundings (1e-3 apart as bf16). Tiles and workgroups follow from the shape,
+ * the device and workspace_bytes alone; with those the same, a call repeats
+ * itself bit for bit. Calls that overlap in time must not share a workspace.
  * A bf16 cache with d = 128 and more than 8 rows runs on the same matrix-core
  * path as yoco_swa_prefill, with the same domain: cached |v| below 65504, and
  * |v| under 2^-14 read with an absolute error below 2^-25.
@@ -201,7 +206,9 @@ int yoco_cross_attn_prefill_workspace(const yoco_kv_cache* c, int64_t q_pos0, in
  * `splits` partial results (running max, sum, d-vector in fp32) per
  * (sequence, query head). Of a batch of four sequences or more up to half of
  * the splits may be to spare for ragged lengths: a workspace that holds the
- * others is accepted as well, and the call does without. Host only. */
+ * others is accepted as well, and the call does without. A call with splits == 1
+ * may use the workspace, too: of more (sequence, KV head) pairs than the GPU has
+ * compute units the first may be cut into parts, which fit it. Host only. */
 int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* bytes, int* splits);
 
 /*
@@ -219,8 +226,10 @@ int yoco_cross_attn_decode_workspace(const yoco_kv_cache* c, int Hq, size_t* byt
  * call, with device-scope stores, and whoever finds every split published
  * merges; nothing waits. Otherwise a second launch merges. How many splits a
  * sequence gets depends on the lengths of the whole batch and, where some are
- * to spare, on whether workspace_bytes holds those, so that the same sequence
- * in another batch or with a smaller workspace may differ by the order of fp32
+ * to spare, on whether workspace_bytes holds those; of more (sequence, KV head)
+ * pairs than compute units, up to twice as many, the first may be cut and the
+ * others not. So the same sequence in another batch, at another place of it, in
+ * another KV head or with a smaller workspace may differ by the order of fp32
  * sums. The workspace needs no clearing; calls that overlap in time must not
  * share one.
  */
