@@ -315,15 +315,14 @@ __global__ void __launch_bounds__(256, 2) decode_bf16_mfma_kernel(yoco_kv_cache 
       for (int t = 0; t < 4; ++t) qraw[t] = *(const u32x4*)(q + ((int64_t)b * Hq + g * G + n) * kD + t * 32 + qg * 8);
     }
   };
-  const int mostly = kSplitsFirst<Last...> && (int)blockIdx.y >= c.B ? 0 : blockIdx.y;
-  load_q(mostly, blockIdx.x);
+  if constexpr (!kSplitsFirst<Last...>) load_q(blockIdx.y, blockIdx.x);
   const SplitRows part = split_rows<128>(out, c, lens, fixed_len, last...);
   const int b = part.b, g = part.g, sp = part.sp;
   if (sp > 0 && sp >= part.splits && out.tag) return;     // a merge launch reads every split, those without rows too
   const int64_t j_lo = part.lo, j_hi = part.hi;
   const int64_t w_lo = j_lo + wave * kMRows;              // the wavefronts take turns at the split's 32-row steps
 
-  if (__builtin_expect(b != mostly || (kSplitsFirst<Last...> && g != (int)blockIdx.x), 0)) load_q(b, g);
+  if (kSplitsFirst<Last...> || __builtin_expect(b != (int)blockIdx.y, 0)) load_q(b, g);
   bf16x8_t qf[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) qf[t] = __builtin_bit_cast(bf16x8_t, qraw[t]);

@@ -119,11 +119,12 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
   r.total = (float)B * (float)c.N_cap;               // unsplit: nothing depends on the other lengths
   if constexpr (kSplitsFirst<Last...>) {
     // Whole, the launch lasts as long as the two units of a CU that has two, or as the longest sequence. Cut, it lasts as long as the longest
-    // and a part of the first, and a meeting's time, some 256 rows; what is too short for parts only waits for their workgroups. So the
-    // lengths decide, the same in all workgroups (us, whole, always cut, so: 12 x 24 heads of 128 to 1024 rows, the draws that are worst and
-    // best for a cut, 15.2, 17.4, 15.1 and 21.4, 16.1, 16.9; 33 x 8:24 x 500 to 4000 in 8 bits 30.1, 32.4, 30.2 and 44.4, 35.9, 35.9; 40 x 8:24 x
-    // 375 to 3000 56.6, 57.5, 57.0 and 88.4, 63.4, 63.4; all of 100 rows 5.4, 6.3, 5.8, where the 0.2 to 0.4 that it takes to look at the lengths
-    // show most).
+    // and a part of the first, and a meeting's time, some 224 rows in bf16; what is too short for parts only waits for their workgroups. So
+    // the lengths decide, the same in all workgroups. 8-bit caches, whose walk waits more for the vector ALU than for memory, lose
+    // nothing down to no rows at all (48 x 8:24 of 128 to 1024 rows, 166 rows more than the longest and a part, 17.0 whole, 16.0 cut). us,
+    // whole, always cut, so: 12 x 24 heads of 128 to 1024 rows, the draws that are worst and best for a cut, 15.2, 17.6, 15.2 and 21.4, 16.5, 16.8; 33
+    // x 8:24 x 500 to 4000 in 8 bits 30.0, 32.3, 30.2 and 44.1, 35.5, 36.2; 40 x 8:24 x 375 to 3000 56.5, 60.1, 57.0 and 88.0, 63.2, 63.6; all of
+    // 100 rows 5.4, 6.3, 5.8. Looking at the lengths takes 0.2 to 0.5.
     const SplitFirst& f = (last, ...);
     asm volatile("" : : "s"(f.split), "s"(f.apart), "s"(f.apart_most), "s"(out.splits));    // not a trip for the arguments behind the branch
     int mine = 0, front = (int)c.N_cap;
@@ -135,7 +136,7 @@ __device__ __forceinline__ SplitRows split_rows(const SplitOut& out, const yoco_
       const int x = clamp_len(n_x), y = i + f.apart_most < B ? clamp_len(n_y) : 0, first = i * c.Hkv < f.split ? mine : 0;
       const int pair = lanes_max(first ? first + (x > y ? x : y) : 0), longest = lanes_max(mine);
       front = lanes_max(first);
-      worth = (pair - longest - 256) * out.splits >= front;
+      worth = (pair - longest - (GRAIN < 256 ? 224 : 0)) * out.splits >= front;
     }
     const int id = r.b * c.Hkv + r.g, more = f.split * (out.splits - 1);
     int unit = id;

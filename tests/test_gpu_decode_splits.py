@@ -190,8 +190,8 @@ def test_units_that_are_over_are_split(dtype, Hq, Hkv, N_cap, lens):
     ("bf16", 33, 33, 639, [639] * 8, False),
     ("bf16", 33, 33, 700, [0] + [700] * 7, False),                     # what would be cut is empty
     ("bf16", 33, 33, 700, [384] + [700] * 7, False),                   # ... saves two steps
-    ("bf16", 33, 33, 1000, [640] + [700] * 6 + [408], True),           # a CU's two units: 1048 rows, 92 more than 256 over the longest
-    ("bf16", 33, 33, 1000, [640] + [700] * 6 + [407], False),          # ... of which a seventh of 640 is more than 91
+    ("bf16", 33, 33, 1000, [640] + [700] * 6 + [376], True),           # a CU's two units: 1016 rows, 92 more than 224 over the longest
+    ("bf16", 33, 33, 1000, [640] + [700] * 6 + [375], False),          # ... of which a seventh of 640 is more than 91
     ("bf16", 33, 33, 1000, [1000] + [128] * 7, False),                 # the long one is the first
     ("bf16", 24, 24, 1024, [1024] * 11 + [700], True),                 # 288 units: a CU's two are heads of sequences 10 or 11 apart
     ("bf16", 86, 43, 1024, [1024] * 8, True),                          # two parts
@@ -203,7 +203,8 @@ def test_units_that_are_over_are_split(dtype, Hq, Hkv, N_cap, lens):
     ("bf16", 297, 33, 1100, [1100] * 8, False),
     ("int8", 36, 36, 1024, [1024] * 8, True),
     ("int8", 36, 36, 1024, [512] * 8, False),                          # two steps of 256
-    ("int8", 36, 36, 1024, [1024, 300, 200, 400, 200, 200, 300, 300], False),
+    ("int8", 36, 36, 1024, [1024, 300, 200, 400, 200, 200, 300, 128], True),       # 1152 rows, an eighth of the first over the longest
+    ("int8", 36, 36, 1024, [1024, 300, 200, 400, 200, 200, 300, 127], False),
 ])
 def test_the_lengths_say_whether_units_that_are_over_are_cut(dtype, Hq, Hkv, N_cap, lens, cut):
     """Only parts write to the workspace."""
